@@ -606,10 +606,21 @@ struct ColsumParams {
     int64_t ld;
     int N, NB, c;
     float sl2;
+    int pieces;   // a chunk's keys are cut into so many runs of whole tiles, one workgroup each
 };
 
+// What bounds it: the vector instructions of the scores.  A score costs an FMA, an exponential (two issue slots) and an
+// add beside a quarter of an MFMA's issue slot, so the issue slots of a SIMD are 78 % taken (counters) while its matrix
+// pipe is 59 % busy; four waves per SIMD cover each other's phases.  Hence: -m - log l of a query enters as one addend
+// (an add per score where a multiplication by 1 / l stood, and half the registers), the 64 sums of a tile are folded
+// over the four lane groups by three swaps and three adds instead of four times two of each, transfers go through a
+// buffer resource (a key beyond N reads as zero and is not stored) with offsets that only step on, and the two
+// buffer halves are two copies of the step, so every LDS offset is an immediate.  24 heads x 18 000 tokens: 2.09 ms
+// before, 1.95 ms now (1.02 PFLOP/s of scores).  Four other orders of the same work (all scores of a tile first,
+// two blocks at a time, exponentials pinned between the products with three and four waves per SIMD) measured equal
+// or slower.
 template <int E, int NQB>
-__global__ __launch_bounds__(256, 2) void attn_colsum_kernel(ColsumParams p) {
+__global__ __launch_bounds__(256, 4) void attn_colsum_kernel(ColsumParams p) {
     constexpr int ROWB = E * 2;
     constexpr int CH = ROWB / 16;
     constexpr int RPI = 64 / CH;
@@ -620,7 +631,8 @@ __global__ __launch_bounds__(256, 2) void attn_colsum_kernel(ColsumParams p) {
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int g = lane >> 4, l16 = lane & 15;
-    const int64_t unit = blockIdx.x;
+    const int64_t unit = blockIdx.x / p.pieces;
+    const int piece = (int)(blockIdx.x % p.pieces);
     const int64_t bh = unit / p.NB;
     const int chunk = (int)(unit % p.NB);
     const int row0 = chunk * p.c;
@@ -630,7 +642,7 @@ __global__ __launch_bounds__(256, 2) void attn_colsum_kernel(ColsumParams p) {
     float* drow = p.colsum + unit * p.ld;
 
     bf16x8 Q[E / 32][NQB];
-    float m2v[NQB][4], il[NQB][4];
+    float off[NQB][4];
 #pragma unroll
     for (int qb = 0; qb < NQB; qb++) {
         int qrow = (w * NQB + qb) * 16 + l16;
@@ -644,70 +656,105 @@ __global__ __launch_bounds__(256, 2) void attn_colsum_kernel(ColsumParams p) {
 #pragma unroll
         for (int r = 0; r < 4; r++) {  // the MFMA result holds query 4g+r of the block in register r
             int qr = (w * NQB + qb) * 16 + 4 * g + r;
-            bool ok = qr < rows_valid;
-            m2v[qb][r] = ok ? p.row_m[bh * p.N + row0 + qr] * 1.4426950408889634f : 0.f;
-            il[qb][r] = ok ? 1.f / p.row_l[bh * p.N + row0 + qr] : 0.f;
+            off[qb][r] = -INFINITY;
+            if (qr < rows_valid) {
+                const int64_t at = bh * p.N + row0 + qr;
+                off[qb][r] = -p.row_m[at] * 1.4426950408889634f - __builtin_amdgcn_logf(p.row_l[at]);
+            }
         }
     }
     const int koff = l16 * ROWB + ((g ^ swizzle<E>(l16)) * 16);
     const int grow0 = w * RPI + lane / CH;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem) + (uint32_t)w * 1024u);
-    const int ntiles = (p.N + kColsumTileRows - 1) / kColsumTileRows;
+    // this piece's tiles [tile0, ntiles) of the chunk's keys (no more pieces than tiles: none is empty)
+    const int all_tiles = (p.N + kColsumTileRows - 1) / kColsumTileRows;
+    const int tile0 = (int)((int64_t)all_tiles * piece / p.pieces);
+    const int ntiles = (int)((int64_t)all_tiles * (piece + 1) / p.pieces);
+    // The head's K matrix through a buffer resource: a key at or beyond N reads as zero; its sum is not stored.
+    const i32x4 kbuf = raw_buffer_words(kh, (uint32_t)p.N * ROWB);
+    uint32_t goff[NI];
+#pragma unroll
+    for (int i = 0; i < NI; i++) {
+        const int row = grow0 + 4 * RPI * i;
+        goff[i] = (uint32_t)(tile0 * kColsumTileRows + row) * ROWB + (uint32_t)(((lane % CH) ^ swizzle<E>(row)) * 16);
+    }
+    const uint32_t smem_at = (uint32_t)(uintptr_t)CHIPMUNK_LDS_PTR(smem);
+    uint32_t kaddr[E / 32];
+#pragma unroll
+    for (int es = 0; es < E / 32; es++) {
+        kaddr[es] = smem_at + (uint32_t)(koff ^ (64 * es));
+        asm volatile("" : "+v"(kaddr[es]));   // just a register: see the attention kernel
+    }
 
-    auto gather = [&](int t, int stage) {
+    auto gather = [&](int stage) {
 #pragma unroll
         for (int i = 0; i < NI; i++) {
-            int row = grow0 + 4 * RPI * i;
-            int pos = min(t * kColsumTileRows + row, p.N - 1);
-            uint32_t goff = (uint32_t)pos * ROWB + (uint32_t)(((lane % CH) ^ swizzle<E>(row)) * 16);
-            load_global_to_lds_16B(kh, goff, lds0 + (uint32_t)(stage * TILE + i * 4096));
+            load_buffer_to_lds_16B(kbuf, goff[i], lds0 + (uint32_t)(stage * TILE + i * 4096));
+            goff[i] += kColsumTileRows * ROWB;
         }
     };
     auto flush = [&](int t) {  // sums of tile t: four waves' partials -> global
         if (tid < kColsumTileRows) {
             int j = t * kColsumTileRows + tid;
-            float v = s_part[t & 1][0][tid] + s_part[t & 1][1][tid] + s_part[t & 1][2][tid] + s_part[t & 1][3][tid];
+            const int s = (t - tile0) & 1;
+            float v = s_part[s][0][tid] + s_part[s][1][tid] + s_part[s][2][tid] + s_part[s][3][tid];
             if (j < p.N) drow[j] = v;
         }
     };
+    // scores of 16 keys (columns of the result) against the wave's queries (rows)
+    auto scores = [&](f32x4 (&S)[NQB], int off_b) {
+        bf16x8 kop[E / 32];
+#pragma unroll
+        for (int es = 0; es < E / 32; es++) kop[es] = lds_read_b128(kaddr[es] + off_b);
+#pragma unroll
+        for (int es = 0; es < E / 32; es++)
+#pragma unroll
+            for (int qb = 0; qb < NQB; qb++)
+                S[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Q[es][qb], kop[es], es == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : S[qb], 0, 0, 0);
+    };
+    // the sum over the lane's queries of one key's weights
+    auto weights = [&](const f32x4 (&S)[NQB]) {
+        float part = 0.f;
+#pragma unroll
+        for (int qb = 0; qb < NQB; qb++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(S[qb][r], p.sl2, off[qb][r]));
+                part = qb + r == 0 ? e : part + e;
+            }
+        return part;
+    };
 
-    gather(0, 0);
-    for (int t = 0; t < ntiles; t++) {
-        const int stage = t & 1;
+    auto step = [&](auto stage_c, int t) {
+        constexpr int stage = decltype(stage_c)::value;
         wait_all_memory();
         __syncthreads();
-        if (t + 1 < ntiles) gather(t + 1, stage ^ 1);
-        if (t > 0) flush(t - 1);
-        const uint8_t* cK = smem + stage * TILE;
+        gather(stage ^ 1);   // past the last tile too: into a buffer nobody reads
+        if (t > tile0) flush(t - 1);
+        float part[kColsumTileRows / 16];
 #pragma unroll
-        for (int sub = 0; sub < 2; sub++) {
-            f32x4 S[2][NQB];
-#pragma unroll
-            for (int u = 0; u < 2; u++)
-#pragma unroll
-                for (int qb = 0; qb < NQB; qb++) S[u][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int es = 0; es < E / 32; es++)
-#pragma unroll
-                for (int u = 0; u < 2; u++) {
-                    bf16x8 kop = *reinterpret_cast<const bf16x8*>(cK + (sub * 32 + u * 16) * ROWB + (koff ^ (64 * es)));
-#pragma unroll
-                    for (int qb = 0; qb < NQB; qb++)
-                        S[u][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Q[es][qb], kop, S[u][qb], 0, 0, 0);
-                }
-#pragma unroll
-            for (int u = 0; u < 2; u++) {
-                float part = 0.f;
-#pragma unroll
-                for (int qb = 0; qb < NQB; qb++)
-#pragma unroll
-                    for (int r = 0; r < 4; r++)
-                        part += __builtin_amdgcn_exp2f(__builtin_fmaf(S[u][qb][r], p.sl2, -m2v[qb][r])) * il[qb][r];
-                part = rows4_sum(part);
-                if (g == 0) s_part[t & 1][w][sub * 32 + u * 16 + l16] = part;
-            }
+        for (int u = 0; u < 4; u++) {
+            f32x4 S[NQB];
+            scores(S, stage * TILE + u * 16 * ROWB);
+            part[u] = weights(S);
         }
+
+        // sums over the four lane groups: each swap brings two keys' halves together, so that a group ends with the
+        // total of one of the four key blocks (group g: block 2 (g % 2) + g / 2)
+        auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(part[0]), __float_as_uint(part[1]), false, false);
+        auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(part[2]), __float_as_uint(part[3]), false, false);
+        const float x01 = __uint_as_float(a[0]) + __uint_as_float(a[1]), x23 = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+        auto d = __builtin_amdgcn_permlane16_swap(__float_as_uint(x01), __float_as_uint(x23), false, false);
+        s_part[stage][w][(((g & 1) << 1) | (g >> 1)) * 16 + l16] = __uint_as_float(d[0]) + __uint_as_float(d[1]);
+    };
+    gather(0);
+#pragma unroll 1
+    for (int t = tile0; t < ntiles; t += 2) {
+        step(std::integral_constant<int, 0>{}, t);
+        if (t + 1 >= ntiles) break;
+        step(std::integral_constant<int, 1>{}, t + 1);
     }
+    wait_all_memory();   // the transfers behind the last tile must have landed before the wave may end
     __syncthreads();
     flush(ntiles - 1);
 }
@@ -751,8 +798,15 @@ static int32_t launch_attn_blocks(const AttnParams& p, int E, int64_t units, hip
     return launch_attn_variant<64, 2, 4, kBlockList>(p, units, s);
 }
 
-static int32_t launch_colsum(const ColsumParams& cp, int E, int64_t units, hipStream_t s) {
-    dim3 grid((unsigned)units), block(256);
+static int32_t launch_colsum(ColsumParams cp, int E, int64_t units, hipStream_t s) {
+    // Four workgroups fit a CU, and a CU with three of them takes longer than one with two: with few chunks the keys
+    // are cut into pieces until there are at least eight workgroups per CU (each piece's sums are its own, so nothing is
+    // merged).  24 heads x 24 chunks x 4608 keys, dense attention and
+    // sums together: 422 us in one piece, 402 in two, 394 in four (the rule), 399 in eight.
+    const int tiles = (cp.N + kColsumTileRows - 1) / kColsumTileRows;
+    cp.pieces = 1;
+    while (units * cp.pieces < 8 * 256 && 2 * cp.pieces * 4 <= tiles) cp.pieces *= 2;   // at least four tiles each
+    dim3 grid((unsigned)(units * cp.pieces)), block(256);
     if (E == 128 && cp.c == 192) hipLaunchKernelGGL((attn_colsum_kernel<128, 3>), grid, block, 0, s, cp);
     else if (E == 128 && cp.c == 128) hipLaunchKernelGGL((attn_colsum_kernel<128, 2>), grid, block, 0, s, cp);
     else if (E == 64 && cp.c == 192) hipLaunchKernelGGL((attn_colsum_kernel<64, 3>), grid, block, 0, s, cp);
