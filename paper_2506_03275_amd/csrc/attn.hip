@@ -36,6 +36,7 @@ struct AttnParams {
                     // scaled scores (natural logarithm); within 2^8 of the row maximum, not necessarily equal to it
     float* row_l;   // optional [B,H,N]: sum_j exp(score_j - row_m)
     int N, NB, c, k_stride;
+    int parts;      // workgroups per chunk: each owns 64 * NQB of its rows and walks the chunk's whole list
     float sl2;      // softmax_scale * log2(e)
     float o_scale;
     // fused column sums with given normalisers (Alg. 4): dense launches of the FUSED kernel only
@@ -279,7 +280,7 @@ static_assert(kBlockColumns % (kTilesPerStep * kTileRows) == 0, "a step never st
 // positions are the blocks' columns in order, so the rows of a step are one contiguous run of K and V.
 enum AttnMode { kColumnList = 0, kFusedDense = 1, kBlockList = 2, kEveryColumn = 3 };
 
-// NWAVES waves per workgroup, each owning NQB blocks of 16 queries: c = 16 * NQB * NWAVES.
+// NWAVES waves per workgroup, each owning NQB blocks of 16 queries: 16 * NQB * NWAVES rows, a chunk or one of its parts.
 template <int E, int NQB, int NWAVES, int MODE = kColumnList>
 __global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_delta_kernel(AttnParams p) {
     constexpr bool FUSED = MODE == kFusedDense;
@@ -307,11 +308,13 @@ __global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_
     const int g = lane >> 4;
     const int l16 = lane & 15;
 
-    const int64_t unit = blockIdx.x;
+    constexpr int ROWS = 16 * NQB * NWAVES;   // query rows of a workgroup
+    const int64_t unit = blockIdx.x / p.parts;
     const int64_t bh = unit / p.NB;
     const int chunk = (int)(unit % p.NB);
-    const int row0 = chunk * p.c;
-    const int rows_valid = min(p.c, p.N - row0);
+    const int row0 = chunk * p.c + (int)(blockIdx.x % p.parts) * ROWS;
+    const int rows_valid = min(ROWS, p.N - row0);
+    if (rows_valid <= 0) return;              // the last chunk may end before this part of it
     // Contents of counts and idx are the caller's precondition; they are clamped all the same so that a bad
     // entry reads a wrong row instead of leaving the tensors.
     // (block lists: counts and k_stride are in blocks; `count` is in list positions = columns all the same)
@@ -771,12 +774,51 @@ static int32_t launch_attn_variant(const AttnParams& p, int64_t units, hipStream
     return launch_status();
 }
 
+// Query rows per workgroup (64 * blocks).  A workgroup of fewer rows takes less time per tile, though more per row: the
+// K and V tiles are fetched and read from LDS all the same.  So three blocks per wave (192 rows) are right for a long
+// launch, and fewer where the last round of workgroups would leave slots empty (two workgroups per CU = 512 slots) or
+// where there are fewer workgroups than CUs.  Measured time of a 32-key tile in us, with two workgroups on the CU and
+// with one (dense launches of 2 to 40 heads, 1024 to 18 000 tokens; for E = 64 more than two fit, the figures stand for
+// the same throughput with two):
+//     E = 128:  1 block 0.60 / 0.37   2 blocks 0.94 / 0.55   3 blocks 1.27 / 0.80
+//     E =  64:  1 block 0.31 / 0.24   2 blocks 0.50 / 0.38   3 blocks 0.74 / 0.52
+// and a launch takes (whole rounds) x (the first) + (a last round of more than half the slots: the first; of at most
+// half: the second), which orders the measured launches correctly: 24 heads x 4608 x 128: 268, 252 and 305 us with
+// three, two and one block; 12 x 2304: 57, 43, 45; 2 x 1024: 29.9, 21.7, 15.7; 24 x 3456 (432 workgroups of 192 rows):
+// 136, 152, 185; 40 x 18 000: 5259, 5833, 7405.
+static double attn_rounds_cost(int E, int blocks, int64_t workgroups) {
+    static const double paired[2][3] = {{0.31, 0.50, 0.74}, {0.60, 0.94, 1.27}};
+    static const double alone[2][3] = {{0.24, 0.38, 0.52}, {0.37, 0.55, 0.80}};
+    const int e = E == 128, last = (int)(workgroups % 512);
+    return (double)(workgroups / 512) * paired[e][blocks - 1] +
+           (last == 0 ? 0. : last <= 256 ? alone[e][blocks - 1] : paired[e][blocks - 1]);
+}
+
 static int32_t launch_attn(const AttnParams& p, int E, int64_t units, hipStream_t s) {
-    if (!p.idx) {
-        if (E == 128 && p.c == 192) return launch_attn_variant<128, 3, 4, kEveryColumn>(p, units, s);
-        if (E == 128 && p.c == 128) return launch_attn_variant<128, 2, 4, kEveryColumn>(p, units, s);
-        if (E == 64 && p.c == 192) return launch_attn_variant<64, 3, 4, kEveryColumn>(p, units, s);
-        return launch_attn_variant<64, 2, 4, kEveryColumn>(p, units, s);
+    const int64_t bh = units / p.NB;
+    if (!p.idx) {   // without a list the rows need not follow the chunks: any of the three
+        auto groups = [&](int blocks) { return bh * ((p.N + 64 * blocks - 1) / (64 * blocks)); };
+        int best = 3;
+        for (int blocks = 2; blocks >= 1; blocks--)
+            if (attn_rounds_cost(E, blocks, groups(blocks)) < attn_rounds_cost(E, best, groups(best))) best = blocks;
+        AttnParams d = p;
+        d.c = 64 * best;
+        d.NB = (p.N + d.c - 1) / d.c;
+        if (E == 128) {
+            if (best == 3) return launch_attn_variant<128, 3, 4, kEveryColumn>(d, groups(3), s);
+            if (best == 2) return launch_attn_variant<128, 2, 4, kEveryColumn>(d, groups(2), s);
+            return launch_attn_variant<128, 1, 4, kEveryColumn>(d, groups(1), s);
+        }
+        if (best == 3) return launch_attn_variant<64, 3, 4, kEveryColumn>(d, groups(3), s);
+        if (best == 2) return launch_attn_variant<64, 2, 4, kEveryColumn>(d, groups(2), s);
+        return launch_attn_variant<64, 1, 4, kEveryColumn>(d, groups(1), s);
+    }
+    // with a list: a chunk whole, or in parts of 64 rows
+    const int blocks = p.c / 64;
+    if (attn_rounds_cost(E, 1, units * blocks) < attn_rounds_cost(E, blocks, units)) {
+        AttnParams d = p;
+        d.parts = blocks;
+        return E == 128 ? launch_attn_variant<128, 1, 4>(d, units * blocks, s) : launch_attn_variant<64, 1, 4>(d, units * blocks, s);
     }
     if (E == 128 && p.c == 192) return launch_attn_variant<128, 3, 4>(p, units, s);
     if (E == 128 && p.c == 128) return launch_attn_variant<128, 2, 4>(p, units, s);
@@ -848,7 +890,7 @@ extern "C" int32_t chipmunk_attn_sparse_delta(const uint16_t* q, const uint16_t*
     p.q = q; p.k = k; p.v = v; p.base = base; p.out = out; p.idx = idx; p.counts = counts;
     p.row_m = nullptr; p.row_l = nullptr;
     p.prev_m = nullptr; p.prev_l = nullptr; p.colsum = nullptr; p.ld_colsum = 0;
-    p.N = N; p.NB = NB; p.c = c; p.k_stride = k_stride;
+    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.k_stride = k_stride;
     p.sl2 = softmax_scale * 1.4426950408889634f;
     p.o_scale = o_scale;
     return launch_attn(p, E, units, (hipStream_t)stream);
@@ -872,7 +914,7 @@ extern "C" int32_t chipmunk_attn_block_sparse_delta(const uint16_t* q, const uin
     p.q = q; p.k = k; p.v = v; p.base = base; p.out = out; p.idx = blocks; p.counts = block_counts;
     p.row_m = nullptr; p.row_l = nullptr;
     p.prev_m = nullptr; p.prev_l = nullptr; p.colsum = nullptr; p.ld_colsum = 0;
-    p.N = N; p.NB = NB; p.c = c; p.k_stride = kb_stride;
+    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.k_stride = kb_stride;
     p.sl2 = softmax_scale * 1.4426950408889634f;
     p.o_scale = o_scale;
     return launch_attn_blocks(p, E, units, (hipStream_t)stream);
@@ -901,7 +943,7 @@ extern "C" int32_t chipmunk_attn_dense(const uint16_t* q, const uint16_t* k, con
     p.row_m = colsum ? (float*)ws : nullptr;
     p.row_l = colsum ? (float*)ws + (int64_t)B * H * N : nullptr;
     p.prev_m = nullptr; p.prev_l = nullptr; p.colsum = nullptr; p.ld_colsum = 0;
-    p.N = N; p.NB = NB; p.c = c; p.k_stride = 0;
+    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.k_stride = 0;
     p.sl2 = softmax_scale * 1.4426950408889634f;
     p.o_scale = 1.f;
     int32_t st = launch_attn(p, E, units, s);
@@ -948,7 +990,7 @@ extern "C" int32_t chipmunk_attn_dense_colsum_stale(const uint16_t* q, const uin
     p.q = q; p.k = k; p.v = v; p.base = nullptr; p.out = out; p.idx = nullptr; p.counts = nullptr;
     p.row_m = new_m; p.row_l = new_l;
     p.prev_m = prev_m; p.prev_l = prev_l; p.colsum = colsum; p.ld_colsum = ld_colsum;
-    p.N = N; p.NB = NB; p.c = c; p.k_stride = 0;
+    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.k_stride = 0;
     p.sl2 = softmax_scale * 1.4426950408889634f;
     p.o_scale = 1.f;
     return launch_attn_fused(p, E, units, (hipStream_t)stream);

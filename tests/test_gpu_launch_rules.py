@@ -45,3 +45,38 @@ def test_column_sums_in_pieces_of_the_keys(cm, oracle, N, E, c):
     got = D.cpu().numpy()
     assert rel_err(got[..., :N].astype(np.float64), ref) <= SUM_TOL
     assert (got[..., N:] == -1.0).all()
+
+
+@pytest.mark.parametrize("E", [64, 128])
+@pytest.mark.parametrize("H,N", [(2, 1), (3, 130), (200, 256), (400, 192), (200, 190), (400, 65)])
+def test_dense_attention_in_workgroups_of_64_128_and_192_rows(cm, oracle, E, H, N):
+    """Without a list a workgroup takes one, two or three blocks of 64 rows, by the number of workgroups; c is 128 here
+    and 192 there, which no longer decides it.  The ends of the sequence leave waves and whole blocks without rows."""
+    q, k, v = recipes.attn_inputs(1, H, N, E, 22, DEV)
+    scale = 1 / math.sqrt(E)
+    c = 128 if N % 2 else 192
+    out, base = torch.full_like(q, 7.0), recipes.attn_base(tuple(q.shape), N, "unit", 22, DEV)
+    cm.attn_sparse_delta(q, k, v, None, None, base, out, c, scale, -1.0)
+    basen = si.np_f32(base).astype(np.float64)
+    dense = oracle.attn_dense(si.np_f32(q), si.np_f32(k), si.np_f32(v), c, scale)
+    assert rel_err(si.np_f32(out), basen - dense, dense) <= REL_TOL
+
+
+@pytest.mark.parametrize("H,N,E,c,k", [(1, 193, 128, 192, 70), (2, 650, 64, 192, 33), (2, 300, 128, 128, 129),
+                                       (110, 320, 64, 128, 20), (200, 384, 128, 192, 9), (200, 500, 128, 192, 70)])
+def test_column_lists_walked_by_parts_of_a_chunk(cm, oracle, H, N, E, c, k):
+    """Few chunks: a workgroup per 64 rows, all of a chunk walking its one list; the last chunk ends before its last
+    part.  The last three cases have enough chunks to be walked whole."""
+    q, kk, v = recipes.attn_inputs(1, H, N, E, 23, DEV)
+    scale, NB = 1 / math.sqrt(E), -(-N // c)
+    base = recipes.attn_base(tuple(q.shape), k, "delta", 23, DEV)
+    idx, counts = recipes.attn_indices(H * NB, N, k, 23, DEV, ragged=True)
+    idx, counts = idx.view(1, H, NB, k), counts.view(1, H, NB)
+    out = torch.full_like(q, 7.0)
+    cm.attn_sparse_delta(q, kk, v, idx, counts, base, out, c, scale, 1.0)
+    basen = si.np_f32(base).astype(np.float64)
+    ref = oracle.attn_sparse_delta(si.np_f32(q), si.np_f32(kk), si.np_f32(v), idx.cpu().numpy(), counts.cpu().numpy(),
+                                   basen, c, scale, 1.0)
+    assert rel_err(si.np_f32(out), ref, ref - basen) <= REL_TOL
+    cm.attn_sparse_delta(q, kk, v, idx, counts, base, base, c, scale, 1.0)      # in place
+    assert torch.equal(base, out)
