@@ -52,15 +52,10 @@ constexpr int kStages = 2 * kTilesPerStep;  // tile buffers (K tile + V tile eac
 constexpr int kColsumTileRows = 64;   // the column-sum kernel keeps 64-row tiles, double buffered
 constexpr float kRescaleSlack = 8.f;  // running max may lag the true max by 2^8 before a rescale
 
-// XOR swizzle of the 16-byte chunk position inside a row of the LDS tile.  For
-// 256-byte rows the map (a GF(2)-linear function of the row's low four bits) was
-// picked by measurement on gfx950 among all such maps: it is free of bank
-// conflicts both for the 128-bit K reads (16 rows, one chunk each per 16 lanes)
-// and for the transposing 64-bit V reads (4 rows x 32 bytes per 16 lanes).
+// XOR swizzle of the 16-byte chunk position inside a row of the LDS tile
 template <int E>
 __device__ __forceinline__ int swizzle(int row) {
-    if (E == 128) return ((row & 1) << 1) ^ (((row >> 1) & 1) * 9) ^ (((row >> 2) & 1) << 2) ^ (((row >> 3) & 1) << 1);
-    return (row >> 1) & 7;
+    return E == 128 ? swizzle_rows16(row) : (row >> 1) & 7;
 }
 
 template <int E, int NQB>
@@ -76,15 +71,6 @@ struct AttnState {
 // the kernel can software-pipeline them: scores of tile t+1 (MFMA) are issued
 // next to the exponentials of tile t (VALU), and the max bookkeeping of tile t+1
 // (VALU) next to the P.V products of tile t (MFMA).
-
-// LDS reads take byte addresses in registers (the LDS base is already added) plus compile-time offsets, so that the
-// offsets become the immediate field of the read instead of an address computation per read.
-__device__ __forceinline__ bf16x8 lds_read_b128(uint32_t addr) {
-    return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>((uintptr_t)addr);
-}
-__device__ __forceinline__ short4v lds_read_tr16_at(uint32_t addr) {
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<__attribute__((address_space(3))) short4v*>((uintptr_t)addr));
-}
 
 // S^T = K Q^T - m for one tile: raw scores relative to the reference max (the MFMA adds -m for free where a
 // separate subtraction would cost one vector instruction per score).  kaddr[es]: the lane's read address for

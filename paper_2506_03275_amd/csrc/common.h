@@ -97,6 +97,22 @@ __device__ __forceinline__ short4v lds_read_tr16(const void* lds_ptr) {
         (__attribute__((address_space(3))) short4v*)(lds_ptr));
 }
 
+// LDS reads that take byte addresses in registers (the LDS base is already added) plus compile-time offsets, so that the
+// offsets become the immediate field of the read instead of an address computation per read.
+__device__ __forceinline__ bf16x8 lds_read_b128(uint32_t addr) {
+    return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>((uintptr_t)addr);
+}
+__device__ __forceinline__ short4v lds_read_tr16_at(uint32_t addr) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<__attribute__((address_space(3))) short4v*>((uintptr_t)addr));
+}
+
+// XOR swizzle of the 16-byte chunk position inside a 256-byte row of an LDS tile: a GF(2)-linear function of the row's low
+// four bits, picked by measurement on gfx950 among all such maps.  It is free of bank conflicts both for 128-bit reads
+// (16 rows, one chunk each per 16 lanes) and for the transposing 64-bit reads (4 rows x 32 bytes per 16 lanes).
+__device__ __forceinline__ int swizzle_rows16(int row) {
+    return ((row & 1) << 1) ^ (((row >> 1) & 1) * 9) ^ (((row >> 2) & 1) << 2) ^ (((row >> 3) & 1) << 1);
+}
+
 // max / sum over the four 16-lane rows of a wave, result in every lane
 __device__ __forceinline__ float rows4_max(float x) {
     uint32_t u = __float_as_uint(x);

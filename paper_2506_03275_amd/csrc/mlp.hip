@@ -21,6 +21,7 @@
 // writes a_cache only and GEMM2 reads its A operand from a_cache and adds b2.
 #include "common.h"
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -75,10 +76,14 @@ static int xcd_grid_size_grouped(int col_tiles, int units) {
 template <int ACT>
 __device__ __forceinline__ float gelu(float x) {
     if (ACT == CHIPMUNK_ACT_GELU_ERF) return 0.5f * x * (1.f + erff(x * 0.70710678118654752f));
-    // tanh form: 0.5 x (1 + tanh(u)) = x / (1 + exp(-2u)),  u = sqrt(2/pi) (x + 0.044715 x^3)
-    float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
-    return x * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-2.885390081777927f * u));  // v_rcp_f32: 1 ulp, the result is rounded to bf16
+    // tanh form: 0.5 x (1 + tanh(u)) = x / (1 + exp(-2u)),  u = sqrt(2/pi) (x + 0.044715 x^3);  -2 u log2(e) = x (A + B x^2)
+    const float t = x * __builtin_fmaf(x * x, -0.10294324f, -2.3022082f);
+    return x * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(t));  // v_rcp_f32: 1 ulp, the result is rounded to bf16
 }
+
+}  // namespace chipmunk
+#include "mlp_dense.h"
+namespace chipmunk {
 
 struct Gemm1Params {
     const uint16_t* x;       // [B, N, ldx] rows of K elements
@@ -751,6 +756,44 @@ static int32_t launch_gemm2(Gemm2Params p, int col_tiles, int units, hipStream_t
     return launch_status();
 }
 
+// Whether a dense GEMM takes the 256 x 256 tiles of mlp_dense.h or the chunk's tiles (192 or 128 x 128).  Both are priced as
+// whole rounds of workgroups over the chip plus a last one that is partly filled, in us per contraction step, with
+// figures measured from 500 x 1024 x 4096 to 18 000 x 5120 x 13 824 (tokens x D x F):
+//   first GEMM, one workgroup per CU:      256 x 256: 1.5 a round, and 12 us a tile for its ends;
+//                                          192 x 128: 0.9 and 6;  128 x 128: 0.68 and 6
+//   second GEMM, 256 x 256: 1.8 a round, 1.25 with at most half the CUs;
+//                192 x 128 (two per CU): 1.75, 0.9 with at most one per CU;  128 x 128: 1.3, 0.7
+// (kernel times, large against small tiles: first GEMM 500 x 1024 x 4096: 36 and 21 us, 2304 x 1152 x 4608: 35 and 47,
+// 2304 x 3072 x 12 288: 158 and 225; second: 1000 x 2048 x 8192: 158 and 107, 3500 x 5120 x 13 824: 626 and 611,
+// 7000 x 2048 x 8192: 255 and 326).
+static bool large_tiles_pay(bool second, int B, int N, int D, int F, int c) {
+    const int64_t chunks = (N + c - 1) / c, large_n = (N + kDenseTile - 1) / kDenseTile;
+    const int width = second ? D : F, steps = (second ? F : D) / kBK;
+    const int64_t small = B * chunks * ((width + kBN - 1) / kBN), large = B * large_n * ((width + kDenseTile - 1) / kDenseTile);
+    auto rounds = [](int64_t tiles, int slots) { return (double)((tiles + slots - 1) / slots); };
+    if (B > 65535) return false;   // the large tiles take the batch from the second grid dimension
+    if (!second) return rounds(large, 256) * (1.5 * steps + 12) < rounds(small, 256) * ((c == 192 ? 0.9 : 0.68) * steps + 6);
+    auto cost = [](int64_t tiles, int slots, double whole, double half) {
+        const int64_t last = tiles % slots;
+        return (double)(tiles / slots) * whole + (last == 0 ? 0. : last <= slots / 2 ? half : whole);
+    };
+    return cost(large, 256, 1.8, 1.25) < (c == 192 ? cost(small, 512, 1.75, 0.9) : cost(small, 512, 1.3, 0.7));
+}
+
+template <bool SECOND>
+static int32_t launch_dense_gemm(DenseGemmParams p, int B, hipStream_t s) {
+    const int tokens = (p.N + kDenseTile - 1) / kDenseTile;
+    p.tiles_p = SECOND ? (p.D + kDenseTile - 1) / kDenseTile : tokens;
+    p.tiles_q = SECOND ? tokens : (p.F + kDenseTile - 1) / kDenseTile;
+    // set at every launch: the attribute is kept per device (a flag remembered here would not be)
+    if (hipFuncSetAttribute((const void*)mlp_dense_gemm_kernel<SECOND>, hipFuncAttributeMaxDynamicSharedMemorySize, kDenseLds) !=
+        hipSuccess)
+        return CHIPMUNK_ERR_LAUNCH;
+    const int per_xcd = (p.tiles_p * p.tiles_q + 7) / 8;
+    hipLaunchKernelGGL((mlp_dense_gemm_kernel<SECOND>), dim3((unsigned)(per_xcd * 8), (unsigned)B), dim3(512), kDenseLds, s, p);
+    return launch_status();
+}
+
 static int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
 static int32_t check_mlp_shapes(int B, int N, int D, int F, int c) {
@@ -875,16 +918,27 @@ extern "C" int32_t chipmunk_mlp_dense(const uint16_t* x, const uint16_t* w1, con
         return CHIPMUNK_ERR_ALIGN;
     const int NB = (N + c - 1) / c, units = B * NB;
     hipStream_t s = (hipStream_t)stream;
+    DenseGemmParams g;
+    g.x = x; g.w1 = w1; g.w2 = w2; g.a_cache = a_cache; g.out = out; g.a_ld = a_ld;
+    g.N = N; g.D = D; g.F = F; g.act = act;
 
-    Gemm1Params g1;
-    g1.x = x; g1.w1 = w1; g1.b1 = b1; g1.idx = nullptr; g1.counts = nullptr; g1.a_cache = a_cache;
-    g1.delta_t = nullptr; g1.act_t = nullptr; g1.out_f32 = nullptr; g1.a_ld = a_ld;
-    g1.N = N; g1.NB = NB; g1.D = D; g1.F = F; g1.K = D; g1.ldx = D;
-    g1.k_stride = F; g1.k_pad = F; g1.act = act; g1.ksplit = 1;
-    st = c == 192 ? launch_gemm1<192, kDenseAct>(g1, (F + kBN - 1) / kBN, units, s)
-                  : launch_gemm1<128, kDenseAct>(g1, (F + kBN - 1) / kBN, units, s);
+    if (large_tiles_pay(false, B, N, D, F, c)) {
+        g.bias = b1;
+        st = launch_dense_gemm<false>(g, B, s);
+    } else {
+        Gemm1Params g1;
+        g1.x = x; g1.w1 = w1; g1.b1 = b1; g1.idx = nullptr; g1.counts = nullptr; g1.a_cache = a_cache;
+        g1.delta_t = nullptr; g1.act_t = nullptr; g1.out_f32 = nullptr; g1.a_ld = a_ld;
+        g1.N = N; g1.NB = NB; g1.D = D; g1.F = F; g1.K = D; g1.ldx = D;
+        g1.k_stride = F; g1.k_pad = F; g1.act = act; g1.ksplit = 1;
+        st = c == 192 ? launch_gemm1<192, kDenseAct>(g1, (F + kBN - 1) / kBN, units, s)
+                      : launch_gemm1<128, kDenseAct>(g1, (F + kBN - 1) / kBN, units, s);
+    }
     if (st != CHIPMUNK_OK) return st;
-
+    if (large_tiles_pay(true, B, N, D, F, c)) {
+        g.bias = b2;
+        return launch_dense_gemm<true>(g, B, s);
+    }
     Gemm2Params g2;
     g2.a_t = a_cache; g2.w2 = w2; g2.bias = b2; g2.idx = nullptr; g2.counts = nullptr; g2.o = out;
     g2.a_ld = a_ld; g2.N = N; g2.NB = NB; g2.D = D; g2.F = F; g2.k_stride = F; g2.k_pad = F; g2.dense = 1;

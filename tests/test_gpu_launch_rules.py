@@ -80,3 +80,25 @@ def test_column_lists_walked_by_parts_of_a_chunk(cm, oracle, H, N, E, c, k):
     assert rel_err(si.np_f32(out), ref, ref - basen) <= REL_TOL
     cm.attn_sparse_delta(q, kk, v, idx, counts, base, base, c, scale, 1.0)      # in place
     assert torch.equal(base, out)
+
+
+@pytest.mark.parametrize("B,N,D,F,c,act,bias", [
+    (1, 521, 128, 11328, 192, 1, True),      # first GEMM on 256 x 256 tiles: two steps, neurons and tokens ragged
+    (2, 300, 256, 9216, 192, 0, False),      # two batches, no bias
+    (1, 8300, 1152, 192, 128, 0, True),      # second GEMM: three steps, half a tile of columns missing, tokens ragged
+    (1, 8301, 1152, 64, 128, 1, False),      # one step
+    (2, 4150, 1152, 128, 128, 1, True),
+])
+def test_dense_mlp_on_large_tiles(cm, oracle, B, N, D, F, c, act, bias):
+    """The dense GEMMs whose problem is large enough for 256 x 256 tiles; the cache cells past N stay as they are."""
+    x, _, w1, b1, w2, b2 = recipes.mlp_inputs(B, N, D, F, 24, DEV)
+    if not bias:
+        b1, b2 = torch.zeros_like(b1), torch.zeros_like(b2)
+    a_ld = -(-N // 8) * 8 + 8
+    out = torch.empty_like(x)
+    a_cache = torch.full((B, F, a_ld), 3.0, dtype=torch.bfloat16, device=DEV)
+    cm.mlp_dense(x, w1, b1 if bias else None, w2, b2 if bias else None, out, a_cache, c, act)
+    ref, a_ref, _ = oracle.mlp_dense(si.np_f32(x), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2), si.np_f32(b2), c, act, a_ld=a_ld)
+    assert rel_err(si.np_f32(a_cache)[..., :N], a_ref[..., :N]) <= REL_TOL
+    assert torch.all(a_cache[..., N:] == 3.0)
+    assert rel_err(si.np_f32(out), ref) <= REL_TOL
