@@ -2,12 +2,12 @@
 // idx = TopK(|T - T_m|)) for gfx950.
 //
 // One workgroup per row.  Scores are mapped to order-preserving 32-bit keys.
-// The k-th largest key (the threshold) is found by a most-significant-digit
-// radix select (digits of up to 11 bits, LDS histograms, wave-level prefix
-// sums on DPP); the selected columns are every column above the threshold plus
-// the first columns equal to it, written in ascending column order.
-//   - Rows of up to kLdsCols columns are read from HBM once and kept in LDS as
-//     keys; every pass runs on LDS.
+// The k-th largest key (the threshold) is found exactly, in long rows by a
+// most-significant-digit radix select (digits of up to 11 bits, LDS histograms,
+// wave-level prefix sums on DPP); the selected columns are every column above
+// the threshold plus the first columns equal to it, written in ascending order.
+//   - Rows of up to kRegisterCols columns are read from HBM once and kept in
+//     registers as keys; their threshold is found by halving the range of keys.
 //   - Longer rows (the attention column sums, 10^5 columns) are read from HBM
 //     once as well: two pivots taken from a 4096-score sample bracket the
 //     threshold; the single pass over the row marks the columns above the
@@ -21,10 +21,10 @@
 #include "common.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace chipmunk {
 
-constexpr int kLdsCols = 14208;   // 55.5 KB of keys + 8 KB histogram fit one 64 KB LDS allocation
 constexpr int kBins = 2048;
 constexpr float kPivotSigmas = 3.5f;  // slack of the sample pivots around the threshold, in standard deviations
 
@@ -121,20 +121,6 @@ struct GlobalRowKeys {
         key[2] = score_key(r.c.z, r.p.z, HAS_PREV);
         key[3] = score_key(r.c.w, r.p.w, HAS_PREV);
         return max(0, min(4, C - 4 * j4));
-    }
-};
-
-// Keys already in LDS (a whole short row, a sample, or the candidates of a long row).
-struct LdsKeys {
-    const uint32_t* data;
-    int n;
-    typedef uint4 Raw;
-    __device__ __forceinline__ Raw load(int j4) const {
-        return *reinterpret_cast<const uint4*>(data + 4 * min(j4, ((n + 3) >> 2) - 1));
-    }
-    __device__ __forceinline__ int keys(const Raw& r, int j4, uint32_t (&key)[4]) const {
-        key[0] = r.x; key[1] = r.y; key[2] = r.z; key[3] = r.w;
-        return max(0, min(4, n - 4 * j4));
     }
 };
 
@@ -302,40 +288,212 @@ __device__ __forceinline__ void emit_selected(const Src& src, int C, uint32_t th
     }
 }
 
-// Rows that fit LDS.
-template <bool HAS_PREV>
-__global__ __launch_bounds__(256) void topk_short_rows_kernel(const float* __restrict__ cur,
-                                                              const float* __restrict__ prev, int C, int64_t ld,
-                                                              int k, int32_t* __restrict__ idx,
-                                                              int32_t* __restrict__ counts, int k_stride) {
-    // dynamic LDS, sized to the row so that short rows leave room for more workgroups per CU:
-    // kBins + 16 words, then the row's keys (a multiple of four)
-    extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
-    SelectScratch sc{smem, smem + kBins, smem + kBins + 8, 0};
-    uint32_t* s_keys = smem + kBins + 16;
-    const int tid = threadIdx.x;
+// Rows of up to kRegisterCols columns: read once, kept as keys in the registers of the row's two, four or eight waves (U
+// groups of 256 columns each, four keys per lane and group).
+//
+// The threshold is found by halving the range of keys that can hold it: a step counts the keys at or above a pivot (a
+// compare and an add per key, a wave sum, one barrier) and ends as soon as at most kLastKeys keys are left between the
+// bounds (five to eight steps for column sums and neuron scores, 32 at most), which one wave then finishes by
+// itself with ballots.  No step depends on how the scores are spread over their bits: a histogram of the leading digit
+// sends most of a wave's atomics to a handful of bins.
+// What bounds it: with few rows a row's chain of loads and barriers, with many the issue slots of the counting; 26 to 77
+// registers per lane and about 1 KB of LDS keep 24 to 32 waves on a CU, where rows kept in LDS (57 KB at 12 288 columns)
+// allowed two workgroups, so that 602 rows took two rounds.  Against histograms of 11-bit digits over keys in LDS: 602 rows
+// of 12 288 with previous scores 36.8 -> 22.9 us, 14 448 x 4608 150 -> 105 us, 4000 x 12 288 (30 % kept) 160 -> 95 us,
+// 5000 x 1024 30.8 -> 14.4 us.
+constexpr int kRegisterCols = 8 * 7 * 256;
+constexpr int kLastKeys = 256;
+
+// sum and maximum over the wave's lanes
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    return (uint32_t)(__builtin_amdgcn_readlane((int)v, 15) + __builtin_amdgcn_readlane((int)v, 31) +
+                      __builtin_amdgcn_readlane((int)v, 47) + __builtin_amdgcn_readlane((int)v, 63));
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));
+    return max(max((uint32_t)__builtin_amdgcn_readlane((int)v, 15), (uint32_t)__builtin_amdgcn_readlane((int)v, 31)),
+               max((uint32_t)__builtin_amdgcn_readlane((int)v, 47), (uint32_t)__builtin_amdgcn_readlane((int)v, 63)));
+}
+
+template <bool HAS_PREV, int NT, int U>
+__global__ __launch_bounds__(NT, U >= 6 ? 6 : 8) void topk_register_rows_kernel(const float* __restrict__ cur,
+                                                                            const float* __restrict__ prev, int C, int64_t ld,
+                                                                            int k, int32_t* __restrict__ idx,
+                                                                            int32_t* __restrict__ counts, int k_stride) {
+    constexpr int NW = NT / 64;
+    __shared__ __attribute__((aligned(16))) uint32_t s_set[2][2 * NW];   // per-wave totals, two sets used in turn
+    __shared__ uint32_t s_last[kLastKeys];
+    __shared__ uint32_t s_found[3];                                      // threshold, how many equal to it; candidates
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t row = blockIdx.x;
-    if (tid == 0) counts[row] = k;
+    if (tid == 0) {
+        counts[row] = k;
+        s_found[2] = 0;
+    }
     if (k == 0) return;
-    GlobalRowKeys<HAS_PREV> g{cur + row * ld, HAS_PREV ? prev + row * ld : nullptr, C};
-    const int C4 = (C + 3) >> 2;
-    constexpr int U = 4;
-    for (int base4 = 0; base4 < C4; base4 += 256 * U) {
-        typename GlobalRowKeys<HAS_PREV>::Raw raw[U];
-#pragma unroll
-        for (int u = 0; u < U; u++) raw[u] = g.load(base4 + u * 256 + tid);
+    const float* c_row = cur + row * ld;
+    const float* p_row = HAS_PREV ? prev + row * ld : nullptr;
+    int32_t* out = idx + row * (int64_t)k_stride;
+
+    // wave w holds the groups [w per_wave, (w + 1) per_wave) of 256 columns; a column that does not exist has key 0
+    const int groups = (C + 255) >> 8, per_wave = (groups + NW - 1) / NW, last4 = ((C + 3) >> 2) - 1;
+    uint32_t key[U][4];
+    {
+        float4 cv[U], pv[U];
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            const int j4 = base4 + u * 256 + tid;
-            uint32_t key[4];
-            if (g.keys(raw[u], j4, key) > 0)
-                *reinterpret_cast<uint4*>(&s_keys[4 * j4]) = uint4{key[0], key[1], key[2], key[3]};
+            const int j4 = min((w * per_wave + u) * 64 + lane, last4);
+            cv[u] = *reinterpret_cast<const float4*>(c_row + 4 * j4);
+            if constexpr (HAS_PREV) pv[u] = *reinterpret_cast<const float4*>(p_row + 4 * j4);
+            else pv[u] = float4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int exist = u < per_wave ? C - ((w * per_wave + u) * 256 + 4 * lane) : 0;
+            key[u][0] = exist > 0 ? score_key(cv[u].x, pv[u].x, HAS_PREV) : 0u;
+            key[u][1] = exist > 1 ? score_key(cv[u].y, pv[u].y, HAS_PREV) : 0u;
+            key[u][2] = exist > 2 ? score_key(cv[u].z, pv[u].z, HAS_PREV) : 0u;
+            key[u][3] = exist > 3 ? score_key(cv[u].w, pv[u].w, HAS_PREV) : 0u;
         }
     }
-    LdsKeys src{s_keys, C};
-    uint32_t take_eq;
-    uint32_t thr = radix_select<256>(src, C, (uint32_t)k, sc, &take_eq);
-    emit_selected<256>(src, C, thr, take_eq, idx + row * (int64_t)k_stride, sc);
+    int flip = 0;   // a set is written again only behind the barrier in between, which no thread passes before it has read it
+    uint32_t lo, hi;
+    {
+        uint32_t top = 0, bottom = 0;   // largest key, largest complement of an existing key
+#pragma unroll
+        for (int u = 0; u < U; u++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                top = max(top, key[u][e]);
+                bottom = max(bottom, key[u][e] != 0 ? ~key[u][e] : 0u);
+            }
+        top = wave_max(top);
+        bottom = wave_max(bottom);
+        if (lane == 0) {
+            s_set[0][w] = top;
+            s_set[0][NW + w] = bottom;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NW; i++) {
+            top = max(top, s_set[0][i]);
+            bottom = max(bottom, s_set[0][NW + i]);
+        }
+        hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)top);
+        lo = ~(uint32_t)__builtin_amdgcn_readfirstlane((int)bottom);
+        flip = 1;
+    }
+    // invariant: at least k keys are >= lo (n_from of them), fewer than k are > hi (n_above of them)
+    uint32_t n_from = (uint32_t)C, n_above = 0;
+#pragma unroll 1
+    while (lo != hi && n_from - n_above > (uint32_t)kLastKeys) {
+        const uint32_t pivot = hi - ((hi - lo) >> 1);   // lo < pivot <= hi
+        uint32_t n = 0;
+#pragma unroll
+        for (int u = 0; u < U; u++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) n += key[u][e] >= pivot;
+        n = wave_sum(n);
+        if (lane == 0) s_set[flip][w] = n;
+        __syncthreads();
+        n = 0;
+#pragma unroll
+        for (int i = 0; i < NW; i++) n += s_set[flip][i];
+        n = (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
+        flip ^= 1;
+        if (n >= (uint32_t)k) {
+            lo = pivot;
+            n_from = n;
+        } else {
+            hi = pivot - 1;
+            n_above = n;
+        }
+    }
+    uint32_t thr = lo, take_eq = (uint32_t)k - n_above;
+    if (lo != hi) {
+        // the keys between the bounds, in any order
+        const uint32_t span = hi - lo;
+        uint32_t mine = 0;
+#pragma unroll
+        for (int u = 0; u < U; u++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) mine += key[u][e] - lo <= span;
+        const uint32_t inc = wave_inclusive_scan(mine);
+        uint32_t at = 0;
+        if (lane == 63) at = atomicAdd(&s_found[2], inc);
+        at = (uint32_t)__builtin_amdgcn_readlane((int)at, 63) + inc - mine;
+#pragma unroll
+        for (int u = 0; u < U; u++)
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+                if (key[u][e] - lo <= span) s_last[at++] = key[u][e];
+        __syncthreads();
+        if (w == 0) {
+            const uint32_t n_last = n_from - n_above, want = (uint32_t)k - n_above;
+            uint32_t last[kLastKeys / 64];
+#pragma unroll
+            for (int i = 0; i < kLastKeys / 64; i++) last[i] = (uint32_t)(i * 64 + lane) < n_last ? s_last[i * 64 + lane] : 0u;
+            uint32_t above = 0;
+            while (lo != hi) {
+                const uint32_t pivot = hi - ((hi - lo) >> 1);
+                uint32_t n = 0;
+#pragma unroll
+                for (int i = 0; i < kLastKeys / 64; i++) n += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(last[i] >= pivot));
+                if (n >= want) {
+                    lo = pivot;
+                } else {
+                    hi = pivot - 1;
+                    above = n;
+                }
+            }
+            if (lane == 0) {
+                s_found[0] = lo;
+                s_found[1] = want - above;
+            }
+        }
+        __syncthreads();
+        thr = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_found[0]);
+        take_eq = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_found[1]);
+    }
+    // every column above the threshold and the first take_eq columns that equal it, ascending
+    uint32_t cnt[U], inc[U], total = 0;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        uint32_t n = 0;
+#pragma unroll
+        for (int e = 0; e < 4; e++) n += key[u][e] > thr ? 1u : key[u][e] == thr ? 0x10000u : 0u;
+        cnt[u] = n;
+        inc[u] = wave_inclusive_scan(n);
+        total += (uint32_t)__builtin_amdgcn_readlane((int)inc[u], 63);
+    }
+    if (lane == 0) s_set[flip][w] = total;
+    __syncthreads();
+    uint32_t before = 0;
+#pragma unroll
+    for (int i = 0; i < NW; i++) before += i < w ? s_set[flip][i] : 0u;
+    before = (uint32_t)__builtin_amdgcn_readfirstlane((int)before);
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const uint32_t mine = before + inc[u] - cnt[u];
+        uint32_t gt = mine & 0xffffu, eq = mine >> 16;
+        const int col = (w * per_wave + u) * 256 + 4 * lane;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const bool is_gt = key[u][e] > thr, is_eq = key[u][e] == thr;
+            if (is_gt || (is_eq && eq < take_eq)) out[gt + min(eq, take_eq)] = col + e;
+            gt += is_gt;
+            eq += is_eq;
+        }
+        before += (uint32_t)__builtin_amdgcn_readlane((int)inc[u], 63);
+    }
 }
 
 // The candidates of a long row are (key, column) pairs.  Their keys:
@@ -820,12 +978,39 @@ extern "C" int32_t chipmunk_topk_cols(const float* cur, const float* prev, int R
         (reinterpret_cast<uintptr_t>(counts) & 3u))
         return CHIPMUNK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)stream;
-    const dim3 grid((unsigned)R), block(256), block_long(kLongThreads);
+    const dim3 grid((unsigned)R), block_long(kLongThreads);
     LongRowPlan plan;
-    if (C <= kLdsCols) {
-        auto kernel = prev ? topk_short_rows_kernel<true> : topk_short_rows_kernel<false>;
-        const size_t lds = (kBins + 16 + (size_t)((C + 3) / 4) * 4) * sizeof(uint32_t);
-        hipLaunchKernelGGL(kernel, grid, block, lds, s, cur, prev, C, ld, k, idx, counts, k_stride);
+    if (C <= kRegisterCols) {
+        // Waves per row: a step costs a wave its share of the counting and about 40 instructions of sums and exchange, so
+        // few waves serve many short rows best, and eight a row whose keys would otherwise fill the registers of four.
+        // Us for 5000 rows of 1024 columns with two, four and eight waves: 14.4, 17.1, 30.9; 14 448 rows of 6500 with
+        // four and eight: 144, 210; 602 rows of 12 288 (with previous scores): 25.9 and 22.9.
+        const int groups = (C + 255) / 256;
+        const int waves = groups <= 4 ? 2 : groups <= 28 ? 4 : 8;
+        const int per_wave = (groups + waves - 1) / waves;
+        auto launch = [&](auto threads, auto u) {
+            constexpr int NT = decltype(threads)::value, U = decltype(u)::value;
+            if (prev)
+                hipLaunchKernelGGL((topk_register_rows_kernel<true, NT, U>), grid, dim3(NT), 0, s, cur, prev, C, ld, k, idx, counts, k_stride);
+            else
+                hipLaunchKernelGGL((topk_register_rows_kernel<false, NT, U>), grid, dim3(NT), 0, s, cur, prev, C, ld, k, idx, counts, k_stride);
+        };
+        std::integral_constant<int, 128> two;
+        std::integral_constant<int, 256> four;
+        std::integral_constant<int, 512> eight;
+        if (waves == 2) {
+            if (per_wave <= 1) launch(two, std::integral_constant<int, 1>{});
+            else launch(two, std::integral_constant<int, 2>{});
+        } else if (waves == 4) {
+            if (per_wave <= 2) launch(four, std::integral_constant<int, 2>{});
+            else if (per_wave <= 3) launch(four, std::integral_constant<int, 3>{});
+            else if (per_wave <= 5) launch(four, std::integral_constant<int, 5>{});
+            else launch(four, std::integral_constant<int, 7>{});
+        } else {
+            if (per_wave <= 5) launch(eight, std::integral_constant<int, 5>{});
+            else if (per_wave <= 6) launch(eight, std::integral_constant<int, 6>{});
+            else launch(eight, std::integral_constant<int, 7>{});
+        }
     } else if (plan_long_rows(C, k, &plan)) {
         auto kernel = plan.sample == 8192
                           ? (prev ? topk_long_rows_kernel<true, true, 8192> : topk_long_rows_kernel<true, false, 8192>)

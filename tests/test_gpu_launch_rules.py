@@ -102,3 +102,35 @@ def test_dense_mlp_on_large_tiles(cm, oracle, B, N, D, F, c, act, bias):
     assert rel_err(si.np_f32(a_cache)[..., :N], a_ref[..., :N]) <= REL_TOL
     assert torch.all(a_cache[..., N:] == 3.0)
     assert rel_err(si.np_f32(out), ref) <= REL_TOL
+
+
+@pytest.mark.parametrize("C", [1, 3, 255, 257, 1024, 1025, 2049, 3073, 5121, 7168, 7169, 10241, 12289, 14336, 14337])
+@pytest.mark.parametrize("kind", ["normal", "constant", "two_values", "few_ulps", "spikes", "wide"])
+def test_topk_of_rows_kept_in_registers(cm, oracle, C, kind):
+    """Both sides of every limit between the instances (and of the long rows), on scores that halving the range of keys
+    finds easy and on scores that it does not: one value, two, a range of a few ulps around a power of two, a few spikes
+    over zeros of both signs, scores of both signs and all exponents with infinities.  Bit-exact, ties to the lower column."""
+    rng = np.random.default_rng([25, C])
+    R, ld = 3, -(-C // 4) * 4
+    if kind == "normal": a = rng.standard_normal((R, C))
+    elif kind == "constant": a = np.full((R, C), -3.25)
+    elif kind == "two_values": a = rng.choice([1.0, 2.0], size=(R, C))
+    elif kind == "few_ulps": a = 1.0 + 2.0 ** -23 * rng.integers(-3, 4, size=(R, C))
+    elif kind == "spikes":
+        a = rng.choice([0.0, -0.0], size=(R, C))
+        a[:, rng.integers(0, C, 5)] = rng.random(5)
+    else:
+        a = rng.standard_normal((R, C)) * 2.0 ** rng.integers(-140, 120, size=(R, C))
+        a[:, ::97], a[:, 5::131] = np.inf, -np.inf
+    a = a.astype(np.float32)
+    b = rng.standard_normal((R, C)).astype(np.float32)
+    cur, prev = (torch.full((R, ld), float("inf"), dtype=torch.float32, device=DEV) for _ in range(2))   # padding is never picked
+    cur[:, :C], prev[:, :C] = torch.from_numpy(a).to(DEV), torch.from_numpy(b).to(DEV)
+    for k in sorted({1, -(-C // 14), C // 2, C} - {0}):
+        for p in (None, b) if kind != "wide" else (None,):
+            idx = torch.full((R, k + 1), -7, dtype=torch.int32, device=DEV)
+            counts = torch.full((R,), -7, dtype=torch.int32, device=DEV)
+            cm.topk_cols(cur[:, :C], None if p is None else prev[:, :C], k, idx, counts)
+            ref_idx, ref_counts = oracle.topk_cols(a, p, k, k_stride=k + 1, idx_fill=-7)
+            assert np.array_equal(idx.cpu().numpy(), ref_idx), k
+            assert np.array_equal(counts.cpu().numpy(), ref_counts)
