@@ -17,8 +17,10 @@
 //        the slow axis (delta^T rows, w2 rows), so both come out of LDS through
 //        the transposing 64-bit read.  Epilogue: fp32 tile through LDS, add to
 //        the cached output in fp32, round once, store in 256-byte runs.
-// The dense MLP is the same two kernels with "every neuron selected": GEMM1
-// writes a_cache only and GEMM2 reads its A operand from a_cache and adds b2.
+// The dense MLP of a small problem is the same two kernels with "every neuron
+// selected": GEMM1 writes a_cache only and GEMM2 reads its A operand from a_cache
+// and adds b2.  Large ones and the scores GEMM have tiles of their own
+// (mlp_dense.h).
 #include "common.h"
 
 #include <algorithm>
@@ -30,7 +32,7 @@ namespace chipmunk {
 constexpr int kBN = 128;  // neurons (GEMM1) or output columns (GEMM2) per workgroup
 constexpr int kBK = 64;   // contraction tile
 
-enum Gemm1Mode { kSparseDelta = 0, kDenseAct = 1, kPlainF32 = 2 };
+enum Gemm1Mode { kSparseDelta = 0, kDenseAct = 1 };
 
 // Workgroups are dispatched to the eight XCDs round-robin by linear id, and each
 // XCD has its own L2.  The tiles of one token chunk share that chunk's x rows
@@ -86,7 +88,7 @@ __device__ __forceinline__ float gelu(float x) {
 namespace chipmunk {
 
 struct Gemm1Params {
-    const uint16_t* x;       // [B, N, ldx] rows of K elements
+    const uint16_t* x;       // [B, N, D]
     const uint16_t* w1;      // [F, D]
     const uint16_t* b1;      // [F] or null
     const int32_t* idx;      // [units, k_stride] or null (dense)
@@ -95,25 +97,22 @@ struct Gemm1Params {
     uint16_t* delta_t;       // workspace [units, k_pad, BM]
     uint16_t* act_t;         // null, or workspace [units, k_pad, BM]: the new activations go here (same layout as
                              // delta_t) instead of into a_cache; the second GEMM's launch writes them back
-    float* out_f32;          // kPlainF32: [B*N, F]
     int64_t a_ld;
-    int N, NB, D, F, K, ldx; // K = contraction length (D, or 2D for the split-precision scores GEMM)
+    int N, NB, D, F;
     int k_stride, k_pad, act;
     int col_tiles, units;    // launch geometry (see xcd_tile_of_block)
-    int ksplit;              // kPlainF32 only: the contraction is cut in ksplit pieces, one workgroup each,
-                             // whose partial results go to out_f32 + piece * N * F (summed by a second kernel)
 };
 
-// NS tile buffers: NS - 1 contraction steps are in flight while one is consumed.  The column-sparse and the dense
-// form run with three (120 KB, one workgroup per CU): measured against two buffers and two workgroups per CU,
-// which keep the same number of bytes in flight, the MLP delta takes 11 % less time and the dense MLP 9 % less.
-// The scores GEMM (few, short workgroups) keeps two.
-template <int BM, int MODE, int NS, bool LOADER>
-__global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : 2) void mlp_gemm1_kernel(Gemm1Params p) {
-    // LOADER: a fifth wave issues every tile transfer of the workgroup; the four product waves issue none.  A wave
-    // issues in order, so a transfer that waits for room in the memory pipeline holds up the products behind it.
+// Three tile buffers: two contraction steps are in flight while one is consumed (120 KB, one workgroup per CU): measured
+// against two buffers and two workgroups per CU, which keep the same number of bytes in flight, the MLP delta takes 11 %
+// less time and the dense MLP 9 % less.
+template <int BM, int MODE>
+__global__ __launch_bounds__(320, 1) void mlp_gemm1_kernel(Gemm1Params p) {
+    // A fifth wave issues every tile transfer of the workgroup; the four product waves issue none.  A wave issues in
+    // order, so a transfer that waits for room in the memory pipeline holds up the products behind it.
     // The loader wave takes part in every barrier of the kernel and in nothing else.
-    constexpr int VW = LOADER ? 4 : 1;             // waves whose share of the transfers one issuing wave carries
+    constexpr int NS = 3;
+    constexpr int VW = 4;                          // waves whose share of the transfers the loader wave carries
     constexpr int MT = BM / 64;                    // 32-row MFMA tiles per wave (wave tile = BM/2 x 64)
     constexpr int XT = BM * 128;                   // bytes of the x tile  [BM][64] bf16
     constexpr int WT = kBN * 128;                  // bytes of the w1 tile [128][64] bf16
@@ -125,19 +124,14 @@ __global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : 2) void mlp_gemm1_
     __shared__ int32_t s_neuron[kBN];
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const bool loader = LOADER && w == 4;          // wave-uniform
+    const bool loader = w == 4;                    // wave-uniform
     const int wm = w >> 1, wn = w & 1;
     const int l32 = lane & 31, h = lane >> 5;
 
-    int unit, col_tile, piece = 0;                 // unit = (batch, token chunk)
-    if (MODE == kPlainF32) {  // few row blocks: plain order, spread over every XCD
-        col_tile = blockIdx.x % p.col_tiles;
-        unit = (blockIdx.x / p.col_tiles) % p.units;
-        piece = blockIdx.x / (p.col_tiles * p.units);
-    } else if (MODE == kDenseAct ? !xcd_tile_of_block_grouped(p.col_tiles, p.units, &unit, &col_tile)
-                                 : !xcd_tile_of_block(p.col_tiles, p.units, &unit, &col_tile)) {
+    int unit, col_tile;                            // unit = (batch, token chunk)
+    if (MODE == kDenseAct ? !xcd_tile_of_block_grouped(p.col_tiles, p.units, &unit, &col_tile)
+                          : !xcd_tile_of_block(p.col_tiles, p.units, &unit, &col_tile))
         return;
-    }
     const int b = unit / p.NB, chunk = unit % p.NB;
     const int row0 = chunk * BM;
     const int col0 = col_tile * kBN;
@@ -162,35 +156,31 @@ __global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : 2) void mlp_gemm1_
     for (int i = 0; i < NIX; i++)
 #pragma unroll
         for (int v = 0; v < VW; v++) {
-            int row = (i * 4 + (LOADER ? v : w)) * 8 + (lane >> 3);
+            int row = (i * 4 + v) * 8 + (lane >> 3);
             int chunk16 = (lane & 7) ^ ((row >> 1) & 7);
             int tok = min(row0 + row, p.N - 1);
-            xoff[i * VW + v] = (uint32_t)tok * (uint32_t)(p.ldx * 2) + chunk16 * 16;
+            xoff[i * VW + v] = (uint32_t)tok * (uint32_t)(p.D * 2) + chunk16 * 16;
         }
 #pragma unroll
     for (int i = 0; i < NIW; i++)
 #pragma unroll
         for (int v = 0; v < VW; v++) {
-            int row = (i * 4 + (LOADER ? v : w)) * 8 + (lane >> 3);
+            int row = (i * 4 + v) * 8 + (lane >> 3);
             int chunk16 = (lane & 7) ^ ((row >> 1) & 7);
             woff[i * VW + v] = (uint32_t)s_neuron[row] * (uint32_t)(p.D * 2) + chunk16 * 16;
         }
-    const uint16_t* xb = p.x + (int64_t)b * p.N * p.ldx;
-    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem) + (LOADER ? 0u : (uint32_t)w * 1024u));
+    const uint16_t* xb = p.x + (int64_t)b * p.N * p.D;
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
 
-    // One of the transfers that bring contraction step kt into buffer `stage`.  Without a loader wave the main loop
-    // issues a wave's NIX + NIW two by two between its products: requested in one burst after the barrier they
-    // queue up in the memory pipeline while the wave issues nothing else.
+    // One of the transfers that bring contraction step kt into buffer `stage`.
     auto issue_piece = [&](int kt, int stage, int j) {   // j < (NIX + NIW) * VW; piece (i, v) = (j / VW, j % VW)
         const int i = j / VW, v = j % VW;
         if (i < NIX) {
             load_global_to_lds_16B(xb + kt * kBK, xoff[j], lds0 + stage * STAGE + i * 4096 + v * 1024);
         } else {
-            const uint16_t* ws = p.w1 + (kt * kBK) % p.D;   // the scores GEMM walks w1's row twice (hi and lo halves of A)
-            load_global_to_lds_16B(ws, woff[j - NIX * VW], lds0 + stage * STAGE + XT + (i - NIX) * 4096 + v * 1024);
+            load_global_to_lds_16B(p.w1 + kt * kBK, woff[j - NIX * VW], lds0 + stage * STAGE + XT + (i - NIX) * 4096 + v * 1024);
         }
     };
-    static_assert(NIX + NIW <= 4 * MT, "one transfer per pair of products");
 
     f32x16 acc[MT][2];
 #pragma unroll
@@ -205,23 +195,22 @@ __global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : 2) void mlp_gemm1_
     const int aoff = (wm * (BM / 2) + l32) * 128 + ((h ^ sw) * 16);
     const int boff = XT + (wn * 64 + l32) * 128 + ((h ^ sw) * 16);
 
-    const int ktiles_all = p.K / kBK;
-    const int kt_begin = MODE == kPlainF32 ? (int)((int64_t)ktiles_all * piece / p.ksplit) : 0;
-    const int kt_end = MODE == kPlainF32 ? (int)((int64_t)ktiles_all * (piece + 1) / p.ksplit) : ktiles_all;
+    const int ktiles = p.D / kBK;
     constexpr int NP = NIX + NIW;
-    if (!LOADER || loader) {
+    if (loader) {
 #pragma unroll
         for (int st = 0; st < NS - 1; st++)
 #pragma unroll
-            for (int j = 0; j < NP * VW; j++) issue_piece(min(kt_begin + st, max(kt_end - 1, kt_begin)), st, j);
+            for (int j = 0; j < NP * VW; j++) issue_piece(min(st, ktiles - 1), st, j);
     }
     int stage = 0;
     static_assert((NS - 2) * NP * VW < 64, "the transfer counter has six bits");
     if (loader) {
-        for (int kt = kt_begin; kt < kt_end; kt++) {
+        for (int kt = 0; kt < ktiles; kt++) {
             wait_vmem_at_most<(NS - 2) * NP * VW>();
             __syncthreads();
-            const int kt_next = min(kt + NS - 1, kt_end - 1);
+            // past the end the last step is fetched again into a buffer nobody reads
+            const int kt_next = min(kt + NS - 1, ktiles - 1);
             const int fill = (stage + NS - 1) % NS;
 #pragma unroll
             for (int j = 0; j < NP * VW; j++) issue_piece(kt_next, fill, j);
@@ -232,14 +221,8 @@ __global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : 2) void mlp_gemm1_
         lds_accesses_then_barrier();
         return;
     }
-    for (int kt = kt_begin; kt < kt_end; kt++) {
-        // The transfers complete in the order they were issued: this step's tiles have landed when no more than
-        // the pieces of the NS - 2 younger steps are outstanding.
-        wait_vmem_at_most<(NS - 2) * NP>();
-        __syncthreads();
-        // NS - 1 steps ahead; past the end the last step is fetched again into a buffer nobody reads
-        const int kt_next = min(kt + NS - 1, kt_end - 1);
-        const int fill = (stage + NS - 1) % NS;    // the buffer the step before this one has just left
+    for (int kt = 0; kt < ktiles; kt++) {
+        __syncthreads();   // the loader wave has waited for this step's transfers
         const uint8_t* sb = smem + stage * STAGE;
         // The operands of contraction sub-step ks + 1 are requested ahead of the products of sub-step ks (two
         // register sets): with one wave per SIMD nothing else covers the LDS latency between a read and its product.
@@ -266,33 +249,9 @@ __global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : 2) void mlp_gemm1_
                 for (int nt = 0; nt < 2; nt++)
                     acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aop[ks & 1][mt], bop[ks & 1][nt], acc[mt][nt], 0, 0, 0);
                 __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-                if (!LOADER) {
-                    const int slot = ks * MT + mt;
-                    if (2 * slot < NP) issue_piece(kt_next, fill, 2 * slot);
-                    if (2 * slot + 1 < NP) issue_piece(kt_next, fill, 2 * slot + 1);
-                }
             }
         }
         stage = stage + 1 == NS ? 0 : stage + 1;
-    }
-
-    wait_all_memory();  // an empty piece of a split contraction still has its first tile in flight
-
-    if (MODE == kPlainF32) {
-        // out[row, col] fp32; a lane holds one column and 4 consecutive rows per register group
-#pragma unroll
-        for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-            for (int nt = 0; nt < 2; nt++) {
-                int col = col0 + wn * 64 + nt * 32 + l32;
-#pragma unroll
-                for (int r = 0; r < 16; r++) {
-                    int row = row0 + wm * (BM / 2) + mt * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
-                    if (row < p.N && col < p.F)
-                        p.out_f32[((int64_t)piece * p.N + row) * p.F + col] = acc[mt][nt][r];
-                }
-            }
-        return;
     }
 
     // ---- epilogue: bias, activation, bf16, transpose to [neuron][token] through LDS ----
@@ -667,11 +626,15 @@ __global__ __launch_bounds__(256, 2) void mlp_gemm2_kernel(Gemm2Params p) {
 
 // Chunk means of x in split precision: mean = hi + lo with hi = bf16(mean),
 // lo = bf16(mean - hi); out row = [hi(0..D-1) | lo(0..D-1)].  A workgroup owns
-// (chunk, 512 columns): each wave sums a quarter of the chunk's rows for 64
-// groups of 8 columns (16-byte reads), the four partial sums meet in LDS.
-__global__ __launch_bounds__(256) void chunk_mean_kernel(const uint16_t* __restrict__ x, uint16_t* __restrict__ xm,
-                                                         int N, int NB, int D, int c) {
-    __shared__ float s_part[3][64][8];
+// (chunk, 512 columns): each of its eight waves sums an eighth of the chunk's rows
+// for 64 groups of 8 columns, the partial sums meet in LDS.
+// Bound: HBM (x read once).  A wave requests six rows (16 bytes per lane each) before it adds the first: with one row at a
+// time and four waves a small problem took as many round trips as a wave had rows: 24 chunks of 192 x 3072 15.5 -> 6.9 us,
+// 8 of 128 x 256 7.2 -> 4.4 us, 602 of 192 x 3072 139 -> 127 us (5.6 TB/s).
+constexpr int kMeanWaves = 8, kMeanAhead = 6;
+__global__ __launch_bounds__(64 * kMeanWaves) void chunk_mean_kernel(const uint16_t* __restrict__ x, uint16_t* __restrict__ xm,
+                                                                     int N, int NB, int D, int c) {
+    __shared__ float s_part[kMeanWaves - 1][8][64];
     const int col_blocks = (D / 8 + 63) / 64;        // grid.x = units * col_blocks
     const int unit = blockIdx.x / col_blocks;
     const int b = unit / NB, chunk = unit % NB;
@@ -681,23 +644,33 @@ __global__ __launch_bounds__(256) void chunk_mean_kernel(const uint16_t* __restr
     const int r0 = chunk * c, r1 = min(N, r0 + c);
     float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (live) {
-        for (int r = r0 + w; r < r1; r += 4) {
-            u32x4 v = *reinterpret_cast<const u32x4*>(x + ((int64_t)b * N + r) * D + col8 * 8);
+        const uint16_t* xc = x + (int64_t)b * N * D + col8 * 8;
+        for (int r = r0 + w; r < r1; r += kMeanWaves * kMeanAhead) {
+            u32x4 v[kMeanAhead];
 #pragma unroll
-            for (int e = 0; e < 4; e++) {
-                s[2 * e] += bf16_bits_to_float(v[e] & 0xffffu);
-                s[2 * e + 1] += bf16_bits_to_float(v[e] >> 16);
+            for (int i = 0; i < kMeanAhead; i++) v[i] = *reinterpret_cast<const u32x4*>(xc + (int64_t)min(r + i * kMeanWaves, r1 - 1) * D);
+#pragma unroll
+            for (int i = 0; i < kMeanAhead; i++) {
+                const bool exists = r + i * kMeanWaves < r1;
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const uint32_t pair = exists ? v[i][e] : 0u;
+                    s[2 * e] += bf16_bits_to_float(pair & 0xffffu);
+                    s[2 * e + 1] += bf16_bits_to_float(pair >> 16);
+                }
             }
         }
     }
     if (w > 0) {
 #pragma unroll
-        for (int e = 0; e < 8; e++) s_part[w - 1][lane][e] = s[e];
+        for (int e = 0; e < 8; e++) s_part[w - 1][e][lane] = s[e];
     }
     __syncthreads();
     if (w > 0 || !live) return;
 #pragma unroll
-    for (int e = 0; e < 8; e++) s[e] += s_part[0][lane][e] + s_part[1][lane][e] + s_part[2][lane][e];
+    for (int i = 0; i < kMeanWaves - 1; i++)
+#pragma unroll
+        for (int e = 0; e < 8; e++) s[e] += s_part[i][e][lane];
     const float inv = 1.f / (float)(r1 - r0);
     u32x4 hi4, lo4;
 #pragma unroll
@@ -717,8 +690,15 @@ __global__ __launch_bounds__(256) void sum_pieces_kernel(const float* __restrict
                                                          int64_t n4, int pieces) {
     int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n4) return;
-    f32x4 acc = reinterpret_cast<const f32x4*>(part)[i];
-    for (int pc = 1; pc < pieces; pc++) acc += reinterpret_cast<const f32x4*>(part)[pc * n4 + i];
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int pc = 0; pc < pieces; pc += 4) {   // four pieces requested before the first is added
+        f32x4 v[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) v[j] = reinterpret_cast<const f32x4*>(part)[min(pc + j, pieces - 1) * n4 + i];
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+            if (pc + j < pieces) acc += v[j];
+    }
     reinterpret_cast<f32x4*>(out)[i] = acc;
 }
 
@@ -726,17 +706,14 @@ template <int BM, int MODE>
 static int32_t launch_gemm1(Gemm1Params p, int col_tiles, int units, hipStream_t s) {
     p.col_tiles = col_tiles;
     p.units = units;
-    constexpr int NS = MODE == kPlainF32 ? 2 : 3;
-    constexpr bool LOADER = MODE != kPlainF32;
-    constexpr int lds = NS * (BM * 128 + kBN * 128);
+    constexpr int lds = 3 * (BM * 128 + kBN * 128);
     // set at every launch: the attribute is kept per device (a flag remembered here would not be)
-    if (hipFuncSetAttribute((const void*)mlp_gemm1_kernel<BM, MODE, NS, LOADER>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) !=
+    if (hipFuncSetAttribute((const void*)mlp_gemm1_kernel<BM, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) !=
         hipSuccess)
         return CHIPMUNK_ERR_LAUNCH;
-    const int grid = MODE == kPlainF32 ? col_tiles * units * p.ksplit
-                     : MODE == kDenseAct ? xcd_grid_size_grouped(col_tiles, units)
-                                         : xcd_grid_size(col_tiles, units);
-    hipLaunchKernelGGL((mlp_gemm1_kernel<BM, MODE, NS, LOADER>), dim3(grid), dim3(LOADER ? 320 : 256), lds, s, p);
+    const int grid = MODE == kDenseAct ? xcd_grid_size_grouped(col_tiles, units)
+                                       : xcd_grid_size(col_tiles, units);
+    hipLaunchKernelGGL((mlp_gemm1_kernel<BM, MODE>), dim3(grid), dim3(320), lds, s, p);
     return launch_status();
 }
 
@@ -780,17 +757,18 @@ static bool large_tiles_pay(bool second, int B, int N, int D, int F, int c) {
     return cost(large, 256, 1.8, 1.25) < (c == 192 ? cost(small, 512, 1.75, 0.9) : cost(small, 512, 1.3, 0.7));
 }
 
-template <bool SECOND>
-static int32_t launch_dense_gemm(DenseGemmParams p, int B, hipStream_t s) {
-    const int tokens = (p.N + kDenseTile - 1) / kDenseTile;
-    p.tiles_p = SECOND ? (p.D + kDenseTile - 1) / kDenseTile : tokens;
-    p.tiles_q = SECOND ? tokens : (p.F + kDenseTile - 1) / kDenseTile;
+template <int MODE>
+static int32_t launch_dense_gemm(DenseGemmParams p, int second_dim, hipStream_t s) {
+    const int width = MODE == kFirst ? p.N : MODE == kSecond ? p.D : p.F, height = MODE == kFirst ? p.F : p.N;
+    const int tile_q = MODE == kScores ? 128 : kDenseTile;
+    p.tiles_p = (width + kDenseTile - 1) / kDenseTile;
+    p.tiles_q = (height + tile_q - 1) / tile_q;
     // set at every launch: the attribute is kept per device (a flag remembered here would not be)
-    if (hipFuncSetAttribute((const void*)mlp_dense_gemm_kernel<SECOND>, hipFuncAttributeMaxDynamicSharedMemorySize, kDenseLds) !=
+    if (hipFuncSetAttribute((const void*)mlp_dense_gemm_kernel<MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, kDenseLds) !=
         hipSuccess)
         return CHIPMUNK_ERR_LAUNCH;
     const int per_xcd = (p.tiles_p * p.tiles_q + 7) / 8;
-    hipLaunchKernelGGL((mlp_dense_gemm_kernel<SECOND>), dim3((unsigned)(per_xcd * 8), (unsigned)B), dim3(512), kDenseLds, s, p);
+    hipLaunchKernelGGL((mlp_dense_gemm_kernel<MODE>), dim3((unsigned)(per_xcd * 8), (unsigned)second_dim), dim3(512), kDenseLds, s, p);
     return launch_status();
 }
 
@@ -815,7 +793,16 @@ extern "C" size_t chipmunk_mlp_workspace_bytes(int B, int N, int D, int F, int c
     return (size_t)(units * round_up(k_stride > 0 ? k_stride : 1, kBN) * c * 2);
 }
 
-// pieces the scores GEMM's contraction is cut into, so that a small problem still fills the GPU
+// Pieces the scores GEMM's contraction is cut into, so that a small problem still fills the GPU: as many as let the tiles of
+// 256 neurons x 128 chunks have a CU each, at least one contraction step per piece.  Whole calls in us with up to 128, 256
+// and 512 workgroups: 24 chunks x 3072 x 12 288 36, 27, 32; 94 x 5120 x 13 824 96, 84, 94; 602 x 3072 x 12 288 (240 tiles)
+// 197, 197, 227.
+static int scores_pieces(int units, int D, int F) {
+    const int tiles = ((F + kDenseTile - 1) / kDenseTile) * ((units + 127) / 128);
+    return std::max(1, std::min(std::min(256 / tiles, 16), D / kBK));
+}
+
+// Pieces the workspace has room for: never fewer than scores_pieces (whose tiles are at least half as many)
 static int tile_mean_pieces(int units, int F) {
     int blocks = ((units + 127) / 128) * ((F + kBN - 1) / kBN);
     int pieces = 1;
@@ -867,9 +854,9 @@ static int32_t run_mlp_sparse_delta(const uint16_t* x, const uint16_t* w1, const
 
     Gemm1Params g1;
     g1.x = x; g1.w1 = w1; g1.b1 = b1; g1.idx = idx; g1.counts = counts; g1.a_cache = a_cache;
-    g1.delta_t = (uint16_t*)ws; g1.act_t = act_t; g1.out_f32 = nullptr; g1.a_ld = a_ld;
-    g1.N = N; g1.NB = NB; g1.D = D; g1.F = F; g1.K = D; g1.ldx = D;
-    g1.k_stride = k_stride; g1.k_pad = k_pad; g1.act = act; g1.ksplit = 1;
+    g1.delta_t = (uint16_t*)ws; g1.act_t = act_t; g1.a_ld = a_ld;
+    g1.N = N; g1.NB = NB; g1.D = D; g1.F = F;
+    g1.k_stride = k_stride; g1.k_pad = k_pad; g1.act = act;
     st = c == 192 ? launch_gemm1<192, kSparseDelta>(g1, k_pad / kBN, units, s)
                   : launch_gemm1<128, kSparseDelta>(g1, k_pad / kBN, units, s);
     if (st != CHIPMUNK_OK) return st;
@@ -920,24 +907,24 @@ extern "C" int32_t chipmunk_mlp_dense(const uint16_t* x, const uint16_t* w1, con
     hipStream_t s = (hipStream_t)stream;
     DenseGemmParams g;
     g.x = x; g.w1 = w1; g.w2 = w2; g.a_cache = a_cache; g.out = out; g.a_ld = a_ld;
-    g.N = N; g.D = D; g.F = F; g.act = act;
+    g.scores = nullptr; g.N = N; g.D = D; g.F = F; g.act = act; g.pieces = 1;
 
     if (large_tiles_pay(false, B, N, D, F, c)) {
         g.bias = b1;
-        st = launch_dense_gemm<false>(g, B, s);
+        st = launch_dense_gemm<kFirst>(g, B, s);
     } else {
         Gemm1Params g1;
         g1.x = x; g1.w1 = w1; g1.b1 = b1; g1.idx = nullptr; g1.counts = nullptr; g1.a_cache = a_cache;
-        g1.delta_t = nullptr; g1.act_t = nullptr; g1.out_f32 = nullptr; g1.a_ld = a_ld;
-        g1.N = N; g1.NB = NB; g1.D = D; g1.F = F; g1.K = D; g1.ldx = D;
-        g1.k_stride = F; g1.k_pad = F; g1.act = act; g1.ksplit = 1;
+        g1.delta_t = nullptr; g1.act_t = nullptr; g1.a_ld = a_ld;
+        g1.N = N; g1.NB = NB; g1.D = D; g1.F = F;
+        g1.k_stride = F; g1.k_pad = F; g1.act = act;
         st = c == 192 ? launch_gemm1<192, kDenseAct>(g1, (F + kBN - 1) / kBN, units, s)
                       : launch_gemm1<128, kDenseAct>(g1, (F + kBN - 1) / kBN, units, s);
     }
     if (st != CHIPMUNK_OK) return st;
     if (large_tiles_pay(true, B, N, D, F, c)) {
         g.bias = b2;
-        return launch_dense_gemm<true>(g, B, s);
+        return launch_dense_gemm<kSecond>(g, B, s);
     }
     Gemm2Params g2;
     g2.a_t = a_cache; g2.w2 = w2; g2.bias = b2; g2.idx = nullptr; g2.counts = nullptr; g2.o = out;
@@ -950,18 +937,17 @@ extern "C" int32_t chipmunk_mlp_dense(const uint16_t* x, const uint16_t* w1, con
 static int32_t run_tile_mean(const uint16_t* x, const uint16_t* w1, float* T, int B, int N, int D, int F, int c,
                              void* ws, int pieces, hipStream_t s) {
     const int NB = (N + c - 1) / c, units = B * NB;
-    hipLaunchKernelGGL(chunk_mean_kernel, dim3((unsigned)(((D / 8 + 63) / 64) * units)), dim3(256), 0, s, x, (uint16_t*)ws,
+    hipLaunchKernelGGL(chunk_mean_kernel, dim3((unsigned)(((D / 8 + 63) / 64) * units)), dim3(64 * kMeanWaves), 0, s, x, (uint16_t*)ws,
                        N, NB, D, c);
     if (launch_status() != CHIPMUNK_OK) return CHIPMUNK_ERR_LAUNCH;
-    // scores[unit, f] = <[hi | lo](unit), [w1_f | w1_f]>: a plain GEMM with "tokens" = units
+    // scores[unit, f] = <hi(unit) + lo(unit), w1_f>
+    pieces = std::min(pieces, scores_pieces(units, D, F));
     size_t means = ((size_t)units * 2 * D * 2 + 255) / 256 * 256;
     float* partial = pieces > 1 ? (float*)((char*)ws + means) : T;
-    Gemm1Params g1;
-    g1.x = (const uint16_t*)ws; g1.w1 = w1; g1.b1 = nullptr; g1.idx = nullptr; g1.counts = nullptr;
-    g1.a_cache = nullptr; g1.delta_t = nullptr; g1.act_t = nullptr; g1.out_f32 = partial; g1.a_ld = 0;
-    g1.N = units; g1.NB = (units + 127) / 128; g1.D = D; g1.F = F; g1.K = 2 * D; g1.ldx = 2 * D;
-    g1.k_stride = F; g1.k_pad = F; g1.act = 0; g1.ksplit = pieces;
-    int32_t st = launch_gemm1<128, kPlainF32>(g1, (F + kBN - 1) / kBN, g1.NB, s);
+    DenseGemmParams g;
+    g.x = (const uint16_t*)ws; g.w1 = w1; g.w2 = nullptr; g.bias = nullptr; g.a_cache = nullptr; g.out = nullptr; g.a_ld = 0;
+    g.scores = partial; g.N = units; g.D = D; g.F = F; g.act = 0; g.pieces = pieces;
+    int32_t st = launch_dense_gemm<kScores>(g, pieces, s);
     if (st != CHIPMUNK_OK || pieces == 1) return st;
     int64_t n4 = (int64_t)units * F / 4;
     hipLaunchKernelGGL(sum_pieces_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, partial, T, n4, pieces);

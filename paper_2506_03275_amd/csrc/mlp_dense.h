@@ -1,5 +1,5 @@
-// The two GEMMs of the dense MLP (Alg. 5) at sizes that fill the chip.  Internal to mlp.hip, which chooses between these
-// and the tiles of 192 or 128 x 128 that the column-sparse form uses.
+// The two GEMMs of the dense MLP (Alg. 5) at sizes that fill the chip, and the scores GEMM (Alg. 7).  Internal to mlp.hip,
+// which chooses between these and the tiles of 192 or 128 x 128 that the column-sparse form uses.
 //
 // One workgroup of eight waves owns a 256 x 256 tile of the result and walks the contraction in steps of 64.  A step's
 // operands are four half tiles of 16 KB in LDS (P0, P1: 128 rows each of the operand that lies along the result's
@@ -9,8 +9,8 @@
 // Bound: the matrix cores, as long as nothing but their instructions is waited for.  With one workgroup per CU and two
 // waves per SIMD the waves take turns: while waves 0-3 run 32 products, waves 4-7 read the operands of theirs from LDS
 // and request tile transfers, and the other way round (waves 4-7 run one barrier behind).  A half tile is requested
-// again as soon as both groups have read it, so that 64 to 96 KB per CU are in flight and a transfer has one and a
-// half steps to land:
+// again as soon as both groups have read it, so that 64 to 96 KB per CU are in flight and a transfer has at least a step
+// (about 1.3 us) to land:
 //     slot    reads                        requests                       then multiplies
 //     0       P0 and Q1 (step t)           Q0 (step t + 2), P1 (t + 1)    P0 x Q0, P0 x Q1
 //     1       P1 (t) and Q0 (step t + 1)   P0 and Q1 (t + 2)              P1 x Q1, P1 x Q0
@@ -25,21 +25,29 @@
 // 1.48 ms instead of 1.89, without the epilogue 1.66.  Persistent workgroups that request the next tile's first steps
 // in the last steps of the one before, with the results turned round in 16 x 64 pieces beside the operands, measured 1 to
 // 5 % slower than one workgroup per tile.
+//
+// The scores GEMM of the token-merged pre-activation (602 chunks x 12 288 neurons x 2 x 3072): 110 us and 13 us for the sum of
+// two pieces with tiles of 128 x 128 over [hi | lo] against [w1 | w1], 75 us in one piece with these (1.22 PFLOP/s); 24
+// chunks: 28 and 19 us.
 #pragma once
 #include "common.h"
 
 namespace chipmunk {
 
+enum DenseGemm { kFirst = 0, kSecond = 1, kScores = 2 };
+
 struct DenseGemmParams {
-    const uint16_t* x;       // [B, N, D]
+    const uint16_t* x;       // [B, N, D]; scores: the chunk means in split precision, [N][hi 0..D-1 | lo 0..D-1]
     const uint16_t* w1;      // [F, D]
     const uint16_t* w2;      // [F, D]
     const uint16_t* bias;    // first GEMM: b1 [F]; second: b2 [D]; or null
     uint16_t* a_cache;       // [B, F, a_ld]: result of the first GEMM, operand of the second
     uint16_t* out;           // [B, N, D]
     int64_t a_ld;
+    float* scores;           // scores: [pieces][N][F]
     int N, D, F, act;
-    int tiles_p, tiles_q;    // 256-wide tiles along the result's contiguous axis and along the other
+    int tiles_p, tiles_q;    // tiles along the result's contiguous axis and along the other
+    int pieces;              // the contraction is cut into so many runs of whole steps (second grid dimension; scores only)
 };
 
 constexpr int kDenseTile = 256;
@@ -66,11 +74,15 @@ __device__ __forceinline__ void mfma_in_place(f32x4& c, bf16x8 a, bf16x8 b) {
 }
 __device__ __forceinline__ void finish_products() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 
-// SECOND = false: a_cache[f][n] = act(<x[n], w1[f]> + b1[f]): P = tokens, Q = neurons, both operands with the contraction
-// index fastest.  SECOND = true: out[n][d] = sum_f a_cache[f][n] w2[f][d] + b2[d]: P = output columns, Q = tokens, both
-// with the contraction index slowest (transposing LDS reads).
-template <bool SECOND>
+// kFirst:  a_cache[f][n] = act(<x[n], w1[f]> + b1[f]): P = tokens, Q = neurons, both operands with the contraction index
+//          fastest.
+// kSecond: out[n][d] = sum_f a_cache[f][n] w2[f][d] + b2[d]: P = output columns, Q = tokens, both with the contraction
+//          index slowest (transposing LDS reads).
+// kScores: scores[n][f] = <hi[n] + lo[n], w1[f]>, n a chunk: P = neurons, Q0 = the high parts of 128 chunk means, Q1 = their
+//          low parts; both go into the same accumulators, so a step fetches w1 once for two products.  256 x 128 tiles.
+template <int MODE>
 __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams p) {
+    constexpr bool SECOND = MODE == kSecond, SCORES = MODE == kScores;
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -87,16 +99,17 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
     const int band = tile / (8 * p.tiles_q), in_band = tile - band * 8 * p.tiles_q;
     const int band_p = min(8, p.tiles_p - 8 * band);
     const int tq = in_band / band_p, tp = 8 * band + (in_band - tq * band_p);
-    const int p0 = tp * kDenseTile, q0 = tq * kDenseTile;
-    const int b = blockIdx.y;
+    const int p0 = tp * kDenseTile, q0 = tq * (SCORES ? 128 : kDenseTile);
+    const int b = SCORES ? 0 : blockIdx.y, piece = SCORES ? blockIdx.y : 0;
 
     // operand sources: per-lane byte offsets of the wave's two transfers per half tile, clamped into the tensors
     // (rows beyond the end repeat the last one and are not stored)
     const uint16_t* xb = p.x + (int64_t)b * p.N * p.D;
     uint16_t* ab = p.a_cache + (int64_t)b * p.F * p.a_ld;
-    const i32x4 pbuf = SECOND ? raw_buffer_words(p.w2, (uint32_t)p.F * p.D * 2u) : raw_buffer_words(xb, (uint32_t)p.N * p.D * 2u);
-    const i32x4 qbuf = SECOND ? raw_buffer_words(ab, (uint32_t)p.F * (uint32_t)p.a_ld * 2u)
-                              : raw_buffer_words(p.w1, (uint32_t)p.F * p.D * 2u);
+    const i32x4 wbuf = raw_buffer_words(SECOND ? p.w2 : p.w1, (uint32_t)p.F * p.D * 2u);
+    const i32x4 xbuf = raw_buffer_words(xb, (uint32_t)p.N * p.D * (SCORES ? 4u : 2u));
+    const i32x4 pbuf = MODE == kFirst ? xbuf : wbuf;
+    const i32x4 qbuf = MODE == kFirst ? wbuf : SCORES ? xbuf : raw_buffer_words(ab, (uint32_t)p.F * (uint32_t)p.a_ld * 2u);
     const uint32_t pstep = SECOND ? 64u * p.D * 2u : 128u, qstep = SECOND ? 64u * (uint32_t)p.a_ld * 2u : 128u;
     uint32_t poff[2][2], qoff[2][2];   // [half][transfer]
 #pragma unroll
@@ -106,8 +119,10 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
             if (!SECOND) {             // 8 rows of 128 bytes; 16-byte chunks XOR-swizzled by the row
                 const int row = (w * 2 + n) * 8 + (lane >> 3);
                 const uint32_t chunk = (uint32_t)((lane & 7) ^ ((row >> 1) & 7)) * 16u;
-                poff[hf][n] = (uint32_t)min(p0 + hf * 128 + row, p.N - 1) * (uint32_t)(p.D * 2) + chunk;
-                qoff[hf][n] = (uint32_t)min(q0 + hf * 128 + row, p.F - 1) * (uint32_t)(p.D * 2) + chunk;
+                const int last_p = SCORES ? p.F - 1 : p.N - 1;
+                poff[hf][n] = (uint32_t)min(p0 + hf * 128 + row, last_p) * (uint32_t)(p.D * 2) + chunk;
+                qoff[hf][n] = SCORES ? (uint32_t)min(q0 + row, p.N - 1) * (uint32_t)(p.D * 4) + (uint32_t)(hf * p.D * 2) + chunk
+                                     : (uint32_t)min(q0 + hf * 128 + row, p.F - 1) * (uint32_t)(p.D * 2) + chunk;
             } else {                   // 4 contraction rows of 256 bytes
                 const int row = (w * 2 + n) * 4 + (lane >> 4);
                 const int col = ((lane & 15) ^ swizzle_rows16(row)) * 8;
@@ -115,12 +130,14 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
                 qoff[hf][n] = (uint32_t)row * (uint32_t)(p.a_ld * 2) + (uint32_t)min(q0 + hf * 128 + col, (p.N - 1) & ~7) * 2u;
             }
         }
-    const int steps = (SECOND ? p.F : p.D) / 64;
+    const int all_steps = (SECOND ? p.F : p.D) / 64;
+    const int step0 = SCORES ? (int)((int64_t)all_steps * piece / p.pieces) : 0;
+    const int steps = (SCORES ? (int)((int64_t)all_steps * (piece + 1) / p.pieces) : all_steps) - step0;   // at least one
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem) + (uint32_t)w * 2048u);
     // half tile `hf` of P or Q of step t (past the end the last step again, into a place nobody reads)
     auto request = [&](bool is_q, int hf, int t) {
         const uint32_t dst = lds0 + (uint32_t)((t & 1) * kDenseStage + (is_q ? 2 : 0) * kDenseHalf + hf * kDenseHalf);
-        const uint32_t from = (uint32_t)min(t, steps - 1) * (is_q ? qstep : pstep);
+        const uint32_t from = (uint32_t)(step0 + min(t, steps - 1)) * (is_q ? qstep : pstep);
 #pragma unroll
         for (int n = 0; n < 2; n++)
             load_buffer_to_lds_16B(is_q ? qbuf : pbuf, is_q ? qoff[hf][n] : poff[hf][n], from, dst + n * 1024);
@@ -166,11 +183,12 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
         }
     };
 
-    f32x4 acc[2][2][4][2];
+    constexpr int NJ = SCORES ? 1 : 2;
+    f32x4 acc[2][NJ][4][2];
 #pragma unroll
     for (int i = 0; i < 2; i++)
 #pragma unroll
-        for (int j = 0; j < 2; j++)
+        for (int j = 0; j < NJ; j++)
 #pragma unroll
             for (int a = 0; a < 4; a++)
 #pragma unroll
@@ -230,7 +248,7 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
         ready();
         __builtin_amdgcn_s_setprio(1);
         multiply(acc[0][0], Q0);
-        multiply(acc[0][1], Q1);
+        multiply(acc[0][NJ - 1], Q1);
         __builtin_amdgcn_s_setprio(0);
         turn();
         read_p(1);
@@ -241,7 +259,7 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
         request(true, 1, t + 2);
         ready();
         __builtin_amdgcn_s_setprio(1);
-        multiply(acc[1][1], Q1);
+        multiply(acc[1][NJ - 1], Q1);
         multiply(acc[1][0], Q0);
         __builtin_amdgcn_s_setprio(0);
         turn();
@@ -250,6 +268,23 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
 #pragma unroll
             for (int c = 0; c < 2; c++) Q0[c][ks] = Q0next[c][ks];
     }
+    if constexpr (SCORES) {
+        // four consecutive neurons of one chunk per lane and block: 64-byte runs, joined in L2
+        finish_products();
+        if (wp == 0) turn();
+        wait_all_memory();                       // the transfers past the end must have landed before the wave may end
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+            const int n = q0 + wq * 32 + c * 16 + l16;
+            float* row = p.scores + ((int64_t)piece * p.N + n) * p.F + p0 + wp * 64 + 4 * g;
+#pragma unroll
+            for (int i = 0; i < 2; i++)
+#pragma unroll
+                for (int a = 0; a < 4; a++)
+                    if (n < p.N && p0 + i * 128 + wp * 64 + a * 16 < p.F) *reinterpret_cast<f32x4*>(row + i * 128 + a * 16) = acc[i][0][a][c];
+        }
+        return;
+    } else {
     // ---- epilogue: bias (and activation), bf16, through LDS as [q][p], out in runs of 512 bytes ----
     // the bias is requested in front of the last waits
     const bool has_bias = p.bias != nullptr;
@@ -315,6 +350,7 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
         for (int n = 0; n < 16; n++)
             for (int e = 0; e < limit_p - pc; e++)
                 if (qr + n * 16 < limit_q) dst[n * 16 * ld + e] = *reinterpret_cast<const uint16_t*>(smem + (n * 16 + (tid >> 5)) * kDenseRow + (tid & 31) * 16 + e * 2);
+    }
     }
 }
 

@@ -134,3 +134,24 @@ def test_topk_of_rows_kept_in_registers(cm, oracle, C, kind):
             ref_idx, ref_counts = oracle.topk_cols(a, p, k, k_stride=k + 1, idx_fill=-7)
             assert np.array_equal(idx.cpu().numpy(), ref_idx), k
             assert np.array_equal(counts.cpu().numpy(), ref_counts)
+
+
+@pytest.mark.parametrize("B,N,D,F,c", [
+    (1, 1, 128, 64, 128),              # one token, one neuron tile a quarter full, two pieces of one step
+    (1, 384, 640, 7680, 192),          # two chunks; ten steps in eight pieces
+    (1, 127 * 128, 128, 320, 128),     # 127, 128 and 129 chunks: both sides of a tile
+    (2, 64 * 192, 256, 576, 192),
+    (1, 128 * 128 + 5, 384, 64, 128),
+])
+def test_neuron_scores_in_pieces_of_the_contraction(cm, oracle, B, N, D, F, c):
+    """Chunk means of full, ragged and one-row chunks, and the scores GEMM cut into pieces.  Tolerance: the mean enters as two
+    bf16 numbers (2^-16 of it is lost at most), the 32-bit sums of D products add less: 1e-4 of the scores' RMS."""
+    g = si.generator(26, DEV)
+    x, w1 = si.randn_bf16((B, N, D), g), si.randn_bf16((F, D), g, 1 / math.sqrt(D))
+    T = torch.full((B, -(-N // c), F), float("nan"), dtype=torch.float32, device=DEV)
+    cm.mlp_tile_mean_preact(x, w1, T, c, _u8(cm.mlp_tile_mean_workspace_bytes(B, N, D, F, c)))
+    ref = oracle.mlp_tile_scores(si.np_f32(x), si.np_f32(w1), c)
+    assert rel_err(T.cpu().numpy(), ref) <= SUM_TOL
+    again = torch.empty_like(T)
+    cm.mlp_tile_mean_preact_static(x, w1, again, c)
+    assert rel_err(again.cpu().numpy(), ref) <= SUM_TOL
