@@ -37,6 +37,7 @@ struct AttnParams {
     float* row_l;   // optional [B,H,N]: sum_j exp(score_j - row_m)
     int N, NB, c, k_stride;
     int parts;      // workgroups per chunk: each owns 64 * NQB of its rows and walks the chunk's whole list
+    int by_xcd;     // see attn_block_of
     float sl2;      // softmax_scale * log2(e)
     float o_scale;
     // fused column sums with given normalisers (Alg. 4): dense launches of the FUSED kernel only
@@ -260,6 +261,18 @@ __device__ __forceinline__ void attn_weights_and_pv(AttnState<E, NQB>& st, const
 constexpr int kBlockColumns = CHIPMUNK_ATTN_BLOCK_COLUMNS;   // key columns per entry of a block list
 static_assert(kBlockColumns % (kTilesPerStep * kTileRows) == 0, "a step never straddles two blocks");
 
+// Workgroups go to the eight XCDs in turn.  With by_xcd each XCD takes one run of the chunks, so that a head's K and V are
+// read through one or two L2s instead of all eight; without, neighbouring chunks of a head run side by side on all XCDs.
+__device__ __forceinline__ int64_t attn_block_of(int by_xcd) {
+    if (!by_xcd) return blockIdx.x;
+    const uint32_t xcd = blockIdx.x & 7, each = gridDim.x >> 3, more = gridDim.x & 7;
+    return (int64_t)xcd * each + min(xcd, more) + (blockIdx.x >> 3);
+}
+// Eight heads in work at a time are worth it while their K and V stay in the last-level cache (256 MB).  Column lists, 7 to
+// 10 % kept: 24 x 2304: 26.6 -> 22.1 us; 24 x 4608 (single round): 34.1 -> 33.0; 40 x 9000: 209 -> 202; 24 x 18 000: 301 -> 295;
+// 24 x 30 000 (8 heads: 123 MB): 734 -> 726; 24 x 60 000 (246 MB): 2677 -> 2736; 24 x 115 456: 9597 -> 10 253 us.
+static int attn_by_xcd(int N, int E) { return (int64_t)N * E <= (1 << 22); }
+
 // What the kernel walks.  kColumnList: the unit's list of columns.  kEveryColumn: no list, every column (dense).
 // kFusedDense: every column, and the column sums of Alg. 4 are formed from the same score tiles.  kBlockList: the
 // unit's list names blocks of kBlockColumns consecutive columns (the [c, 128] block sparsity of Table 2); the list
@@ -295,10 +308,11 @@ __global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_
     const int l16 = lane & 15;
 
     constexpr int ROWS = 16 * NQB * NWAVES;   // query rows of a workgroup
-    const int64_t unit = blockIdx.x / p.parts;
+    const int64_t block = attn_block_of(p.by_xcd);
+    const int64_t unit = block / p.parts;
     const int64_t bh = unit / p.NB;
     const int chunk = (int)(unit % p.NB);
-    const int row0 = chunk * p.c + (int)(blockIdx.x % p.parts) * ROWS;
+    const int row0 = chunk * p.c + (int)(block % p.parts) * ROWS;
     const int rows_valid = min(ROWS, p.N - row0);
     if (rows_valid <= 0) return;              // the last chunk may end before this part of it
     // Contents of counts and idx are the caller's precondition; they are clamped all the same so that a bad
@@ -876,7 +890,7 @@ extern "C" int32_t chipmunk_attn_sparse_delta(const uint16_t* q, const uint16_t*
     p.q = q; p.k = k; p.v = v; p.base = base; p.out = out; p.idx = idx; p.counts = counts;
     p.row_m = nullptr; p.row_l = nullptr;
     p.prev_m = nullptr; p.prev_l = nullptr; p.colsum = nullptr; p.ld_colsum = 0;
-    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.k_stride = k_stride;
+    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.by_xcd = attn_by_xcd(N, E); p.k_stride = k_stride;
     p.sl2 = softmax_scale * 1.4426950408889634f;
     p.o_scale = o_scale;
     return launch_attn(p, E, units, (hipStream_t)stream);
@@ -900,7 +914,7 @@ extern "C" int32_t chipmunk_attn_block_sparse_delta(const uint16_t* q, const uin
     p.q = q; p.k = k; p.v = v; p.base = base; p.out = out; p.idx = blocks; p.counts = block_counts;
     p.row_m = nullptr; p.row_l = nullptr;
     p.prev_m = nullptr; p.prev_l = nullptr; p.colsum = nullptr; p.ld_colsum = 0;
-    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.k_stride = kb_stride;
+    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.by_xcd = attn_by_xcd(N, E); p.k_stride = kb_stride;
     p.sl2 = softmax_scale * 1.4426950408889634f;
     p.o_scale = o_scale;
     return launch_attn_blocks(p, E, units, (hipStream_t)stream);
@@ -929,7 +943,7 @@ extern "C" int32_t chipmunk_attn_dense(const uint16_t* q, const uint16_t* k, con
     p.row_m = colsum ? (float*)ws : nullptr;
     p.row_l = colsum ? (float*)ws + (int64_t)B * H * N : nullptr;
     p.prev_m = nullptr; p.prev_l = nullptr; p.colsum = nullptr; p.ld_colsum = 0;
-    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.k_stride = 0;
+    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.by_xcd = attn_by_xcd(N, E); p.k_stride = 0;
     p.sl2 = softmax_scale * 1.4426950408889634f;
     p.o_scale = 1.f;
     int32_t st = launch_attn(p, E, units, s);
@@ -976,7 +990,7 @@ extern "C" int32_t chipmunk_attn_dense_colsum_stale(const uint16_t* q, const uin
     p.q = q; p.k = k; p.v = v; p.base = nullptr; p.out = out; p.idx = nullptr; p.counts = nullptr;
     p.row_m = new_m; p.row_l = new_l;
     p.prev_m = prev_m; p.prev_l = prev_l; p.colsum = colsum; p.ld_colsum = ld_colsum;
-    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.k_stride = 0;
+    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.by_xcd = attn_by_xcd(N, E); p.k_stride = 0;
     p.sl2 = softmax_scale * 1.4426950408889634f;
     p.o_scale = 1.f;
     return launch_attn_fused(p, E, units, (hipStream_t)stream);
