@@ -118,14 +118,16 @@ __device__ __forceinline__ int list_pos_in_step(int s, int q) {
     return (q % LANEROWS) * (kTilesPerStep * NI) + s * NI + q / LANEROWS;
 }
 
-// The last tiles of a unit: rows whose list position is at or beyond `count` score -inf.
-template <int E, int NQB>
+// The last tiles of a unit: rows whose list position is at or beyond `count` score -inf.  IN_ORDER: the rows of the step's
+// tiles are its positions in order (the last step of a column list).
+template <int E, int NQB, bool IN_ORDER = false>
 __device__ __forceinline__ void attn_mask_tail(f32x4 (&S)[2][NQB], int step_base, int s, int count, int g) {
 #pragma unroll
     for (int u = 0; u < 2; u++)
 #pragma unroll
         for (int r = 0; r < 4; r++) {
-            bool dead = step_base + list_pos_in_step<E>(s, u * 16 + 4 * g + r) >= count;
+            const int row = u * 16 + 4 * g + r;
+            bool dead = step_base + (IN_ORDER ? s * kTileRows + row : list_pos_in_step<E>(s, row)) >= count;
 #pragma unroll
             for (int qb = 0; qb < NQB; qb++)
                 if (dead) S[u][qb][r] = -INFINITY;
@@ -296,7 +298,7 @@ __global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_
     constexpr int TILE = kTileRows * ROWB;
     constexpr int STAGE = 2 * TILE;       // K tile then V tile
 
-    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];  // kStages * STAGE bytes
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];  // the tile buffers and, with three query blocks, base rows
     // FUSED: per-wave column sums of the two tiles of a step, double buffered over steps
     __shared__ float s_part[FUSED ? 2 * NWAVES * kTilesPerStep * kTileRows : 1];
 
@@ -422,6 +424,7 @@ __global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_
     // at or beyond `count` reads as column 0: a valid row, whose scores the last tile masks.
     const i32x4 kbuf = raw_buffer_words(kh, (uint32_t)p.N * ROWB);
     const i32x4 vbuf = raw_buffer_words(vh, (uint32_t)p.N * ROWB);
+    const i32x4 bbuf = raw_buffer_words(baseh ? baseh + (int64_t)row0 * E : nullptr, baseh ? (uint32_t)rows_valid * ROWB : 0u);
     const int32_t* idxg = !NOLIST && p.idx ? p.idx + unit * (int64_t)p.k_stride : nullptr;
     // two views of the unit's list: its whole row (positions below k_stride: the vector loads of the steps that lie
     // inside the list) and the part below count (a position at or beyond count reads as 0: the list's last step)
@@ -439,9 +442,13 @@ __global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_
     int colv[RPL], colt[RPL];
     int next_pos = (w * RPI + sel) * RPL;         // the lane's first list position in the next step to load
     if constexpr (MODE == kColumnList) {
-        const int last_pos = (ntiles / kTilesPerStep - 1) * (kTilesPerStep * kTileRows) + next_pos;
+        // (in order, not interleaved: a last step of at most one tile's positions then needs only its first tile)
+        const int last_pos = (ntiles - kTilesPerStep) * kTileRows + w * RPI + sel;
 #pragma unroll
-        for (int j = 0; j < RPL; j++) colt[j] = __builtin_amdgcn_raw_buffer_load_b32(ibuf, (last_pos + j) * 4, 0, 0);
+        for (int s = 0; s < kTilesPerStep; s++)
+#pragma unroll
+            for (int i = 0; i < NI; i++)
+                colt[s * NI + i] = __builtin_amdgcn_raw_buffer_load_b32(ibuf, (last_pos + s * kTileRows + i * NWAVES * RPI) * 4, 0, 0);
     }
     int blockv = 0;                               // BLOCKS: the block that holds the next step to gather (the same in every lane)
     int block_now = 0, block_next = 0;            // BLOCKS: first column of the block of the step in work / of the next step
@@ -510,32 +517,62 @@ __global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_
     for (int j = 0; j < E / 16; j++) gather_piece(std::integral_constant<int, 0>{}, j);
     load_cols();
 
+    // The base rows that the results are merged with are brought to LDS in the last step, in the place of a next step's
+    // tiles: each wave its own rows, a query block's 16 rows at a time, two blocks of every wave in the free buffer half
+    // and a third behind the buffers.  Fetched after the last step instead, they cost a round trip of their own in which
+    // nothing else runs (and in a short launch all workgroups ask for theirs at once).  16-byte chunks are XOR-swizzled
+    // by the row.
+    constexpr int BLOCKB = 16 * ROWB;     // bytes of a query block's base rows
+    constexpr int BASE_PIECES = BLOCKB / 1024;
+    const int base_row = (w * NQB * 16 + sel) * ROWB;
+    auto base_place = [&](int half_in_use, int qb) -> uint32_t {   // within the buffers, without the LDS base
+        return qb < 2 ? (uint32_t)((half_in_use ^ 1) * kTilesPerStep * STAGE + (w * 2 + qb) * BLOCKB)
+                      : (uint32_t)(kStages * STAGE + (w * (NQB - 2) + qb - 2) * BLOCKB);
+    };
+    auto base_swizzle = [](int row) { return (E == 128 ? row : row >> 1) & (CH - 1); };   // of the row inside the block
+
     // One step: the kTilesPerStep tiles in buffer half `half`.  The half is a compile-time constant (the loop
     // below alternates two copies of the step), so every LDS offset of the step is an immediate of its read.
     // The next step's tiles are requested between the score products of this step's first tile, and the columns
-    // of the step after that behind them.  Both happen on every step: past the end of the list the columns read
-    // as 0 (the buffer's range check), so the last step fetches row 0 into buffers nobody reads.
-    auto step = [&](auto half_c, int t) {
+    // of the step after that behind them.  The list's last step has a copy of its own (LAST): it requests the base rows
+    // instead, masks the positions beyond the list, and leaves out a tile that has none; its half, `last_half`, has
+    // been added to the addresses.  The kernel with the column sums, which merges with nothing and has no registers left
+    // for a third copy (244 bytes of spills, 8.0 ms instead of 5.9 at 40 heads x 18 000), runs its last step in the loop.
+    auto step = [&](auto half_c, auto last_c, int t, int last_half) {
         constexpr int half = decltype(half_c)::value;
+        constexpr bool LAST = decltype(last_c)::value;
         wait_all_memory();
         __syncthreads();  // this step's tiles have landed for every wave; the other half is free to refill
-        gather_offsets(t + 2 * kTilesPerStep >= ntiles);
+        if constexpr (!LAST) gather_offsets(t + 2 * kTilesPerStep >= ntiles);
+        if constexpr (LAST && BLOCKS) block_now = block_next;
         if (FUSED && t > 0) flush_column_sums(t - kTilesPerStep);
 #pragma unroll
         for (int s = 0; s < kTilesPerStep; s++) {
             const int tile_off = (half * kTilesPerStep + s) * STAGE;   // a constant once the loop over s is unrolled
+            if (LAST && MODE == kColumnList && s > 0 && (t + s) * kTileRows >= count) break;
             f32x4 S[2][NQB];
-            if (s == 0) {
+            if (s == 0 && !LAST) {
                 attn_scores<E, NQB, 1>(S, st, kaddr, tile_off,
                                     [&](int j) { gather_piece(std::integral_constant<int, half ^ 1>{}, j); });
                 load_cols();
+            } else if (s == 0) {
+                attn_scores<E, NQB, 1>(S, st, kaddr, tile_off, [&](int j) {
+                    if (!baseh) return;
+                    for (int n = j; n < NQB * BASE_PIECES; n += E / 16) {
+                        const int qb = n / BASE_PIECES, i = n % BASE_PIECES, row = i * RPI + sel;
+                        load_buffer_to_lds_16B(bbuf, (uint32_t)(base_row + (qb * 16 + i * RPI) * ROWB + (((lane % CH) ^ base_swizzle(row)) * 16)),
+                                               lds_address(smem) + __builtin_amdgcn_readfirstlane(base_place(last_half, qb)) + i * 1024);
+                    }
+                });
             } else {
                 attn_scores<E, NQB, 1>(S, st, kaddr, tile_off, [](int) {});
             }
             if constexpr (BLOCKS) {   // only the sequence's last block can reach beyond N; it may stand anywhere in the list
                 const int col0 = block_now + (t * kTileRows) % kBlockColumns;
                 if (col0 + kTilesPerStep * kTileRows > p.N) attn_mask_tail<E, NQB>(S, col0, s, p.N, g);
-            } else {
+            } else if constexpr (LAST) {
+                attn_mask_tail<E, NQB, MODE == kColumnList>(S, t * kTileRows, s, count, g);
+            } else if constexpr (FUSED) {
                 if (t + kTilesPerStep >= ntiles) attn_mask_tail<E, NQB>(S, t * kTileRows, s, count, g);
             }
             attn_update_max<E, NQB>(st, S, t + s == 0, p.sl2, slack);
@@ -543,28 +580,27 @@ __global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_
                                                s_part + ((half * NWAVES + w) * kTilesPerStep + s) * kTileRows, g, l16);
         }
     };
+    const int last_tile = ntiles - kTilesPerStep;   // first tile of the last step
+    const int loop_end = FUSED ? ntiles : last_tile;
 #pragma unroll 1
-    for (int t = 0; t < ntiles; t += 2 * kTilesPerStep) {
-        step(std::integral_constant<int, 0>{}, t);
-        if (t + kTilesPerStep >= ntiles) break;
-        step(std::integral_constant<int, 1>{}, t + kTilesPerStep);
+    for (int t = 0; t < loop_end; t += 2 * kTilesPerStep) {
+        step(std::integral_constant<int, 0>{}, std::false_type{}, t, 0);
+        if (t + kTilesPerStep >= loop_end) break;
+        step(std::integral_constant<int, 1>{}, std::false_type{}, t + kTilesPerStep, 0);
     }
-    // The base rows that the results are merged with are requested here, for every query block at once and in front
-    // of the wait for the last step's transfers: one round trip for all of it.  Without a branch: a query row that
-    // does not exist reads the chunk's last row, a call without base reads the output buffer; neither value is used.
-    const uint16_t* base_src = baseh ? baseh : outh;
-    u32x2 bv[NQB][E / 16];
+    const int last_half = (last_tile / kTilesPerStep) & 1;
+    if constexpr (!FUSED) {
+        const uint32_t shift = (uint32_t)(last_half * kTilesPerStep * STAGE);
 #pragma unroll
-    for (int qb = 0; qb < NQB; qb++) {
-        int qrow = (w * NQB + qb) * 16 + l16;
-        const int64_t row_off = (int64_t)(row0 + min(qrow, rows_valid - 1)) * E + 4 * g;
+        for (int es = 0; es < E / 32; es++) kaddr[es] += shift;
 #pragma unroll
-        for (int eb = 0; eb < E / 16; eb++) bv[qb][eb] = *reinterpret_cast<const u32x2*>(base_src + row_off + eb * 16);
+        for (int eb = 0; eb < E / 16; eb++) vaddr[eb] += shift;
+        step(std::integral_constant<int, 0>{}, std::true_type{}, last_tile, last_half);
     }
-    wait_all_memory();  // the last step's transfers into the unused half must have landed before the wave may end
+    wait_all_memory();  // the base rows (FUSED: the transfers behind the last step) have landed
     if (FUSED) {
         __syncthreads();  // the last step's partial sums are complete
-        flush_column_sums(((ntiles - 1) / kTilesPerStep) * kTilesPerStep);
+        flush_column_sums(last_tile);
     }
 
     if (!wave_active) return;
@@ -581,7 +617,10 @@ __global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_
             }
 #pragma unroll
             for (int eb = 0; eb < E / 16; eb++) {
-                u32x2 b = baseh ? bv[qb][eb] : u32x2{0, 0};
+                u32x2 b = u32x2{0, 0};
+                if (!FUSED && baseh)
+                    b = *reinterpret_cast<const u32x2*>(smem + base_place(last_half, qb) + l16 * ROWB +
+                                                        (((2 * eb + (g >> 1)) ^ base_swizzle(l16)) * 16) + (g & 1) * 8);
                 float o0 = bf16_bits_to_float(b[0] & 0xffffu) + f * st.O[eb][qb][0];
                 float o1 = bf16_bits_to_float(b[0] >> 16) + f * st.O[eb][qb][1];
                 float o2 = bf16_bits_to_float(b[1] & 0xffffu) + f * st.O[eb][qb][2];
@@ -764,7 +803,8 @@ __global__ __launch_bounds__(256, 4) void attn_colsum_kernel(ColsumParams p) {
 
 template <int E, int NQB, int NWAVES, int MODE = kColumnList>
 static int32_t launch_attn_variant(const AttnParams& p, int64_t units, hipStream_t s) {
-    constexpr int lds = kStages * 2 * kTileRows * E * 2;
+    // the tile buffers, and behind them each wave's third block of base rows
+    constexpr int lds = kStages * 2 * kTileRows * E * 2 + (MODE != kFusedDense && NQB > 2 ? NWAVES * (NQB - 2) * 16 * E * 2 : 0);
     // set at every launch: the attribute is kept per device, and a flag remembered here would be neither
     // per device nor safe between host threads
     if (hipFuncSetAttribute((const void*)attn_sparse_delta_kernel<E, NQB, NWAVES, MODE>,

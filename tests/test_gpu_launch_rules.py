@@ -155,3 +155,25 @@ def test_neuron_scores_in_pieces_of_the_contraction(cm, oracle, B, N, D, F, c):
     again = torch.empty_like(T)
     cm.mlp_tile_mean_preact_static(x, w1, again, c)
     assert rel_err(again.cpu().numpy(), ref) <= SUM_TOL
+
+
+@pytest.mark.parametrize("E", [64, 128])
+@pytest.mark.parametrize("H,N,c", [(2, 900, 192), (2, 600, 128), (70, 700, 192)])
+def test_last_step_of_column_lists(cm, oracle, E, H, N, c):
+    """Lists that end at, before and behind the edges of tiles (32 columns) and steps (64), one step to three, in either half
+    of the buffers: the last step leaves out an empty second tile and brings the base rows (ragged last chunk: some do
+    not exist).  70 heads: chunks walked whole."""
+    NB, k = -(-N // c), 193
+    q, kk, v = recipes.attn_inputs(1, H, N, E, 27, DEV)
+    base = recipes.attn_base(tuple(q.shape), 64, "delta", 27, DEV)
+    idx, counts = recipes.attn_indices(H * NB, N, k, 27, DEV)
+    edges = torch.tensor([1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 160, 161, 192, 193], dtype=torch.int32)
+    counts = edges[torch.arange(H * NB) % len(edges)].to(DEV)
+    idx, counts = idx.view(1, H, NB, k), counts.view(1, H, NB)
+    out = torch.full_like(q, 7.0)
+    scale = 1 / math.sqrt(E)
+    cm.attn_sparse_delta(q, kk, v, idx, counts, base, out, c, scale, 1.0)
+    basen = si.np_f32(base).astype(np.float64)
+    ref = oracle.attn_sparse_delta(si.np_f32(q), si.np_f32(kk), si.np_f32(v), idx.cpu().numpy(), counts.cpu().numpy(),
+                                   basen, c, scale, 1.0)
+    assert rel_err(si.np_f32(out), ref, ref - basen) <= REL_TOL
