@@ -36,8 +36,8 @@ struct AttnParams {
                     // scaled scores (natural logarithm); within 2^8 of the row maximum, not necessarily equal to it
     float* row_l;   // optional [B,H,N]: sum_j exp(score_j - row_m)
     int N, NB, c, k_stride;
-    int parts;      // workgroups per chunk: each owns 64 * NQB of its rows and walks the chunk's whole list
-    int by_xcd;     // see attn_block_of
+    int whole;      // the first so many chunks have a workgroup each, the others one per 64 rows (see attn_sparse_delta_kernel)
+    int by_xcd;     // see attn_run_of_xcd
     float sl2;      // softmax_scale * log2(e)
     float o_scale;
     // fused column sums with given normalisers (Alg. 4): dense launches of the FUSED kernel only
@@ -263,12 +263,12 @@ __device__ __forceinline__ void attn_weights_and_pv(AttnState<E, NQB>& st, const
 constexpr int kBlockColumns = CHIPMUNK_ATTN_BLOCK_COLUMNS;   // key columns per entry of a block list
 static_assert(kBlockColumns % (kTilesPerStep * kTileRows) == 0, "a step never straddles two blocks");
 
-// Workgroups go to the eight XCDs in turn.  With by_xcd each XCD takes one run of the chunks, so that a head's K and V are
-// read through one or two L2s instead of all eight; without, neighbouring chunks of a head run side by side on all XCDs.
-__device__ __forceinline__ int64_t attn_block_of(int by_xcd) {
-    if (!by_xcd) return blockIdx.x;
-    const uint32_t xcd = blockIdx.x & 7, each = gridDim.x >> 3, more = gridDim.x & 7;
-    return (int64_t)xcd * each + min(xcd, more) + (blockIdx.x >> 3);
+// Workgroups go to the eight XCDs in turn (id modulo 8).  Position of workgroup `id` of `all` when each XCD takes one run of
+// the positions, so that a head's K and V are read through one or two L2s instead of all eight; without it neighbouring
+// chunks of a head run side by side on all XCDs.
+__device__ __forceinline__ uint32_t attn_run_of_xcd(uint32_t id, uint32_t all) {
+    const uint32_t xcd = id & 7, each = all >> 3, more = all & 7;
+    return xcd * each + min(xcd, more) + (id >> 3);
 }
 // Eight heads in work at a time are worth it while their K and V stay in the last-level cache (256 MB).  Column lists, 7 to
 // 10 % kept: 24 x 2304: 26.6 -> 22.1 us; 24 x 4608 (single round): 34.1 -> 33.0; 40 x 9000: 209 -> 202; 24 x 18 000: 301 -> 295;
@@ -281,9 +281,10 @@ static int attn_by_xcd(int N, int E) { return (int64_t)N * E <= (1 << 22); }
 // positions are the blocks' columns in order, so the rows of a step are one contiguous run of K and V.
 enum AttnMode { kColumnList = 0, kFusedDense = 1, kBlockList = 2, kEveryColumn = 3 };
 
-// NWAVES waves per workgroup, each owning NQB blocks of 16 queries: 16 * NQB * NWAVES rows, a chunk or one of its parts.
-template <int E, int NQB, int NWAVES, int MODE = kColumnList>
-__global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_delta_kernel(AttnParams p) {
+// The work of one workgroup: NWAVES waves, each owning NQB blocks of 16 queries; 16 * NQB * NWAVES rows, chunk `unit` or part
+// `part` of it.
+template <int E, int NQB, int NWAVES, int MODE>
+__device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int part) {
     constexpr bool FUSED = MODE == kFusedDense;
     constexpr bool BLOCKS = MODE == kBlockList;
     // Every column in order: the columns are the list positions.  A mode of its own and not a null list inside
@@ -310,11 +311,9 @@ __global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_
     const int l16 = lane & 15;
 
     constexpr int ROWS = 16 * NQB * NWAVES;   // query rows of a workgroup
-    const int64_t block = attn_block_of(p.by_xcd);
-    const int64_t unit = block / p.parts;
     const int64_t bh = unit / p.NB;
     const int chunk = (int)(unit % p.NB);
-    const int row0 = chunk * p.c + (int)(block % p.parts) * ROWS;
+    const int row0 = chunk * p.c + part * ROWS;
     const int rows_valid = min(ROWS, p.N - row0);
     if (rows_valid <= 0) return;              // the last chunk may end before this part of it
     // Contents of counts and idx are the caller's precondition; they are clamped all the same so that a bad
@@ -632,6 +631,26 @@ __global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_
     }
 }
 
+// A workgroup per chunk, or, with a column list or every column, for the first p.whole chunks only: each of the others is
+// walked by a workgroup per 64 rows.  Those are the launch's last, partly filled round, or all of a small launch.
+template <int E, int NQB, int NWAVES, int MODE = kColumnList>
+__global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_delta_kernel(AttnParams p) {
+    uint32_t id = blockIdx.x, all = gridDim.x;
+    if constexpr (MODE == kColumnList || MODE == kEveryColumn) {
+        const uint32_t whole = (uint32_t)p.whole;   // a multiple of eight, or all of them
+        if (id >= whole) {
+            id -= whole;
+            all -= whole;
+            if (p.by_xcd) id = attn_run_of_xcd(id, all);
+            attn_rows<E, 1, NWAVES, MODE>(p, whole + id / NQB, (int)(id % NQB));
+            return;
+        }
+        all = whole;
+    }
+    if (p.by_xcd) id = attn_run_of_xcd(id, all);
+    attn_rows<E, NQB, NWAVES, MODE>(p, id, 0);
+}
+
 // Column sums of the attention probabilities (Sec. 3.3.1, the tensor D; Alg. 4):
 //   D[b,h,i,j] = sum over the rows q of chunk i of exp(scale*s_qj - m_q) / l_q
 // with (m_q, l_q) either from the dense attention pass of the same step (exact sums) or
@@ -815,17 +834,18 @@ static int32_t launch_attn_variant(const AttnParams& p, int64_t units, hipStream
 }
 
 // Query rows per workgroup (64 * blocks).  A workgroup of fewer rows takes less time per tile, though more per row: the
-// K and V tiles are fetched and read from LDS all the same.  So three blocks per wave (192 rows) are right for a long
-// launch, and fewer where the last round of workgroups would leave slots empty (two workgroups per CU = 512 slots) or
-// where there are fewer workgroups than CUs.  Measured time of a 32-key tile in us, with two workgroups on the CU and
-// with one (dense launches of 2 to 40 heads, 1024 to 18 000 tokens; for E = 64 more than two fit, the figures stand for
-// the same throughput with two):
+// K and V tiles are fetched and read from LDS all the same.  So three blocks per wave (192 rows) are right for whole
+// rounds of the 512 workgroup slots (two per CU), and 64 rows for a last round that would leave slots empty.
+// Measured time of a 32-key tile in us, with two workgroups on the CU and with one (dense launches of 2 to 40 heads, 1024
+// to 18 000 tokens; for E = 64 more than two fit, the figures stand for the same throughput with two):
 //     E = 128:  1 block 0.60 / 0.37   2 blocks 0.94 / 0.55   3 blocks 1.27 / 0.80
 //     E =  64:  1 block 0.31 / 0.24   2 blocks 0.50 / 0.38   3 blocks 0.74 / 0.52
 // and a launch takes (whole rounds) x (the first) + (a last round of more than half the slots: the first; of at most
 // half: the second), which orders the measured launches correctly: 24 heads x 4608 x 128: 268, 252 and 305 us with
-// three, two and one block; 12 x 2304: 57, 43, 45; 2 x 1024: 29.9, 21.7, 15.7; 24 x 3456 (432 workgroups of 192 rows):
-// 136, 152, 185; 40 x 18 000: 5259, 5833, 7405.
+// three, two and one block throughout; 12 x 2304: 57, 43, 45; 2 x 1024: 29.9, 21.7, 15.7; 24 x 3456 (432 workgroups of 192
+// rows): 136, 152, 185; 40 x 18 000: 5259, 5833, 7405.
+// With the last round alone in parts: 24 x 4608 x 128 220 us (512 whole chunks and 64 in three parts each), as a column list
+// of 323 40.2 -> 34.9 us; 24 x 4608 x 64 145 -> 136 us.
 static double attn_rounds_cost(int E, int blocks, int64_t workgroups) {
     static const double paired[2][3] = {{0.31, 0.50, 0.74}, {0.60, 0.94, 1.27}};
     static const double alone[2][3] = {{0.24, 0.38, 0.52}, {0.37, 0.55, 0.80}};
@@ -834,36 +854,42 @@ static double attn_rounds_cost(int E, int blocks, int64_t workgroups) {
            (last == 0 ? 0. : last <= 256 ? alone[e][blocks - 1] : paired[e][blocks - 1]);
 }
 
-static int32_t launch_attn(const AttnParams& p, int E, int64_t units, hipStream_t s) {
-    const int64_t bh = units / p.NB;
-    if (!p.idx) {   // without a list the rows need not follow the chunks: any of the three
-        auto groups = [&](int blocks) { return bh * ((p.N + 64 * blocks - 1) / (64 * blocks)); };
-        int best = 3;
-        for (int blocks = 2; blocks >= 1; blocks--)
-            if (attn_rounds_cost(E, blocks, groups(blocks)) < attn_rounds_cost(E, best, groups(best))) best = blocks;
-        AttnParams d = p;
-        d.c = 64 * best;
-        d.NB = (p.N + d.c - 1) / d.c;
-        if (E == 128) {
-            if (best == 3) return launch_attn_variant<128, 3, 4, kEveryColumn>(d, groups(3), s);
-            if (best == 2) return launch_attn_variant<128, 2, 4, kEveryColumn>(d, groups(2), s);
-            return launch_attn_variant<128, 1, 4, kEveryColumn>(d, groups(1), s);
-        }
-        if (best == 3) return launch_attn_variant<64, 3, 4, kEveryColumn>(d, groups(3), s);
-        if (best == 2) return launch_attn_variant<64, 2, 4, kEveryColumn>(d, groups(2), s);
-        return launch_attn_variant<64, 1, 4, kEveryColumn>(d, groups(1), s);
-    }
-    // with a list: a chunk whole, or in parts of 64 rows
+// How many of `units` chunks of `blocks` * 64 rows have a workgroup each: all, or those of the whole rounds.  *cost: what
+// the launch then takes.
+static int64_t attn_whole_chunks(int E, int blocks, int64_t units, double* cost) {
+    const int64_t last = units % 512, rounds = units - last;
+    const double whole = attn_rounds_cost(E, blocks, units);
+    const double parts = attn_rounds_cost(E, blocks, rounds) + attn_rounds_cost(E, 1, last * blocks);
+    *cost = parts < whole ? parts : whole;
+    return parts < whole ? rounds : units;
+}
+
+template <int MODE>
+static int32_t launch_attn_parts(AttnParams p, int E, int64_t units, hipStream_t s) {
     const int blocks = p.c / 64;
-    if (attn_rounds_cost(E, 1, units * blocks) < attn_rounds_cost(E, blocks, units)) {
-        AttnParams d = p;
-        d.parts = blocks;
-        return E == 128 ? launch_attn_variant<128, 1, 4>(d, units * blocks, s) : launch_attn_variant<64, 1, 4>(d, units * blocks, s);
+    double cost;
+    const int64_t whole = attn_whole_chunks(E, blocks, units, &cost);
+    p.whole = (int)whole;
+    const int64_t groups = whole + (units - whole) * blocks;
+    if (E == 128 && blocks == 3) return launch_attn_variant<128, 3, 4, MODE>(p, groups, s);
+    if (E == 128) return launch_attn_variant<128, 2, 4, MODE>(p, groups, s);
+    if (blocks == 3) return launch_attn_variant<64, 3, 4, MODE>(p, groups, s);
+    return launch_attn_variant<64, 2, 4, MODE>(p, groups, s);
+}
+
+static int32_t launch_attn(const AttnParams& p, int E, int64_t units, hipStream_t s) {
+    if (p.idx) return launch_attn_parts<kColumnList>(p, E, units, s);
+    // without a list the rows need not follow the chunks: 128 or 192 at a time, whichever is cheaper
+    const int64_t bh = units / p.NB;
+    AttnParams d[2] = {p, p};
+    double cost[2];
+    for (int i = 0; i < 2; i++) {
+        d[i].c = i == 0 ? 192 : 128;
+        d[i].NB = (p.N + d[i].c - 1) / d[i].c;
+        attn_whole_chunks(E, d[i].c / 64, bh * d[i].NB, &cost[i]);
     }
-    if (E == 128 && p.c == 192) return launch_attn_variant<128, 3, 4>(p, units, s);
-    if (E == 128 && p.c == 128) return launch_attn_variant<128, 2, 4>(p, units, s);
-    if (E == 64 && p.c == 192) return launch_attn_variant<64, 3, 4>(p, units, s);
-    return launch_attn_variant<64, 2, 4>(p, units, s);
+    const AttnParams& best = cost[1] < cost[0] ? d[1] : d[0];
+    return launch_attn_parts<kEveryColumn>(best, E, bh * best.NB, s);
 }
 
 static int32_t launch_attn_fused(const AttnParams& p, int E, int64_t units, hipStream_t s) {
@@ -930,7 +956,7 @@ extern "C" int32_t chipmunk_attn_sparse_delta(const uint16_t* q, const uint16_t*
     p.q = q; p.k = k; p.v = v; p.base = base; p.out = out; p.idx = idx; p.counts = counts;
     p.row_m = nullptr; p.row_l = nullptr;
     p.prev_m = nullptr; p.prev_l = nullptr; p.colsum = nullptr; p.ld_colsum = 0;
-    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.by_xcd = attn_by_xcd(N, E); p.k_stride = k_stride;
+    p.N = N; p.NB = NB; p.c = c; p.whole = 0; p.by_xcd = attn_by_xcd(N, E); p.k_stride = k_stride;
     p.sl2 = softmax_scale * 1.4426950408889634f;
     p.o_scale = o_scale;
     return launch_attn(p, E, units, (hipStream_t)stream);
@@ -954,7 +980,7 @@ extern "C" int32_t chipmunk_attn_block_sparse_delta(const uint16_t* q, const uin
     p.q = q; p.k = k; p.v = v; p.base = base; p.out = out; p.idx = blocks; p.counts = block_counts;
     p.row_m = nullptr; p.row_l = nullptr;
     p.prev_m = nullptr; p.prev_l = nullptr; p.colsum = nullptr; p.ld_colsum = 0;
-    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.by_xcd = attn_by_xcd(N, E); p.k_stride = kb_stride;
+    p.N = N; p.NB = NB; p.c = c; p.whole = 0; p.by_xcd = attn_by_xcd(N, E); p.k_stride = kb_stride;
     p.sl2 = softmax_scale * 1.4426950408889634f;
     p.o_scale = o_scale;
     return launch_attn_blocks(p, E, units, (hipStream_t)stream);
@@ -983,7 +1009,7 @@ extern "C" int32_t chipmunk_attn_dense(const uint16_t* q, const uint16_t* k, con
     p.row_m = colsum ? (float*)ws : nullptr;
     p.row_l = colsum ? (float*)ws + (int64_t)B * H * N : nullptr;
     p.prev_m = nullptr; p.prev_l = nullptr; p.colsum = nullptr; p.ld_colsum = 0;
-    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.by_xcd = attn_by_xcd(N, E); p.k_stride = 0;
+    p.N = N; p.NB = NB; p.c = c; p.whole = 0; p.by_xcd = attn_by_xcd(N, E); p.k_stride = 0;
     p.sl2 = softmax_scale * 1.4426950408889634f;
     p.o_scale = 1.f;
     int32_t st = launch_attn(p, E, units, s);
@@ -1030,7 +1056,7 @@ extern "C" int32_t chipmunk_attn_dense_colsum_stale(const uint16_t* q, const uin
     p.q = q; p.k = k; p.v = v; p.base = nullptr; p.out = out; p.idx = nullptr; p.counts = nullptr;
     p.row_m = new_m; p.row_l = new_l;
     p.prev_m = prev_m; p.prev_l = prev_l; p.colsum = colsum; p.ld_colsum = ld_colsum;
-    p.N = N; p.NB = NB; p.c = c; p.parts = 1; p.by_xcd = attn_by_xcd(N, E); p.k_stride = 0;
+    p.N = N; p.NB = NB; p.c = c; p.whole = 0; p.by_xcd = attn_by_xcd(N, E); p.k_stride = 0;
     p.sl2 = softmax_scale * 1.4426950408889634f;
     p.o_scale = 1.f;
     return launch_attn_fused(p, E, units, (hipStream_t)stream);

@@ -48,10 +48,11 @@ def test_column_sums_in_pieces_of_the_keys(cm, oracle, N, E, c):
 
 
 @pytest.mark.parametrize("E", [64, 128])
-@pytest.mark.parametrize("H,N", [(2, 1), (3, 130), (200, 256), (400, 192), (200, 190), (400, 65)])
+@pytest.mark.parametrize("H,N", [(2, 1), (3, 130), (200, 256), (400, 192), (200, 190), (400, 65), (520, 190), (530, 129)])
 def test_dense_attention_in_workgroups_of_64_128_and_192_rows(cm, oracle, E, H, N):
-    """Without a list a workgroup takes one, two or three blocks of 64 rows, by the number of workgroups; c is 128 here
-    and 192 there, which no longer decides it.  The ends of the sequence leave waves and whole blocks without rows."""
+    """Without a list a workgroup takes one, two or three blocks of 64 rows, by the number of workgroups, those of the last
+    round one where that is cheaper (the last two sizes); c is 128 here and 192 there, which no longer decides it.  The
+    ends of the sequence leave waves and whole blocks without rows."""
     q, k, v = recipes.attn_inputs(1, H, N, E, 22, DEV)
     scale = 1 / math.sqrt(E)
     c = 128 if N % 2 else 192
@@ -63,10 +64,11 @@ def test_dense_attention_in_workgroups_of_64_128_and_192_rows(cm, oracle, E, H, 
 
 
 @pytest.mark.parametrize("H,N,E,c,k", [(1, 193, 128, 192, 70), (2, 650, 64, 192, 33), (2, 300, 128, 128, 129),
-                                       (110, 320, 64, 128, 20), (200, 384, 128, 192, 9), (200, 500, 128, 192, 70)])
+                                       (110, 320, 64, 128, 20), (200, 384, 128, 192, 9), (200, 500, 128, 192, 70),
+                                       (260, 300, 128, 192, 40), (520, 129, 64, 128, 65)])
 def test_column_lists_walked_by_parts_of_a_chunk(cm, oracle, H, N, E, c, k):
     """Few chunks: a workgroup per 64 rows, all of a chunk walking its one list; the last chunk ends before its last
-    part.  The last three cases have enough chunks to be walked whole."""
+    part.  Then three cases with enough chunks to be walked whole, and two whose last round alone is in parts."""
     q, kk, v = recipes.attn_inputs(1, H, N, E, 23, DEV)
     scale, NB = 1 / math.sqrt(E), -(-N // c)
     base = recipes.attn_base(tuple(q.shape), k, "delta", 23, DEV)
