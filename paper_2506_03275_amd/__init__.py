@@ -90,13 +90,13 @@ def _check(status, where):
 def _ptr(t, dtype, name):
     if t is None:
         return None
+    if isinstance(t, torch.Tensor) and t.dtype is dtype and t.is_cuda and t.is_contiguous():
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor) or t.dtype != dtype:
         raise TypeError(f"{name}: expected a torch tensor of {dtype}")
     if not t.is_cuda:
         raise ValueError(f"{name}: must live on the GPU")
-    if not t.is_contiguous():
-        raise ValueError(f"{name}: must be contiguous")
-    return t.data_ptr()
+    raise ValueError(f"{name}: must be contiguous")
 
 
 def _ptr_rows(t, dtype, name):
@@ -112,8 +112,13 @@ def _ptr_rows(t, dtype, name):
     return t.data_ptr()
 
 
+_current_device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+
+
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    """The current stream of the current device as torch.cuda.current_stream().cuda_stream gives it, without the Stream object
+    (2.8 us a call, of the 9 that a small attention call took on the host; 0.2 us this way)."""
+    return _raw_stream(_current_device())
 
 
 def voxel_reorder(src, dst, perm, inv_perm, n_prefix, T, H, W, n_suffix, vt, vh, vw, inverse=False):
