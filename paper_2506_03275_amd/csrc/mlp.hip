@@ -772,6 +772,30 @@ static int32_t launch_dense_gemm(DenseGemmParams p, int second_dim, hipStream_t 
     return launch_status();
 }
 
+// Whether the column-sparse first GEMM takes 256 selected neurons per workgroup (mlp_dense.h, eight waves) or 128.  All
+// tiles of a chunk run on one XCD (32 CUs, a workgroup each), so a launch takes whole rounds of the busiest XCD; us per
+// contraction step and per tile end, measured: c = 192: 1.45 and 8 against 0.82 and 5, c = 128: 1.02 and 5 against 0.62 and 3.
+// Kernel times, 256 against 128: 24 chunks x 1229 of 12 288 x 3072: 69 and 43 us; 47 chunks: 82 and 96; 94 x 968 of 13 824 x
+// 5120: 274 and 229; 394: 881 and 945 (whole delta 1993 -> 1895 us); c = 128, 36 x 1229 of 12 288 x 3072: 54 and 65.
+static bool wide_delta_pays(int units, int D, int c, int k_stride) {
+    const int chunks = (units + 7) / 8, steps = D / kBK;
+    auto rounds = [&](int width) { return ((int64_t)chunks * ((k_stride + width - 1) / width) + 31) / 32; };
+    return c == 192 ? (double)rounds(kDenseTile) * (1.45 * steps + 8) < (double)rounds(kBN) * (0.82 * steps + 5)
+                    : (double)rounds(kDenseTile) * (1.02 * steps + 5) < (double)rounds(kBN) * (0.62 * steps + 3);
+}
+
+template <int BM>
+static int32_t launch_delta_gemm(DenseGemmParams p, hipStream_t s) {
+    p.tiles_p = 1;
+    p.tiles_q = (p.k_stride + kDenseTile - 1) / kDenseTile;
+    constexpr int lds = 2 * kDenseStage;
+    static_assert(kDenseTile * (BM * 2 + 16) <= lds, "the activations' tile fits the stages");
+    if (hipFuncSetAttribute((const void*)mlp_dense_gemm_kernel<kDelta, BM>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+        return CHIPMUNK_ERR_LAUNCH;
+    hipLaunchKernelGGL((mlp_dense_gemm_kernel<kDelta, BM>), dim3((unsigned)xcd_grid_size(p.tiles_q, p.units)), dim3(512), lds, s, p);
+    return launch_status();
+}
+
 static int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
 static int32_t check_mlp_shapes(int B, int N, int D, int F, int c) {
@@ -857,8 +881,17 @@ static int32_t run_mlp_sparse_delta(const uint16_t* x, const uint16_t* w1, const
     g1.delta_t = (uint16_t*)ws; g1.act_t = act_t; g1.a_ld = a_ld;
     g1.N = N; g1.NB = NB; g1.D = D; g1.F = F;
     g1.k_stride = k_stride; g1.k_pad = k_pad; g1.act = act;
-    st = c == 192 ? launch_gemm1<192, kSparseDelta>(g1, k_pad / kBN, units, s)
-                  : launch_gemm1<128, kSparseDelta>(g1, k_pad / kBN, units, s);
+    if (wide_delta_pays(units, D, c, k_stride)) {
+        DenseGemmParams g;
+        g.x = x; g.w1 = w1; g.w2 = nullptr; g.bias = b1; g.a_cache = a_cache; g.out = nullptr; g.scores = nullptr; g.a_ld = a_ld;
+        g.N = N; g.D = D; g.F = F; g.act = act; g.pieces = 1;
+        g.idx = idx; g.counts = counts; g.delta_t = (uint16_t*)ws; g.act_t = act_t;
+        g.NB = NB; g.k_stride = k_stride; g.k_pad = k_pad; g.units = units;
+        st = c == 192 ? launch_delta_gemm<192>(g, s) : launch_delta_gemm<128>(g, s);
+    } else {
+        st = c == 192 ? launch_gemm1<192, kSparseDelta>(g1, k_pad / kBN, units, s)
+                      : launch_gemm1<128, kSparseDelta>(g1, k_pad / kBN, units, s);
+    }
     if (st != CHIPMUNK_OK) return st;
 
     Gemm2Params g2;

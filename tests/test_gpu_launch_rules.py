@@ -179,3 +179,31 @@ def test_last_step_of_column_lists(cm, oracle, E, H, N, c):
     ref = oracle.attn_sparse_delta(si.np_f32(q), si.np_f32(kk), si.np_f32(v), idx.cpu().numpy(), counts.cpu().numpy(),
                                    basen, c, scale, 1.0)
     assert rel_err(si.np_f32(out), ref, ref - basen) <= REL_TOL
+
+
+@pytest.mark.parametrize("N,D,F,c,k,act,bias", [(700, 128, 4480, 192, 4300, 1, True), (900, 256, 4416, 128, 4300, 0, False),
+                                                (192, 128, 4352, 192, 4352, 1, True)])
+def test_mlp_delta_with_256_neurons_per_workgroup(cm, oracle, N, D, F, c, k, act, bias):
+    """The first GEMM of the MLP delta on its wide tiles (few chunks, many neurons): counts that end in a tile's first half, in
+    its second, at its edge, at nothing; a ragged last chunk; both forms of the cache write-back, bit for bit alike."""
+    x1, x2, w1, b1, w2, b2 = recipes.mlp_inputs(1, N, D, F, 28, DEV)
+    if not bias:
+        b1 = torch.zeros_like(b1)
+    NB, a_ld = -(-N // c), -(-N // 8) * 8 + 8
+    o_ref, a_ref, _ = oracle.mlp_dense(si.np_f32(x1), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2), si.np_f32(b2), c, act, a_ld=a_ld)
+    o_cache, a_cache = (torch.from_numpy(t).to(torch.bfloat16).to(DEV) for t in (o_ref, a_ref))
+    o_ref, a_ref = (si.np_f32(t).astype(np.float64) for t in (o_cache, a_cache))
+    o_before, a_before = o_ref.copy(), a_cache.clone()
+    idx, _ = recipes.mlp_indices(NB, F, k, 28, DEV)
+    counts = torch.tensor([k, 0, 256, 300, 129, 1, 512, k - 1][:NB], dtype=torch.int32, device=DEV)
+    idx, counts = idx.view(1, NB, k), counts.view(1, NB)
+    o2, a2 = o_cache.clone(), a_cache.clone()
+    bias1 = b1 if bias else None
+    cm.mlp_sparse_delta(x2, w1, bias1, w2, idx, counts, a_cache, o_cache, c, act, _u8(cm.mlp_workspace_bytes(1, N, D, F, c, k)))
+    cm.mlp_sparse_delta_overlapped(x2, w1, bias1, w2, idx, counts, a2, o2, c, act, _u8(cm.mlp_overlapped_workspace_bytes(1, N, D, F, c, k)))
+    assert torch.equal(a_cache, a2) and torch.equal(o_cache, o2)
+    oracle.mlp_sparse_delta(si.np_f32(x2), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2), idx.cpu().numpy(), counts.cpu().numpy(),
+                            a_ref, o_ref, c, act)
+    assert rel_err(si.np_f32(a_cache)[..., :N], a_ref[..., :N]) <= REL_TOL
+    assert rel_err(si.np_f32(o_cache), o_ref, o_ref - o_before) <= REL_TOL
+    assert torch.equal(a_cache[..., N:], a_before[..., N:])
