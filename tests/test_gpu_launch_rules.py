@@ -139,7 +139,8 @@ def test_topk_of_rows_kept_in_registers(cm, oracle, C, kind):
 
 
 @pytest.mark.parametrize("B,N,D,F,c", [
-    (1, 1, 128, 64, 128),              # one token, one neuron tile a quarter full, two pieces of one step
+    (1, 1, 128, 64, 128),              # one token, one neuron tile a quarter full, one piece
+    (1, 300, 512, 64, 128),            # eight pieces of one step
     (1, 384, 640, 7680, 192),          # two chunks; ten steps in eight pieces
     (1, 127 * 128, 128, 320, 128),     # 127, 128 and 129 chunks: both sides of a tile
     (2, 64 * 192, 256, 576, 192),
