@@ -535,8 +535,10 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
     // The next step's tiles are requested between the score products of this step's first tile, and the columns
     // of the step after that behind them.  The list's last step has a copy of its own (LAST): it requests the base rows
     // instead, masks the positions beyond the list, and leaves out a tile that has none; its half, `last_half`, has
-    // been added to the addresses.  The kernel with the column sums, which merges with nothing and has no registers left
-    // for a third copy (244 bytes of spills, 8.0 ms instead of 5.9 at 40 heads x 18 000), runs its last step in the loop.
+    // been added to the addresses.  Without a list the last step runs in the loop, and its requests reach past the end into
+    // the buffer that nobody reads: few callers merge there, the kernel with the column sums has no registers left for a
+    // third copy (244 bytes of spills, 8.0 ms instead of 5.9 at 40 heads x 18 000), and the plain one is faster as well
+    // (24 x 115 456: 125.6 -> 124.0 ms, 40 x 18 000: 5.23 -> 5.17).
     auto step = [&](auto half_c, auto last_c, int t, int last_half) {
         constexpr int half = decltype(half_c)::value;
         constexpr bool LAST = decltype(last_c)::value;
@@ -571,7 +573,7 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
                 if (col0 + kTilesPerStep * kTileRows > p.N) attn_mask_tail<E, NQB>(S, col0, s, p.N, g);
             } else if constexpr (LAST) {
                 attn_mask_tail<E, NQB, MODE == kColumnList>(S, t * kTileRows, s, count, g);
-            } else if constexpr (FUSED) {
+            } else if constexpr (NOLIST) {
                 if (t + kTilesPerStep >= ntiles) attn_mask_tail<E, NQB>(S, t * kTileRows, s, count, g);
             }
             attn_update_max<E, NQB>(st, S, t + s == 0, p.sl2, slack);
@@ -580,7 +582,7 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
         }
     };
     const int last_tile = ntiles - kTilesPerStep;   // first tile of the last step
-    const int loop_end = FUSED ? ntiles : last_tile;
+    const int loop_end = NOLIST ? ntiles : last_tile;
 #pragma unroll 1
     for (int t = 0; t < loop_end; t += 2 * kTilesPerStep) {
         step(std::integral_constant<int, 0>{}, std::false_type{}, t, 0);
@@ -588,7 +590,7 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
         step(std::integral_constant<int, 1>{}, std::false_type{}, t + kTilesPerStep, 0);
     }
     const int last_half = (last_tile / kTilesPerStep) & 1;
-    if constexpr (!FUSED) {
+    if constexpr (!NOLIST) {
         const uint32_t shift = (uint32_t)(last_half * kTilesPerStep * STAGE);
 #pragma unroll
         for (int es = 0; es < E / 32; es++) kaddr[es] += shift;
@@ -596,7 +598,7 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
         for (int eb = 0; eb < E / 16; eb++) vaddr[eb] += shift;
         step(std::integral_constant<int, 0>{}, std::true_type{}, last_tile, last_half);
     }
-    wait_all_memory();  // the base rows (FUSED: the transfers behind the last step) have landed
+    wait_all_memory();  // the base rows (NOLIST: the transfers behind the last step) have landed
     if (FUSED) {
         __syncthreads();  // the last step's partial sums are complete
         flush_column_sums(last_tile);
@@ -609,6 +611,11 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
         float f = p.o_scale / ltot;
         int qrow = (w * NQB + qb) * 16 + l16;
         const int64_t row_off = (int64_t)(row0 + min(qrow, rows_valid - 1)) * E + 4 * g;
+        u32x2 bases[NOLIST ? E / 16 : 1];
+        if (MODE == kEveryColumn && baseh) {   // all requested before the first store
+#pragma unroll
+            for (int eb = 0; eb < E / 16; eb++) bases[eb] = *reinterpret_cast<const u32x2*>(baseh + row_off + eb * 16);
+        }
         if (qrow < rows_valid) {
             if (p.row_m && g == 0) {
                 p.row_m[bh * p.N + row0 + qrow] = -st.negm[qb][0] * (p.sl2 * 0.6931471805599453f);
@@ -617,7 +624,8 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
 #pragma unroll
             for (int eb = 0; eb < E / 16; eb++) {
                 u32x2 b = u32x2{0, 0};
-                if (!FUSED && baseh)
+                if (MODE == kEveryColumn && baseh) b = bases[eb];
+                if (!NOLIST && baseh)
                     b = *reinterpret_cast<const u32x2*>(smem + base_place(last_half, qb) + l16 * ROWB +
                                                         (((2 * eb + (g >> 1)) ^ base_swizzle(l16)) * 16) + (g & 1) * 8);
                 float o0 = bf16_bits_to_float(b[0] & 0xffffu) + f * st.O[eb][qb][0];
@@ -822,8 +830,8 @@ __global__ __launch_bounds__(256, 4) void attn_colsum_kernel(ColsumParams p) {
 
 template <int E, int NQB, int NWAVES, int MODE = kColumnList>
 static int32_t launch_attn_variant(const AttnParams& p, int64_t units, hipStream_t s) {
-    // the tile buffers, and behind them each wave's third block of base rows
-    constexpr int lds = kStages * 2 * kTileRows * E * 2 + (MODE != kFusedDense && NQB > 2 ? NWAVES * (NQB - 2) * 16 * E * 2 : 0);
+    // the tile buffers, and behind them, where there is a list, each wave's third block of base rows
+    constexpr int lds = kStages * 2 * kTileRows * E * 2 + ((MODE == kColumnList || MODE == kBlockList) && NQB > 2 ? NWAVES * (NQB - 2) * 16 * E * 2 : 0);
     // set at every launch: the attribute is kept per device, and a flag remembered here would be neither
     // per device nor safe between host threads
     if (hipFuncSetAttribute((const void*)attn_sparse_delta_kernel<E, NQB, NWAVES, MODE>,
