@@ -734,27 +734,29 @@ static int32_t launch_gemm2(Gemm2Params p, int col_tiles, int units, hipStream_t
 }
 
 // Whether a dense GEMM takes the 256 x 256 tiles of mlp_dense.h or the chunk's tiles (192 or 128 x 128).  Both are priced as
-// whole rounds of workgroups over the chip plus a last one that is partly filled, in us per contraction step, with
-// figures measured from 500 x 1024 x 4096 to 18 000 x 5120 x 13 824 (tokens x D x F):
-//   first GEMM, one workgroup per CU:      256 x 256: 1.5 a round, and 12 us a tile for its ends;
-//                                          192 x 128: 0.9 and 6;  128 x 128: 0.68 and 6
-//   second GEMM, 256 x 256: 1.8 a round, 1.25 with at most half the CUs;
-//                192 x 128 (two per CU): 1.75, 0.9 with at most one per CU;  128 x 128: 1.3, 0.7
-// (kernel times, large against small tiles: first GEMM 500 x 1024 x 4096: 36 and 21 us, 2304 x 1152 x 4608: 35 and 47,
-// 2304 x 3072 x 12 288: 158 and 225; second: 1000 x 2048 x 8192: 158 and 107, 3500 x 5120 x 13 824: 626 and 611,
-// 7000 x 2048 x 8192: 255 and 326).
+// whole rounds of workgroups over the chip plus a last one that is partly filled: a round with a share x of its slots
+// taken costs g + (1 - g) x of a whole one, because few workgroups leave the others' memory rate and power to each other.
+// In us per contraction step, fitted to a hundred sizes from 500 x 1792 x 2816 to 54 000 x 512 x 8576 (tokens x D x F):
+//   first GEMM, one workgroup per CU:  256 x 256: 0.94 a round, and 12 us a tile for its ends, g = 0.79;
+//                                      192 x 128: 0.62 and 5;  128 x 128: 0.58 and 4;  g = 0.26
+//   second GEMM:                       256 x 256: 1.37, g = 0.46, and 5.5 us more than the others in all;
+//                                      192 x 128 (two per CU): 1.70;  128 x 128: 1.20;  g = 0.21
+// (times of the two GEMMs with large - small tiles, us: first 500 x 1792 x 2816: +29; 2 x 548 x 1792 x 7424: +6; 2928 x 3072 x
+// 12 224: -57; second 2755 x 1792 x 9408 in chunks of 128: +30; 1969 x 4992 x 14 080 in chunks of 192: -159; two of
+// 5309 x 4864 x 12 416: -206.  Priced with whole and half rounds the rule took the slower tiles for 23 of these two hundred
+// GEMMs, 2 x 548 x 1792 x 7424 in 185 instead of 163 us; now for ten, and for 7 of a hundred that the fit had not seen.)
 static bool large_tiles_pay(bool second, int B, int N, int D, int F, int c) {
     const int64_t chunks = (N + c - 1) / c, large_n = (N + kDenseTile - 1) / kDenseTile;
     const int width = second ? D : F, steps = (second ? F : D) / kBK;
     const int64_t small = B * chunks * ((width + kBN - 1) / kBN), large = B * large_n * ((width + kDenseTile - 1) / kDenseTile);
-    auto rounds = [](int64_t tiles, int slots) { return (double)((tiles + slots - 1) / slots); };
     if (B > 65535) return false;   // the large tiles take the batch from the second grid dimension
-    if (!second) return rounds(large, 256) * (1.5 * steps + 12) < rounds(small, 256) * ((c == 192 ? 0.9 : 0.68) * steps + 6);
-    auto cost = [](int64_t tiles, int slots, double whole, double half) {
+    auto rounds = [](int64_t tiles, int slots, double g) {
         const int64_t last = tiles % slots;
-        return (double)(tiles / slots) * whole + (last == 0 ? 0. : last <= slots / 2 ? half : whole);
+        return (double)(tiles / slots) + (last == 0 ? 0. : g + (1. - g) * (double)last / slots);
     };
-    return cost(large, 256, 1.8, 1.25) < (c == 192 ? cost(small, 512, 1.75, 0.9) : cost(small, 512, 1.3, 0.7));
+    if (!second) return rounds(large, 256, 0.79) * (0.94 * steps + 12.) <
+                        rounds(small, 256, 0.26) * (c == 192 ? 0.62 * steps + 5. : 0.58 * steps + 4.);
+    return rounds(large, 256, 0.46) * 1.37 * steps + 5.5 < rounds(small, 512, 0.21) * (c == 192 ? 1.70 : 1.20) * steps;
 }
 
 template <int MODE>

@@ -85,11 +85,11 @@ def test_column_lists_walked_by_parts_of_a_chunk(cm, oracle, H, N, E, c, k):
 
 
 @pytest.mark.parametrize("B,N,D,F,c,act,bias", [
-    (1, 521, 128, 11328, 192, 1, True),      # first GEMM on 256 x 256 tiles: two steps, neurons and tokens ragged
-    (2, 300, 256, 9216, 192, 0, False),      # two batches, no bias
-    (1, 8300, 1152, 192, 128, 0, True),      # second GEMM: three steps, half a tile of columns missing, tokens ragged
-    (1, 8301, 1152, 64, 128, 1, False),      # one step
-    (2, 4150, 1152, 128, 128, 1, True),
+    (1, 1021, 128, 16320, 192, 1, True),     # first GEMM on 256 x 256 tiles: two steps, neurons and tokens ragged
+    (2, 509, 256, 16320, 192, 0, False),     # two batches, no bias
+    (1, 4090, 3968, 320, 192, 0, True),      # second GEMM: five steps, half a tile of columns missing, tokens ragged
+    (1, 28660, 4096, 64, 192, 1, False),     # one step
+    (2, 2041, 3968, 384, 192, 1, True),
 ])
 def test_dense_mlp_on_large_tiles(cm, oracle, B, N, D, F, c, act, bias):
     """The dense GEMMs whose problem is large enough for 256 x 256 tiles; the cache cells past N stay as they are."""
