@@ -984,7 +984,8 @@ extern "C" int32_t chipmunk_topk_cols(const float* cur, const float* prev, int R
         // Waves per row: a step costs a wave its share of the counting and about 40 instructions of sums and exchange, so
         // few waves serve many short rows best, and eight a row whose keys would otherwise fill the registers of four.
         // Us for 5000 rows of 1024 columns with two, four and eight waves: 14.4, 17.1, 30.9; 14 448 rows of 6500 with
-        // four and eight: 144, 210; 602 rows of 12 288 (with previous scores): 25.9 and 22.9.
+        // four and eight: 144, 210; 602 rows of 12 288 (with previous scores): 25.9 and 22.9.  Registers for four units of a wave
+        // rather than five: 509 rows of 3392 (with previous scores) 9.9 -> 9.1.
         const int groups = (C + 255) / 256;
         const int waves = groups <= 4 ? 2 : groups <= 28 ? 4 : 8;
         const int per_wave = (groups + waves - 1) / waves;
@@ -1004,6 +1005,7 @@ extern "C" int32_t chipmunk_topk_cols(const float* cur, const float* prev, int R
         } else if (waves == 4) {
             if (per_wave <= 2) launch(four, std::integral_constant<int, 2>{});
             else if (per_wave <= 3) launch(four, std::integral_constant<int, 3>{});
+            else if (per_wave <= 4) launch(four, std::integral_constant<int, 4>{});
             else if (per_wave <= 5) launch(four, std::integral_constant<int, 5>{});
             else launch(four, std::integral_constant<int, 7>{});
         } else {
