@@ -775,15 +775,20 @@ static int32_t launch_dense_gemm(DenseGemmParams p, int second_dim, hipStream_t 
 }
 
 // Whether the column-sparse first GEMM takes 256 selected neurons per workgroup (mlp_dense.h, eight waves) or 128.  All
-// tiles of a chunk run on one XCD (32 CUs, a workgroup each), so a launch takes whole rounds of the busiest XCD; us per
-// contraction step and per tile end, measured: c = 192: 1.45 and 8 against 0.82 and 5, c = 128: 1.02 and 5 against 0.62 and 3.
-// Kernel times, 256 against 128: 24 chunks x 1229 of 12 288 x 3072: 69 and 43 us; 47 chunks: 82 and 96; 94 x 968 of 13 824 x
-// 5120: 274 and 229; 394: 881 and 945 (whole delta 1993 -> 1895 us); c = 128, 36 x 1229 of 12 288 x 3072: 54 and 65.
+// tiles of a chunk run on one XCD (32 CUs, a workgroup each), so a launch takes rounds of the busiest XCD, the last one priced
+// by its share as above; us per contraction step and per tile end: c = 192: 1.45 and 13 against 0.87 and 5, c = 128: 1.02 and 5
+// against 0.66 and 3.  Kernel times, 256 against 128: 24 chunks x 1229 of 12 288 x 3072: 69 and 43 us; 47 chunks: 82 and 96; 94 x
+// 968 of 13 824 x 5120: 274 and 229; 394: 881 and 945 (whole delta 1993 -> 1895 us); c = 128, 36 x 1229 of 12 288 x 3072: 54 and
+// 65.  Whole deltas: c = 128, 81 x 337 of 1024 x 4608: 148 and 127; c = 192, 351 x 2534 of 7680 x 640: 771 and 742.
 static bool wide_delta_pays(int units, int D, int c, int k_stride) {
     const int chunks = (units + 7) / 8, steps = D / kBK;
-    auto rounds = [&](int width) { return ((int64_t)chunks * ((k_stride + width - 1) / width) + 31) / 32; };
-    return c == 192 ? (double)rounds(kDenseTile) * (1.45 * steps + 8) < (double)rounds(kBN) * (0.82 * steps + 5)
-                    : (double)rounds(kDenseTile) * (1.02 * steps + 5) < (double)rounds(kBN) * (0.62 * steps + 3);
+    auto rounds = [&](int width, double g) {
+        const int64_t tiles = (int64_t)chunks * ((k_stride + width - 1) / width), last = tiles % 32;
+        return (double)(tiles / 32) + (last == 0 ? 0. : g + (1. - g) * (double)last / 32.);
+    };
+    const double wide = rounds(kDenseTile, 0.79), narrow = rounds(kBN, 0.26);
+    return c == 192 ? wide * (1.45 * steps + 13.) < narrow * (0.87 * steps + 5.)
+                    : wide * (1.02 * steps + 5.) < narrow * (0.66 * steps + 3.);
 }
 
 template <int BM>

@@ -106,7 +106,7 @@ def test_dense_mlp_on_large_tiles(cm, oracle, B, N, D, F, c, act, bias):
     assert rel_err(si.np_f32(out), ref) <= REL_TOL
 
 
-@pytest.mark.parametrize("C", [1, 3, 255, 257, 1024, 1025, 2049, 3073, 5121, 7168, 7169, 10241, 12289, 14336, 14337])
+@pytest.mark.parametrize("C", [1, 3, 255, 257, 1024, 1025, 2049, 3073, 4096, 5121, 7168, 7169, 10241, 12289, 14336, 14337])
 @pytest.mark.parametrize("kind", ["normal", "constant", "two_values", "few_ulps", "spikes", "wide"])
 def test_topk_of_rows_kept_in_registers(cm, oracle, C, kind):
     """Both sides of every limit between the instances (and of the long rows), on scores that halving the range of keys
@@ -182,8 +182,8 @@ def test_last_step_of_column_lists(cm, oracle, E, H, N, c):
     assert rel_err(si.np_f32(out), ref, ref - basen) <= REL_TOL
 
 
-@pytest.mark.parametrize("N,D,F,c,k,act,bias", [(700, 128, 4480, 192, 4300, 1, True), (900, 256, 4416, 128, 4300, 0, False),
-                                                (192, 128, 4352, 192, 4352, 1, True)])
+@pytest.mark.parametrize("N,D,F,c,k,act,bias", [(700, 768, 8192, 192, 8130, 1, True), (900, 256, 8192, 128, 8130, 0, False),
+                                                (192, 768, 8192, 192, 8192, 1, True)])
 def test_mlp_delta_with_256_neurons_per_workgroup(cm, oracle, N, D, F, c, k, act, bias):
     """The first GEMM of the MLP delta on its wide tiles (few chunks, many neurons): counts that end in a tile's first half, in
     its second, at its edge, at nothing; a ragged last chunk; both forms of the cache write-back, bit for bit alike."""
