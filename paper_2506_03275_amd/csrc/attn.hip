@@ -679,15 +679,15 @@ struct ColsumParams {
 };
 
 // What bounds it: the vector instructions of the scores.  A score costs an FMA, an exponential (two issue slots) and an
-// add beside a quarter of an MFMA's issue slot, so the issue slots of a SIMD are 78 % taken (counters) while its matrix
-// pipe is 59 % busy; four waves per SIMD cover each other's phases.  Hence: -m - log l of a query enters as one addend
-// (an add per score where a multiplication by 1 / l stood, and half the registers), the 64 sums of a tile are folded
-// over the four lane groups by three swaps and three adds instead of four times two of each, transfers go through a
-// buffer resource (a key beyond N reads as zero and is not stored) with offsets that only step on, and the two
-// buffer halves are two copies of the step, so every LDS offset is an immediate.  24 heads x 18 000 tokens: 2.09 ms
-// before, 1.95 ms now (1.02 PFLOP/s of scores).  Four other orders of the same work (all scores of a tile first,
-// two blocks at a time, exponentials pinned between the products with three and four waves per SIMD) measured equal
-// or slower.
+// FMA (the weight's 1 / l) beside a quarter of an MFMA's issue slot; four waves per SIMD cover each other's phases.
+// The 64 sums of a tile are folded over the four lane groups by three swaps and three adds instead of four times two of
+// each, transfers go through a buffer resource (a key beyond N reads as zero and is not stored) with offsets that only
+// step on, and the two buffer halves are two copies of the step, so every LDS offset is an immediate.  24 heads x 18 000
+// tokens: 1.90 ms in one run over the keys with two waves per SIMD, 1.78 ms now (1.12 PFLOP/s of scores); 24 x 4608: 165
+// and 126 us.  1 / l is a factor: as part of the exponential's addend (-m - log l, half the registers, 1.75 ms) it is
+// rounded at twice the argument's magnitude, and the sums are three times as far off (7e-8 against 2.2e-7 and more).
+// Four other orders of the same work (all scores of a tile first, two blocks at a time, exponentials pinned between the
+// products with three and four waves per SIMD) measured equal or slower.
 template <int E, int NQB>
 __global__ __launch_bounds__(256, 4) void attn_colsum_kernel(ColsumParams p) {
     constexpr int ROWB = E * 2;
@@ -711,7 +711,7 @@ __global__ __launch_bounds__(256, 4) void attn_colsum_kernel(ColsumParams p) {
     float* drow = p.colsum + unit * p.ld;
 
     bf16x8 Q[E / 32][NQB];
-    float off[NQB][4];
+    float m2v[NQB][4], il[NQB][4];
 #pragma unroll
     for (int qb = 0; qb < NQB; qb++) {
         int qrow = (w * NQB + qb) * 16 + l16;
@@ -725,11 +725,9 @@ __global__ __launch_bounds__(256, 4) void attn_colsum_kernel(ColsumParams p) {
 #pragma unroll
         for (int r = 0; r < 4; r++) {  // the MFMA result holds query 4g+r of the block in register r
             int qr = (w * NQB + qb) * 16 + 4 * g + r;
-            off[qb][r] = -INFINITY;
-            if (qr < rows_valid) {
-                const int64_t at = bh * p.N + row0 + qr;
-                off[qb][r] = -p.row_m[at] * 1.4426950408889634f - __builtin_amdgcn_logf(p.row_l[at]);
-            }
+            bool ok = qr < rows_valid;
+            m2v[qb][r] = ok ? p.row_m[bh * p.N + row0 + qr] * 1.4426950408889634f : 0.f;
+            il[qb][r] = ok ? 1.f / p.row_l[bh * p.N + row0 + qr] : 0.f;
         }
     }
     const int koff = l16 * ROWB + ((g ^ swizzle<E>(l16)) * 16);
@@ -788,8 +786,8 @@ __global__ __launch_bounds__(256, 4) void attn_colsum_kernel(ColsumParams p) {
         for (int qb = 0; qb < NQB; qb++)
 #pragma unroll
             for (int r = 0; r < 4; r++) {
-                const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(S[qb][r], p.sl2, off[qb][r]));
-                part = qb + r == 0 ? e : part + e;
+                const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(S[qb][r], p.sl2, -m2v[qb][r]));
+                part = qb + r == 0 ? e * il[qb][r] : __builtin_fmaf(e, il[qb][r], part);
             }
         return part;
     };
