@@ -759,18 +759,18 @@ static bool large_tiles_pay(bool second, int B, int N, int D, int F, int c) {
     return rounds(large, 256, 0.46) * 1.37 * steps + 5.5 < rounds(small, 512, 0.21) * (c == 192 ? 1.70 : 1.20) * steps;
 }
 
-template <int MODE>
+template <int MODE, int BM = kDenseTile>
 static int32_t launch_dense_gemm(DenseGemmParams p, int second_dim, hipStream_t s) {
     const int width = MODE == kFirst ? p.N : MODE == kSecond ? p.D : p.F, height = MODE == kFirst ? p.F : p.N;
     const int tile_q = MODE == kScores ? 128 : kDenseTile;
-    p.tiles_p = (width + kDenseTile - 1) / kDenseTile;
+    p.tiles_p = (width + BM - 1) / BM;
     p.tiles_q = (height + tile_q - 1) / tile_q;
     // set at every launch: the attribute is kept per device (a flag remembered here would not be)
-    if (hipFuncSetAttribute((const void*)mlp_dense_gemm_kernel<MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, kDenseLds) !=
+    if (hipFuncSetAttribute((const void*)mlp_dense_gemm_kernel<MODE, BM>, hipFuncAttributeMaxDynamicSharedMemorySize, kDenseLds) !=
         hipSuccess)
         return CHIPMUNK_ERR_LAUNCH;
     const int per_xcd = (p.tiles_p * p.tiles_q + 7) / 8;
-    hipLaunchKernelGGL((mlp_dense_gemm_kernel<MODE>), dim3((unsigned)(per_xcd * 8), (unsigned)second_dim), dim3(512), kDenseLds, s, p);
+    hipLaunchKernelGGL((mlp_dense_gemm_kernel<MODE, BM>), dim3((unsigned)(per_xcd * 8), (unsigned)second_dim), dim3(512), kDenseLds, s, p);
     return launch_status();
 }
 
@@ -824,22 +824,41 @@ extern "C" size_t chipmunk_mlp_workspace_bytes(int B, int N, int D, int F, int c
     return (size_t)(units * round_up(k_stride > 0 ? k_stride : 1, kBN) * c * 2);
 }
 
-// Pieces the scores GEMM's contraction is cut into, so that a small problem still fills the GPU: as many as let the tiles of
-// 256 neurons x 128 chunks have a CU each, at least one contraction step per piece.  Whole calls in us with up to 128, 256
-// and 512 workgroups: 24 chunks x 3072 x 12 288 36, 27, 32; 94 x 5120 x 13 824 96, 84, 94; 602 x 3072 x 12 288 (240 tiles)
-// 197, 197, 227.
-static int scores_pieces(int units, int D, int F) {
-    const int tiles = ((F + kDenseTile - 1) / kDenseTile) * ((units + 127) / 128);
-    if (D / kBK <= 6) return 1;   // so few steps take less than the sum's launch: 8 chunks x 1024 x 256 (four) 12.3 -> 11.6 us
-    return std::max(1, std::min(std::min(256 / tiles, 16), D / kBK));
-}
-
-// Pieces the workspace has room for: never fewer than scores_pieces (whose tiles are at least half as many)
+// Pieces of the contraction that the workspace has room for: what workgroups of 128 neurons x 128 chunks over [hi | lo] would
+// take to fill the GPU.  The plan below never takes more.
 static int tile_mean_pieces(int units, int F) {
     int blocks = ((units + 127) / 128) * ((F + kBN - 1) / kBN);
     int pieces = 1;
     while (pieces < 16 && blocks * pieces < 768) pieces *= 2;
     return pieces;
+}
+
+// How the scores GEMM runs: into how many pieces its contraction is cut, and whether on the tiles of 128 neurons that add
+// the high parts in two sums (mlp_dense.h) or on those of 256 that add them in one.
+//   - Up to six contraction steps: one piece, two sums; a sum of pieces is a launch of its own, and 128 neurons fill more
+//     CUs.  Whole calls in us on tiles of 256 in one piece, in pieces, and like this, D = 256: 8 chunks x 1024 neurons 12.3,
+//     12.3, 10.6; 94 x 4096 14.6, 17.2, 11.6; 300 x 12 288 20.8, 32.9, 22.2; D = 384: 14.2, 12.3, 11.6; 16.5, 19.2, 12.6; 24.2,
+//     36.5, 25.6; D = 128: 10.4, 11.6, 9.4; 13.1, 15.9, 10.6; 17.1, 30.3, 17.8.
+//   - Otherwise as many pieces as let the tiles of 256 neurons x 128 chunks have a CU each (24 chunks x 3072 x 12 288 with up
+//     to 128, 256 and 512 workgroups: 36, 27, 32 us; 94 x 5120 x 13 824: 96, 84, 94), if the sums are then no longer than is
+//     exact enough, and else half as many pieces as that takes, in two sums each (in one sum each, twice the pieces: 156 tiles of
+//     D = 2688 172 us, like this 160; 70 tiles of D = 2048 99, 89; 46 of D = 1024 35, 29; 130 of D = 5120 178, 180).
+// Exact enough: no larger an error than the sum of tile_mean_pieces() pieces over [hi | lo], half of them high parts.  Eight
+// products are added with one rounding, whose error goes with the sum so far; in units of the variance that one
+// rounding of the result has, a sum of n = D / 8 such additions cut into h chains leaves n / (2 h), adding the chains up h / 2,
+// and each rounding at the size of the result 1.  (GEMM alone against 64 bits at 602 x 3072 x 12 288: 3.4e-7, by this count 3.4e-7.)
+struct ScoresPlan {
+    int pieces;
+    bool two_sums;
+};
+static ScoresPlan scores_plan(int units, int D, int F) {
+    const int steps = D / kBK, tiles = ((F + kDenseTile - 1) / kDenseTile) * ((units + 127) / 128);
+    if (steps <= 6) return {1, true};
+    const int fill = std::min(std::max(1, std::min(256 / tiles, 16)), steps);
+    const int chains = std::min(std::max(1, tile_mean_pieces(units, F) / 2), steps);
+    const double additions = D / 8;
+    if (additions / (2 * fill) + 0.5 * (fill + 1) <= additions / (2 * chains) + 1.5 * chains) return {fill, false};
+    return {std::max(1, chains / 2), true};
 }
 
 // Workspace of the token-merged pre-activation with the contraction cut in `pieces`: the chunk means in split
@@ -982,13 +1001,14 @@ static int32_t run_tile_mean(const uint16_t* x, const uint16_t* w1, float* T, in
                        N, NB, D, c);
     if (launch_status() != CHIPMUNK_OK) return CHIPMUNK_ERR_LAUNCH;
     // scores[unit, f] = <hi(unit) + lo(unit), w1_f>
-    pieces = std::min(pieces, scores_pieces(units, D, F));
+    const ScoresPlan plan = scores_plan(units, D, F);
+    pieces = std::min(pieces, plan.pieces);
     size_t means = ((size_t)units * 2 * D * 2 + 255) / 256 * 256;
     float* partial = pieces > 1 ? (float*)((char*)ws + means) : T;
     DenseGemmParams g;
     g.x = (const uint16_t*)ws; g.w1 = w1; g.w2 = nullptr; g.bias = nullptr; g.a_cache = nullptr; g.out = nullptr; g.a_ld = 0;
     g.scores = partial; g.N = units; g.D = D; g.F = F; g.act = 0; g.pieces = pieces;
-    int32_t st = launch_dense_gemm<kScores>(g, pieces, s);
+    int32_t st = plan.two_sums ? launch_dense_gemm<kScores, 128>(g, pieces, s) : launch_dense_gemm<kScores>(g, pieces, s);
     if (st != CHIPMUNK_OK || pieces == 1) return st;
     int64_t n4 = (int64_t)units * F / 4;
     hipLaunchKernelGGL(sum_pieces_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, partial, T, n4, pieces);
@@ -1048,10 +1068,10 @@ extern "C" int32_t chipmunk_mlp_tile_mean_preact_static(const uint16_t* x, const
     if (!aligned16(x) || !aligned16(w1) || !aligned16(T)) return CHIPMUNK_ERR_ALIGN;
     const int64_t units = (int64_t)B * ((N + c - 1) / c);
     if (units > 0x7fffff || units * 2 * D * 2 >= (1LL << 32)) return CHIPMUNK_ERR_SHAPE;
-    // as many pieces of the contraction as the general entry point would use, halved until the chunk means and the
-    // pieces' partial results fit the array; with one piece the scores go straight to T
-    int pieces = tile_mean_pieces((int)units, F);
-    while (pieces > 1 && tile_mean_bytes(B, N, D, F, c, pieces) > kStaticScratchBytes) pieces /= 2;
+    // as many pieces of the contraction as the general entry point uses, or as many as fit the array beside the chunk
+    // means; with one piece the scores go straight to T
+    int pieces = scores_plan((int)units, D, F).pieces;
+    while (pieces > 1 && tile_mean_bytes(B, N, D, F, c, pieces) > kStaticScratchBytes) pieces--;
     const size_t need = tile_mean_bytes(B, N, D, F, c, pieces);
     if (need == 0 || need > kStaticScratchBytes) return CHIPMUNK_ERR_WORKSPACE;   // the chunk means alone do not fit
     void* ws = nullptr;

@@ -83,12 +83,16 @@ __device__ __forceinline__ void finish_products() { asm volatile("s_nop 15\n\ts_
 //          fastest.
 // kSecond: out[n][d] = sum_f a_cache[f][n] w2[f][d] + b2[d]: P = output columns, Q = tokens, both with the contraction
 //          index slowest (transposing LDS reads).
-// kScores: scores[n][f] = <hi[n] + lo[n], w1[f]>, n a chunk: P = neurons, Q0 = the high parts of 128 chunk means, Q1 = their
-//          low parts; both go into the same accumulators, so a step fetches w1 once for two products.  256 x 128 tiles.
+// kScores: scores[n][f] = <hi[n] + lo[n], w1[f]>, n a chunk: P = BM neurons, Q0 = the high parts of 128 chunk means, Q1 = their
+//          low parts, so a step fetches w1 once for two products.  High and low parts have accumulators of their own:
+//          added to the high parts' sum, every low product costs it a rounding (602 x 3072 x 12 288, the GEMM alone: 4.9e-7
+//          off, apart 3.4e-7; same time).  With BM = 128 the high parts are added in two sums, one per slice of a step,
+//          half as long.
 // kDelta:  kFirst for the BM tokens of a chunk and 256 of its selected neurons, with the epilogue of the column-sparse form.
 template <int MODE, int BM = kDenseTile>
 __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams p) {
     constexpr bool SECOND = MODE == kSecond, SCORES = MODE == kScores, DELTA = MODE == kDelta;
+    constexpr bool TWO_SUMS = SCORES && BM == 128;           // the high parts' products in two sums, one per slice of a step
     constexpr int PB = BM / 64;                              // 16-row blocks of P per wave and half
     constexpr int HP = BM * 64;                              // bytes of a half tile of P
     constexpr int PT = HP / 1024;                            // its transfers: 16, 12 or 8 for the eight waves
@@ -126,7 +130,7 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
         const int band = tile / (8 * p.tiles_q), in_band = tile - band * 8 * p.tiles_q;
         const int band_p = min(8, p.tiles_p - 8 * band);
         const int tq = in_band / band_p, tp = 8 * band + (in_band - tq * band_p);
-        p0 = tp * kDenseTile;
+        p0 = tp * BM;
         q0 = tq * (SCORES ? 128 : kDenseTile);
         b = SCORES ? 0 : blockIdx.y;
         piece = SCORES ? blockIdx.y : 0;
@@ -220,12 +224,11 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
         }
     };
 
-    constexpr int NJ = SCORES ? 1 : 2;
-    f32x4 acc[2][NJ][PB][2];
+    f32x4 acc[2][TWO_SUMS ? 3 : 2][PB][2];   // [half of P][half of Q; third: Q0's second slice]
 #pragma unroll
     for (int i = 0; i < 2; i++)
 #pragma unroll
-        for (int j = 0; j < NJ; j++)
+        for (int j = 0; j < (TWO_SUMS ? 3 : 2); j++)
 #pragma unroll
             for (int a = 0; a < PB; a++)
 #pragma unroll
@@ -258,13 +261,13 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
         else asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)" ::: "memory");
         turn();
     };
-    auto multiply = [&](f32x4 (&C)[PB][2], const bf16x8 (&Q)[2][2]) {
+    auto multiply = [&](f32x4 (&C)[PB][2], f32x4 (&C1)[PB][2], const bf16x8 (&Q)[2][2]) {   // C1: of the second slice
 #pragma unroll
         for (int ks = 0; ks < 2; ks++)
 #pragma unroll
             for (int a = 0; a < PB; a++)
 #pragma unroll
-                for (int c = 0; c < 2; c++) mfma_in_place(C[a][c], P[a][ks], Q[c][ks]);
+                for (int c = 0; c < 2; c++) mfma_in_place(ks == 0 ? C[a][c] : C1[a][c], P[a][ks], Q[c][ks]);
     };
 
     request(true, 0, 0);
@@ -288,8 +291,8 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
         request(false, 1, t + 1);
         ready();
         __builtin_amdgcn_s_setprio(1);
-        multiply(acc[0][0], Q0);
-        if constexpr (both) multiply(acc[0][NJ - 1], Q1);
+        multiply(acc[0][0], acc[0][TWO_SUMS ? 2 : 0], Q0);
+        if constexpr (both) multiply(acc[0][1], acc[0][1], Q1);
         __builtin_amdgcn_s_setprio(0);
         turn();
         read_p(1);
@@ -300,8 +303,8 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
         request(true, 1, t + 2);
         ready();
         __builtin_amdgcn_s_setprio(1);
-        if constexpr (both) multiply(acc[1][NJ - 1], Q1);
-        multiply(acc[1][0], Q0);
+        if constexpr (both) multiply(acc[1][1], acc[1][1], Q1);
+        multiply(acc[1][0], acc[1][TWO_SUMS ? 2 : 0], Q0);
         __builtin_amdgcn_s_setprio(0);
         if (t + 1 == steps) finish_products();   // in the loop: behind it the compiler may move accumulators at once
         turn();
@@ -322,12 +325,16 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
 #pragma unroll
         for (int c = 0; c < 2; c++) {
             const int n = q0 + wq * 32 + c * 16 + l16;
-            float* row = p.scores + ((int64_t)piece * p.N + n) * p.F + p0 + wp * 64 + 4 * g;
+            float* row = p.scores + ((int64_t)piece * p.N + n) * p.F + p0 + wp * (BM / 4) + 4 * g;
 #pragma unroll
             for (int i = 0; i < 2; i++)
 #pragma unroll
-                for (int a = 0; a < PB; a++)
-                    if (n < p.N && p0 + i * 128 + wp * 64 + a * 16 < p.F) *reinterpret_cast<f32x4*>(row + i * 128 + a * 16) = acc[i][0][a][c];
+                for (int a = 0; a < PB; a++) {
+                    f32x4 sum = acc[i][0][a][c];
+                    if (TWO_SUMS) sum += acc[i][TWO_SUMS ? 2 : 0][a][c];
+                    sum += acc[i][1][a][c];
+                    if (n < p.N && p0 + i * (BM / 2) + wp * (BM / 4) + a * 16 < p.F) *reinterpret_cast<f32x4*>(row + i * (BM / 2) + a * 16) = sum;
+                }
         }
         return;
     } else if constexpr (DELTA) {

@@ -44,3 +44,35 @@ def test_column_sums_of_given_normalisers(cm, N, E, c):
     weights = torch.exp(scores - m[..., None].to(F64)) / l[..., None].to(F64)
     ref = torch.stack([weights[:, u * c:(u + 1) * c].sum(1) for u in range(NB)], 1)
     assert _rms_err(D[0, :, :, :N], ref) <= 1.2e-7
+
+
+@pytest.mark.parametrize("chunks,D,F", [
+    (1, 128, 64), (8, 256, 1024), (300, 384, 2048),   # one piece, the high parts in two sums
+    (8, 1792, 1024),                     # 16 pieces of one step or two
+    (24, 3072, 10240), (14, 2048, 8704), # six and seven pieces: a workgroup per CU
+    (40, 4096, 10240),                   # four pieces, two sums each, where six in one would be too long
+    (258, 1024, 6912), (129, 1024, 16640),   # two pieces and one, two sums each
+    (602, 1024, 12288),                  # one piece, one sum
+])
+def test_neuron_scores_add_no_longer_sums_than_the_workspace_has_pieces_for(cm, chunks, D, F):
+    """Chunk means that two bf16 numbers hold exactly, so that what is left is the error of the GEMM's 32-bit sums.  One rounding
+    of the result is 2^-23 * sqrt(0.52 / 12) in the mean square (0.52: of the squared mantissas).  Eight products are added
+    with one rounding, so D / 8 additions in h chains of the high parts leave D / 16 / h of its variance; merging h chains of
+    high and as many of low parts leaves 1.5 h.  h is half of the pieces that the workspace is sized for."""
+    c = 128
+    g = si.generator(32, DEV)
+    pair = (1 + torch.randint(0, 128, (2, chunks, D), generator=g, device=DEV) / 128)
+    pair = pair * (1 - 2 * torch.randint(0, 2, (chunks, D), generator=g, device=DEV))
+    x = pair.permute(1, 0, 2)[:, None].expand(chunks, c // 2, 2, D).reshape(1, chunks * c, D).to(torch.bfloat16)
+    w1 = si.randn_bf16((F, D), g, 1 / math.sqrt(D))
+    ws = torch.empty(max(cm.mlp_tile_mean_workspace_bytes(1, chunks * c, D, F, c), 16), dtype=torch.uint8, device=DEV)
+    T = torch.empty((1, chunks, F), dtype=torch.float32, device=DEV)
+    cm.mlp_tile_mean_preact(x, w1, T, c, ws)
+    ref = pair.to(F64).mean(0) @ w1.to(F64).t().contiguous()
+    h = min(max((ws.numel() - chunks * D * 4) // (chunks * F * 4) // 2, 1), D // 64)
+    bound = 2.0 ** -23 * math.sqrt(0.52 / 12 * (D / 16 / h + 1.5 * h))
+    # a rounding is counted at the mean square of its sum; a few sums of small problems scatter around that
+    assert _rms_err(T[0], ref) <= bound * (1 + 2 / math.sqrt(chunks * F))
+    again = torch.empty_like(T)
+    cm.mlp_tile_mean_preact_static(x, w1, again, c)
+    assert _rms_err(again[0], ref) <= bound * (1 + 2 / math.sqrt(chunks * F)) or chunks * (D + F) * 4 > 1 << 25
