@@ -599,6 +599,9 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
         step(std::integral_constant<int, 0>{}, std::true_type{}, last_tile, last_half);
     }
     wait_all_memory();  // the base rows (NOLIST: the transfers behind the last step) have landed
+    // The transfers' asm names no memory and the wait is no barrier to the compiler: without this it might read the base rows
+    // from LDS ahead of the wait (other tiles are read behind a workgroup barrier; a wave's base rows are its own).
+    asm volatile("" ::: "memory");
     if (FUSED) {
         __syncthreads();  // the last step's partial sums are complete
         flush_column_sums(last_tile);
