@@ -112,13 +112,14 @@ def _ptr_rows(t, dtype, name):
     return t.data_ptr()
 
 
-_current_device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
-
-
 def _stream():
-    """The current stream of the current device as torch.cuda.current_stream().cuda_stream gives it, without the Stream object
-    (2.8 us a call, of the 9 that a small attention call took on the host; 0.2 us this way)."""
-    return _raw_stream(_current_device())
+    """The current stream of the current device, as torch.cuda.current_stream().cuda_stream gives it but without the Stream
+    object (2.8 us a call, of the 9 that a small attention call took on the host; 0.2 us this way).  The names are torch's own,
+    so they are looked up here and not needed."""
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
 
 
 def voxel_reorder(src, dst, perm, inv_perm, n_prefix, T, H, W, n_suffix, vt, vh, vw, inverse=False):

@@ -129,6 +129,28 @@ def test_bad_arguments_are_rejected_without_a_launch(lib):
     assert tm(a, a, a, 1, 1024, 256, 1024, 100, a, 1 << 30, None) == -4
 
 
+def test_package_needs_no_private_names_of_torch():
+    """The current stream is looked up the short way where torch has the names for it; without them the package imports and
+    takes torch's public way."""
+    import subprocess
+    import sys
+    code = """
+import torch
+for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+    if hasattr(torch._C, name):
+        delattr(torch._C, name)
+import paper_2506_03275_amd as cm
+class Stream:
+    cuda_stream = 1234
+torch.cuda.current_stream = lambda: Stream
+assert cm._stream() == 1234
+torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream = (lambda: 3), (lambda device: 100 + device)
+assert cm._stream() == 103
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+
+
 def test_ceiling_probe_library_loads_and_rejects_bad_arguments():
     from paper_2506_03275_amd import ceilings
     lib = ceilings.load()
