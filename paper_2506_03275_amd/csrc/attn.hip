@@ -886,19 +886,23 @@ static int32_t launch_attn_parts(AttnParams p, int E, int64_t units, hipStream_t
     return launch_attn_variant<64, 2, 4, MODE>(p, groups, s);
 }
 
-static int32_t launch_attn(const AttnParams& p, int E, int64_t units, hipStream_t s) {
-    if (p.idx) return launch_attn_parts<kColumnList>(p, E, units, s);
-    // without a list the rows need not follow the chunks: 128 or 192 at a time, whichever is cheaper
-    const int64_t bh = units / p.NB;
-    AttnParams d[2] = {p, p};
+// Without a list the rows need not follow the chunks: 128 or 192 at a time, whichever is cheaper.
+static int attn_dense_rows(int64_t bh, int N, int E) {
     double cost[2];
     for (int i = 0; i < 2; i++) {
-        d[i].c = i == 0 ? 192 : 128;
-        d[i].NB = (p.N + d[i].c - 1) / d[i].c;
-        attn_whole_chunks(E, d[i].c / 64, bh * d[i].NB, &cost[i]);
+        const int rows = i == 0 ? 192 : 128;
+        attn_whole_chunks(E, rows / 64, bh * ((N + rows - 1) / rows), &cost[i]);
     }
-    const AttnParams& best = cost[1] < cost[0] ? d[1] : d[0];
-    return launch_attn_parts<kEveryColumn>(best, E, bh * best.NB, s);
+    return cost[1] < cost[0] ? 128 : 192;
+}
+
+static int32_t launch_attn(const AttnParams& p, int E, int64_t units, hipStream_t s) {
+    if (p.idx) return launch_attn_parts<kColumnList>(p, E, units, s);
+    const int64_t bh = units / p.NB;
+    AttnParams d = p;
+    d.c = attn_dense_rows(bh, p.N, E);
+    d.NB = (p.N + d.c - 1) / d.c;
+    return launch_attn_parts<kEveryColumn>(d, E, bh * d.NB, s);
 }
 
 static int32_t launch_attn_fused(const AttnParams& p, int E, int64_t units, hipStream_t s) {
@@ -915,14 +919,19 @@ static int32_t launch_attn_blocks(const AttnParams& p, int E, int64_t units, hip
     return launch_attn_variant<64, 2, 4, kBlockList>(p, units, s);
 }
 
+// Into how many pieces the column-sum pass cuts a chunk's keys.  Four workgroups fit a CU, and a CU with three of them takes
+// longer than one with two: with few chunks the keys are cut until there are at least eight workgroups per CU, each with at
+// least four tiles (each piece's sums are its own, so nothing is merged).  24 heads x 24 chunks x 4608 keys, dense attention
+// and sums together: 422 us in one piece, 402 in two, 394 in four (the rule), 399 in eight.
+static int colsum_pieces(int64_t units, int N) {
+    const int tiles = (N + kColsumTileRows - 1) / kColsumTileRows;
+    int pieces = 1;
+    while (units * pieces < 8 * 256 && 2 * pieces * 4 <= tiles) pieces *= 2;
+    return pieces;
+}
+
 static int32_t launch_colsum(ColsumParams cp, int E, int64_t units, hipStream_t s) {
-    // Four workgroups fit a CU, and a CU with three of them takes longer than one with two: with few chunks the keys
-    // are cut into pieces until there are at least eight workgroups per CU (each piece's sums are its own, so nothing is
-    // merged).  24 heads x 24 chunks x 4608 keys, dense attention and
-    // sums together: 422 us in one piece, 402 in two, 394 in four (the rule), 399 in eight.
-    const int tiles = (cp.N + kColsumTileRows - 1) / kColsumTileRows;
-    cp.pieces = 1;
-    while (units * cp.pieces < 8 * 256 && 2 * cp.pieces * 4 <= tiles) cp.pieces *= 2;   // at least four tiles each
+    cp.pieces = colsum_pieces(units, cp.N);
     dim3 grid((unsigned)(units * cp.pieces)), block(256);
     if (E == 128 && cp.c == 192) hipLaunchKernelGGL((attn_colsum_kernel<128, 3>), grid, block, 0, s, cp);
     else if (E == 128 && cp.c == 128) hipLaunchKernelGGL((attn_colsum_kernel<128, 2>), grid, block, 0, s, cp);
@@ -1069,4 +1078,19 @@ extern "C" int32_t chipmunk_attn_dense_colsum_stale(const uint16_t* q, const uin
     p.sl2 = softmax_scale * 1.4426950408889634f;
     p.o_scale = 1.f;
     return launch_attn_fused(p, E, units, (hipStream_t)stream);
+}
+
+// What the rules above choose for these sizes: the rows of a workgroup that takes a whole chunk, the chunks that have one, the
+// chunks walked by a workgroup per 64 rows, and the pieces of the column-sum pass.  Not part of the library's interface:
+// for the tests, which have to reach each form and otherwise would not see that a rule has moved.
+extern "C" void chipmunk_internal_attn_form(int B, int H, int N, int E, int c, int list, int32_t* out) {
+    const int64_t bh = (int64_t)B * H;
+    const int rows = list ? c : attn_dense_rows(bh, N, E);
+    const int64_t units = bh * ((N + rows - 1) / rows);
+    double cost;
+    const int64_t whole = attn_whole_chunks(E, rows / 64, units, &cost);
+    out[0] = rows;
+    out[1] = (int32_t)whole;
+    out[2] = (int32_t)(units - whole);
+    out[3] = colsum_pieces(bh * ((N + c - 1) / c), N);
 }

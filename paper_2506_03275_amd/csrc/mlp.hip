@@ -1081,3 +1081,16 @@ extern "C" int32_t chipmunk_mlp_tile_mean_preact_static(const uint16_t* x, const
     // by chunk_mean_kernel, every piece's partial scores by the scores GEMM): nothing has to start at zero
     return run_tile_mean(x, w1, T, B, N, D, F, c, ws, pieces, (hipStream_t)stream);
 }
+
+// What the rules above choose for these sizes: whether the two dense GEMMs take the tiles of 256 x 256, whether the delta
+// takes 256 neurons per workgroup, and the scores GEMM's pieces and sums.  Not part of the library's interface: for the
+// tests, which have to reach each form and otherwise would not see that a rule has moved.
+extern "C" void chipmunk_internal_mlp_form(int B, int N, int D, int F, int c, int k_stride, int32_t* out) {
+    const int units = B * ((N + c - 1) / c);
+    const ScoresPlan plan = scores_plan(units, D, F);
+    out[0] = large_tiles_pay(false, B, N, D, F, c);
+    out[1] = large_tiles_pay(true, B, N, D, F, c);
+    out[2] = wide_delta_pays(units, D, c, k_stride);
+    out[3] = plan.pieces;
+    out[4] = plan.two_sums ? 2 : 1;
+}

@@ -1,7 +1,9 @@
 """Branches of the launch rules (how many rows, keys or columns a workgroup takes, by the size of the problem): each at the
-sizes where it can go wrong, against the oracle.  Tolerances: REL_TOL for bf16 outputs; 1e-4 for 32-bit sums of
+sizes where it can go wrong, against the oracle.  The forms that a rule chooses by cost are asked of the library and asserted,
+so that a size that a changed rule sends elsewhere fails instead of testing another form.  Tolerances: REL_TOL for bf16 outputs; 1e-4 for 32-bit sums of
 exponentials, whose argument, below 32 in magnitude, is rounded to 2^-19 at most twice (2 * 2^-19 * ln 2 = 2.6e-6 of a
 weight) before a sum of up to 192 positive terms (192 * 2^-24 = 1.1e-5)."""
+import ctypes
 import math
 
 import numpy as np
@@ -25,14 +27,29 @@ def cm():
     return cm
 
 
+def _attn_form(cm, H, N, E, c, with_list):
+    """(rows of a whole chunk's workgroup, chunks taken whole, chunks in parts of 64 rows), pieces of the column-sum pass"""
+    out = (ctypes.c_int32 * 4)()
+    cm.load().chipmunk_internal_attn_form(1, H, N, E, c, int(with_list), out)
+    return tuple(out[:3]), out[3]
+
+
+def _mlp_form(cm, B, N, D, F, c, k=1):
+    """first and second dense GEMM on 256 x 256 tiles, delta with 256 neurons per workgroup; scores: pieces, sums"""
+    out = (ctypes.c_int32 * 5)()
+    cm.load().chipmunk_internal_mlp_form(B, N, D, F, c, k, out)
+    return [bool(v) for v in out[:3]], tuple(out[3:])
+
+
 def _u8(nbytes):
     return torch.empty(max(int(nbytes), 16), dtype=torch.uint8, device=DEV)
 
 
-@pytest.mark.parametrize("N,E,c", [(1, 128, 192), (64, 64, 128), (130, 128, 192), (511, 64, 192), (513, 128, 128),
-                                   (1100, 128, 192), (2113, 64, 128), (2113, 128, 192)])   # 1, 1, 1, 2, 2, 4, 8, 8 pieces
-def test_column_sums_in_pieces_of_the_keys(cm, oracle, N, E, c):
+@pytest.mark.parametrize("N,E,c,pieces", [(1, 128, 192, 1), (64, 64, 128, 1), (130, 128, 192, 1), (511, 64, 192, 2),
+                                          (513, 128, 128, 2), (1100, 128, 192, 4), (2113, 64, 128, 8), (2113, 128, 192, 8)])
+def test_column_sums_in_pieces_of_the_keys(cm, oracle, N, E, c, pieces):
     """The column-sum pass cuts a chunk's keys into 1 to 8 runs of 64-key tiles, the last tile ragged or not."""
+    assert _attn_form(cm, 1, N, E, c, False)[1] == pieces
     (q, k, _), _, _ = si.attn_steps(1, 1, N, E, 21, DEV)
     scale, NB, ld = 1 / math.sqrt(E), -(-N // c), -(-N // 4) * 4 + 4
     m_ref, l_ref = oracle.attn_row_stats(si.np_f32(q), si.np_f32(k), scale)
@@ -48,11 +65,16 @@ def test_column_sums_in_pieces_of_the_keys(cm, oracle, N, E, c):
 
 
 @pytest.mark.parametrize("E", [64, 128])
-@pytest.mark.parametrize("H,N", [(2, 1), (3, 130), (200, 256), (400, 192), (200, 190), (400, 65), (520, 190), (530, 129)])
-def test_dense_attention_in_workgroups_of_64_128_and_192_rows(cm, oracle, E, H, N):
+@pytest.mark.parametrize("H,N,form", [
+    (2, 1, (192, 0, 2)), (3, 130, (192, 0, 3)),                                      # all in parts of 64 rows
+    (200, 256, (128, 400, 0)), (400, 65, (128, 400, 0)), (400, 192, (192, 400, 0)),  # all whole
+    (520, 190, (192, 512, 8)), (530, 129, (192, 512, 18)),                           # the last round in parts
+    (200, 190, None)])                                                               # another form for each E
+def test_dense_attention_in_workgroups_of_64_128_and_192_rows(cm, oracle, E, H, N, form):
     """Without a list a workgroup takes one, two or three blocks of 64 rows, by the number of workgroups, those of the last
-    round one where that is cheaper (the last two sizes); c is 128 here and 192 there, which no longer decides it.  The
-    ends of the sequence leave waves and whole blocks without rows."""
+    round one where that is cheaper; c is 128 here and 192 there, which no longer decides it.  The ends of the sequence
+    leave waves and whole blocks without rows."""
+    assert _attn_form(cm, H, N, E, 128 if N % 2 else 192, False)[0] == (form or {64: (128, 400, 0), 128: (192, 200, 0)}[E])
     q, k, v = recipes.attn_inputs(1, H, N, E, 22, DEV)
     scale = 1 / math.sqrt(E)
     c = 128 if N % 2 else 192
@@ -63,12 +85,14 @@ def test_dense_attention_in_workgroups_of_64_128_and_192_rows(cm, oracle, E, H, 
     assert rel_err(si.np_f32(out), basen - dense, dense) <= REL_TOL
 
 
-@pytest.mark.parametrize("H,N,E,c,k", [(1, 193, 128, 192, 70), (2, 650, 64, 192, 33), (2, 300, 128, 128, 129),
-                                       (110, 320, 64, 128, 20), (200, 384, 128, 192, 9), (200, 500, 128, 192, 70),
-                                       (260, 300, 128, 192, 40), (520, 129, 64, 128, 65)])
-def test_column_lists_walked_by_parts_of_a_chunk(cm, oracle, H, N, E, c, k):
+@pytest.mark.parametrize("H,N,E,c,k,form", [
+    (1, 193, 128, 192, 70, (0, 2)), (2, 650, 64, 192, 33, (0, 8)), (2, 300, 128, 128, 129, (0, 6)),   # all in parts
+    (110, 320, 64, 128, 20, (330, 0)), (200, 384, 128, 192, 9, (400, 0)),                             # all whole
+    (200, 500, 128, 192, 70, (512, 88)), (260, 300, 128, 192, 40, (512, 8)), (520, 129, 64, 128, 65, (1024, 16))])
+def test_column_lists_walked_by_parts_of_a_chunk(cm, oracle, H, N, E, c, k, form):
     """Few chunks: a workgroup per 64 rows, all of a chunk walking its one list; the last chunk ends before its last
-    part.  Then three cases with enough chunks to be walked whole, and two whose last round alone is in parts."""
+    part.  Then cases with enough chunks to be walked whole, and cases whose last round alone is in parts."""
+    assert _attn_form(cm, H, N, E, c, True)[0] == (c, *form)
     q, kk, v = recipes.attn_inputs(1, H, N, E, 23, DEV)
     scale, NB = 1 / math.sqrt(E), -(-N // c)
     base = recipes.attn_base(tuple(q.shape), k, "delta", 23, DEV)
@@ -84,15 +108,16 @@ def test_column_lists_walked_by_parts_of_a_chunk(cm, oracle, H, N, E, c, k):
     assert torch.equal(base, out)
 
 
-@pytest.mark.parametrize("B,N,D,F,c,act,bias", [
-    (1, 1021, 128, 16320, 192, 1, True),     # first GEMM on 256 x 256 tiles: two steps, neurons and tokens ragged
-    (2, 509, 256, 16320, 192, 0, False),     # two batches, no bias
-    (1, 4090, 3968, 320, 192, 0, True),      # second GEMM: five steps, half a tile of columns missing, tokens ragged
-    (1, 28660, 4096, 64, 192, 1, False),     # one step
-    (2, 2041, 3968, 384, 192, 1, True),
+@pytest.mark.parametrize("B,N,D,F,c,act,bias,large", [
+    (1, 1021, 128, 16320, 192, 1, True, (True, False)),   # first GEMM on 256 x 256 tiles: two steps, neurons and tokens ragged
+    (2, 509, 256, 16320, 192, 0, False, (True, False)),   # two batches, no bias
+    (1, 4090, 3968, 640, 192, 0, True, (False, True)),    # second GEMM: ten steps, half a tile of columns missing, tokens ragged
+    (1, 28660, 4096, 64, 192, 1, False, (False, True)),   # one step
+    (2, 2041, 3968, 384, 192, 1, True, (False, True)),
 ])
-def test_dense_mlp_on_large_tiles(cm, oracle, B, N, D, F, c, act, bias):
+def test_dense_mlp_on_large_tiles(cm, oracle, B, N, D, F, c, act, bias, large):
     """The dense GEMMs whose problem is large enough for 256 x 256 tiles; the cache cells past N stay as they are."""
+    assert tuple(_mlp_form(cm, B, N, D, F, c)[0][:2]) == large
     x, _, w1, b1, w2, b2 = recipes.mlp_inputs(B, N, D, F, 24, DEV)
     if not bias:
         b1, b2 = torch.zeros_like(b1), torch.zeros_like(b2)
@@ -138,17 +163,20 @@ def test_topk_of_rows_kept_in_registers(cm, oracle, C, kind):
             assert np.array_equal(counts.cpu().numpy(), ref_counts)
 
 
-@pytest.mark.parametrize("B,N,D,F,c", [
-    (1, 1, 128, 64, 128),              # one token, one neuron tile a quarter full, one piece
-    (1, 300, 512, 64, 128),            # eight pieces of one step
-    (1, 384, 640, 7680, 192),          # two chunks; ten steps in eight pieces
-    (1, 127 * 128, 128, 320, 128),     # 127, 128 and 129 chunks: both sides of a tile
-    (2, 64 * 192, 256, 576, 192),
-    (1, 128 * 128 + 5, 384, 64, 128),
+@pytest.mark.parametrize("B,N,D,F,c,plan", [
+    (1, 1, 128, 64, 128, (1, 2)),            # one token, one neuron tile half full, one piece, the high parts in two sums
+    (1, 300, 512, 64, 128, (8, 1)),          # eight pieces of one step
+    (1, 384, 640, 7680, 192, (8, 1)),        # two chunks; ten steps in eight pieces
+    (1, 127 * 128, 128, 320, 128, (1, 2)),   # 127, 128 and 129 chunks: both sides of a tile
+    (2, 64 * 192, 256, 576, 192, (1, 2)),
+    (1, 128 * 128 + 5, 384, 64, 128, (1, 2)),
+    (1, 128 * 128 + 5, 512, 16960, 128, (1, 2)),   # eight steps, one piece in two sums, many neuron tiles
+    (2, 700, 3968, 10304, 192, (4, 2)),      # 62 steps in four pieces, two sums each, the last neuron tile half full
 ])
-def test_neuron_scores_in_pieces_of_the_contraction(cm, oracle, B, N, D, F, c):
-    """Chunk means of full, ragged and one-row chunks, and the scores GEMM cut into pieces.  Tolerance: the mean enters as two
+def test_neuron_scores_in_pieces_of_the_contraction(cm, oracle, B, N, D, F, c, plan):
+    """Chunk means of full, ragged and one-row chunks, and the scores GEMM's pieces and sums.  Tolerance: the mean enters as two
     bf16 numbers (2^-16 of it is lost at most), the 32-bit sums of D products add less: 1e-4 of the scores' RMS."""
+    assert _mlp_form(cm, B, N, D, F, c)[1] == plan
     g = si.generator(26, DEV)
     x, w1 = si.randn_bf16((B, N, D), g), si.randn_bf16((F, D), g, 1 / math.sqrt(D))
     T = torch.full((B, -(-N // c), F), float("nan"), dtype=torch.float32, device=DEV)
@@ -161,11 +189,13 @@ def test_neuron_scores_in_pieces_of_the_contraction(cm, oracle, B, N, D, F, c):
 
 
 @pytest.mark.parametrize("E", [64, 128])
-@pytest.mark.parametrize("H,N,c", [(2, 900, 192), (2, 600, 128), (70, 700, 192)])
-def test_last_step_of_column_lists(cm, oracle, E, H, N, c):
+@pytest.mark.parametrize("H,N,c,form", [(2, 900, 192, (0, 10)), (2, 600, 128, (0, 10)), (100, 700, 192, (400, 0)),
+                                        (80, 600, 128, (400, 0))])
+def test_last_step_of_column_lists(cm, oracle, E, H, N, c, form):
     """Lists that end at, before and behind the edges of tiles (32 columns) and steps (64), one step to three, in either half
     of the buffers: the last step leaves out an empty second tile and brings the base rows (ragged last chunk: some do
-    not exist).  70 heads: chunks walked whole."""
+    not exist).  Chunks in parts of 64 rows, and chunks walked whole: two or three blocks of rows per wave."""
+    assert _attn_form(cm, H, N, E, c, True)[0] == (c, *form)
     NB, k = -(-N // c), 193
     q, kk, v = recipes.attn_inputs(1, H, N, E, 27, DEV)
     base = recipes.attn_base(tuple(q.shape), 64, "delta", 27, DEV)
@@ -182,29 +212,56 @@ def test_last_step_of_column_lists(cm, oracle, E, H, N, c):
     assert rel_err(si.np_f32(out), ref, ref - basen) <= REL_TOL
 
 
-@pytest.mark.parametrize("N,D,F,c,k,act,bias", [(700, 768, 8192, 192, 8130, 1, True), (900, 256, 8192, 128, 8130, 0, False),
-                                                (192, 768, 8192, 192, 8192, 1, True)])
-def test_mlp_delta_with_256_neurons_per_workgroup(cm, oracle, N, D, F, c, k, act, bias):
+@pytest.mark.parametrize("B,N,D,F,c,k,act,bias", [
+    (1, 700, 1536, 8192, 192, 8130, 1, True), (1, 900, 512, 8192, 128, 8130, 0, False), (1, 192, 1536, 8192, 192, 8192, 1, True),
+    (2, 700, 1536, 8192, 192, 8130, 0, False), (2, 440, 512, 8192, 128, 8130, 1, True)])
+def test_mlp_delta_with_256_neurons_per_workgroup(cm, oracle, B, N, D, F, c, k, act, bias):
     """The first GEMM of the MLP delta on its wide tiles (few chunks, many neurons): counts that end in a tile's first half, in
-    its second, at its edge, at nothing; a ragged last chunk; both forms of the cache write-back, bit for bit alike."""
-    x1, x2, w1, b1, w2, b2 = recipes.mlp_inputs(1, N, D, F, 28, DEV)
+    its second, at its edge, at nothing; a ragged last chunk, one batch and two; both forms of the cache write-back, bit for
+    bit alike.  The caches hold noise, which the delta takes as it takes activations."""
+    assert _mlp_form(cm, B, N, D, F, c, k)[0][2]
+    _, x2, w1, b1, w2, _ = recipes.mlp_inputs(B, N, D, F, 28, DEV)
     if not bias:
         b1 = torch.zeros_like(b1)
     NB, a_ld = -(-N // c), -(-N // 8) * 8 + 8
-    o_ref, a_ref, _ = oracle.mlp_dense(si.np_f32(x1), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2), si.np_f32(b2), c, act, a_ld=a_ld)
-    o_cache, a_cache = (torch.from_numpy(t).to(torch.bfloat16).to(DEV) for t in (o_ref, a_ref))
+    g = si.generator(28, DEV)
+    a_cache, o_cache = si.randn_bf16((B, F, a_ld), g, 0.5), si.randn_bf16((B, N, D), g)
     o_ref, a_ref = (si.np_f32(t).astype(np.float64) for t in (o_cache, a_cache))
     o_before, a_before = o_ref.copy(), a_cache.clone()
-    idx, _ = recipes.mlp_indices(NB, F, k, 28, DEV)
-    counts = torch.tensor([k, 0, 256, 300, 129, 1, 512, k - 1][:NB], dtype=torch.int32, device=DEV)
-    idx, counts = idx.view(1, NB, k), counts.view(1, NB)
+    idx, _ = recipes.mlp_indices(B * NB, F, k, 28, DEV)
+    counts = torch.tensor([k, 0, 256, 300, 129, 1, 512, k - 1][:B * NB], dtype=torch.int32, device=DEV)
+    idx, counts = idx.view(B, NB, k), counts.view(B, NB)
     o2, a2 = o_cache.clone(), a_cache.clone()
     bias1 = b1 if bias else None
-    cm.mlp_sparse_delta(x2, w1, bias1, w2, idx, counts, a_cache, o_cache, c, act, _u8(cm.mlp_workspace_bytes(1, N, D, F, c, k)))
-    cm.mlp_sparse_delta_overlapped(x2, w1, bias1, w2, idx, counts, a2, o2, c, act, _u8(cm.mlp_overlapped_workspace_bytes(1, N, D, F, c, k)))
+    cm.mlp_sparse_delta(x2, w1, bias1, w2, idx, counts, a_cache, o_cache, c, act, _u8(cm.mlp_workspace_bytes(B, N, D, F, c, k)))
+    cm.mlp_sparse_delta_overlapped(x2, w1, bias1, w2, idx, counts, a2, o2, c, act, _u8(cm.mlp_overlapped_workspace_bytes(B, N, D, F, c, k)))
     assert torch.equal(a_cache, a2) and torch.equal(o_cache, o2)
     oracle.mlp_sparse_delta(si.np_f32(x2), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2), idx.cpu().numpy(), counts.cpu().numpy(),
                             a_ref, o_ref, c, act)
     assert rel_err(si.np_f32(a_cache)[..., :N], a_ref[..., :N]) <= REL_TOL
     assert rel_err(si.np_f32(o_cache), o_ref, o_ref - o_before) <= REL_TOL
     assert torch.equal(a_cache[..., N:], a_before[..., N:])
+
+
+@pytest.mark.parametrize("act", [0, 1])
+@pytest.mark.parametrize("B,N,D,F,c,k,large,wide", [
+    (1, 1021, 256, 16320, 128, 16300, True, True), (1, 1021, 256, 16320, 128, 1000, True, False),
+    (1, 700, 1536, 8192, 192, 8130, False, True), (2, 2000, 1536, 4096, 192, 500, True, False),
+    (1, 192, 1536, 8192, 192, 8192, False, True), (1, 300, 768, 2048, 192, 300, False, False),
+    (2, 440, 512, 1024, 128, 1024, False, False)])
+def test_unchanged_input_leaves_the_caches_alone(cm, B, N, D, F, c, k, large, wide, act):
+    """The delta of an input that has not changed is nothing, bit for bit, whichever tiles filled the cache (256 x 256 or 192 or
+    128 x 128) and whichever the delta takes (256 neurons or 128): their products (16x16x32 and 32x32x16) add in the same
+    order.  So a chunk's results do not hang on how many chunks a call has."""
+    form = _mlp_form(cm, B, N, D, F, c, k)[0]
+    assert (form[0], form[2]) == (large, wide)
+    x, _, w1, b1, w2, b2 = recipes.mlp_inputs(B, N, D, F, 30, DEV)
+    out = torch.empty_like(x)
+    a_cache = torch.zeros((B, F, -(-N // 8) * 8), dtype=torch.bfloat16, device=DEV)
+    cm.mlp_dense(x, w1, b1, w2, b2, out, a_cache, c, act)
+    o_before, a_before = out.clone(), a_cache.clone()
+    NB = -(-N // c)
+    idx, _ = recipes.mlp_indices(B * NB, F, k, 30, DEV)
+    counts = torch.full((B, NB), k, dtype=torch.int32, device=DEV)
+    cm.mlp_sparse_delta(x, w1, b1, w2, idx.view(B, NB, k), counts, a_cache, out, c, act, _u8(cm.mlp_workspace_bytes(B, N, D, F, c, k)))
+    assert torch.equal(a_cache, a_before) and torch.equal(out, o_before)
