@@ -72,8 +72,10 @@ __device__ __forceinline__ void load_buffer_to_lds_16B(i32x4 buffer, uint32_t by
 
 // C += A B (16x16x32) with C in accumulation registers.  With the builtin the compiler keeps the 128 accumulators among
 // the other registers, moves them from product to product and spills (364 bytes); held apart, they leave 128 registers to
-// the operands and addresses, of which the kernel needs about 100.  The compiler does not know the products' latency:
-// whatever else reads C waits first (finish_products: 32 cycles, the products' results take at most 19).
+// the operands and addresses, of which the loops need about 110 (the second GEMM's epilogue keeps 20 bytes in scratch
+// memory, the other forms nothing).  The compiler does not know the products' latency: whatever else reads C waits first
+// (finish_products: 32 cycles, the products' results take at most 19), and no accumulator may be moved inside a loop,
+// which a test checks in the compiled kernels.
 __device__ __forceinline__ void mfma_in_place(f32x4& c, bf16x8 a, bf16x8 b) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
@@ -349,13 +351,16 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
         for (int j = 0; j < 2; j++)
 #pragma unroll
             for (int c = 0; c < 2; c++) b1[j][c] = bias_src[s_neuron[j * 128 + wq * 32 + c * 16 + l16]];
+        // address of a cached cell; tokens clamped to the row's start where the chunk ends early: read, not used
+        auto cell = [&](int nl, int ch) -> uint16_t* {
+            const int tok0 = p0 + ch * 8;
+            return ab + (int64_t)s_neuron[nl] * p.a_ld + (tok0 < p.N ? tok0 : 0);
+        };
         u32x4 old8[ITEMS];
-        uint16_t* cell[ITEMS];   // tokens clamped to the row's start where the chunk ends early: read, not used
 #pragma unroll
         for (int n = 0; n < ITEMS; n++) {
-            const int item = tid + n * 512, nl = item / CPR, tok0 = p0 + (item - nl * CPR) * 8;
-            cell[n] = ab + (int64_t)s_neuron[nl] * p.a_ld + (tok0 < p.N ? tok0 : 0);
-            old8[n] = *reinterpret_cast<const u32x4*>(cell[n]);
+            const int item = tid + n * 512, nl = item / CPR;
+            old8[n] = *reinterpret_cast<const u32x4*>(cell(nl, item - nl * CPR));
         }
         if (wp == 0) turn();
         wait_all_memory();                           // the transfers past the end have landed before LDS is reused
@@ -382,16 +387,21 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
         if (p.act == CHIPMUNK_ACT_GELU_ERF) to_lds(std::integral_constant<int, CHIPMUNK_ACT_GELU_ERF>{});
         else to_lds(std::integral_constant<int, CHIPMUNK_ACT_GELU_TANH>{});
         lds_accesses_then_barrier();
+        // The thread's cells are worked out again from here on: held across the activations, beside the accumulators and what
+        // the cells held, the addresses of all loads and stores went to scratch memory (72 bytes at BM = 192; without them
+        // the whole delta of 394 chunks x 968 of 13 824 x 5120 1891 -> 1873 us, of 47 x 1229 of 12 288 x 3072 188 -> 184).
+        int tid_again = tid;
+        asm volatile("" : "+v"(tid_again));
         u32x4 a8[ITEMS];
 #pragma unroll
         for (int n = 0; n < ITEMS; n++) {
-            const int item = tid + n * 512, nl = item / CPR;
+            const int item = tid_again + n * 512, nl = item / CPR;
             a8[n] = *reinterpret_cast<const u32x4*>(smem + nl * ROW + (item - nl * CPR) * 16);
         }
         const int64_t at0 = (int64_t)unit * p.k_pad * BM;
 #pragma unroll
         for (int n = 0; n < ITEMS; n++) {
-            const int item = tid + n * 512, nl = item / CPR, ch = item - nl * CPR, s = q0 + nl;
+            const int item = tid_again + n * 512, nl = item / CPR, ch = item - nl * CPR, s = q0 + nl;
             // tokens past N and padding rows of the contraction must read as zero in the second GEMM
             const int nvalid = s < count ? min(8, p.N - (p0 + ch * 8)) : 0;
             u32x4 d8;
@@ -407,14 +417,14 @@ __global__ __launch_bounds__(512, 2) void mlp_dense_gemm_kernel(DenseGemmParams 
         }
 #pragma unroll
         for (int n = 0; n < ITEMS; n++) {
-            const int item = tid + n * 512, nl = item / CPR, ch = item - nl * CPR, s = q0 + nl;
+            const int item = tid_again + n * 512, nl = item / CPR, ch = item - nl * CPR, s = q0 + nl;
             const int nvalid = s < count ? min(8, p.N - (p0 + ch * 8)) : 0;
             if (p.act_t) {   // deferred write-back: one coalesced store, whole cell
                 if (nvalid > 0) *reinterpret_cast<u32x4*>(p.act_t + at0 + (int64_t)s * BM + ch * 8) = a8[n];
             } else if (nvalid == 8) {
-                *reinterpret_cast<u32x4*>(cell[n]) = a8[n];
+                *reinterpret_cast<u32x4*>(cell(nl, ch)) = a8[n];
             } else {         // the cells past N in the last chunk stay as they are
-                for (int e = 0; e < nvalid; e++) cell[n][e] = (uint16_t)(a8[n][e >> 1] >> (16 * (e & 1)));
+                for (int e = 0; e < nvalid; e++) cell(nl, ch)[e] = (uint16_t)(a8[n][e >> 1] >> (16 * (e & 1)));
             }
         }
     } else {
