@@ -6,8 +6,9 @@
 // most-significant-digit radix select (digits of up to 11 bits, LDS histograms,
 // wave-level prefix sums on DPP); the selected columns are every column above
 // the threshold plus the first columns equal to it, written in ascending order.
-//   - Rows of up to kRegisterCols columns are read from HBM once and kept in
-//     registers as keys; their threshold is found by halving the range of keys.
+//   - Rows of up to kRegisterCols columns (with few of them kept: fewer, see the
+//     entry point) are read from HBM once and kept in registers as keys; their
+//     threshold is found by halving the range of keys.
 //   - Longer rows (the attention column sums, 10^5 columns) are read from HBM
 //     once as well: two pivots taken from a 4096-score sample bracket the
 //     threshold; the single pass over the row marks the columns above the
@@ -300,7 +301,10 @@ __device__ __forceinline__ void emit_selected(const Src& src, int C, uint32_t th
 // registers per lane and about 1 KB of LDS keep 24 to 32 waves on a CU, where rows kept in LDS (57 KB at 12 288 columns)
 // allowed two workgroups, so that 602 rows took two rounds.  Against histograms of 11-bit digits over keys in LDS: 602 rows
 // of 12 288 with previous scores 36.8 -> 22.9 us, 14 448 x 4608 150 -> 105 us, 4000 x 12 288 (30 % kept) 160 -> 95 us,
-// 5000 x 1024 30.8 -> 14.4 us.
+// 5000 x 1024 30.8 -> 14.4 us.  The steps grow with the exponents that the range spans: column sums and |T - T_m| lie
+// within a few, but scores of both signs take about ten steps, and rows of just over 7168 of them (eight waves with registers for
+// five units each, of which four are filled) are the one place where the histograms were faster: 768 normal rows of 7200 15.7
+// and 20.7 us, of 9000 20.0 and 21.4.
 constexpr int kRegisterCols = 8 * 7 * 256;
 constexpr int kLastKeys = 256;
 
@@ -980,7 +984,13 @@ extern "C" int32_t chipmunk_topk_cols(const float* cur, const float* prev, int R
     hipStream_t s = (hipStream_t)stream;
     const dim3 grid((unsigned)R), block_long(kLongThreads);
     LongRowPlan plan;
-    if (C <= kRegisterCols) {
+    // Rows that fit the registers of eight waves go there, except where the long rows' kernel is the faster one: single scores,
+    // more than 12 288 columns (seven units a wave, so fewer waves on a CU), a tenth of them kept at most.  Us in registers and
+    // there, column sums: 768 rows x 14 336, 3 % kept: 23.2, 19.1; 7 %: 24.7, 22.0; 12 %: 25.4, 23.7; 30 %: 27.3, 29.4; 14 448 x
+    // 13 000: 307, 277; 325, 293; 340, 332; 353, 421; 14 448 x 11 776: 272, 260; 287, 274; 293, 308; 308, 393; 14 448 x 10 240:
+    // 216, 250; 227, 273.  With previous scores 14 448 x 14 336, 7 %: 359, 460.
+    const bool in_registers = C <= kRegisterCols && (prev || C <= 12288 || (int64_t)k * 10 > C);
+    if (in_registers) {
         // Waves per row: a step costs a wave its share of the counting and about 40 instructions of sums and exchange, so
         // few waves serve many short rows best, and eight a row whose keys would otherwise fill the registers of four.
         // Us for 5000 rows of 1024 columns with two, four and eight waves: 14.4, 17.1, 30.9; 14 448 rows of 6500 with
