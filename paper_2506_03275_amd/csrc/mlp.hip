@@ -839,10 +839,13 @@ static int tile_mean_pieces(int units, int F) {
 //     CUs.  Whole calls in us on tiles of 256 in one piece, in pieces, and like this, D = 256: 8 chunks x 1024 neurons 12.3,
 //     12.3, 10.6; 94 x 4096 14.6, 17.2, 11.6; 300 x 12 288 20.8, 32.9, 22.2; D = 384: 14.2, 12.3, 11.6; 16.5, 19.2, 12.6; 24.2,
 //     36.5, 25.6; D = 128: 10.4, 11.6, 9.4; 13.1, 15.9, 10.6; 17.1, 30.3, 17.8.
-//   - Otherwise as many pieces as let the tiles of 256 neurons x 128 chunks have a CU each (24 chunks x 3072 x 12 288 with up
-//     to 128, 256 and 512 workgroups: 36, 27, 32 us; 94 x 5120 x 13 824: 96, 84, 94), if the sums are then no longer than is
-//     exact enough, and else half as many pieces as that takes, in two sums each (in one sum each, twice the pieces: 156 tiles of
-//     D = 2688 172 us, like this 160; 70 tiles of D = 2048 99, 89; 46 of D = 1024 35, 29; 130 of D = 5120 178, 180).
+//   - Otherwise as many pieces as let the tiles have a CU each.  Every XCD takes an eighth of the tiles, rounded up, so 32 CUs
+//     over that: with 256 over the tiles, 20 tiles in 12 pieces were 36 workgroups on one XCD and a second round (12 chunks x
+//     2688 x 4928: 24.5 us, in 10 pieces 19.3; 50 tiles: 28.3, 21.2).  Tiles of 128 where there are pieces and they fill
+//     as many CUs: they leave half as many partial results (the same two sizes 16.8 and 20.1; 4 tiles of 256 34.4, 30.4; 60
+//     34.3, 29.9).  48 tiles of 256, five pieces: 28.4 us; 240, one piece: 198.6.
+//   - If the sums are then longer than is exact enough, half as many pieces as that takes, in two sums each (in one sum each,
+//     twice the pieces: 156 tiles of D = 2688 172 us, like this 160; 70 tiles of D = 2048 99, 89).
 // Exact enough: no larger an error than the sum of tile_mean_pieces() pieces over [hi | lo], half of them high parts.  Eight
 // products are added with one rounding, whose error goes with the sum so far; in units of the variance that one
 // rounding of the result has, a sum of n = D / 8 such additions cut into h chains leaves n / (2 h), adding the chains up h / 2,
@@ -852,13 +855,20 @@ struct ScoresPlan {
     bool two_sums;
 };
 static ScoresPlan scores_plan(int units, int D, int F) {
-    const int steps = D / kBK, tiles = ((F + kDenseTile - 1) / kDenseTile) * ((units + 127) / 128);
+    const int steps = D / kBK;
     if (steps <= 6) return {1, true};
-    const int fill = std::min(std::max(1, std::min(256 / tiles, 16)), steps);
+    auto fill = [&](int width) {   // pieces of tiles this wide
+        const int tiles = ((F + width - 1) / width) * ((units + 127) / 128);
+        return std::min(std::max(1, std::min(32 / ((tiles + 7) / 8), 16)), steps);
+    };
+    const int one = fill(kDenseTile), two = fill(128);
     const int chains = std::min(std::max(1, tile_mean_pieces(units, F) / 2), steps);
-    const double additions = D / 8;
-    if (additions / (2 * fill) + 0.5 * (fill + 1) <= additions / (2 * chains) + 1.5 * chains) return {fill, false};
-    return {std::max(1, chains / 2), true};
+    const double additions = D / 8, allowed = additions / (2 * chains) + 1.5 * chains;
+    const bool one_is_exact = additions / (2 * one) + 0.5 * (one + 1) <= allowed;
+    const bool two_is_exact = additions / (4 * two) + 0.5 * (two + 3) <= allowed;
+    if (one > 1 && 2 * two >= one && two_is_exact) return {two, true};
+    if (one_is_exact) return {one, false};
+    return {two_is_exact ? two : std::max(1, chains / 2), true};
 }
 
 // Workspace of the token-merged pre-activation with the contraction cut in `pieces`: the chunk means in split

@@ -166,8 +166,9 @@ def test_topk_of_rows_kept_in_registers(cm, oracle, C, kind):
 
 @pytest.mark.parametrize("B,N,D,F,c,plan", [
     (1, 1, 128, 64, 128, (1, 2)),            # one token, one neuron tile half full, one piece, the high parts in two sums
-    (1, 300, 512, 64, 128, (8, 1)),          # eight pieces of one step
-    (1, 384, 640, 7680, 192, (8, 1)),        # two chunks; ten steps in eight pieces
+    (1, 300, 512, 64, 128, (8, 2)),          # eight pieces of one step
+    (1, 384, 640, 7680, 192, (4, 2)),        # two chunks; ten steps in four pieces
+    (1, 4500, 640, 12288, 192, (5, 1)),      # ten steps in five pieces, one sum each
     (1, 127 * 128, 128, 320, 128, (1, 2)),   # 127, 128 and 129 chunks: both sides of a tile
     (2, 64 * 192, 256, 576, 192, (1, 2)),
     (1, 128 * 128 + 5, 384, 64, 128, (1, 2)),

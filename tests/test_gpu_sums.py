@@ -47,12 +47,12 @@ def test_column_sums_of_given_normalisers(cm, N, E, c):
 
 
 @pytest.mark.parametrize("chunks,D,F", [
-    (1, 128, 64), (8, 256, 1024), (300, 384, 2048),   # one piece, the high parts in two sums
-    (8, 1792, 1024),                     # 16 pieces of one step or two
-    (24, 3072, 10240), (14, 2048, 8704), # six and seven pieces: a workgroup per CU
-    (40, 4096, 10240),                   # four pieces, two sums each, where six in one would be too long
-    (258, 1024, 6912), (129, 1024, 16640),   # two pieces and one, two sums each
-    (602, 1024, 12288),                  # one piece, one sum
+    (1, 128, 64), (8, 256, 1024), (300, 384, 2048),          # one piece, two sums
+    (8, 1792, 1024), (14, 2048, 8704), (24, 3072, 10240),    # 16 and 3 pieces, two sums each
+    (24, 3072, 12288),                                       # five pieces, one sum each
+    (40, 4096, 10240),                                       # four pieces, two sums each: fewer would be too long
+    (258, 1024, 6912), (129, 1024, 16640),                   # two pieces and one, two sums each
+    (602, 1024, 12288),                                      # one piece, one sum
 ])
 def test_neuron_scores_add_no_longer_sums_than_the_workspace_has_pieces_for(cm, chunks, D, F):
     """Chunk means that two bf16 numbers hold exactly, so that what is left is the error of the GEMM's 32-bit sums.  One rounding
