@@ -302,9 +302,8 @@ __device__ __forceinline__ void emit_selected(const Src& src, int C, uint32_t th
 // allowed two workgroups, so that 602 rows took two rounds.  Against histograms of 11-bit digits over keys in LDS: 602 rows
 // of 12 288 with previous scores 36.8 -> 22.9 us, 14 448 x 4608 150 -> 105 us, 4000 x 12 288 (30 % kept) 160 -> 95 us,
 // 5000 x 1024 30.8 -> 14.4 us.  The steps grow with the exponents that the range spans: column sums and |T - T_m| lie
-// within a few, but scores of both signs take about ten steps, and rows of just over 7168 of them (eight waves with registers for
-// five units each, of which four are filled) are the one place where the histograms were faster: 768 normal rows of 7200 15.7
-// and 20.7 us, of 9000 20.0 and 21.4.
+// within a few, but scores of both signs take about ten steps, and rows of just over 7168 of them are the one place where the
+// histograms were faster: 768 normal rows of 7200 15.8 and 18.3 us, of 9000 20.0 and 21.4.
 constexpr int kRegisterCols = 8 * 7 * 256;
 constexpr int kLastKeys = 256;
 
@@ -995,7 +994,7 @@ extern "C" int32_t chipmunk_topk_cols(const float* cur, const float* prev, int R
         // few waves serve many short rows best, and eight a row whose keys would otherwise fill the registers of four.
         // Us for 5000 rows of 1024 columns with two, four and eight waves: 14.4, 17.1, 30.9; 14 448 rows of 6500 with
         // four and eight: 144, 210; 602 rows of 12 288 (with previous scores): 25.9 and 22.9.  Registers for four units of a wave
-        // rather than five: 509 rows of 3392 (with previous scores) 9.9 -> 9.1.
+        // rather than five: 509 rows of 3392 (with previous scores) 9.9 -> 9.1, 769 of 8128 24.8 -> 21.9.
         const int groups = (C + 255) / 256;
         const int waves = groups <= 4 ? 2 : groups <= 28 ? 4 : 8;
         const int per_wave = (groups + waves - 1) / waves;
@@ -1019,7 +1018,8 @@ extern "C" int32_t chipmunk_topk_cols(const float* cur, const float* prev, int R
             else if (per_wave <= 5) launch(four, std::integral_constant<int, 5>{});
             else launch(four, std::integral_constant<int, 7>{});
         } else {
-            if (per_wave <= 5) launch(eight, std::integral_constant<int, 5>{});
+            if (per_wave <= 4) launch(eight, std::integral_constant<int, 4>{});
+            else if (per_wave <= 5) launch(eight, std::integral_constant<int, 5>{});
             else if (per_wave <= 6) launch(eight, std::integral_constant<int, 6>{});
             else launch(eight, std::integral_constant<int, 7>{});
         }

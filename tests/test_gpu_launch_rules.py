@@ -131,7 +131,7 @@ def test_dense_mlp_on_large_tiles(cm, oracle, B, N, D, F, c, act, bias, large):
     assert rel_err(si.np_f32(out), ref) <= REL_TOL
 
 
-@pytest.mark.parametrize("C", [1, 3, 255, 257, 1024, 1025, 2049, 3073, 4096, 5121, 7168, 7169, 10241, 12288, 12289, 14336, 14337])
+@pytest.mark.parametrize("C", [1, 3, 255, 257, 1024, 1025, 2049, 3073, 4096, 5121, 7168, 7169, 8192, 8193, 10241, 12288, 12289, 14336, 14337])
 @pytest.mark.parametrize("kind", ["normal", "constant", "two_values", "few_ulps", "spikes", "wide"])
 def test_topk_of_rows_kept_in_registers(cm, oracle, C, kind):
     """Both sides of every limit between the instances (and of the long rows, which without previous scores and with few columns
