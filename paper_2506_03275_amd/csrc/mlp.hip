@@ -734,29 +734,35 @@ static int32_t launch_gemm2(Gemm2Params p, int col_tiles, int units, hipStream_t
 }
 
 // Whether a dense GEMM takes the 256 x 256 tiles of mlp_dense.h or the chunk's tiles (192 or 128 x 128).  Both are priced as
-// whole rounds of workgroups over the chip plus a last one that is partly filled: a round with a share x of its slots
-// taken costs g + (1 - g) x of a whole one, because few workgroups leave the others' memory rate and power to each other.
-// In us per contraction step, fitted to a hundred sizes from 500 x 1792 x 2816 to 54 000 x 512 x 8576 (tokens x D x F):
-//   first GEMM, one workgroup per CU:  256 x 256: 0.94 a round, and 12 us a tile for its ends, g = 0.79;
-//                                      192 x 128: 0.62 and 5;  128 x 128: 0.58 and 4;  g = 0.26
-//   second GEMM:                       256 x 256: 1.37, g = 0.46, and 5.5 us more than the others in all;
-//                                      192 x 128 (two per CU): 1.70;  128 x 128: 1.20;  g = 0.21
-// (times of the two GEMMs with large - small tiles, us: first 500 x 1792 x 2816: +29; 2 x 548 x 1792 x 7424: +6; 2928 x 3072 x
-// 12 224: -57; second 2755 x 1792 x 9408 in chunks of 128: +30; 1969 x 4992 x 14 080 in chunks of 192: -159; two of
-// 5309 x 4864 x 12 416: -206.  Priced with whole and half rounds the rule took the slower tiles for 23 of these two hundred
-// GEMMs, 2 x 548 x 1792 x 7424 in 185 instead of 163 us; now for ten, and for 7 of a hundred that the fit had not seen.)
+// whole rounds of the busiest XCD's workgroups over its 32 CUs plus a last one that is partly filled: an XCD takes an eighth of
+// each batch's large tiles, or of the chunks, rounded up.  In us, with n contraction steps and a share x of the last round's
+// slots taken, fitted to 1420 sizes from 500 x 512 x 1024 to 30 000 x 5120 x 14 080 (tokens x D x F):
+//   first GEMM, one workgroup per CU:  256 x 256: 1.05 n + 9.5 a round, the last one 0.88 + 0.08 x of it
+//                                      192 x 128: 0.64 n + 6.1;  128 x 128: 0.42 n + 4.5;  the last one 0.24 + 0.44 x
+//   second GEMM:                       256 x 256: 1.39 n a round, also the last, and 2.8 in all
+//                                      192 x 128 (two per CU): 1.77 n + 1.1;  128 x 128: 1.40 n + 0.8;  the last one
+//                                      0.28 + 0.32 (2 x) while each workgroup has a CU, 0.74 + 0.28 (2 x - 1) when some share one
+// (times of the two GEMMs with large - small tiles, us: first 3995 x 5120 x 1856 in chunks of 128: +14; 2 x 571 x 640 x 9216:
+// -25; 6024 x 2944 x 11 008: -54; second 2 x 916 x 3456 x 8320 in chunks of 128: +18, 6024 x 2944 x 11 008: +37, 2 x 595 x 4224 x
+// 3840: -30.  For 400 further sizes the slower tiles cost 0.14 % of a call in the mean for each GEMM, with rounds over the
+// whole chip 0.44 and 0.49 %; the large ones were slower by more than 2 % of a call in 5 sizes, and in 18: what the prices
+// miss is the erf form in chunks of 192 with 1.6 to 2 rounds of small tiles, 895 x 2432 x 6784: +26.)
 static bool large_tiles_pay(bool second, int B, int N, int D, int F, int c) {
-    const int64_t chunks = (N + c - 1) / c, large_n = (N + kDenseTile - 1) / kDenseTile;
-    const int width = second ? D : F, steps = (second ? F : D) / kBK;
-    const int64_t small = B * chunks * ((width + kBN - 1) / kBN), large = B * large_n * ((width + kDenseTile - 1) / kDenseTile);
     if (B > 65535) return false;   // the large tiles take the batch from the second grid dimension
-    auto rounds = [](int64_t tiles, int slots, double g) {
-        const int64_t last = tiles % slots;
-        return (double)(tiles / slots) + (last == 0 ? 0. : g + (1. - g) * (double)last / slots);
+    const int64_t chunks = (int64_t)B * ((N + c - 1) / c), large_n = (N + kDenseTile - 1) / kDenseTile;
+    const int width = second ? D : F, steps = (second ? F : D) / kBK;
+    const int64_t small = (chunks + 7) / 8 * ((width + kBN - 1) / kBN);
+    const int64_t large = B * ((large_n * ((width + kDenseTile - 1) / kDenseTile) + 7) / 8);
+    auto rounds = [](int64_t tiles, double at_least, double by_share) {
+        const int64_t last = tiles % 32;
+        return (double)(tiles / 32) + (last == 0 ? 0. : at_least + by_share * (double)last / 32.);
     };
-    if (!second) return rounds(large, 256, 0.79) * (0.94 * steps + 12.) <
-                        rounds(small, 256, 0.26) * (c == 192 ? 0.62 * steps + 5. : 0.58 * steps + 4.);
-    return rounds(large, 256, 0.46) * 1.37 * steps + 5.5 < rounds(small, 512, 0.21) * (c == 192 ? 1.70 : 1.20) * steps;
+    if (!second) return rounds(large, 0.88, 0.08) * (1.05 * steps + 9.5) <
+                        rounds(small, 0.24, 0.44) * (c == 192 ? 0.64 * steps + 6.1 : 0.42 * steps + 4.5);
+    const int64_t last = small % 64;
+    const double share = (double)last / 32., last_round = last == 0 ? 0. : last <= 32 ? 0.28 + 0.32 * share : std::min(1., 0.74 + 0.28 * (share - 1.));
+    return rounds(large, 1., 0.) * 1.39 * steps + 2.8 <
+           ((double)(small / 64) + last_round) * (c == 192 ? 1.77 * steps + 1.1 : 1.40 * steps + 0.8);
 }
 
 template <int MODE, int BM = kDenseTile>
