@@ -112,13 +112,17 @@ def _ptr_rows(t, dtype, name):
     return t.data_ptr()
 
 
-def _stream():
-    """The current stream of the current device, as torch.cuda.current_stream().cuda_stream gives it but without the Stream
-    object (2.8 us a call, of the 9 that a small attention call took on the host; 0.2 us this way).  The names are torch's own,
-    so they are looked up here and not needed."""
-    try:
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-    except AttributeError:
+# The current stream of the current device as torch.cuda.current_stream().cuda_stream gives it, but without the Stream object
+# (2.8 us a call, of the 9 that a small attention call took on the host; 0.2 us this way).  The names are torch's own: where
+# it has them no longer, its public way takes their place.
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+if _current_device is not None and _raw_stream is not None:
+    def _stream():
+        return _raw_stream(_current_device())
+else:
+    def _stream():
         return torch.cuda.current_stream().cuda_stream
 
 

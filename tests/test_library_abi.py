@@ -129,23 +129,25 @@ def test_bad_arguments_are_rejected_without_a_launch(lib):
     assert tm(a, a, a, 1, 1024, 256, 1024, 100, a, 1 << 30, None) == -4
 
 
-def test_package_needs_no_private_names_of_torch():
+@pytest.mark.parametrize("has_names", [False, True])
+def test_package_needs_no_private_names_of_torch(has_names):
     """The current stream is looked up the short way where torch has the names for it; without them the package imports and
     takes torch's public way."""
     import subprocess
     import sys
-    code = """
+    code = f"""
 import torch
-for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
-    if hasattr(torch._C, name):
-        delattr(torch._C, name)
-import paper_2506_03275_amd as cm
 class Stream:
     cuda_stream = 1234
 torch.cuda.current_stream = lambda: Stream
-assert cm._stream() == 1234
-torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream = (lambda: 3), (lambda device: 100 + device)
-assert cm._stream() == 103
+if {has_names}:
+    torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream = (lambda: 3), (lambda device: 100 + device)
+else:
+    for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+        if hasattr(torch._C, name):
+            delattr(torch._C, name)
+import paper_2506_03275_amd as cm
+assert cm._stream() == (103 if {has_names} else 1234)
 """
     r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr
