@@ -784,7 +784,7 @@ static int32_t launch_dense_gemm(DenseGemmParams p, int second_dim, hipStream_t 
 // tiles of a chunk run on one XCD (32 CUs, a workgroup each), so a launch takes rounds of the busiest XCD, the last one priced
 // by its share as above; us per contraction step and per tile end: c = 192: 1.45 and 13 against 0.87 and 5, c = 128: 1.02 and 5
 // against 0.66 and 3.  Kernel times, 256 against 128: 24 chunks x 1229 of 12 288 x 3072: 69 and 43 us; 47 chunks: 82 and 96; 94 x
-// 968 of 13 824 x 5120: 274 and 229; 394: 881 and 945 (whole delta 1993 -> 1895 us); c = 128, 36 x 1229 of 12 288 x 3072: 54 and
+// 968 of 13 824 x 5120: 274 and 229; 394: 815 and 945 (whole delta 1988 -> 1874 us); c = 128, 36 x 1229 of 12 288 x 3072: 54 and
 // 65.  Whole deltas: c = 128, 81 x 337 of 1024 x 4608: 148 and 127; c = 192, 351 x 2534 of 7680 x 640: 771 and 742.
 static bool wide_delta_pays(int units, int D, int c, int k_stride) {
     const int chunks = (units + 7) / 8, steps = D / kBK;

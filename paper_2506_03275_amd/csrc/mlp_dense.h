@@ -1,5 +1,6 @@
 // The two GEMMs of the dense MLP (Alg. 5) at sizes that fill the chip, the scores GEMM (Alg. 7), and the first GEMM of the
-// column-sparse form where its tiles make fewer rounds.  Internal to mlp.hip, which chooses between these and the tiles of 192 or 128 x 128 that the column-sparse form uses.
+// column-sparse form where its tiles make fewer rounds.  Internal to mlp.hip, which chooses between these and the tiles of
+// 192 or 128 x 128 that the column-sparse form uses.
 //
 // One workgroup of eight waves owns a 256 x 256 tile of the result and walks the contraction in steps of 64.  A step's
 // operands are four half tiles of 16 KB in LDS (P0, P1: 128 rows each of the operand that lies along the result's
@@ -15,10 +16,11 @@
 //     0       P0 and Q1 (step t)           Q0 (step t + 2), P1 (t + 1)    P0 x Q0, P0 x Q1
 //     1       P1 (t) and Q0 (step t + 1)   P0 and Q1 (t + 2)              P1 x Q1, P1 x Q0
 // A slot ends with its LDS reads complete and with the wave's share of what the next slot reads landed: always all but
-// the youngest 8 transfers.
+// the transfers of the last two slots (8, or fewer where P is narrower).
 //
-// Measured at 18 000 tokens, D 5120, F 13 824 (5.1 TFLOP): both GEMMs 4.79 ms with 192 x 128 tiles, 3.72 ms with these
-// (1.37 PFLOP/s; the second GEMM's 1420 tiles are 5.5 rounds of the CUs); 4608 x 3072 x 12 288: 734 and 569 us.  The matrix pipes are busy 76 % of the cycles at 1.7 to 1.8 GHz: the chip is at its power limit, so cycles
+// Measured at 18 000 tokens, D 5120, F 13 824 (5.1 TFLOP): both GEMMs 4.79 ms with 192 x 128 tiles, 3.74 ms with these
+// (1.36 PFLOP/s; the second GEMM's 1420 tiles are 5.5 rounds of the CUs); 4608 x 3072 x 12 288: 721 and 547 us.  The matrix
+// pipes are busy 75 % of the cycles (83 % in the second GEMM) at 1.7 to 1.8 GHz: the chip is at its power limit, so cycles
 // saved by themselves come back as a lower clock (with four slots of 16 products per step instead of two of 32 it took
 // 2 % more cycles and the same time).  Without the transfers (the same two steps over and over) the first GEMM takes
 // 1.48 ms instead of 1.89, without the epilogue 1.66.  Persistent workgroups that request the next tile's first steps
@@ -27,7 +29,7 @@
 //
 // The scores GEMM of the token-merged pre-activation (602 chunks x 12 288 neurons x 2 x 3072): 110 us and 13 us for the sum of
 // two pieces with tiles of 128 x 128 over [hi | lo] against [w1 | w1], 75 us in one piece with these (1.22 PFLOP/s); 24
-// chunks: 28 and 19 us.
+// chunks: 28 and 21 us.
 #pragma once
 #include "common.h"
 
