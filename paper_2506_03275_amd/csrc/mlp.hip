@@ -34,43 +34,50 @@ constexpr int kBK = 64;   // contraction tile
 
 enum Gemm1Mode { kSparseDelta = 0, kDenseAct = 1 };
 
-// Workgroups are dispatched to the eight XCDs round-robin by linear id, and each
-// XCD has its own L2.  The tiles of one token chunk share that chunk's x rows
-// (GEMM1) or delta^T rows (GEMM2), so they are mapped to ids that are congruent
-// modulo 8: chunk u runs on XCD u % 8, its column tiles back to back.
-// Returns false for the padding ids of the last group of eight chunks.
+// Workgroups are dispatched to the eight XCDs round-robin by linear id, and each XCD has its own L2.  Tile of the workgroup in
+// slot `slot` of XCD `xcd` when each XCD takes one run of `tiles` tiles, the runs equally long to one tile; false for the ids that
+// pad the grid.
+__device__ __forceinline__ bool xcd_run_tile(int xcd, int slot, int tiles, int* tile) {
+    const int each = tiles >> 3, more = tiles & 7;
+    *tile = xcd * each + min(xcd, more) + slot;
+    return slot < each + (xcd < more ? 1 : 0);
+}
+static int xcd_grid_size(int col_tiles, int units) { return (col_tiles * units + 7) / 8 * 8; }
+
+// The column-sparse forms: the tiles of one token chunk share that chunk's x rows (GEMM1) or delta^T rows (GEMM2) and nothing
+// else, so they run on one XCD, chunk u on XCD u % 8, its column tiles back to back.  The last units % 8 chunks are cut into
+// eight runs of tiles instead: as whole chunks they left XCDs idle.  Whole deltas in us, 12 chunks x 1515 of 4096 x 3072: 134 -> 97,
+// 18 x 2216 of 9088 x 3200: 160 -> 133, 9 x 4914 of 10 112 x 3840: 242 -> 199; 394 x 968 of 13 824 x 5120: 1884 and 1884 (every
+// chunk in such a run: 1887 against 1870, 434 chunks of 2432 x 4992 624 against 614).
 __device__ __forceinline__ bool xcd_tile_of_block(int col_tiles, int units, int* unit, int* col_tile) {
-    const int id = blockIdx.x;
-    const int xcd = id & 7, slot = id >> 3;
-    const int u = (slot / col_tiles) * 8 + xcd;
-    *unit = u;
-    *col_tile = slot % col_tiles;
-    return u < units;
+    const int xcd = (int)blockIdx.x & 7, slot = (int)blockIdx.x >> 3;
+    const int whole = units >> 3, local = slot / col_tiles;   // chunks per XCD taken whole
+    if (local < whole) {
+        *unit = local * 8 + xcd;
+        *col_tile = slot - local * col_tiles;
+        return true;
+    }
+    int tile;
+    if (!xcd_run_tile(xcd, slot - whole * col_tiles, (units & 7) * col_tiles, &tile)) return false;
+    const int of_rest = tile / col_tiles;
+    *unit = whole * 8 + of_rest;
+    *col_tile = tile - of_rest * col_tiles;
+    return true;
 }
-static int xcd_grid_size(int col_tiles, int units) { return ((units + 7) / 8) * 8 * col_tiles; }
 
-// The dense forms (every neuron selected) share the weight tiles between chunks as well, and a weight tile is as
-// large as a chunk's rows: here 8 chunks x 8 column tiles of one XCD are mapped to 64 consecutive slots, so that what
-// runs side by side on an XCD reads 8 weight tiles and 8 row tiles, each eight times, instead of 64 weight tiles once.
-// Chunks and column tiles are padded to multiples of 8 per XCD; padding ids return false.
+// The dense forms (every neuron selected) share the weight tiles between chunks as well, and a weight tile is as large as a
+// chunk's rows: the tiles stand in bands of eight chunks, column tile by column tile, so that what runs side by side on an
+// XCD (64 workgroups at most) reads eight row tiles and eight weight tiles, each eight times.  (Eight chunks and eight column
+// tiles at a time with both padded to eight, whole MLP in us: 19 chunks of 192 x 1536 x 11 264 330 -> 272, 17 x 3584 x 1728 113 -> 88.)
 __device__ __forceinline__ bool xcd_tile_of_block_grouped(int col_tiles, int units, int* unit, int* col_tile) {
-    const int id = blockIdx.x;
-    const int xcd = id & 7, slot = id >> 3;
-    const int ctb_count = (col_tiles + 7) >> 3;          // blocks of 8 column tiles
-    const int ct8 = slot & 7, lc8 = (slot >> 3) & 7;
-    const int rest = slot >> 6;                          // = group of 8 local chunks * ctb_count + column-tile block
-    const int g = rest / ctb_count, ctb = rest - g * ctb_count;
-    const int u = (g * 8 + lc8) * 8 + xcd;               // local chunk g*8+lc8 of this XCD
-    const int ct = ctb * 8 + ct8;
-    *unit = u;
-    *col_tile = ct;
-    return u < units && ct < col_tiles;
+    int tile;
+    if (!xcd_run_tile((int)blockIdx.x & 7, (int)blockIdx.x >> 3, col_tiles * units, &tile)) return false;
+    const int band = tile / (8 * col_tiles), in_band = tile - band * 8 * col_tiles;
+    const int height = min(8, units - 8 * band);
+    *col_tile = in_band / height;
+    *unit = 8 * band + in_band - *col_tile * height;
+    return true;
 }
-static int xcd_grid_size_grouped(int col_tiles, int units) {
-    const int local = (units + 7) / 8;                   // chunks per XCD
-    return ((local + 7) / 8) * ((col_tiles + 7) / 8) * 64 * 8;
-}
-
 
 // ACT is a template argument so that a tile's activations are straight-line code: with the form chosen by a
 // run-time branch inside, every element became a basic block of its own and its dozen dependent instructions
@@ -711,9 +718,7 @@ static int32_t launch_gemm1(Gemm1Params p, int col_tiles, int units, hipStream_t
     if (hipFuncSetAttribute((const void*)mlp_gemm1_kernel<BM, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) !=
         hipSuccess)
         return CHIPMUNK_ERR_LAUNCH;
-    const int grid = MODE == kDenseAct ? xcd_grid_size_grouped(col_tiles, units)
-                                       : xcd_grid_size(col_tiles, units);
-    hipLaunchKernelGGL((mlp_gemm1_kernel<BM, MODE>), dim3(grid), dim3(320), lds, s, p);
+    hipLaunchKernelGGL((mlp_gemm1_kernel<BM, MODE>), dim3((unsigned)xcd_grid_size(col_tiles, units)), dim3(320), lds, s, p);
     return launch_status();
 }
 
@@ -727,7 +732,7 @@ static int32_t launch_gemm2(Gemm2Params p, int col_tiles, int units, hipStream_t
     if (hipFuncSetAttribute((const void*)mlp_gemm2_kernel<BM>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) !=
         hipSuccess)
         return CHIPMUNK_ERR_LAUNCH;
-    p.tile_blocks = p.dense ? xcd_grid_size_grouped(col_tiles, units) : xcd_grid_size(col_tiles, units);
+    p.tile_blocks = xcd_grid_size(col_tiles, units);
     const int grid = p.tile_blocks + (p.act_t ? units : 0);
     hipLaunchKernelGGL((mlp_gemm2_kernel<BM>), dim3((unsigned)grid), dim3(256), lds, s, p);
     return launch_status();

@@ -267,3 +267,27 @@ def test_unchanged_input_leaves_the_caches_alone(cm, B, N, D, F, c, k, large, wi
     counts = torch.full((B, NB), k, dtype=torch.int32, device=DEV)
     cm.mlp_sparse_delta(x, w1, b1, w2, idx.view(B, NB, k), counts, a_cache, out, c, act, _u8(cm.mlp_workspace_bytes(B, N, D, F, c, k)))
     assert torch.equal(a_cache, a_before) and torch.equal(out, o_before)
+
+
+@pytest.mark.parametrize("B,N,D,F,c,k", [(1, 100, 384, 320, 128, 200), (1, 7 * 128 - 5, 256, 512, 128, 140), (1, 9 * 192, 128, 640, 192, 300),
+                                         (3, 5 * 128 - 60, 640, 256, 128, 256), (1, 17 * 192 - 1, 256, 448, 192, 65)])
+def test_mlp_of_any_number_of_chunks(cm, oracle, B, N, D, F, c, k):
+    """1, 7, 9, 15 and 17 chunks: the tiles of the chunks beyond a multiple of eight are dealt out over the XCDs one by one, in the
+    sparse and in the dense form, each exactly once."""
+    x1, x2, w1, b1, w2, b2 = recipes.mlp_inputs(B, N, D, F, 31, DEV)
+    NB, a_ld = -(-N // c), -(-N // 8) * 8
+    out = torch.empty_like(x1)
+    a_cache = torch.zeros((B, F, a_ld), dtype=torch.bfloat16, device=DEV)
+    cm.mlp_dense(x1, w1, b1, w2, b2, out, a_cache, c, 1)
+    ref, a_ref, _ = oracle.mlp_dense(si.np_f32(x1), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2), si.np_f32(b2), c, 1, a_ld=a_ld)
+    assert rel_err(si.np_f32(a_cache)[..., :N], a_ref[..., :N]) <= REL_TOL
+    assert rel_err(si.np_f32(out), ref) <= REL_TOL
+    o_ref, a_ref = (si.np_f32(t).astype(np.float64) for t in (out, a_cache))
+    o_before = o_ref.copy()
+    idx, counts = recipes.mlp_indices(B * NB, F, k, 31, DEV, ragged=True)
+    idx, counts = idx.view(B, NB, k), counts.view(B, NB)
+    cm.mlp_sparse_delta(x2, w1, b1, w2, idx, counts, a_cache, out, c, 1, _u8(cm.mlp_workspace_bytes(B, N, D, F, c, k)))
+    oracle.mlp_sparse_delta(si.np_f32(x2), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2), idx.cpu().numpy(), counts.cpu().numpy(),
+                            a_ref, o_ref, c, 1)
+    assert rel_err(si.np_f32(a_cache)[..., :N], a_ref[..., :N]) <= REL_TOL
+    assert rel_err(si.np_f32(out), o_ref, o_ref - o_before) <= REL_TOL
