@@ -370,7 +370,6 @@ struct Gemm2Params {
     uint16_t* o;             // sparse: o_cache in/out; dense: out
     int64_t a_ld;
     int N, NB, D, F, k_stride, k_pad;
-    int dense;
     int col_tiles, units;    // launch geometry (see xcd_tile_of_block)
     // Deferred cache write-back (App. B.3.3): workgroups with id >= tile_blocks, one per unit, copy the new
     // activations that the first GEMM left in act_t into a_cache while the tile workgroups of this launch compute.
@@ -379,114 +378,137 @@ struct Gemm2Params {
     int tile_blocks;
 };
 
-template <int BM>
-__device__ __forceinline__ int swizzle_at(int row) {  // for rows of BM tokens (BM*2 bytes)
-    if (BM == 192) return (row & 2) << 1;
+// The deferred write-back of chunk u's new activations, by a workgroup of 256 threads.  These workgroups have the highest ids,
+// so they start when the tile workgroups' last round leaves compute units free, and their memory traffic runs beside that
+// round's products.
+__device__ __forceinline__ void write_back_activations(const Gemm2Params& p, int u, int c) {
+    const int ub = u / p.NB, urow0 = (u % p.NB) * c;
+    const int ucount = max(min(p.counts[u], p.k_stride), 0);
+    const int cells = c / 8;
+    for (int item = threadIdx.x; item < ucount * cells; item += 256) {
+        const int s = item / cells, ch = item - s * cells;
+        const int tok0 = urow0 + ch * 8;
+        const int nvalid = min(8, p.N - tok0);
+        if (nvalid <= 0) continue;
+        const int f = min(max(p.idx[(int64_t)u * p.k_stride + s], 0), p.F - 1);
+        const u32x4 a8 = *reinterpret_cast<const u32x4*>(p.act_t + ((int64_t)u * p.k_pad + s) * c + ch * 8);
+        uint16_t* arow = p.a_cache + ((int64_t)ub * p.F + f) * p.a_ld + tok0;
+        if (nvalid == 8) {
+            *reinterpret_cast<u32x4*>(arow) = a8;
+        } else {  // the cells past N in the last chunk stay as they are
+            for (int e = 0; e < nvalid; e++) arow[e] = (uint16_t)(a8[e >> 1] >> (16 * (e & 1)));
+        }
+    }
+}
+
+// 16-byte chunk position of an A^T or w2 tile row: four rows of 64 bytes (what 32 lanes of a transposing read ask for) lie in 256
+// different bytes.  Rows of 128 or 384 bytes alternate between the halves by themselves.
+template <int ROWB>
+__device__ __forceinline__ int swizzle_at(int row) {
+    if (ROWB % 256 != 0) return (row & 2) << 1;
     return ((row & 3) << 2) | ((row >> 2) & 3);
 }
-__device__ __forceinline__ int swizzle_w2(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
 
-template <int BM>
-__global__ __launch_bounds__(256, 2) void mlp_gemm2_kernel(Gemm2Params p) {
-    constexpr int MT = BM / 64;
-    constexpr int RBA = BM * 2;                    // bytes per row of the A^T tile
-    constexpr int CPA = BM / 8;                    // 16-byte chunks per A^T row
-    constexpr int AT = kBK * RBA;                  // A^T tile bytes [64][BM]
-    constexpr int WT = kBK * 256;                  // w2 tile bytes  [64][128]
-    constexpr int STAGE = AT + WT;
-    constexpr int NIA = kBK * CPA / 256;           // loads per lane, A^T tile
-    constexpr int NIW = kBK * 16 / 256;            // loads per lane, w2 tile
-    constexpr int CS = 128 * 4 + 32;               // row stride (bytes) of the fp32 epilogue tile
+// 4-byte form of load_buffer_to_lds_16B: lane l deposits its dword at lds_wave_base + 4 l
+__device__ __forceinline__ void load_buffer_to_lds_4B(i32x4 buffer, uint32_t byte_offset, uint32_t lds_wave_base) {
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                 :
+                 : "s"(lds_wave_base), "v"(byte_offset), "s"(buffer)
+                 : "memory");
+}
+
+constexpr int kGemm2K = 32;   // contraction tile of the second GEMM
+template <int ROWS>
+struct Gemm2Shape {           // of a workgroup that owns ROWS token rows
+    static constexpr int kStages = ROWS == 192 ? 3 : 4;
+    static constexpr int kListSlots = 8;                            // kStages + 2 are in use at a time
+    static constexpr int kStage = kGemm2K * (ROWS * 2 + kBN * 2);   // A^T tile [32][ROWS], w2 tile [32][128]
+    static constexpr int kList = kListSlots * 4 * 256;              // 64 list entries per wave and slot
+    static constexpr int kEpilogue = (ROWS / 2) * (kBN * 4 + 32);   // half the fp32 result
+    static constexpr int kLds = (kStages * kStage > kEpilogue ? kStages * kStage : kEpilogue) + kList;
+};
+
+// The work of one workgroup: ROWS rows (the chunk's, or its 64 rows `part`) and 128 output columns.
+// The contraction runs in steps of 32 through a ring of kStages stages; the step after the one that is multiplied is already in
+// registers, so a stage is free again as soon as its operands have been read.  The list comes the same way: every wave keeps
+// a ring of its own of slices of 64 entries in LDS, kStages steps ahead of the gather that uses them, so no load into
+// registers stands between the transfers and nothing waits for more than the step it needs.  With two buffers of 64 rows, one
+// drained at the head of every step, a CU had 40 KB in flight on average and took 10 TB/s into LDS.  Whole deltas in us, two
+// buffers and this ring: 394 chunks x 968 of 13 824 x 5120 1860 -> 1785, 24 x 1229 of 12 288 x 3072 101 -> 96.5, c = 128: 1350 x
+// 442 of 6144 x 2944 1440 -> 1324; dense, 11 chunks of 128 x 2176 x 5760: 120 -> 104.
+template <int BM, int ROWS, bool DENSE>
+__device__ __forceinline__ void gemm2_rows(const Gemm2Params& p, int unit, int part, int col_tile) {
+    typedef Gemm2Shape<ROWS> Shape;
+    constexpr int NS = Shape::kStages, SLOTS = Shape::kListSlots, STAGE = Shape::kStage;
+    constexpr int MT = ROWS / 64;                  // 32-row MFMA tiles per wave (wave tile = ROWS/2 x 64)
+    constexpr int RBA = ROWS * 2;                  // bytes per row of the A^T tile
+    constexpr int CPA = ROWS / 8;                  // 16-byte chunks per A^T row
+    constexpr int AT = kGemm2K * RBA;              // A^T tile bytes
+    constexpr int NIA = kGemm2K * CPA / 256;       // loads per lane, A^T tile
+    constexpr int NIW = kGemm2K * 16 / 256;        // loads per lane, w2 tile
+    constexpr int G = NIA + NIW + (DENSE ? 0 : 1); // transfers of a wave and step, with the slice of the list
+    constexpr int CS = kBN * 4 + 32;               // row stride (bytes) of the fp32 epilogue tile
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
 
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = w >> 1, wn = w & 1;
     const int l16 = lane & 15, mb = (lane >> 4) & 1, h = lane >> 5;
-
-    if (p.act_t && (int)blockIdx.x >= p.tile_blocks) {
-        // A write-back workgroup.  They have the highest ids, so they start when the tile workgroups' last round
-        // leaves compute units free, and their memory traffic runs beside that round's products.
-        const int u = (int)blockIdx.x - p.tile_blocks;
-        const int ub = u / p.NB, urow0 = (u % p.NB) * BM;
-        const int ucount = max(min(p.counts[u], p.k_stride), 0);
-        constexpr int CPR = BM / 8;
-        for (int item = tid; item < ucount * CPR; item += 256) {
-            const int s = item / CPR, ch = item - s * CPR;
-            const int tok0 = urow0 + ch * 8;
-            const int nvalid = min(8, p.N - tok0);
-            if (nvalid <= 0) continue;
-            const int f = min(max(p.idx[(int64_t)u * p.k_stride + s], 0), p.F - 1);
-            const u32x4 a8 = *reinterpret_cast<const u32x4*>(p.act_t + ((int64_t)u * p.k_pad + s) * BM + ch * 8);
-            uint16_t* arow = p.a_cache + ((int64_t)ub * p.F + f) * p.a_ld + tok0;
-            if (nvalid == 8) {
-                *reinterpret_cast<u32x4*>(arow) = a8;
-            } else {  // the cells past N in the last chunk stay as they are
-                for (int e = 0; e < nvalid; e++) arow[e] = (uint16_t)(a8[e >> 1] >> (16 * (e & 1)));
-            }
-        }
-        return;
-    }
-    int unit, col_tile;
-    if (p.dense ? !xcd_tile_of_block_grouped(p.col_tiles, p.units, &unit, &col_tile)
-                : !xcd_tile_of_block(p.col_tiles, p.units, &unit, &col_tile))
-        return;
     const int b = unit / p.NB, chunk = unit % p.NB;
-    const int row0 = chunk * BM;
+    const int row0 = chunk * BM + part * ROWS;
     const int d0 = col_tile * kBN;
-    const int count = p.counts ? min(p.counts[unit], p.k_stride) : p.F;
-    if (count <= 0 && !p.dense) return;            // nothing selected: the cache stays as it is
-    const int32_t* idxp = p.idx ? p.idx + (int64_t)unit * p.k_stride : nullptr;
-    const int ktiles = (count + kBK - 1) / kBK;
+    const int count = DENSE ? p.F : min(p.counts[unit], p.k_stride);
+    if (row0 >= p.N || count <= 0) return;         // nothing selected: the cache stays as it is
+    const int steps = (count + kGemm2K - 1) / kGemm2K;
 
     // A^T source: row (selected slot or neuron) -> tokens of this chunk
-    const uint16_t* abase;
-    int64_t a_row_stride;                          // elements between consecutive contraction rows
-    if (p.dense) {
-        abase = p.a_t + (int64_t)b * p.F * p.a_ld + row0;
-        a_row_stride = p.a_ld;
-    } else {
-        abase = p.a_t + (int64_t)unit * p.k_pad * BM;
-        a_row_stride = BM;
-    }
-    uint32_t aoff_g[NIA];
+    const int64_t a_row = DENSE ? p.a_ld : BM;     // elements between consecutive contraction rows
+    const i32x4 abuf = DENSE ? raw_buffer_words(p.a_t + (int64_t)b * p.F * p.a_ld, (uint32_t)p.F * (uint32_t)p.a_ld * 2u)
+                             : raw_buffer_words(p.a_t + (int64_t)unit * p.k_pad * BM, (uint32_t)p.k_pad * BM * 2u);
+    const i32x4 wbuf = raw_buffer_words(p.w2, (uint32_t)p.F * p.D * 2u);
+    const i32x4 ibuf = DENSE ? wbuf : raw_buffer_words(p.idx + (int64_t)unit * p.k_stride, (uint32_t)p.k_stride * 4u);
+    const uint32_t astep = (uint32_t)(kGemm2K * a_row * 2), wstep = DENSE ? (uint32_t)(kGemm2K * p.D * 2) : 0u;
+    uint32_t aoff[NIA], woff[NIW];
 #pragma unroll
     for (int i = 0; i < NIA; i++) {
-        int q = (i * 4 + w) * 64 + lane;           // linear 16-byte chunk of the tile
-        int row = q / CPA, pos = q - row * CPA;
-        int c16 = pos ^ swizzle_at<BM>(row);
-        if (p.dense && row0 + c16 * 8 >= p.N) c16 = 0;  // tokens beyond N: any valid data, the rows are not stored
-        aoff_g[i] = (uint32_t)((int64_t)row * a_row_stride * 2 + c16 * 16);
+        const int q = (i * 4 + w) * 64 + lane;     // linear 16-byte chunk of the tile
+        const int row = q / CPA, pos = q - row * CPA;
+        int c16 = pos ^ swizzle_at<RBA>(row);
+        // dense: tokens beyond N read any valid data, their rows are not stored
+        const int tok = DENSE ? (row0 + c16 * 8 < p.N ? row0 + c16 * 8 : row0) : part * ROWS + c16 * 8;
+        aoff[i] = (uint32_t)(row * a_row * 2) + (uint32_t)tok * 2u;
     }
     int wrow[NIW];
-    uint32_t wchunk[NIW];
 #pragma unroll
     for (int i = 0; i < NIW; i++) {
         wrow[i] = (i * 4 + w) * 4 + (lane >> 4);
-        wchunk[i] = (uint32_t)(((lane & 15) ^ swizzle_w2(wrow[i])) * 16);
+        woff[i] = (uint32_t)((lane & 15) ^ swizzle_at<256>(wrow[i])) * 16u + (uint32_t)d0 * 2u + (DENSE ? (uint32_t)wrow[i] * (uint32_t)(p.D * 2) : 0u);
     }
-    const uint16_t* w2b = p.w2 + d0;
-    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem) + (uint32_t)w * 1024u);
-
-    int cols[NIW];
-    auto load_cols = [&](int kt) {
+    const uint32_t lds0 = lds_address(smem);
+    const uint32_t list0 = lds0 + (uint32_t)(Shape::kLds - Shape::kList) + (uint32_t)w * (SLOTS * 256u);
+    // slice s: list entries 32 s ..; entries past the end repeat the last one (their deltas are zero)
+    auto request_slice = [&](int s) {
+        if (!DENSE) load_buffer_to_lds_4B(ibuf, (uint32_t)min(s * kGemm2K + lane, count - 1) * 4u, list0 + (uint32_t)((s & (SLOTS - 1)) * 256));
+    };
+    uint32_t row_at[NIW] = {};                     // byte offsets of the w2 rows of the step that is requested next
+    auto read_slice = [&](int s) {
+        if (!DENSE) {
+            const uint32_t at = list0 + (uint32_t)((s & (SLOTS - 1)) * 256);
 #pragma unroll
-        for (int i = 0; i < NIW; i++) {
-            int pos = min(kt * kBK + wrow[i], count - 1);
-            cols[i] = idxp ? idxp[pos] : pos;
+            for (int i = 0; i < NIW; i++)
+                row_at[i] = *reinterpret_cast<const __attribute__((address_space(3))) uint32_t*>((uintptr_t)(at + (uint32_t)wrow[i] * 4u));
         }
     };
-    // One of the NIA + NIW transfers of contraction step kt into buffer `stage` (issued one by one between the
-    // products of the step before, not in one burst); the w2 pieces use the columns that load_cols brought.
-    auto issue_piece = [&](int kt, int stage, int j) {
+    // one of the NIA + NIW transfers of step t into stage t % NS
+    auto request_piece = [&](int t, uint32_t stage, int j) {
         if (j < NIA) {
-            load_global_to_lds_16B(abase + (int64_t)kt * kBK * a_row_stride, aoff_g[j], lds0 + stage * STAGE + j * 4096);
+            load_buffer_to_lds_16B(abuf, aoff[j], (uint32_t)t * astep, stage + (uint32_t)((j * 4 + w) * 1024));
         } else {
             const int i = j - NIA;
-            load_global_to_lds_16B(w2b, (uint32_t)min(max(cols[i], 0), p.F - 1) * (uint32_t)(p.D * 2) + wchunk[i],
-                                   lds0 + stage * STAGE + AT + i * 4096);
+            const uint32_t row = DENSE ? 0u : (uint32_t)min(max((int)row_at[i], 0), p.F - 1) * (uint32_t)(p.D * 2);
+            load_buffer_to_lds_16B(wbuf, woff[i] + row, (uint32_t)t * wstep, stage + (uint32_t)(AT + (i * 4 + w) * 1024));
         }
     };
-    static_assert(NIA + NIW <= 4 * MT, "one transfer per pair of products");
 
     f32x16 acc[MT][2];
 #pragma unroll
@@ -496,74 +518,119 @@ __global__ __launch_bounds__(256, 2) void mlp_gemm2_kernel(Gemm2Params p) {
 #pragma unroll
             for (int r = 0; r < 16; r++) acc[mt][nt][r] = 0.f;
 
-    // Transposing reads.  For a k-step of 16 contraction rows, half h of the wave
-    // takes rows 8h..8h+7 as two groups of 4; inside a block of 16 lanes, lane i
-    // addresses row (i/4) of the group and 4 consecutive columns 4*(i%4).
-    const int trow = 8 * h + (l16 >> 2);           // + 4*rd, + 16*ks
-    const int tcol = 4 * (l16 & 3);                // element offset inside the 16-column block
-
-    if (ktiles > 0) {
-        load_cols(0);
+    // Transposing reads.  For a k-step of 16 contraction rows, half h of the wave takes rows 8h..8h+7 as two groups of 4;
+    // inside a block of 16 lanes, lane i addresses row (i/4) of the group and 4 consecutive columns 4*(i%4).
+    typedef __attribute__((ext_vector_type(8))) short short8v;
+    uint32_t rat[MT][2], rwt[2][2];                // [block][group of 4 rows]: read addresses in stage 0, + 16 rows per k-step
+    const uint32_t smem_at = (uint32_t)(uintptr_t)CHIPMUNK_LDS_PTR(smem);
 #pragma unroll
-        for (int j = 0; j < NIA + NIW; j++) issue_piece(0, 0, j);
-        load_cols(min(1, ktiles - 1));
+    for (int rd = 0; rd < 2; rd++) {
+        const int row = 8 * h + (l16 >> 2) + 4 * rd, tcol = 4 * (l16 & 3);
+#pragma unroll
+        for (int mt = 0; mt < MT; mt++) {
+            const int col = wm * (ROWS / 2) + mt * 32 + mb * 16 + tcol;
+            rat[mt][rd] = smem_at + (uint32_t)(row * RBA + ((col >> 3) ^ swizzle_at<RBA>(row)) * 16 + (col & 7) * 2);
+        }
+#pragma unroll
+        for (int nt = 0; nt < 2; nt++) {
+            const int col = wn * 64 + nt * 32 + mb * 16 + tcol;
+            rwt[nt][rd] = smem_at + (uint32_t)(AT + row * 256 + ((col >> 3) ^ swizzle_at<256>(row)) * 16 + (col & 7) * 2);
+        }
+        // opaque, so that the k-step stays in the reads' offset field
+#pragma unroll
+        for (int mt = 0; mt < MT; mt++) asm volatile("" : "+v"(rat[mt][rd]));
+#pragma unroll
+        for (int nt = 0; nt < 2; nt++) asm volatile("" : "+v"(rwt[nt][rd]));
     }
-    for (int kt = 0; kt < ktiles; kt++) {
-        const int stage = kt & 1;
+    struct Operands { bf16x8 a[2][MT], w[2][2]; };   // [k-step]
+    auto read = [&](Operands& op, uint32_t stage) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++) {
+#pragma unroll
+            for (int nt = 0; nt < 2; nt++)
+                op.w[ks][nt] = __builtin_bit_cast(bf16x8, (short8v)__builtin_shufflevector(
+                    lds_read_tr16_at(rwt[nt][0] + stage + ks * 16 * 256), lds_read_tr16_at(rwt[nt][1] + stage + ks * 16 * 256), 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++)
+                op.a[ks][mt] = __builtin_bit_cast(bf16x8, (short8v)__builtin_shufflevector(
+                    lds_read_tr16_at(rat[mt][0] + stage + ks * 16 * RBA), lds_read_tr16_at(rat[mt][1] + stage + ks * 16 * RBA), 0, 1, 2, 3, 4, 5, 6, 7));
+        }
+    };
+
+    if (!DENSE) {
+#pragma unroll
+        for (int s = 0; s < NS + 2; s++) request_slice(s);
         wait_all_memory();
-        __syncthreads();
-        // the step after this one; past the end the last step is fetched once more into the buffer nobody reads
-        const int kt_next = min(kt + 1, ktiles - 1);
-        const uint8_t* sa = smem + stage * STAGE;
-        const uint8_t* sw = sa + AT;
+        asm volatile("" ::: "memory");
+    }
 #pragma unroll
-        for (int ks = 0; ks < 4; ks++) {
-            bf16x8 bop[2];
+    for (int t = 0; t < NS; t++) {
+        if (t < steps) {
+            read_slice(t);
 #pragma unroll
-            for (int nt = 0; nt < 2; nt++) {
-                short4v part[2];
+            for (int j = 0; j < NIA + NIW; j++) request_piece(t, lds0 + t * STAGE, j);
+            if (t >= 2) request_slice(t + NS);
+        }
+    }
+    read_slice(NS);
+    if (steps >= NS) wait_vmem_at_most<(NS - 1) * G - (DENSE ? 0 : 1)>();
+    else wait_vmem_at_most<0>();
+    lds_accesses_then_barrier();
+    Operands even, odd;
+    read(even, 0);
+    // (stage numbers wrap at NS, which is no power of two: they travel with the steps)
+    uint32_t here = 0;                             // byte offset of the stage of step t
+    auto after = [&](uint32_t stage) { return stage + STAGE == NS * STAGE ? 0u : stage + STAGE; };
+    auto step = [&](auto ends_c, int t, Operands& now, Operands& next) {
+        constexpr bool ends = decltype(ends_c)::value;   // no more steps to request
+        if (!ends || steps - 2 - t >= NS - 2) wait_vmem_at_most<(NS - 2) * G>();   // step t + 1 has landed
+        else if (NS == 4 && steps - 2 - t == 1) wait_vmem_at_most<G>();
+        else wait_vmem_at_most<0>();
+        lds_accesses_then_barrier();               // for every wave; and every wave holds its operands of step t
+        const uint32_t there = after(here);
+        if (!ends || t + 1 < steps) read(next, there);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int rd = 0; rd < 2; rd++) {
-                    int row = ks * 16 + trow + 4 * rd;
-                    int col = wn * 64 + nt * 32 + mb * 16 + tcol;       // element column
-                    int c16 = (col >> 3) ^ swizzle_w2(row);
-                    part[rd] = lds_read_tr16(sw + row * 256 + c16 * 16 + (col & 7) * 2);
-                }
-                typedef __attribute__((ext_vector_type(8))) short short8v;
-                bop[nt] = __builtin_bit_cast(bf16x8, (short8v)__builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7));
-            }
+        for (int ks = 0; ks < 2; ks++)
 #pragma unroll
             for (int mt = 0; mt < MT; mt++) {
-                short4v part[2];
-#pragma unroll
-                for (int rd = 0; rd < 2; rd++) {
-                    int row = ks * 16 + trow + 4 * rd;
-                    int col = wm * (BM / 2) + mt * 32 + mb * 16 + tcol;  // token column
-                    int c16 = (col >> 3) ^ swizzle_at<BM>(row);
-                    part[rd] = lds_read_tr16(sa + row * RBA + c16 * 16 + (col & 7) * 2);
-                }
-                typedef __attribute__((ext_vector_type(8))) short short8v;
-                bf16x8 aop = __builtin_bit_cast(bf16x8, (short8v)__builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
                 for (int nt = 0; nt < 2; nt++)
-                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aop, bop[nt], acc[mt][nt], 0, 0, 0);
-                {
-                    const int slot = ks * MT + mt;
-                    if (2 * slot < NIA + NIW) issue_piece(kt_next, stage ^ 1, 2 * slot);
-                    if (2 * slot + 1 < NIA + NIW) issue_piece(kt_next, stage ^ 1, 2 * slot + 1);
+                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(now.a[ks][mt], now.w[ks][nt], acc[mt][nt], 0, 0, 0);
+                if (!ends) {
+                    constexpr int each = (NIA + NIW + 2 * MT - 1) / (2 * MT);
+#pragma unroll
+                    for (int e = 0; e < each; e++)
+                        if ((ks * MT + mt) * each + e < NIA + NIW) request_piece(t + NS, lds0 + here, (ks * MT + mt) * each + e);
                 }
             }
+        if (!ends) {
+            request_slice(t + 2 * NS);
+            read_slice(t + NS + 1);
         }
-        load_cols(min(kt + 2, ktiles - 1));   // for the transfers that the next step issues
+        here = there;
+    };
+    int t = 0;
+    for (; t + NS + 1 < steps; t += 2) {
+        step(std::false_type{}, t, even, odd);
+        step(std::false_type{}, t + 1, odd, even);
     }
-    wait_all_memory();  // the last step's transfers into the unused buffer must have landed before LDS is reused
+    if (t + NS < steps) {
+        step(std::false_type{}, t, even, odd);
+        t++;
+        even = odd;
+    }
+    for (; t < steps; t += 2) {
+        step(std::true_type{}, t, even, odd);
+        if (t + 1 < steps) step(std::true_type{}, t + 1, odd, even);
+    }
 
     // ---- epilogue: fp32 tile through LDS, one half of the token rows at a time ----
     // What is added to (the cached output, or the bias of the dense form) is requested for both halves before the
     // tile goes through LDS: the reads are in flight behind the barriers instead of one round trip per item.
     const int l32 = lane & 31;
-    constexpr int ITEMS = (BM / 2) * 32 / 256;     // 16-byte groups of four output columns per thread and half
-    static_assert((BM / 2) * 32 % 256 == 0, "the half tile must divide over the threads");
+    constexpr int ITEMS = (ROWS / 2) * 32 / 256;     // 16-byte groups of four output columns per thread and half
+    static_assert((ROWS / 2) * 32 % 256 == 0, "the half tile must divide over the threads");
     u32x2 old[2][ITEMS];
 #pragma unroll
     for (int half = 0; half < 2; half++)
@@ -571,16 +638,16 @@ __global__ __launch_bounds__(256, 2) void mlp_gemm2_kernel(Gemm2Params p) {
         for (int n = 0; n < ITEMS; n++) {
             const int item = tid + n * 256;
             const int tl = item >> 5, ch = item & 31;
-            const int tok = row0 + half * (BM / 2) + tl;
+            const int tok = row0 + half * (ROWS / 2) + tl;
             // one load per item whatever the case (a token past the end reads the last token's row, the dense form
             // without a bias reads the output buffer; neither value is used): branches here would make every
             // load wait for the one before
-            const uint16_t* src = (p.dense && p.bias)
+            const uint16_t* src = (DENSE && p.bias)
                                       ? p.bias + d0 + ch * 4
                                       : p.o + ((int64_t)b * p.N + min(tok, p.N - 1)) * p.D + d0 + ch * 4;
             old[half][n] = *reinterpret_cast<const u32x2*>(src);
         }
-    const bool add_nothing = p.dense && !p.bias;
+    const bool add_nothing = DENSE && !p.bias;
 #pragma unroll
     for (int half = 0; half < 2; half++) {
         lds_accesses_then_barrier();
@@ -618,7 +685,7 @@ __global__ __launch_bounds__(256, 2) void mlp_gemm2_kernel(Gemm2Params p) {
         for (int n = 0; n < ITEMS; n++) {
             const int item = tid + n * 256;
             const int tl = item >> 5, ch = item & 31;
-            const int tok = row0 + half * (BM / 2) + tl;
+            const int tok = row0 + half * (ROWS / 2) + tl;
             uint16_t* orow = p.o + ((int64_t)b * p.N + tok) * p.D + d0 + ch * 4;
             const u32x2 o2 = add_nothing ? u32x2{0, 0} : old[half][n];
             float o0 = bf16_bits_to_float(o2[0] & 0xffffu) + a4[n][0];
@@ -629,6 +696,20 @@ __global__ __launch_bounds__(256, 2) void mlp_gemm2_kernel(Gemm2Params p) {
             if (tok < p.N) *reinterpret_cast<u32x2*>(orow) = res;
         }
     }
+}
+
+
+template <int BM, bool DENSE>
+__global__ __launch_bounds__(256, 2) void mlp_gemm2_kernel(Gemm2Params p) {
+    if (!DENSE && p.act_t && (int)blockIdx.x >= p.tile_blocks) {
+        write_back_activations(p, (int)blockIdx.x - p.tile_blocks, BM);
+        return;
+    }
+    int unit, col_tile;
+    if (DENSE ? !xcd_tile_of_block_grouped(p.col_tiles, p.units, &unit, &col_tile)
+              : !xcd_tile_of_block(p.col_tiles, p.units, &unit, &col_tile))
+        return;
+    gemm2_rows<BM, BM, DENSE>(p, unit, 0, col_tile);
 }
 
 // Chunk means of x in split precision: mean = hi + lo with hi = bf16(mean),
@@ -722,19 +803,16 @@ static int32_t launch_gemm1(Gemm1Params p, int col_tiles, int units, hipStream_t
     return launch_status();
 }
 
-template <int BM>
+template <int BM, bool DENSE>
 static int32_t launch_gemm2(Gemm2Params p, int col_tiles, int units, hipStream_t s) {
     p.col_tiles = col_tiles;
     p.units = units;
-    constexpr int stage = kBK * BM * 2 + kBK * 256;
-    constexpr int epi = (BM / 2) * (128 * 4 + 32);
-    constexpr int lds = 2 * stage > epi ? 2 * stage : epi;
-    if (hipFuncSetAttribute((const void*)mlp_gemm2_kernel<BM>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) !=
-        hipSuccess)
+    constexpr int lds = Gemm2Shape<BM>::kLds;
+    if (hipFuncSetAttribute((const void*)mlp_gemm2_kernel<BM, DENSE>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
         return CHIPMUNK_ERR_LAUNCH;
     p.tile_blocks = xcd_grid_size(col_tiles, units);
     const int grid = p.tile_blocks + (p.act_t ? units : 0);
-    hipLaunchKernelGGL((mlp_gemm2_kernel<BM>), dim3((unsigned)grid), dim3(256), lds, s, p);
+    hipLaunchKernelGGL((mlp_gemm2_kernel<BM, DENSE>), dim3((unsigned)grid), dim3(256), lds, s, p);
     return launch_status();
 }
 
@@ -944,9 +1022,9 @@ static int32_t run_mlp_sparse_delta(const uint16_t* x, const uint16_t* w1, const
 
     Gemm2Params g2;
     g2.a_t = (const uint16_t*)ws; g2.w2 = w2; g2.bias = nullptr; g2.idx = idx; g2.counts = counts; g2.o = o_cache;
-    g2.a_ld = a_ld; g2.N = N; g2.NB = NB; g2.D = D; g2.F = F; g2.k_stride = k_stride; g2.k_pad = k_pad; g2.dense = 0;
+    g2.a_ld = a_ld; g2.N = N; g2.NB = NB; g2.D = D; g2.F = F; g2.k_stride = k_stride; g2.k_pad = k_pad;
     g2.act_t = act_t; g2.a_cache = a_cache;
-    return c == 192 ? launch_gemm2<192>(g2, D / kBN, units, s) : launch_gemm2<128>(g2, D / kBN, units, s);
+    return c == 192 ? launch_gemm2<192, false>(g2, D / kBN, units, s) : launch_gemm2<128, false>(g2, D / kBN, units, s);
 }
 
 extern "C" int32_t chipmunk_mlp_sparse_delta(const uint16_t* x, const uint16_t* w1, const uint16_t* b1,
@@ -1009,9 +1087,9 @@ extern "C" int32_t chipmunk_mlp_dense(const uint16_t* x, const uint16_t* w1, con
     }
     Gemm2Params g2;
     g2.a_t = a_cache; g2.w2 = w2; g2.bias = b2; g2.idx = nullptr; g2.counts = nullptr; g2.o = out;
-    g2.a_ld = a_ld; g2.N = N; g2.NB = NB; g2.D = D; g2.F = F; g2.k_stride = F; g2.k_pad = F; g2.dense = 1;
+    g2.a_ld = a_ld; g2.N = N; g2.NB = NB; g2.D = D; g2.F = F; g2.k_stride = F; g2.k_pad = F;
     g2.act_t = nullptr; g2.a_cache = nullptr;
-    return c == 192 ? launch_gemm2<192>(g2, D / kBN, units, s) : launch_gemm2<128>(g2, D / kBN, units, s);
+    return c == 192 ? launch_gemm2<192, true>(g2, D / kBN, units, s) : launch_gemm2<128, true>(g2, D / kBN, units, s);
 }
 
 // chunk means -> scores GEMM (-> sum of the pieces); ws holds tile_mean_bytes(..., pieces) bytes

@@ -291,3 +291,32 @@ def test_mlp_of_any_number_of_chunks(cm, oracle, B, N, D, F, c, k):
                             a_ref, o_ref, c, 1)
     assert rel_err(si.np_f32(a_cache)[..., :N], a_ref[..., :N]) <= REL_TOL
     assert rel_err(si.np_f32(out), o_ref, o_ref - o_before) <= REL_TOL
+
+
+@pytest.mark.parametrize("c", [128, 192])
+def test_mlp_second_gemm_at_the_ends_of_its_ring(cm, oracle, c):
+    """Lists of 0 to 13 steps of 32 neurons, on both sides of a step's edge, and dense contractions of 2 to 10 steps: fewer steps
+    than the ring has stages, as many, more, odd and even."""
+    counts_of = [0, 1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 224, 257, 288, 320, 400]
+    B, N, D, F, k = 1, len(counts_of) * c - 37, 256, 448, 400
+    _, x2, w1, b1, w2, _ = recipes.mlp_inputs(B, N, D, F, 32, DEV)
+    NB, a_ld = -(-N // c), -(-N // 8) * 8
+    g = si.generator(32, DEV)
+    a_cache, o_cache = si.randn_bf16((B, F, a_ld), g, 0.5), si.randn_bf16((B, N, D), g)
+    o_ref, a_ref = (si.np_f32(t).astype(np.float64) for t in (o_cache, a_cache))
+    o_before = o_ref.copy()
+    idx, _ = recipes.mlp_indices(NB, F, k, 32, DEV)
+    counts = torch.tensor(counts_of, dtype=torch.int32, device=DEV)
+    idx, counts = idx.view(B, NB, k), counts.view(B, NB)
+    ws = torch.full((cm.mlp_workspace_bytes(B, N, D, F, c, k),), 255, dtype=torch.uint8, device=DEV)   # NaN wherever nothing is written
+    cm.mlp_sparse_delta(x2, w1, b1, w2, idx, counts, a_cache, o_cache, c, 1, ws)
+    oracle.mlp_sparse_delta(si.np_f32(x2), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2), idx.cpu().numpy(), counts.cpu().numpy(),
+                            a_ref, o_ref, c, 1)
+    assert rel_err(si.np_f32(a_cache)[..., :N], a_ref[..., :N]) <= REL_TOL
+    assert rel_err(si.np_f32(o_cache), o_ref, o_ref - o_before) <= REL_TOL
+    for F in (64, 128, 192, 320):
+        x, _, w1, b1, w2, b2 = recipes.mlp_inputs(1, 333, 128, F, 33, DEV)
+        out, a = torch.empty_like(x), torch.zeros((1, F, 336), dtype=torch.bfloat16, device=DEV)
+        cm.mlp_dense(x, w1, b1, w2, b2, out, a, c, 1)
+        ref, _, _ = oracle.mlp_dense(si.np_f32(x), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2), si.np_f32(b2), c, 1, a_ld=336)
+        assert rel_err(si.np_f32(out), ref) <= REL_TOL
