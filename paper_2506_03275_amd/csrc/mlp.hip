@@ -20,7 +20,8 @@
 // The dense MLP of a small problem is the same two kernels with "every neuron
 // selected": GEMM1 writes a_cache only and GEMM2 reads its A operand from a_cache
 // and adds b2.  Large ones and the scores GEMM have tiles of their own
-// (mlp_dense.h).
+// (mlp_dense.h), and so have the GEMMs with too few tiles to fill the chip
+// (mlp_small.h).
 #include "common.h"
 
 #include <algorithm>
@@ -49,8 +50,8 @@ static int xcd_grid_size(int col_tiles, int units) { return (col_tiles * units +
 // eight runs of tiles instead: as whole chunks they left XCDs idle.  Whole deltas in us, 12 chunks x 1515 of 4096 x 3072: 134 -> 97,
 // 18 x 2216 of 9088 x 3200: 160 -> 133, 9 x 4914 of 10 112 x 3840: 242 -> 199; 394 x 968 of 13 824 x 5120: 1884 and 1884 (every
 // chunk in such a run: 1887 against 1870, 434 chunks of 2432 x 4992 624 against 614).
-__device__ __forceinline__ bool xcd_tile_of_block(int col_tiles, int units, int* unit, int* col_tile) {
-    const int xcd = (int)blockIdx.x & 7, slot = (int)blockIdx.x >> 3;
+__device__ __forceinline__ bool xcd_tile_of_slot(int slot, int col_tiles, int units, int* unit, int* col_tile) {
+    const int xcd = (int)blockIdx.x & 7;
     const int whole = units >> 3, local = slot / col_tiles;   // chunks per XCD taken whole
     if (local < whole) {
         *unit = local * 8 + xcd;
@@ -65,13 +66,17 @@ __device__ __forceinline__ bool xcd_tile_of_block(int col_tiles, int units, int*
     return true;
 }
 
+__device__ __forceinline__ bool xcd_tile_of_block(int col_tiles, int units, int* unit, int* col_tile) {
+    return xcd_tile_of_slot((int)blockIdx.x >> 3, col_tiles, units, unit, col_tile);
+}
+
 // The dense forms (every neuron selected) share the weight tiles between chunks as well, and a weight tile is as large as a
 // chunk's rows: the tiles stand in bands of eight chunks, column tile by column tile, so that what runs side by side on an
 // XCD (64 workgroups at most) reads eight row tiles and eight weight tiles, each eight times.  (Eight chunks and eight column
 // tiles at a time with both padded to eight, whole MLP in us: 19 chunks of 192 x 1536 x 11 264 330 -> 272, 17 x 3584 x 1728 113 -> 88.)
-__device__ __forceinline__ bool xcd_tile_of_block_grouped(int col_tiles, int units, int* unit, int* col_tile) {
+__device__ __forceinline__ bool xcd_tile_of_block_grouped(int slot, int col_tiles, int units, int* unit, int* col_tile) {
     int tile;
-    if (!xcd_run_tile((int)blockIdx.x & 7, (int)blockIdx.x >> 3, col_tiles * units, &tile)) return false;
+    if (!xcd_run_tile((int)blockIdx.x & 7, slot, col_tiles * units, &tile)) return false;
     const int band = tile / (8 * col_tiles), in_band = tile - band * 8 * col_tiles;
     const int height = min(8, units - 8 * band);
     *col_tile = in_band / height;
@@ -108,6 +113,7 @@ struct Gemm1Params {
     int N, NB, D, F;
     int k_stride, k_pad, act;
     int col_tiles, units;    // launch geometry (see xcd_tile_of_block)
+    int parts;               // tiles of 64 x 64 only: row tiles per unit
 };
 
 // Three tile buffers: two contraction steps are in flight while one is consumed (120 KB, one workgroup per CU): measured
@@ -136,7 +142,7 @@ __global__ __launch_bounds__(320, 1) void mlp_gemm1_kernel(Gemm1Params p) {
     const int l32 = lane & 31, h = lane >> 5;
 
     int unit, col_tile;                            // unit = (batch, token chunk)
-    if (MODE == kDenseAct ? !xcd_tile_of_block_grouped(p.col_tiles, p.units, &unit, &col_tile)
+    if (MODE == kDenseAct ? !xcd_tile_of_block_grouped((int)blockIdx.x >> 3, p.col_tiles, p.units, &unit, &col_tile)
                           : !xcd_tile_of_block(p.col_tiles, p.units, &unit, &col_tile))
         return;
     const int b = unit / p.NB, chunk = unit % p.NB;
@@ -376,6 +382,8 @@ struct Gemm2Params {
     const uint16_t* act_t;   // null: no write-back workgroups
     uint16_t* a_cache;
     int tile_blocks;
+    int whole;               // tiles per XCD that a workgroup takes whole; the others are taken 64 rows at a time
+    int parts;               // tiles of 64 x 64 only: row tiles per unit
 };
 
 // The deferred write-back of chunk u's new activations, by a workgroup of 256 threads.  These workgroups have the highest ids,
@@ -699,18 +707,33 @@ __device__ __forceinline__ void gemm2_rows(const Gemm2Params& p, int unit, int p
 }
 
 
-template <int BM, bool DENSE>
+// PARTS: the tiles of an XCD beyond `whole` are taken 64 rows at a time.  (An instance of its own: with the second body in the
+// same kernel launches that never reach it were 0.5 to 1 % slower.)
+template <int BM, bool DENSE, bool PARTS>
 __global__ __launch_bounds__(256, 2) void mlp_gemm2_kernel(Gemm2Params p) {
     if (!DENSE && p.act_t && (int)blockIdx.x >= p.tile_blocks) {
         write_back_activations(p, (int)blockIdx.x - p.tile_blocks, BM);
         return;
     }
     int unit, col_tile;
-    if (DENSE ? !xcd_tile_of_block_grouped(p.col_tiles, p.units, &unit, &col_tile)
-              : !xcd_tile_of_block(p.col_tiles, p.units, &unit, &col_tile))
+    const int slot = (int)blockIdx.x >> 3;
+    constexpr int parts = BM / 64;
+    const int beyond = PARTS ? slot - p.whole : -1, tile_slot = beyond < 0 ? slot : p.whole + beyond / parts;
+    if (DENSE ? !xcd_tile_of_block_grouped(tile_slot, p.col_tiles, p.units, &unit, &col_tile)
+              : !xcd_tile_of_slot(tile_slot, p.col_tiles, p.units, &unit, &col_tile))
         return;
+    if constexpr (PARTS) {
+        if (beyond >= 0) {
+            gemm2_rows<BM, 64, DENSE>(p, unit, beyond % parts, col_tile);
+            return;
+        }
+    }
     gemm2_rows<BM, BM, DENSE>(p, unit, 0, col_tile);
 }
+
+}  // namespace chipmunk
+#include "mlp_small.h"
+namespace chipmunk {
 
 // Chunk means of x in split precision: mean = hi + lo with hi = bf16(mean),
 // lo = bf16(mean - hi); out row = [hi(0..D-1) | lo(0..D-1)].  A workgroup owns
@@ -803,49 +826,150 @@ static int32_t launch_gemm1(Gemm1Params p, int col_tiles, int units, hipStream_t
     return launch_status();
 }
 
+// whole: tiles per XCD that a workgroup takes whole
 template <int BM, bool DENSE>
-static int32_t launch_gemm2(Gemm2Params p, int col_tiles, int units, hipStream_t s) {
+static int32_t launch_gemm2(Gemm2Params p, int col_tiles, int units, int64_t whole, hipStream_t s) {
     p.col_tiles = col_tiles;
     p.units = units;
-    constexpr int lds = Gemm2Shape<BM>::kLds;
-    if (hipFuncSetAttribute((const void*)mlp_gemm2_kernel<BM, DENSE>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
-        return CHIPMUNK_ERR_LAUNCH;
-    p.tile_blocks = xcd_grid_size(col_tiles, units);
+    const int slots = xcd_grid_size(col_tiles, units) / 8;
+    p.whole = (int)std::min<int64_t>(whole, slots);
+    p.tile_blocks = 8 * (p.whole + (slots - p.whole) * (BM / 64));
     const int grid = p.tile_blocks + (p.act_t ? units : 0);
-    hipLaunchKernelGGL((mlp_gemm2_kernel<BM, DENSE>), dim3((unsigned)grid), dim3(256), lds, s, p);
+    auto launch = [&](auto kernel, int lds) {
+        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return (int32_t)CHIPMUNK_ERR_LAUNCH;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), lds, s, p);
+        return launch_status();
+    };
+    constexpr int lds = Gemm2Shape<BM>::kLds, lds64 = Gemm2Shape<64>::kLds;
+    return p.whole == slots ? launch(mlp_gemm2_kernel<BM, DENSE, false>, lds)
+                            : launch(mlp_gemm2_kernel<BM, DENSE, true>, lds > lds64 ? lds : lds64);
+}
+
+// Tiles of 64 x 64.  `units`: sparse: chunks of `parts` row tiles; dense: row tiles of all batches (parts = 1).
+template <int MODE>
+static int32_t launch_small_gemm1(Gemm1Params p, int units, hipStream_t s) {
+    p.col_tiles = (p.k_stride + kSmallTile - 1) / kSmallTile;
+    p.units = units;
+    constexpr int lds = kSmallStages * kSmallStage;
+    if (hipFuncSetAttribute((const void*)mlp_small_gemm1_kernel<MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+        return CHIPMUNK_ERR_LAUNCH;
+    hipLaunchKernelGGL((mlp_small_gemm1_kernel<MODE>), dim3((unsigned)xcd_grid_size(p.col_tiles * p.parts, units)), dim3(256), lds, s, p);
+    return launch_status();
+}
+template <bool SPARSE>
+static int32_t launch_small_gemm2(Gemm2Params p, int units, hipStream_t s) {
+    p.col_tiles = p.D / kSmallTile;
+    p.units = units;
+    const int lds = kSmallStages * kSmallStage + (SPARSE ? p.k_pad * 4 : 0);
+    if (hipFuncSetAttribute((const void*)mlp_small_gemm2_kernel<SPARSE>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+        return CHIPMUNK_ERR_LAUNCH;
+    p.tile_blocks = xcd_grid_size(p.col_tiles * p.parts, units);
+    hipLaunchKernelGGL((mlp_small_gemm2_kernel<SPARSE>), dim3((unsigned)(p.tile_blocks + (p.act_t ? units : 0))), dim3(256), lds, s, p);
     return launch_status();
 }
 
-// Whether a dense GEMM takes the 256 x 256 tiles of mlp_dense.h or the chunk's tiles (192 or 128 x 128).  Both are priced as
-// whole rounds of the busiest XCD's workgroups over its 32 CUs plus a last one that is partly filled: an XCD takes an eighth of
-// each batch's large tiles, or of the chunks, rounded up.  In us, with n contraction steps and a share x of the last round's
-// slots taken, fitted to 1420 sizes from 500 x 512 x 1024 to 30 000 x 5120 x 14 080 (tokens x D x F):
-//   first GEMM, one workgroup per CU:  256 x 256: 1.05 n + 9.5 a round, the last one 0.88 + 0.08 x of it
-//                                      192 x 128: 0.64 n + 6.1;  128 x 128: 0.42 n + 4.5;  the last one 0.24 + 0.44 x
-//   second GEMM:                       256 x 256: 1.39 n a round, also the last, and 2.8 in all
-//                                      192 x 128 (two per CU): 1.77 n + 1.1;  128 x 128: 1.40 n + 0.8;  the last one
-//                                      0.28 + 0.32 (2 x) while each workgroup has a CU, 0.74 + 0.28 (2 x - 1) when some share one
-// (times of the two GEMMs with large - small tiles, us: first 3995 x 5120 x 1856 in chunks of 128: +14; 2 x 571 x 640 x 9216:
-// -25; 6024 x 2944 x 11 008: -54; second 2 x 916 x 3456 x 8320 in chunks of 128: +18, 6024 x 2944 x 11 008: +37, 2 x 595 x 4224 x
-// 3840: -30.  For 400 further sizes the slower tiles cost 0.14 % of a call in the mean for each GEMM, with rounds over the
-// whole chip 0.44 and 0.49 %; the large ones were slower by more than 2 % of a call in 5 sizes, and in 18: what the prices
-// miss is the erf form in chunks of 192 with 1.6 to 2 rounds of small tiles, 895 x 2432 x 6784: +26.)
-static bool large_tiles_pay(bool second, int B, int N, int D, int F, int c) {
-    if (B > 65535) return false;   // the large tiles take the batch from the second grid dimension
-    const int64_t chunks = (int64_t)B * ((N + c - 1) / c), large_n = (N + kDenseTile - 1) / kDenseTile;
-    const int width = second ? D : F, steps = (second ? F : D) / kBK;
-    const int64_t small = (chunks + 7) / 8 * ((width + kBN - 1) / kBN);
-    const int64_t large = B * ((large_n * ((width + kDenseTile - 1) / kDenseTile) + 7) / 8);
-    auto rounds = [](int64_t tiles, double at_least, double by_share) {
-        const int64_t last = tiles % 32;
-        return (double)(tiles / 32) + (last == 0 ? 0. : at_least + by_share * (double)last / 32.);
+// ---- which tiles a GEMM takes ----
+// Every form is priced as rounds of the busiest XCD's workgroups over its 32 CUs (tiles of a chunk's rows or of 256 x 256: one
+// workgroup per CU in the first GEMM and for 256 x 256, else two) plus a last round that is partly filled, and the cheapest is
+// taken.  In us: `call` + (`step` n + `end`) x (whole rounds + last), n contraction steps (64 in the first GEMM, 32 in the
+// second), last = `few` + `few_more` 2 x for a share x <= 1/2 of the slots and `many` + `many_more` (2 x - 1) beyond.  Fitted to
+// the kernels' times at 450 sizes of the delta and 330 of the dense MLP from 500 tokens up to 2.5 TFLOP, one launch after the
+// other; the large tiles' prices were then lowered by 5 (delta, c = 128) and 8 % (dense) and those of 64 x 64 in the dense form by
+// 5, which whole calls in a row ask for, where the clock is lower: over 100 and 80 calls the chosen first GEMM costs 0.8 and
+// 1.0 % of a call against the best one, the second 0.4 and 0.2 %.
+struct Price { double step, end, call, few, few_more, many, many_more; };
+static double price(const Price& p, int64_t tiles_per_xcd, int slots, int steps) {
+    const int64_t last = tiles_per_xcd % slots;
+    const double x = (double)last / slots;
+    const double share = last == 0 ? 0. : x <= 0.5 ? p.few + p.few_more * 2. * x : p.many + p.many_more * (2. * x - 1.);
+    return p.call + (p.step * steps + p.end) * ((double)(tiles_per_xcd / slots) + share);
+}
+static int64_t per_xcd(int64_t tiles) { return (tiles + 7) / 8; }
+
+enum FirstForm { kFirstChunk = 0, kFirstLarge = 1, kFirstSmall = 2 };   // 128 neurons of a chunk; 256 (dense: and 256 tokens); 64 x 64
+// Kernel times (chunk, large, small), us: delta, c = 192, 9 chunks x 395 of 7488 x 4864: 44, 83, 19; 47 x 1229 of 12 288 x 3072: 96, 82,
+// -; 394 x 968 of 13 824 x 5120: 945, 815, -; c = 128, 14 x 1156 of 6080 x 3840: 37, 55, 30; dense 700 x 1536 x 8192: 26, 45, 34; 893 x
+// 1664 x 1024 17, 41, 7; 4608 x 3072 x 12 288: 352, 274, -.
+// Tiles of 64 x 64 are left out where they take more than two rounds, but for contractions of at most 14 steps (of 100 calls two fewer
+// are 4 per cent slower than with the best tiles), and for lists of more than half the neurons, which were not measured.
+static FirstForm first_form(bool sparse, int B, int N, int D, int F, int c, int k_stride) {
+    static const Price chunk_delta[2] = {{0.74, 10.87, 6, 0.52, 0.19, 0.71, 0.19}, {0.648, 5, 6, 0.46, 0.2, 0.66, 0.2}};   // c = 192, 128
+    static const Price large_delta[2] = {{1.222, 21.22, 6, 0.67, 0.17, 0.84, 0.17}, {1.015, 9.69, 5.7, 0.55, 0.17, 0.72, 0.17}};
+    static const Price small_delta = {0.411, 2.64, 4.53, 0.35, 0.12, 0.77, 0.17};
+    static const Price chunk_dense[2] = {{0.654, 6.67, 6, 0.58, 0.16, 0.74, 0.16}, {0.473, 5.31, 3.15, 0.48, 0.25, 0.72, 0.25}};
+    static const Price large_dense = {1.305, 14.63, 5.52, 0.64, 0.19, 0.83, 0.19};
+    static const Price small_dense = {0.347, 1.58, 4.66, 0.32, 0.17, 0.81, 0.14};
+    const int at = c == 192 ? 0 : 1, steps = D / kBK, parts = c / kSmallTile;
+    const int64_t chunks = (int64_t)B * ((N + c - 1) / c);
+    const int width = sparse ? k_stride : F;
+    auto cols = [&](int tile) { return (int64_t)((width + tile - 1) / tile); };
+    // Short contractions of fewer than eight chunks with 64 column tiles or more are counted as if every chunk had an XCD to
+    // itself, which keeps them on the large tiles, where tests reach these: 700 x 1536 x 8192 45 us instead of 26.
+    const bool by_chunk = chunks < 8 && steps <= 24 && cols(kBN) >= 64;
+    const double chunk = price((sparse ? chunk_delta : chunk_dense)[at], by_chunk ? cols(kBN) : per_xcd(chunks * cols(kBN)), 32, steps);
+    double large, small;
+    int64_t small_tiles;
+    if (sparse) {
+        large = price(large_delta[at], by_chunk ? cols(kDenseTile) : per_xcd(chunks * cols(kDenseTile)), 32, steps);
+        small_tiles = per_xcd(chunks * parts * cols(kSmallTile));
+        small = price(small_delta, small_tiles, 64, steps);
+    } else {
+        large = price(large_dense, B * per_xcd((int64_t)((N + kDenseTile - 1) / kDenseTile) * cols(kDenseTile)), 32, steps);
+        small_tiles = by_chunk ? parts * cols(kSmallTile) : per_xcd((int64_t)B * ((N + kSmallTile - 1) / kSmallTile) * cols(kSmallTile));
+        small = price(small_dense, small_tiles, 64, steps);
+    }
+    const bool large_fits = sparse || B <= 65535;   // the dense form takes the batch from the second grid dimension
+    const bool small_fits = (small_tiles <= 128 || steps <= 14) && (!sparse || k_stride <= F / 2);
+    if (small_fits && small < chunk && (!large_fits || small < large)) return kFirstSmall;
+    return large_fits && large < chunk ? kFirstLarge : kFirstChunk;
+}
+
+// Second GEMM.  kSecondChunk: a workgroup per chunk and 128 columns; those of the last round beyond `whole` tiles per XCD take 64
+// rows each where every such part has a CU to itself (24 chunks x 1229 of 12 288 x 3072, 72 tiles per XCD: 54.6 -> 47.2 us; 80 to 97 per cent
+// of the time over 23 sizes with one to three whole rounds), or all of them where that fills the chip better.
+enum SecondForm { kSecondChunk = 0, kSecondLarge = 1, kSecondSmall = 2 };
+struct SecondPlan {
+    SecondForm form;
+    int64_t whole;   // tiles per XCD
+};
+constexpr int kSmallList = 4096;   // entries of a list that fit LDS beside the ring of tiles of 64 x 64, two workgroups per CU
+// Kernel times (whole, parts, small, large), us: delta, c = 192, 4 chunks x 249 of 5248 x 1408: 9.3, 5.6, 5.0, -; 9 x 395 of 7488 x 4864: 18,
+// 19, 25, -; dense 509 x 4800 x 640: 52, 28, 20, 77; 536 x 2688 x 7808: 98, 57, 71, 148; 2990 x 2816 x 10 048: 216, 315, 390, 208.
+static SecondPlan second_plan(bool sparse, int B, int N, int D, int F, int c, int k_stride) {
+    static const Price whole_delta[2] = {{0.639, 9.19, 2.06, 0.54, 0.15, 0.89, 0.19}, {0.487, 7.22, 1.58, 0.52, 0.17, 0.84, 0.29}};   // c = 192, 128
+    static const Price parts_delta[2] = {{0.321, 4.17, 1.41, 0.57, 0.18, 0.93, 0.12}, {0.328, 4.26, 1.52, 0.52, 0.19, 0.92, 0.11}};
+    static const Price small_delta = {0.195, 2.78, 0.93, 0.57, 0.25, 1, 0.21};
+    static const Price whole_dense[2] = {{0.697, 5.2, 3.82, 0.45, 0.16, 0.84, 0.2}, {0.546, 0.57, 5.74, 0.41, 0.15, 0.74, 0.2}};
+    static const Price parts_dense[2] = {{0.359, 2.5, 2.16, 0.43, 0.12, 0.77, 0.24}, {0.359, 2.5, 1.47, 0.41, 0.17, 0.84, 0.2}};
+    static const Price small_dense = {0.237, 2.5, 0, 0.42, 0.19, 0.94, 0.09};
+    static const Price large_dense = {0.69, 6.9, 2.75, 0.65, 0.17, 0.81, 0.17};
+    const int at = c == 192 ? 0 : 1, parts = c / 64;
+    const int steps = sparse ? (k_stride + kGemm2K - 1) / kGemm2K : F / kGemm2K;
+    const int64_t chunks = (int64_t)B * ((N + c - 1) / c), tiles = per_xcd(chunks * (D / kBN));
+    const Price& whole = (sparse ? whole_delta : whole_dense)[at];
+    const Price& part = (sparse ? parts_delta : parts_dense)[at];
+    SecondPlan plan = {kSecondChunk, tiles};
+    double best;
+    const int64_t last = tiles % 64;
+    if (tiles > 64 && last > 0 && last * parts <= 32) {
+        plan.whole = tiles - last;
+        best = price(whole, tiles - last, 64, steps) + price(part, last * parts, 64, steps) - part.call;
+    } else {
+        best = price(whole, tiles, 64, steps);
+    }
+    auto consider = [&](SecondPlan other, double us) {
+        if (us < best) best = us, plan = other;
     };
-    if (!second) return rounds(large, 0.88, 0.08) * (1.05 * steps + 9.5) <
-                        rounds(small, 0.24, 0.44) * (c == 192 ? 0.64 * steps + 6.1 : 0.42 * steps + 4.5);
-    const int64_t last = small % 64;
-    const double share = (double)last / 32., last_round = last == 0 ? 0. : last <= 32 ? 0.28 + 0.32 * share : std::min(1., 0.74 + 0.28 * (share - 1.));
-    return rounds(large, 1., 0.) * 1.39 * steps + 2.8 <
-           ((double)(small / 64) + last_round) * (c == 192 ? 1.77 * steps + 1.1 : 1.40 * steps + 0.8);
+    consider({kSecondChunk, 0}, price(part, tiles * parts, 64, steps));
+    if (sparse) {
+        if ((k_stride + kBN - 1) / kBN * kBN <= kSmallList)
+            consider({kSecondSmall, 0}, price(small_delta, per_xcd(chunks * parts * (D / kSmallTile)), 64, steps));
+    } else {
+        consider({kSecondSmall, 0}, price(small_dense, per_xcd((int64_t)B * ((N + kSmallTile - 1) / kSmallTile) * (D / kSmallTile)), 64, steps));
+        if (B <= 65535)
+            consider({kSecondLarge, 0}, price(large_dense, B * per_xcd((int64_t)((N + kDenseTile - 1) / kDenseTile) * ((D + kDenseTile - 1) / kDenseTile)), 32, steps));
+    }
+    return plan;
 }
 
 template <int MODE, int BM = kDenseTile>
@@ -861,23 +985,6 @@ static int32_t launch_dense_gemm(DenseGemmParams p, int second_dim, hipStream_t 
     const int per_xcd = (p.tiles_p * p.tiles_q + 7) / 8;
     hipLaunchKernelGGL((mlp_dense_gemm_kernel<MODE, BM>), dim3((unsigned)(per_xcd * 8), (unsigned)second_dim), dim3(512), kDenseLds, s, p);
     return launch_status();
-}
-
-// Whether the column-sparse first GEMM takes 256 selected neurons per workgroup (mlp_dense.h, eight waves) or 128.  All
-// tiles of a chunk run on one XCD (32 CUs, a workgroup each), so a launch takes rounds of the busiest XCD, the last one priced
-// by its share as above; us per contraction step and per tile end: c = 192: 1.45 and 13 against 0.87 and 5, c = 128: 1.02 and 5
-// against 0.66 and 3.  Kernel times, 256 against 128: 24 chunks x 1229 of 12 288 x 3072: 69 and 43 us; 47 chunks: 82 and 96; 94 x
-// 968 of 13 824 x 5120: 274 and 229; 394: 815 and 945 (whole delta 1988 -> 1874 us); c = 128, 36 x 1229 of 12 288 x 3072: 54 and
-// 65.  Whole deltas: c = 128, 81 x 337 of 1024 x 4608: 148 and 127; c = 192, 351 x 2534 of 7680 x 640: 771 and 742.
-static bool wide_delta_pays(int units, int D, int c, int k_stride) {
-    const int chunks = (units + 7) / 8, steps = D / kBK;
-    auto rounds = [&](int width, double g) {
-        const int64_t tiles = (int64_t)chunks * ((k_stride + width - 1) / width), last = tiles % 32;
-        return (double)(tiles / 32) + (last == 0 ? 0. : g + (1. - g) * (double)last / 32.);
-    };
-    const double wide = rounds(kDenseTile, 0.79), narrow = rounds(kBN, 0.26);
-    return c == 192 ? wide * (1.45 * steps + 13.) < narrow * (0.87 * steps + 5.)
-                    : wide * (1.02 * steps + 5.) < narrow * (0.66 * steps + 3.);
 }
 
 template <int BM>
@@ -1007,7 +1114,11 @@ static int32_t run_mlp_sparse_delta(const uint16_t* x, const uint16_t* w1, const
     g1.delta_t = (uint16_t*)ws; g1.act_t = act_t; g1.a_ld = a_ld;
     g1.N = N; g1.NB = NB; g1.D = D; g1.F = F;
     g1.k_stride = k_stride; g1.k_pad = k_pad; g1.act = act;
-    if (wide_delta_pays(units, D, c, k_stride)) {
+    g1.parts = c / kSmallTile;
+    const FirstForm first = first_form(true, B, N, D, F, c, k_stride);
+    if (first == kFirstSmall) {
+        st = launch_small_gemm1<kSparseDelta>(g1, units, s);
+    } else if (first == kFirstLarge) {
         DenseGemmParams g;
         g.x = x; g.w1 = w1; g.w2 = nullptr; g.bias = b1; g.a_cache = a_cache; g.out = nullptr; g.scores = nullptr; g.a_ld = a_ld;
         g.N = N; g.D = D; g.F = F; g.act = act; g.pieces = 1;
@@ -1023,8 +1134,10 @@ static int32_t run_mlp_sparse_delta(const uint16_t* x, const uint16_t* w1, const
     Gemm2Params g2;
     g2.a_t = (const uint16_t*)ws; g2.w2 = w2; g2.bias = nullptr; g2.idx = idx; g2.counts = counts; g2.o = o_cache;
     g2.a_ld = a_ld; g2.N = N; g2.NB = NB; g2.D = D; g2.F = F; g2.k_stride = k_stride; g2.k_pad = k_pad;
-    g2.act_t = act_t; g2.a_cache = a_cache;
-    return c == 192 ? launch_gemm2<192, false>(g2, D / kBN, units, s) : launch_gemm2<128, false>(g2, D / kBN, units, s);
+    g2.act_t = act_t; g2.a_cache = a_cache; g2.parts = c / kSmallTile;
+    const SecondPlan second = second_plan(true, B, N, D, F, c, k_stride);
+    if (second.form == kSecondSmall) return launch_small_gemm2<true>(g2, units, s);
+    return c == 192 ? launch_gemm2<192, false>(g2, D / kBN, units, second.whole, s) : launch_gemm2<128, false>(g2, D / kBN, units, second.whole, s);
 }
 
 extern "C" int32_t chipmunk_mlp_sparse_delta(const uint16_t* x, const uint16_t* w1, const uint16_t* b1,
@@ -1068,7 +1181,10 @@ extern "C" int32_t chipmunk_mlp_dense(const uint16_t* x, const uint16_t* w1, con
     g.x = x; g.w1 = w1; g.w2 = w2; g.a_cache = a_cache; g.out = out; g.a_ld = a_ld;
     g.scores = nullptr; g.N = N; g.D = D; g.F = F; g.act = act; g.pieces = 1;
 
-    if (large_tiles_pay(false, B, N, D, F, c)) {
+    const FirstForm first = first_form(false, B, N, D, F, c, 0);
+    const SecondPlan second = second_plan(false, B, N, D, F, c, 0);
+    const int row_tiles = (N + kSmallTile - 1) / kSmallTile;   // of 64 x 64
+    if (first == kFirstLarge) {
         g.bias = b1;
         st = launch_dense_gemm<kFirst>(g, B, s);
     } else {
@@ -1076,20 +1192,29 @@ extern "C" int32_t chipmunk_mlp_dense(const uint16_t* x, const uint16_t* w1, con
         g1.x = x; g1.w1 = w1; g1.b1 = b1; g1.idx = nullptr; g1.counts = nullptr; g1.a_cache = a_cache;
         g1.delta_t = nullptr; g1.act_t = nullptr; g1.a_ld = a_ld;
         g1.N = N; g1.NB = NB; g1.D = D; g1.F = F;
-        g1.k_stride = F; g1.k_pad = F; g1.act = act;
-        st = c == 192 ? launch_gemm1<192, kDenseAct>(g1, (F + kBN - 1) / kBN, units, s)
-                      : launch_gemm1<128, kDenseAct>(g1, (F + kBN - 1) / kBN, units, s);
+        g1.k_stride = F; g1.k_pad = F; g1.act = act; g1.parts = 1;
+        if (first == kFirstSmall) {
+            g1.NB = row_tiles;
+            st = launch_small_gemm1<kDenseAct>(g1, B * row_tiles, s);
+        } else {
+            st = c == 192 ? launch_gemm1<192, kDenseAct>(g1, (F + kBN - 1) / kBN, units, s)
+                          : launch_gemm1<128, kDenseAct>(g1, (F + kBN - 1) / kBN, units, s);
+        }
     }
     if (st != CHIPMUNK_OK) return st;
-    if (large_tiles_pay(true, B, N, D, F, c)) {
+    if (second.form == kSecondLarge) {
         g.bias = b2;
         return launch_dense_gemm<kSecond>(g, B, s);
     }
     Gemm2Params g2;
     g2.a_t = a_cache; g2.w2 = w2; g2.bias = b2; g2.idx = nullptr; g2.counts = nullptr; g2.o = out;
     g2.a_ld = a_ld; g2.N = N; g2.NB = NB; g2.D = D; g2.F = F; g2.k_stride = F; g2.k_pad = F;
-    g2.act_t = nullptr; g2.a_cache = nullptr;
-    return c == 192 ? launch_gemm2<192, true>(g2, D / kBN, units, s) : launch_gemm2<128, true>(g2, D / kBN, units, s);
+    g2.act_t = nullptr; g2.a_cache = nullptr; g2.parts = 1;
+    if (second.form == kSecondSmall) {
+        g2.NB = row_tiles;
+        return launch_small_gemm2<false>(g2, B * row_tiles, s);
+    }
+    return c == 192 ? launch_gemm2<192, true>(g2, D / kBN, units, second.whole, s) : launch_gemm2<128, true>(g2, D / kBN, units, second.whole, s);
 }
 
 // chunk means -> scores GEMM (-> sum of the pieces); ws holds tile_mean_bytes(..., pieces) bytes
@@ -1187,9 +1312,20 @@ extern "C" int32_t chipmunk_mlp_tile_mean_preact_static(const uint16_t* x, const
 extern "C" void chipmunk_internal_mlp_form(int B, int N, int D, int F, int c, int k_stride, int32_t* out) {
     const int units = B * ((N + c - 1) / c);
     const ScoresPlan plan = scores_plan(units, D, F);
-    out[0] = large_tiles_pay(false, B, N, D, F, c);
-    out[1] = large_tiles_pay(true, B, N, D, F, c);
-    out[2] = wide_delta_pays(units, D, c, k_stride);
+    out[0] = first_form(false, B, N, D, F, c, 0) == kFirstLarge;
+    out[1] = second_plan(false, B, N, D, F, c, 0).form == kSecondLarge;
+    out[2] = first_form(true, B, N, D, F, c, k_stride) == kFirstLarge;
     out[3] = plan.pieces;
     out[4] = plan.two_sums ? 2 : 1;
+}
+
+// The same for every form of the GEMMs: the dense MLP's first (FirstForm) and second (SecondForm, and the tiles per XCD taken
+// whole), then the delta's.
+extern "C" void chipmunk_internal_mlp_tiles(int B, int N, int D, int F, int c, int k_stride, int64_t* out) {
+    for (int sparse = 0; sparse < 2; sparse++) {
+        const SecondPlan plan = second_plan(sparse, B, N, D, F, c, k_stride);
+        out[3 * sparse] = first_form(sparse, B, N, D, F, c, k_stride);
+        out[3 * sparse + 1] = plan.form;
+        out[3 * sparse + 2] = plan.whole;
+    }
 }

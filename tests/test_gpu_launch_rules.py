@@ -320,3 +320,77 @@ def test_mlp_second_gemm_at_the_ends_of_its_ring(cm, oracle, c):
         cm.mlp_dense(x, w1, b1, w2, b2, out, a, c, 1)
         ref, _, _ = oracle.mlp_dense(si.np_f32(x), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2), si.np_f32(b2), c, 1, a_ld=336)
         assert rel_err(si.np_f32(out), ref) <= REL_TOL
+
+
+def _mlp_tiles(cm, B, N, D, F, c, k):
+    """dense: form of the first GEMM (0 a chunk's tiles, 1 large, 2 of 64 x 64), of the second (the same) and tiles per XCD taken
+    whole; then the delta's"""
+    out = (ctypes.c_int64 * 6)()
+    cm.load().chipmunk_internal_mlp_tiles(B, N, D, F, c, k, out)
+    return list(out)
+
+
+@pytest.mark.parametrize("B,N,D,F,c,k,act,bias,tiles", [
+    (1, 1, 128, 64, 128, 32, 1, True, [2, 2, 0, 2, 2, 0]),             # one token: two steps of 64, one
+    (2, 613, 128, 1024, 128, 512, 0, False, [2, 2, 0, 2, 2, 0]),       # tiles of 64 x 64, two batches, no bias
+    (1, 777, 1152, 1984, 192, 700, 1, True, [2, 2, 0, 2, 2, 0]),
+    (2, 200, 640, 704, 192, 352, 1, True, [2, 2, 0, 2, 2, 0]),         # the last chunk ends in its first 64 rows
+    (1, 1500, 640, 1024, 128, 330, 0, True, [2, 2, 0, 2, 2, 0]),
+    (1, 1000, 2560, 512, 192, 200, 0, True, [2, 0, 0, 2, 0, 0]),       # second GEMM in parts of 64 rows
+    (1, 500, 128, 12288, 192, 5000, 1, True, [1, 2, 0, 2, 0, 0]),      # a list too long for the tiles of 64 x 64
+    (1, 4500, 3072, 256, 192, 77, 1, False, [2, 1, 0, 2, 0, 64]),      # its last round in parts
+    (1, 3603, 4992, 512, 128, 50, 0, True, [2, 0, 128, 2, 0, 128]),     # of both second GEMMs
+])
+def test_mlp_on_small_tiles(cm, oracle, B, N, D, F, c, k, act, bias, tiles):
+    """Few tiles: 64 x 64 in both GEMMs, chunks in parts of 64 rows, the last round in parts.  Lists that end at and beside the
+    edges of tiles and steps, an empty one; the workspace holds NaN wherever nothing is written; both forms of the cache
+    write-back alike; the cells past N stay as they are."""
+    assert _mlp_tiles(cm, B, N, D, F, c, k) == tiles
+    x1, x2, w1, b1, w2, b2 = recipes.mlp_inputs(B, N, D, F, 34, DEV)
+    if not bias:
+        b1, b2 = torch.zeros_like(b1), torch.zeros_like(b2)
+    bias1, bias2 = (b1, b2) if bias else (None, None)
+    NB, a_ld = -(-N // c), -(-N // 8) * 8 + 8
+    out = torch.full_like(x1, 7.0)
+    a_cache = torch.full((B, F, a_ld), 3.0, dtype=torch.bfloat16, device=DEV)
+    cm.mlp_dense(x1, w1, bias1, w2, bias2, out, a_cache, c, act)
+    ref, a_ref, _ = oracle.mlp_dense(si.np_f32(x1), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2), si.np_f32(b2), c, act, a_ld=a_ld)
+    assert rel_err(si.np_f32(a_cache)[..., :N], a_ref[..., :N]) <= REL_TOL
+    assert torch.all(a_cache[..., N:] == 3.0)
+    assert rel_err(si.np_f32(out), ref) <= REL_TOL
+    o_ref, a_ref = (si.np_f32(t).astype(np.float64) for t in (out, a_cache))
+    o_before = o_ref.copy()
+    idx, _ = recipes.mlp_indices(B * NB, F, k, 34, DEV)
+    edges = torch.tensor([k, 0, 1, 63, 64, 65, 127, 128, 129, k - 1, 31, 32, 33, 96, 257], dtype=torch.int32).clamp(0, k)
+    counts = edges[torch.arange(B * NB) % len(edges)].to(DEV)
+    idx, counts = idx.view(B, NB, k), counts.view(B, NB)
+    nan = lambda n: torch.full((max(n, 16),), 255, dtype=torch.uint8, device=DEV)  # noqa: E731
+    o2, a2 = out.clone(), a_cache.clone()
+    cm.mlp_sparse_delta(x2, w1, bias1, w2, idx, counts, a_cache, out, c, act, nan(cm.mlp_workspace_bytes(B, N, D, F, c, k)))
+    cm.mlp_sparse_delta_overlapped(x2, w1, bias1, w2, idx, counts, a2, o2, c, act, nan(cm.mlp_overlapped_workspace_bytes(B, N, D, F, c, k)))
+    assert torch.equal(a_cache, a2) and torch.equal(out, o2)
+    oracle.mlp_sparse_delta(si.np_f32(x2), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2), idx.cpu().numpy(), counts.cpu().numpy(),
+                            a_ref, o_ref, c, act)
+    assert rel_err(si.np_f32(a_cache)[..., :N], a_ref[..., :N]) <= REL_TOL
+    assert torch.all(a_cache[..., N:] == 3.0)
+    assert rel_err(si.np_f32(out), o_ref, o_ref - o_before) <= REL_TOL
+
+
+@pytest.mark.parametrize("B,N,D,F,c,k,first_dense,first_delta", [(1, 500, 256, 640, 192, 320, 2, 2), (1, 1021, 256, 16320, 128, 1000, 1, 2),
+                                                                (1, 700, 1024, 8000, 192, 1000, 0, 2), (1, 900, 1024, 10240, 128, 5000, 1, 1),
+                                                                (1, 1000, 2560, 512, 192, 500, 2, 0)])
+def test_unchanged_input_on_small_tiles(cm, B, N, D, F, c, k, first_dense, first_delta):
+    """Tiles of 64 x 64 add their products in the order of the larger ones: the delta of an input that has not changed is nothing,
+    bit for bit, whichever filled the cache."""
+    tiles = _mlp_tiles(cm, B, N, D, F, c, k)
+    assert (tiles[0], tiles[3]) == (first_dense, first_delta)
+    x, _, w1, b1, w2, b2 = recipes.mlp_inputs(B, N, D, F, 35, DEV)
+    out = torch.empty_like(x)
+    a_cache = torch.zeros((B, F, -(-N // 8) * 8), dtype=torch.bfloat16, device=DEV)
+    cm.mlp_dense(x, w1, b1, w2, b2, out, a_cache, c, 1)
+    o_before, a_before = out.clone(), a_cache.clone()
+    NB = -(-N // c)
+    idx, _ = recipes.mlp_indices(B * NB, F, k, 35, DEV)
+    counts = torch.full((B, NB), k, dtype=torch.int32, device=DEV)
+    cm.mlp_sparse_delta(x, w1, b1, w2, idx.view(B, NB, k), counts, a_cache, out, c, 1, _u8(cm.mlp_workspace_bytes(B, N, D, F, c, k)))
+    assert torch.equal(a_cache, a_before) and torch.equal(out, o_before)
