@@ -187,15 +187,29 @@ __device__ __forceinline__ float dpp_f32(float x) {  // x of the lane that the D
 // the row (the wave's 16 queries of a block) and writes them to part[32] in tile key order.  Halving exchange:
 // at each step a lane keeps half of its values and hands the other half to a partner that keeps those, so 8 adds
 // stand in for 32.  Partners: lane ^ 15, ^ 7, ^ 3, ^ 1; the value a lane ends with is 4 bit3 + 2 bit2 + bit1.
-__device__ __forceinline__ void row16_sums_to_lds(const float (&acc)[8], float* part, int g, int l16) {
-    const bool b3 = l16 & 8, b2 = l16 & 4, b1 = l16 & 2;
-    float x[4], y[2];
-#pragma unroll
-    for (int i = 0; i < 4; i++) x[i] = (b3 ? acc[i + 4] : acc[i]) + dpp_f32<0x140>(b3 ? acc[i] : acc[i + 4]);  // row_mirror
-#pragma unroll
-    for (int i = 0; i < 2; i++) y[i] = (b2 ? x[i + 2] : x[i]) + dpp_f32<0x141>(b2 ? x[i] : x[i + 2]);          // row_half_mirror
-    float z = (b1 ? y[1] : y[0]) + dpp_f32<0x1b>(b1 ? y[0] : y[1]);                                              // quad_perm 3,2,1,0
-    z += dpp_f32<0xb1>(z);                                                                                       // quad_perm 1,0,3,2
+// In the first two steps the lanes that keep the other half are whole banks of four, so a second add with a bank mask takes
+// the place of the two selects: 16 instructions instead of 22 (40 heads x 18 000 with column sums 5673 -> 5602 us, the same
+// sums).  A DPP operand must not have been written by the two instructions before: the order below keeps them apart, and the nop
+// what the compiler puts in front, because it does not look inside.
+__device__ __forceinline__ void row16_sums_to_lds(float (&x)[8], float* part, int g, int l16) {
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %2, %2 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %3, %3, %3 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %4, %4 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %1, %5, %5 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %2, %6, %6 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %3, %7, %7 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %1, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa"
+        : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3])
+        : "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]));
+    const bool b1 = l16 & 2;
+    float z = (b1 ? x[1] : x[0]) + dpp_f32<0x1b>(b1 ? x[0] : x[1]);   // quad_perm 3,2,1,0
+    z += dpp_f32<0xb1>(z);                                             // quad_perm 1,0,3,2
     if (!(l16 & 1)) part[(l16 & 8 ? 16 : 0) + 4 * g + ((l16 >> 1) & 3)] = z;
 }
 
