@@ -2,19 +2,38 @@
 //
 // The permutation has a closed form, so no index table is read: every wave
 // computes the source (or destination) row of its token from the grid geometry
-// and moves the row with 128-bit (or 32-bit) accesses.  The copy touches each
+// and moves the row with 128-bit (or 32-bit) accesses, five of them in flight.  The copy touches each
 // byte once on the way in and once on the way out: it is bound by HBM.
 #include "common.h"
 
 namespace chipmunk {
 
+// n / d for 0 <= n < 2^31 as (mulhi(n, m) + n) >> s with s = ceil(log2 d), m = floor(2^32 (2^s - d) / d) + 1 (Granlund and
+// Montgomery, "Division by invariant integers using multiplication"): three instructions where the compiler's division by a
+// run-time number takes about twenty, ten times over before a wave can ask for its row.
+struct Divisor {
+    uint32_t d, m, s;
+    explicit Divisor(int64_t value) : d((uint32_t)(value > 1 ? value : 1)), s(0) {
+        while (s < 31 && (1u << s) < d) s++;
+        m = (uint32_t)(((((uint64_t)1 << s) - d) << 32) / d) + 1u;
+    }
+    __device__ __forceinline__ int div(int n) const { return (int)((__umulhi((uint32_t)n, m) + (uint32_t)n) >> s); }
+    __device__ __forceinline__ int div_mod(int n, int* rest) const {
+        const int q = div(n);
+        *rest = n - q * (int)d;
+        return q;
+    }
+};
+
 struct VoxelGeom {
-    int n_prefix, T, H, W, n_suffix;
+    int n_prefix, H, W;
     int vt, vh, vw;
     int Tf, Hf, Wf;   // extent covered by full voxels in each dimension
     int n_full;       // tokens inside full voxels
     int grid;         // T*H*W
     int N;
+    // divisors that a grid without full voxels, or without a remainder, does not reach stand at 1
+    Divisor volume, voxels_w, voxels_h, by_vh, by_vw, edge_w, frame_rest, by_w, by_hw, by_n;
 };
 
 // position before the reorder of the token that sits at position i after it
@@ -24,11 +43,9 @@ __device__ __forceinline__ int voxel_old_position(const VoxelGeom& g, int i) {
     if (j >= g.grid) return i;  // suffix
     int t, h, w;
     if (j < g.n_full) {
-        int vol = g.vt * g.vh * g.vw;
-        int v = j / vol, r = j - v * vol;
-        int wc_n = g.Wf / g.vw, hc_n = g.Hf / g.vh;
-        int wc = v % wc_n, hc = (v / wc_n) % hc_n, tc = v / (wc_n * hc_n);
-        int dw = r % g.vw, dh = (r / g.vw) % g.vh, dt = r / (g.vw * g.vh);
+        int r, wc, hc, dh, dw;
+        const int tc = g.voxels_h.div_mod(g.voxels_w.div_mod(g.volume.div_mod(j, &r), &wc), &hc);
+        const int dt = g.by_vh.div_mod(g.by_vw.div_mod(r, &dw), &dh);
         t = tc * g.vt + dt;
         h = hc * g.vh + dh;
         w = wc * g.vw + dw;
@@ -39,23 +56,18 @@ __device__ __forceinline__ int voxel_old_position(const VoxelGeom& g, int i) {
         int edge = g.Hf * (g.W - g.Wf);
         int per_frame = edge + (g.H - g.Hf) * g.W;
         int in_frames = g.Tf * per_frame;
+        int r;
         if (rho < in_frames) {
-            t = rho / per_frame;
-            int r = rho - t * per_frame;
+            t = g.frame_rest.div_mod(rho, &r);
             if (r < edge) {
-                h = r / (g.W - g.Wf);
-                w = g.Wf + (r - h * (g.W - g.Wf));
+                h = g.edge_w.div_mod(r, &w);
+                w += g.Wf;
             } else {
-                r -= edge;
-                h = g.Hf + r / g.W;
-                w = r % g.W;
+                h = g.Hf + g.by_w.div_mod(r - edge, &w);
             }
         } else {
-            int r = rho - in_frames;
-            t = g.Tf + r / (g.H * g.W);
-            r = r % (g.H * g.W);
-            h = r / g.W;
-            w = r % g.W;
+            t = g.Tf + g.by_hw.div_mod(rho - in_frames, &r);
+            h = g.by_w.div_mod(r, &w);
         }
     }
     return g.n_prefix + (t * g.H + h) * g.W + w;
@@ -69,23 +81,44 @@ __global__ __launch_bounds__(256) void voxel_perm_kernel(VoxelGeom g, int32_t* p
     if (inv_perm) inv_perm[old] = i;
 }
 
-// One wave moves one row at a time.  VEC is uint4 (16-byte words) or uint32_t.
-template <typename VEC>
-__global__ __launch_bounds__(256) void voxel_copy_kernel(VoxelGeom g, const VEC* __restrict__ src,
-                                                         VEC* __restrict__ dst, int64_t total_rows,
-                                                         int words_per_row, int inverse) {
+// One wave per row; the waves of the first batch also write the permutation, which would be a launch of its own.  VEC is
+// u32x4 (16-byte words) or uint32_t.  STREAM: loads and stores past the caches' usual order of replacement, for a source and a
+// destination that do not fit the last-level cache (256 MB) together.  us before (one word per lane at a time, the permutation
+// by a kernel of its own, plain divisions), now, and with the other choice of STREAM: 7 MB 9.8, 7.4, 7.4; 25 MB 12.1, 9.6, 10.8; 69
+// MB 30.3, 27.7, 24.9; 290 MB 108, 94.6, 109; 774 MB 293, 259.5 (6.0 TB/s), 285.  From the writer of the source to a reader of the
+// destination: 25 MB 36.3, 33.3, 35.4; 184 MB 179, 155, 174; 774 MB 721, 655, 722.
+template <typename VEC, bool STREAM>
+__global__ __launch_bounds__(256) void voxel_copy_kernel(VoxelGeom g, const VEC* __restrict__ src, VEC* __restrict__ dst, int64_t total_rows,
+                                                         int words_per_row, int inverse, int32_t* __restrict__ perm,
+                                                         int32_t* __restrict__ inv_perm) {
+    constexpr int U = 5;
     const int lane = threadIdx.x & 63;
-    const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t nwaves = (int64_t)gridDim.x * 4;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t wave = (int64_t)blockIdx.x * 4 + w, nwaves = (int64_t)gridDim.x * 4;
     for (int64_t row = wave; row < total_rows; row += nwaves) {
-        int b = (int)(row / g.N);
-        int i = (int)(row - (int64_t)b * g.N);
-        int old = voxel_old_position(g, i);
-        int64_t from = (int64_t)b * g.N + (inverse ? i : old);
-        int64_t to = (int64_t)b * g.N + (inverse ? old : i);
+        const int b = total_rows <= 0x7fffffff ? g.by_n.div((int)row) : (int)(row / g.N);
+        const int i = (int)(row - (int64_t)b * g.N);
+        const int old = voxel_old_position(g, i);
+        if (b == 0 && lane == 0) {
+            if (perm) perm[i] = old;
+            if (inv_perm) inv_perm[old] = i;
+        }
+        const int64_t from = (int64_t)b * g.N + (inverse ? i : old);
+        const int64_t to = (int64_t)b * g.N + (inverse ? old : i);
         const VEC* s = src + from * words_per_row;
         VEC* d = dst + to * words_per_row;
-        for (int x = lane; x < words_per_row; x += 64) d[x] = s[x];
+        for (int x = lane; x < words_per_row; x += 64 * U) {   // U words per lane requested before the first is stored
+            VEC v[U];
+#pragma unroll
+            for (int u = 0; u < U; u++)
+                if (x + 64 * u < words_per_row) v[u] = STREAM ? __builtin_nontemporal_load(s + x + 64 * u) : s[x + 64 * u];
+#pragma unroll
+            for (int u = 0; u < U; u++)
+                if (x + 64 * u < words_per_row) {
+                    if (STREAM) __builtin_nontemporal_store(v[u], d + x + 64 * u);
+                    else d[x + 64 * u] = v[u];
+                }
+        }
     }
 }
 
@@ -113,29 +146,30 @@ extern "C" int32_t chipmunk_voxel_reorder(const void* src, void* dst, int32_t* p
         int64_t bytes = (int64_t)batch * N64 * row_bytes;
         if (s0 < d0 + bytes && d0 < s0 + bytes) return CHIPMUNK_ERR_SHAPE;
     }
-    VoxelGeom g;
-    g.n_prefix = n_prefix; g.T = T; g.H = H; g.W = W; g.n_suffix = n_suffix;
-    g.vt = vt; g.vh = vh; g.vw = vw;
-    g.Tf = (T / vt) * vt; g.Hf = (H / vh) * vh; g.Wf = (W / vw) * vw;
-    g.n_full = g.Tf * g.Hf * g.Wf;
-    g.grid = T * H * W;
-    g.N = (int)N64;
+    const int Tf = (T / vt) * vt, Hf = (H / vh) * vh, Wf = (W / vw) * vw;
+    const int64_t rest = (int64_t)Hf * (W - Wf) + (int64_t)(H - Hf) * W;   // of a frame t < Tf
+    const bool full = Tf > 0 && Hf > 0 && Wf > 0;
+    const VoxelGeom g = {n_prefix, H, W, vt, vh, vw, Tf, Hf, Wf, Tf * Hf * Wf, T * H * W, (int)N64,
+                         Divisor(full ? (int64_t)vt * vh * vw : 1), Divisor(Wf / vw), Divisor(Hf / vh), Divisor(full ? vh : 1),
+                         Divisor(full ? vw : 1), Divisor(W - Wf), Divisor(rest), Divisor(W), Divisor((int64_t)H * W), Divisor(N64)};
     hipStream_t s = (hipStream_t)stream;
-    if (perm || inv_perm) {
+    if (!src) {
         hipLaunchKernelGGL(voxel_perm_kernel, dim3((g.N + 255) / 256), dim3(256), 0, s, g, perm, inv_perm);
-        if (launch_status() != CHIPMUNK_OK) return CHIPMUNK_ERR_LAUNCH;
+        return launch_status();
     }
-    if (src) {
-        int64_t total_rows = (int64_t)batch * g.N;
-        int64_t blocks = (total_rows + 3) / 4;
-        if (blocks > 256 * 64) blocks = 256 * 64;  // 64 resident-sized groups per CU, rows strided over them
-        if (row_bytes % 16 == 0 && aligned16(src) && aligned16(dst))
-            hipLaunchKernelGGL((voxel_copy_kernel<uint4>), dim3((unsigned)blocks), dim3(256), 0, s, g,
-                               (const uint4*)src, (uint4*)dst, total_rows, row_bytes / 16, inverse);
-        else
-            hipLaunchKernelGGL((voxel_copy_kernel<uint32_t>), dim3((unsigned)blocks), dim3(256), 0, s, g,
-                               (const uint32_t*)src, (uint32_t*)dst, total_rows, row_bytes / 4, inverse);
-        if (launch_status() != CHIPMUNK_OK) return CHIPMUNK_ERR_LAUNCH;
+    const int64_t total_rows = (int64_t)batch * g.N;
+    int64_t blocks = (total_rows + 3) / 4;
+    if (blocks > 1 << 22) blocks = 1 << 22;   // a launch has fewer than 2^32 threads; rows beyond are strided over the waves
+    const bool stream_through = total_rows * row_bytes > (int64_t)128 << 20;
+    auto launch = [&](auto kernel, auto from, auto to, int word) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, g, from, to, total_rows, row_bytes / word, inverse, perm, inv_perm);
+    };
+    if (row_bytes % 16 == 0 && aligned16(src) && aligned16(dst)) {
+        if (stream_through) launch(voxel_copy_kernel<u32x4, true>, (const u32x4*)src, (u32x4*)dst, 16);
+        else launch(voxel_copy_kernel<u32x4, false>, (const u32x4*)src, (u32x4*)dst, 16);
+    } else {
+        if (stream_through) launch(voxel_copy_kernel<uint32_t, true>, (const uint32_t*)src, (uint32_t*)dst, 4);
+        else launch(voxel_copy_kernel<uint32_t, false>, (const uint32_t*)src, (uint32_t*)dst, 4);
     }
-    return CHIPMUNK_OK;
+    return launch_status();
 }

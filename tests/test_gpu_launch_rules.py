@@ -394,3 +394,30 @@ def test_unchanged_input_on_small_tiles(cm, B, N, D, F, c, k, first_dense, first
     counts = torch.full((B, NB), k, dtype=torch.int32, device=DEV)
     cm.mlp_sparse_delta(x, w1, b1, w2, idx.view(B, NB, k), counts, a_cache, out, c, 1, _u8(cm.mlp_workspace_bytes(B, N, D, F, c, k)))
     assert torch.equal(a_cache, a_before) and torch.equal(out, o_before)
+
+
+@pytest.mark.parametrize("geom,batch,words,dtype", [
+    ((3, 5, 9, 13, 2, 2, 4, 3), 3, 2560, torch.bfloat16),       # rows of 320 16-byte words: one sweep of five per lane
+    ((0, 4, 6, 7, 5, 4, 6, 8), 2, 2568, torch.bfloat16),        # 321 words; the voxel is wider than the grid
+    ((1, 3, 50, 1, 0, 1, 7, 1), 1, 701, torch.int32),           # 4-byte words, more than one sweep, remainder rows
+    ((7, 1, 1, 1, 0, 3, 3, 3), 4, 1, torch.int32),              # no full voxel at all
+    ((0, 7, 64, 67, 1, 4, 6, 8), 1, 2304, torch.bfloat16),      # 138 MB: streamed
+    ((2, 7, 64, 67, 0, 2, 5, 8), 1, 1201, torch.int32),         # 144 MB in 4-byte words
+])
+def test_voxel_rows_and_permutation_in_one_launch(cm, oracle, geom, batch, words, dtype):
+    """The copy's launch also writes the permutation and its inverse; rows of one and more sweeps, small and streamed copies."""
+    npre, T, H, W, nsuf, vt, vh, vw = geom
+    N = npre + T * H * W + nsuf
+    perm_ref, inv_ref = oracle.voxel_perm(*geom)
+    src = torch.randint(-2 ** 15, 2 ** 15 - 1, (batch, N, words), device=DEV, dtype=torch.int32)
+    src = src.to(torch.int16).view(torch.bfloat16) if dtype == torch.bfloat16 else src
+    dst = torch.zeros_like(src)
+    perm, inv = (torch.full((N,), -1, dtype=torch.int32, device=DEV) for _ in range(2))
+    cm.voxel_reorder(src, dst, perm, inv, npre, T, H, W, nsuf, vt, vh, vw)
+    assert np.array_equal(perm.cpu().numpy(), perm_ref) and np.array_equal(inv.cpu().numpy(), inv_ref)
+    bits = torch.int16 if dtype == torch.bfloat16 else torch.int32
+    assert torch.equal(dst.view(bits), src.view(bits)[:, torch.from_numpy(perm_ref).long().to(DEV)])
+    back = torch.zeros_like(src)
+    perm.fill_(-1)
+    cm.voxel_reorder(dst, back, perm, None, npre, T, H, W, nsuf, vt, vh, vw, inverse=True)
+    assert torch.equal(back.view(bits), src.view(bits)) and np.array_equal(perm.cpu().numpy(), perm_ref)
