@@ -638,19 +638,29 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
                 p.row_m[bh * p.N + row0 + qrow] = -st.negm[qb][0] * (p.sl2 * 0.6931471805599453f);
                 p.row_l[bh * p.N + row0 + qrow] = ltot;
             }
+            // A lane holds four columns of each block of 16; lanes 16 apart exchange halves of two blocks, so that each stores
+            // eight columns in one piece and a row leaves in runs of 64 bytes.  (In runs of 32: 24 heads x 4608, 7 % of the
+            // columns 34.8 us, like this 32.4; 16 x 2 heads x 3982, 3 %: 25.9, 23.5; 24 x 115 456 0.2 %.)
 #pragma unroll
-            for (int eb = 0; eb < E / 16; eb++) {
-                u32x2 b = u32x2{0, 0};
-                if (MODE == kEveryColumn && baseh) b = bases[eb];
-                if (!NOLIST && baseh)
-                    b = *reinterpret_cast<const u32x2*>(smem + base_place(last_half, qb) + l16 * ROWB +
-                                                        (((2 * eb + (g >> 1)) ^ base_swizzle(l16)) * 16) + (g & 1) * 8);
-                float o0 = bf16_bits_to_float(b[0] & 0xffffu) + f * st.O[eb][qb][0];
-                float o1 = bf16_bits_to_float(b[0] >> 16) + f * st.O[eb][qb][1];
-                float o2 = bf16_bits_to_float(b[1] & 0xffffu) + f * st.O[eb][qb][2];
-                float o3 = bf16_bits_to_float(b[1] >> 16) + f * st.O[eb][qb][3];
-                u32x2 r2 = {pack_bf16x2(o0, o1), pack_bf16x2(o2, o3)};
-                *reinterpret_cast<u32x2*>(outh + row_off + eb * 16) = r2;
+            for (int pair = 0; pair < E / 32; pair++) {
+                u32x2 r[2];
+#pragma unroll
+                for (int i = 0; i < 2; i++) {
+                    const int eb = 2 * pair + i;
+                    u32x2 b = u32x2{0, 0};
+                    if (MODE == kEveryColumn && baseh) b = bases[eb];
+                    if (!NOLIST && baseh)
+                        b = *reinterpret_cast<const u32x2*>(smem + base_place(last_half, qb) + l16 * ROWB +
+                                                            (((2 * eb + (g >> 1)) ^ base_swizzle(l16)) * 16) + (g & 1) * 8);
+                    float o0 = bf16_bits_to_float(b[0] & 0xffffu) + f * st.O[eb][qb][0];
+                    float o1 = bf16_bits_to_float(b[0] >> 16) + f * st.O[eb][qb][1];
+                    float o2 = bf16_bits_to_float(b[1] & 0xffffu) + f * st.O[eb][qb][2];
+                    float o3 = bf16_bits_to_float(b[1] >> 16) + f * st.O[eb][qb][3];
+                    r[i] = u32x2{pack_bf16x2(o0, o1), pack_bf16x2(o2, o3)};
+                }
+                const auto lo = __builtin_amdgcn_permlane16_swap(r[0][0], r[1][0], false, false);
+                const auto hi = __builtin_amdgcn_permlane16_swap(r[0][1], r[1][1], false, false);
+                *reinterpret_cast<u32x4*>(outh + row_off - 4 * g + (2 * pair + (g & 1)) * 16 + (g >> 1) * 8) = u32x4{lo[0], hi[0], lo[1], hi[1]};
             }
         }
     }
