@@ -30,6 +30,7 @@
 
 namespace chipmunk {
 
+constexpr int64_t kAllL2 = 32 << 20, kLastLevelCache = 256 << 20;   // bytes
 constexpr int kBN = 128;  // neurons (GEMM1) or output columns (GEMM2) per workgroup
 constexpr int kBK = 64;   // contraction tile
 
@@ -444,7 +445,7 @@ struct Gemm2Shape {           // of a workgroup that owns ROWS token rows
 // drained at the head of every step, a CU had 40 KB in flight on average and took 10 TB/s into LDS.  Whole deltas in us, two
 // buffers and this ring: 394 chunks x 968 of 13 824 x 5120 1860 -> 1785, 24 x 1229 of 12 288 x 3072 101 -> 96.5, c = 128: 1350 x
 // 442 of 6144 x 2944 1440 -> 1324; dense, 11 chunks of 128 x 2176 x 5760: 120 -> 104.
-template <int BM, int ROWS, bool DENSE>
+template <int BM, int ROWS, bool DENSE, bool STREAM>
 __device__ __forceinline__ void gemm2_rows(const Gemm2Params& p, int unit, int part, int col_tile) {
     typedef Gemm2Shape<ROWS> Shape;
     constexpr int NS = Shape::kStages, SLOTS = Shape::kListSlots, STAGE = Shape::kStage;
@@ -653,7 +654,8 @@ __device__ __forceinline__ void gemm2_rows(const Gemm2Params& p, int unit, int p
             const uint16_t* src = (DENSE && p.bias)
                                       ? p.bias + d0 + ch * 4
                                       : p.o + ((int64_t)b * p.N + min(tok, p.N - 1)) * p.D + d0 + ch * 4;
-            old[half][n] = *reinterpret_cast<const u32x2*>(src);
+            const u32x2* at = reinterpret_cast<const u32x2*>(src);
+            old[half][n] = STREAM ? __builtin_nontemporal_load(at) : *at;
         }
     const bool add_nothing = DENSE && !p.bias;
 #pragma unroll
@@ -701,7 +703,10 @@ __device__ __forceinline__ void gemm2_rows(const Gemm2Params& p, int unit, int p
             float o2f = bf16_bits_to_float(o2[1] & 0xffffu) + a4[n][2];
             float o3 = bf16_bits_to_float(o2[1] >> 16) + a4[n][3];
             u32x2 res = {pack_bf16x2(o0, o1), pack_bf16x2(o2f, o3)};
-            if (tok < p.N) *reinterpret_cast<u32x2*>(orow) = res;
+            if (tok < p.N) {
+                if (STREAM) __builtin_nontemporal_store(res, reinterpret_cast<u32x2*>(orow));
+                else *reinterpret_cast<u32x2*>(orow) = res;
+            }
         }
     }
 }
@@ -709,7 +714,10 @@ __device__ __forceinline__ void gemm2_rows(const Gemm2Params& p, int unit, int p
 
 // PARTS: the tiles of an XCD beyond `whole` are taken 64 rows at a time.  (An instance of its own: with the second body in the
 // same kernel launches that never reach it were 0.5 to 1 % slower.)
-template <int BM, bool DENSE, bool PARTS>
+// STREAM: the cached output is read and written past the caches' usual order of replacement, which leaves them to the weights:
+// where it is over twice the XCDs' L2s.  Whole deltas in us without and with: 75 600 x 5120 (774 MB) 1777, 1728; 28 438 x 4096
+// (233 MB) 216, 196; 19 327 x 2304 (89 MB) 92.6, 85.3; 2 x 7394 x 1792 (53 MB) 41.7, 42.9; 7669 x 1536 (24 MB) 37.6, 39.0.
+template <int BM, bool DENSE, bool PARTS, bool STREAM>
 __global__ __launch_bounds__(256, 2) void mlp_gemm2_kernel(Gemm2Params p) {
     if (!DENSE && p.act_t && (int)blockIdx.x >= p.tile_blocks) {
         write_back_activations(p, (int)blockIdx.x - p.tile_blocks, BM);
@@ -724,11 +732,11 @@ __global__ __launch_bounds__(256, 2) void mlp_gemm2_kernel(Gemm2Params p) {
         return;
     if constexpr (PARTS) {
         if (beyond >= 0) {
-            gemm2_rows<BM, 64, DENSE>(p, unit, beyond % parts, col_tile);
+            gemm2_rows<BM, 64, DENSE, STREAM>(p, unit, beyond % parts, col_tile);
             return;
         }
     }
-    gemm2_rows<BM, BM, DENSE>(p, unit, 0, col_tile);
+    gemm2_rows<BM, BM, DENSE, STREAM>(p, unit, 0, col_tile);
 }
 
 }  // namespace chipmunk
@@ -742,7 +750,10 @@ namespace chipmunk {
 // Bound: HBM (x read once).  A wave requests six rows (16 bytes per lane each) before it adds the first: with one row at a
 // time and four waves a small problem took as many round trips as a wave had rows: 24 chunks of 192 x 3072 15.5 -> 6.9 us,
 // 8 of 128 x 256 7.2 -> 4.4 us, 602 of 192 x 3072 139 -> 127 us (5.6 TB/s).
+// STREAM: loads past the caches' usual order of replacement, for an x that does not fit the last-level cache.  Means and scores
+// together, us without and with: 709 MB 220.6, 201.6; 414 MB 127, 109; 298 MB 108, 99; 162 MB (just read) 43.8, 47.3.
 constexpr int kMeanWaves = 8, kMeanAhead = 6;
+template <bool STREAM>
 __global__ __launch_bounds__(64 * kMeanWaves) void chunk_mean_kernel(const uint16_t* __restrict__ x, uint16_t* __restrict__ xm,
                                                                      int N, int NB, int D, int c) {
     __shared__ float s_part[kMeanWaves - 1][8][64];
@@ -759,7 +770,10 @@ __global__ __launch_bounds__(64 * kMeanWaves) void chunk_mean_kernel(const uint1
         for (int r = r0 + w; r < r1; r += kMeanWaves * kMeanAhead) {
             u32x4 v[kMeanAhead];
 #pragma unroll
-            for (int i = 0; i < kMeanAhead; i++) v[i] = *reinterpret_cast<const u32x4*>(xc + (int64_t)min(r + i * kMeanWaves, r1 - 1) * D);
+            for (int i = 0; i < kMeanAhead; i++) {
+                const u32x4* at = reinterpret_cast<const u32x4*>(xc + (int64_t)min(r + i * kMeanWaves, r1 - 1) * D);
+                v[i] = STREAM ? __builtin_nontemporal_load(at) : *at;
+            }
 #pragma unroll
             for (int i = 0; i < kMeanAhead; i++) {
                 const bool exists = r + i * kMeanWaves < r1;
@@ -841,8 +855,12 @@ static int32_t launch_gemm2(Gemm2Params p, int col_tiles, int units, int64_t who
         return launch_status();
     };
     constexpr int lds = Gemm2Shape<BM>::kLds, lds64 = Gemm2Shape<64>::kLds;
-    return p.whole == slots ? launch(mlp_gemm2_kernel<BM, DENSE, false>, lds)
-                            : launch(mlp_gemm2_kernel<BM, DENSE, true>, lds > lds64 ? lds : lds64);
+    constexpr int lds_parts = lds > lds64 ? lds : lds64;
+    if (!DENSE && (int64_t)units * BM * p.D * 2 > 2 * kAllL2)
+        return p.whole == slots ? launch(mlp_gemm2_kernel<BM, DENSE, false, !DENSE>, lds)
+                                : launch(mlp_gemm2_kernel<BM, DENSE, true, !DENSE>, lds_parts);
+    return p.whole == slots ? launch(mlp_gemm2_kernel<BM, DENSE, false, false>, lds)
+                            : launch(mlp_gemm2_kernel<BM, DENSE, true, false>, lds_parts);
 }
 
 // Tiles of 64 x 64.  `units`: sparse: chunks of `parts` row tiles; dense: row tiles of all batches (parts = 1).
@@ -1221,8 +1239,9 @@ extern "C" int32_t chipmunk_mlp_dense(const uint16_t* x, const uint16_t* w1, con
 static int32_t run_tile_mean(const uint16_t* x, const uint16_t* w1, float* T, int B, int N, int D, int F, int c,
                              void* ws, int pieces, hipStream_t s) {
     const int NB = (N + c - 1) / c, units = B * NB;
-    hipLaunchKernelGGL(chunk_mean_kernel, dim3((unsigned)(((D / 8 + 63) / 64) * units)), dim3(64 * kMeanWaves), 0, s, x, (uint16_t*)ws,
-                       N, NB, D, c);
+    const bool stream_x = (int64_t)B * N * D * 2 > kLastLevelCache;
+    hipLaunchKernelGGL(stream_x ? chunk_mean_kernel<true> : chunk_mean_kernel<false>, dim3((unsigned)(((D / 8 + 63) / 64) * units)),
+                       dim3(64 * kMeanWaves), 0, s, x, (uint16_t*)ws, N, NB, D, c);
     if (launch_status() != CHIPMUNK_OK) return CHIPMUNK_ERR_LAUNCH;
     // scores[unit, f] = <hi(unit) + lo(unit), w1_f>
     const ScoresPlan plan = scores_plan(units, D, F);

@@ -396,6 +396,48 @@ def test_unchanged_input_on_small_tiles(cm, B, N, D, F, c, k, first_dense, first
     assert torch.equal(a_cache, a_before) and torch.equal(out, o_before)
 
 
+@pytest.mark.parametrize("B,N,D,c,whole", [(1, 88 * 192 - 37, 2048, 192, 176), (2, 33 * 192 - 5, 3072, 192, 192),
+                                           (1, 70 * 128 - 100, 4096, 128, 280), (2, 44 * 128 - 1, 3072, 128, 256)])
+def test_mlp_delta_of_an_output_past_the_caches(cm, oracle, B, N, D, c, whole):
+    """Outputs of over 64 MB, with and without a last round in parts of 64 rows; the first two and the last two chunks of each
+    batch against the oracle."""
+    F, k = 256, 70
+    assert B * N * D * 2 > 64 << 20 and _mlp_tiles(cm, B, N, D, F, c, k)[5] == whole
+    g = si.generator(35, DEV)
+    x, w1, w2 = si.randn_bf16((B, N, D), g), si.randn_bf16((F, D), g, D ** -0.5), si.randn_bf16((F, D), g, F ** -0.5)
+    b1, NB, a_ld = si.randn_bf16((F,), g), -(-N // c), -(-N // 8) * 8
+    a_cache, o_cache = si.randn_bf16((B, F, a_ld), g, 0.5), si.randn_bf16((B, N, D), g)
+    idx, counts = recipes.mlp_indices(B * NB, F, k, 35, DEV, ragged=True)
+    idx, counts = idx.view(B, NB, k), counts.view(B, NB)
+    a_new, o_new = a_cache.clone(), o_cache.clone()
+    cm.mlp_sparse_delta(x, w1, b1, w2, idx, counts, a_new, o_new, c, 1, _u8(cm.mlp_workspace_bytes(B, N, D, F, c, k)))
+    for first in (0, NB - 2):
+        rows, n = slice(first * c, min((first + 2) * c, N)), min((first + 2) * c, N) - first * c
+        o_ref = si.np_f32(o_cache[:, rows].contiguous()).astype(np.float64)
+        a_ref = np.zeros((B, F, -(-n // 8) * 8))
+        a_ref[..., :n] = si.np_f32(a_cache[..., rows].contiguous())
+        o_before = o_ref.copy()
+        oracle.mlp_sparse_delta(si.np_f32(x[:, rows].contiguous()), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2),
+                                idx[:, first:first + 2].contiguous().cpu().numpy(),
+                                counts[:, first:first + 2].contiguous().cpu().numpy(), a_ref, o_ref, c, 1)
+        assert rel_err(si.np_f32(a_new[..., rows].contiguous()), a_ref[..., :n]) <= REL_TOL
+        assert rel_err(si.np_f32(o_new[:, rows].contiguous()), o_ref, o_ref - o_before) <= REL_TOL
+
+
+@pytest.mark.parametrize("B,N,D,c", [(1, 27001, 5120, 192), (2, 16500, 4096, 128)])
+def test_neuron_scores_of_an_input_past_the_caches(cm, oracle, B, N, D, c):
+    """An x of over 256 MB; the first two and the last two chunks of each batch against the oracle."""
+    F, NB = 64, -(-N // c)
+    assert B * N * D * 2 > 256 << 20
+    g = si.generator(36, DEV)
+    x, w1 = si.randn_bf16((B, N, D), g), si.randn_bf16((F, D), g, D ** -0.5)
+    T = torch.full((B, NB, F), float("nan"), dtype=torch.float32, device=DEV)
+    cm.mlp_tile_mean_preact(x, w1, T, c, _u8(cm.mlp_tile_mean_workspace_bytes(B, N, D, F, c)))
+    for first in (0, NB - 2):
+        ref = oracle.mlp_tile_scores(si.np_f32(x[:, first * c:(first + 2) * c].contiguous()), si.np_f32(w1), c)
+        assert rel_err(T[:, first:first + 2].cpu().numpy(), ref) <= SUM_TOL
+
+
 @pytest.mark.parametrize("geom,batch,words,dtype", [
     ((3, 5, 9, 13, 2, 2, 4, 3), 3, 2560, torch.bfloat16),       # rows of 320 16-byte words: one sweep of five per lane
     ((0, 4, 6, 7, 5, 4, 6, 8), 2, 2568, torch.bfloat16),        # 321 words; the voxel is wider than the grid
