@@ -167,18 +167,20 @@ int32_t chipmunk_attn_colsum_stale(const uint16_t* q, const uint16_t* k, const f
                                    const float* prev_l, float* colsum, int64_t ld_colsum,
                                    int B, int H, int N, int E, int c, float softmax_scale, void* stream);
 
-/* Dense attention and the column sums with given normalisers in one pass (Alg. 4):
+/* Dense attention and the column sums with given normalisers in one call (Alg. 4):
  *   out = softmax(softmax_scale * q k^T) v            with this step's own normalisers,
  *   colsum[b,h,i,j] = sum over the rows n of chunk i of
  *                     exp(softmax_scale * <q[n],k[j]> - prev_m[n]) / prev_l[n]
- * from the same score tiles (no second pass over q k^T and no workspace).
+ * from the same score tiles (no second pass over q k^T and no workspace); with
+ * few chunks of many keys, which one pass would leave most of the chip idle
+ * for, by chipmunk_attn_colsum_stale's pass and then the attention's.
  * new_m, new_l: [B,H,N] fp32 or both NULL; they receive this step's statistics
  * in the form chipmunk_attn_dense leaves them, for the next step's prev_m,
  * prev_l.  new_m == prev_m and new_l == prev_l (update in place) is allowed:
- * the workgroup of a chunk reads the old values of its own rows, and only
- * those, before it writes the new ones; any other overlap is not.  Other
+ * the old values of a chunk's rows are read, by its workgroup alone or by the
+ * pass before, before the new ones are written; any other overlap is not.  Other
  * arguments as for chipmunk_attn_colsum_stale and chipmunk_attn_dense.
- * Range: this kernel forms a weight as (probability against the running
+ * Range: the one pass forms a weight as (probability against the running
  * softmax reference) x (one factor per query), and caps that factor at 2^126.
  * While the largest weight exp(score - prev_m) / prev_l of every query row
  * stays below 2^118 the sums agree with chipmunk_attn_colsum_stale; beyond

@@ -1083,6 +1083,14 @@ extern "C" int32_t chipmunk_attn_colsum_stale(const uint16_t* q, const uint16_t*
     return launch_colsum(cp, E, units, (hipStream_t)stream);
 }
 
+// A refresh in one kernel has a workgroup per chunk and no other split; apart, the sums come in pieces of the keys and the
+// attention in workgroups of 64 rows.  One kernel and apart, us: 48 chunks 4 heads x 2201 x 128 68.5, 47.9; 30, 6 x 826 x 64
+// 25.5, 22.6; 78, 13 x 1008 x 64 29.5, 25.2; 96, 16 x 1091 x 128 41.2, 41.8; 110, 22 x 928 x 128 36.3, 38.1, but 10 x 2026 x 128
+// 64.7, 63.1; 117, 9 x 2390 x 64 58.0, 50.7 (81 to 121 chunks of 1587 keys and more: 1.03 to 1.34 times, ten sizes).  Short keys
+// cost the second launch: 16 chunks, 8 x 199 x 64 15.3, 17.9; 48, 16 x 456 x 64 19.1, 18.7; 78, 26 x 438 x 128 23.1, 24.5.
+// The sums' error against 64 bits, one kernel and apart: 2e-7 to 4e-7, 5e-8 to 7e-8 (RMS).
+static bool refresh_apart(int64_t units, int N) { return (units <= 80 && N >= 640) || (units <= 120 && N >= 1536); }
+
 extern "C" int32_t chipmunk_attn_dense_colsum_stale(const uint16_t* q, const uint16_t* k, const uint16_t* v,
                                                     uint16_t* out, const float* prev_m, const float* prev_l,
                                                     float* colsum, int64_t ld_colsum, float* new_m, float* new_l,
@@ -1105,6 +1113,11 @@ extern "C" int32_t chipmunk_attn_dense_colsum_stale(const uint16_t* q, const uin
     p.N = N; p.NB = NB; p.c = c; p.whole = 0; p.by_xcd = attn_by_xcd(N, E); p.k_stride = 0;
     p.sl2 = softmax_scale * 1.4426950408889634f;
     p.o_scale = 1.f;
+    if (refresh_apart(units, N)) {
+        // the sums first: the attention may write its statistics over the ones that the sums take
+        const int32_t st = chipmunk_attn_colsum_stale(q, k, prev_m, prev_l, colsum, ld_colsum, B, H, N, E, c, softmax_scale, stream);
+        return st != CHIPMUNK_OK ? st : launch_attn(p, E, units, (hipStream_t)stream);
+    }
     return launch_attn_fused(p, E, units, (hipStream_t)stream);
 }
 

@@ -45,6 +45,36 @@ def _u8(nbytes):
     return torch.empty(max(int(nbytes), 16), dtype=torch.uint8, device=DEV)
 
 
+@pytest.mark.parametrize("E", [64, 128])
+@pytest.mark.parametrize("B,H,N,c,apart", [(1, 20, 700, 192, True), (2, 8, 640, 128, True), (1, 27, 640, 192, False),
+                                           (1, 20, 639, 192, False), (2, 7, 1031, 128, False), (1, 15, 1536, 192, True),
+                                           (1, 15, 1535, 192, False), (1, 11, 2101, 192, False)])
+def test_refresh_in_one_kernel_and_apart(cm, oracle, B, H, N, E, c, apart):
+    """Both sides of the rule, statistics updated in place.  Apart, the sums and the output are those of the two entry points
+    that make them alone, bit by bit; the one kernel's are rounded differently, which also shows which was taken."""
+    (q1, k1, _), (q2, k2, v), _ = si.attn_steps(B, H, N, E, 38, DEV)
+    scale, NB, ld = 1 / math.sqrt(E), -(-N // c), -(-N // 4) * 4 + 4
+    m_ref, l_ref = oracle.attn_row_stats(si.np_f32(q1), si.np_f32(k1), scale)
+    m, l = (torch.from_numpy(t.astype(np.float32)).to(DEV) for t in (m_ref, l_ref))
+    m0, l0 = m.clone(), l.clone()
+    out, D = torch.empty_like(q2), torch.full((B, H, NB, ld), -1.0, dtype=torch.float32, device=DEV)
+    cm.attn_dense_colsum_stale(q2, k2, v, out, m, l, D, c, scale, m, l)
+    qn, kn, vn = si.np_f32(q2), si.np_f32(k2), si.np_f32(v)
+    ref = oracle.attn_colsum_stale(qn, kn, m0.cpu().numpy().astype(np.float64), l0.cpu().numpy().astype(np.float64), c, scale)
+    assert rel_err(D[..., :N].cpu().numpy().astype(np.float64), ref) <= SUM_TOL
+    assert bool((D[..., N:] == -1.0).all())
+    assert rel_err(si.np_f32(out), oracle.attn_dense(qn, kn, vn, c, scale)) <= REL_TOL
+    m_ref, l_ref = oracle.attn_row_stats(qn, kn, scale)
+    lse = m.cpu().numpy().astype(np.float64) + np.log(l.cpu().numpy().astype(np.float64))
+    assert np.abs(lse - (m_ref + np.log(l_ref))).max() <= 2e-3
+    D_alone, out_alone = torch.full_like(D, -1.0), torch.empty_like(out)
+    cm.attn_colsum_stale(q2, k2, m0, l0, D_alone, c, scale)
+    cm.attn_dense(q2, k2, v, out_alone, None, c, scale, None)
+    assert torch.equal(D, D_alone) == apart
+    if apart:
+        assert torch.equal(out, out_alone)
+
+
 @pytest.mark.parametrize("N,E,c,pieces", [(1, 128, 192, 1), (64, 64, 128, 1), (130, 128, 192, 1), (511, 64, 192, 2),
                                           (513, 128, 128, 2), (1100, 128, 192, 4), (2113, 64, 128, 8), (2113, 128, 192, 8)])
 def test_column_sums_in_pieces_of_the_keys(cm, oracle, N, E, c, pieces):
