@@ -6,9 +6,9 @@
 // most-significant-digit radix select (digits of up to 11 bits, LDS histograms,
 // wave-level prefix sums on DPP); the selected columns are every column above
 // the threshold plus the first columns equal to it, written in ascending order.
-//   - Rows of up to kRegisterCols columns (with few of them kept: fewer, see the
-//     entry point) are read from HBM once and kept in registers as keys; their
-//     threshold is found by halving the range of keys.
+//   - Rows of up to kRegisterCols columns (with a third of them kept: up to
+//     kRegisterColsOf16) are read from HBM once and kept in registers as keys;
+//     their threshold is found by halving the range of keys.
 //   - Longer rows (the attention column sums, 10^5 columns) are read from HBM
 //     once as well: two pivots taken from a 4096-score sample bracket the
 //     threshold; the single pass over the row marks the columns above the
@@ -32,8 +32,8 @@ constexpr float kPivotSigmas = 3.5f;  // slack of the sample pivots around the t
 // key(a) > key(b) exactly when a > b; no finite or infinite score has key 0
 __device__ __forceinline__ uint32_t key_of_score(float s) {
     if (s == 0.f) s = 0.f;  // -0 and +0 are the same score
-    uint32_t u = __float_as_uint(s);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    const uint32_t u = __float_as_uint(s);
+    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);   // a negative one: its complement
 }
 
 __device__ __forceinline__ float score_of_key(uint32_t key) {
@@ -41,7 +41,9 @@ __device__ __forceinline__ float score_of_key(uint32_t key) {
 }
 
 __device__ __forceinline__ uint32_t score_key(float cur, float prev, bool has_prev) {
-    return key_of_score(has_prev ? fabsf(cur - prev) : cur);
+    if (!has_prev) return key_of_score(cur);
+    const float change = fabsf(cur - prev);
+    return __float_as_uint(change == 0.f ? 0.f : change) | 0x80000000u;   // key_of_score of a score without a sign
 }
 
 // inclusive prefix sum over the 64 lanes of a wave: DPP row shifts inside each
@@ -289,22 +291,23 @@ __device__ __forceinline__ void emit_selected(const Src& src, int C, uint32_t th
     }
 }
 
-// Rows of up to kRegisterCols columns: read once, kept as keys in the registers of the row's two, four or eight waves (U
-// groups of 256 columns each, four keys per lane and group).
+// Rows of up to kRegisterColsOf16 columns: read once, kept as keys in the registers of the row's two, four, eight or sixteen
+// waves (U groups of 256 columns each, four keys per lane and group).
 //
 // The threshold is found by halving the range of keys that can hold it: a step counts the keys at or above a pivot (a
-// compare and an add per key, a wave sum, one barrier) and ends as soon as at most kLastKeys keys are left between the
-// bounds (five to eight steps for column sums and neuron scores, 32 at most), which one wave then finishes by
-// itself with ballots.  No step depends on how the scores are spread over their bits: a histogram of the leading digit
-// sends most of a wave's atomics to a handful of bins.
-// What bounds it: with few rows a row's chain of loads and barriers, with many the issue slots of the counting; 26 to 77
-// registers per lane and about 1 KB of LDS keep 24 to 32 waves on a CU, where rows kept in LDS (57 KB at 12 288 columns)
-// allowed two workgroups, so that 602 rows took two rounds.  Against histograms of 11-bit digits over keys in LDS: 602 rows
-// of 12 288 with previous scores 36.8 -> 22.9 us, 14 448 x 4608 150 -> 105 us, 4000 x 12 288 (30 % kept) 160 -> 95 us,
-// 5000 x 1024 30.8 -> 14.4 us.  The steps grow with the exponents that the range spans: column sums and |T - T_m| lie
-// within a few, but scores of both signs take about ten steps, and rows of just over 7168 of them are the one place where the
-// histograms were faster: 768 normal rows of 7200 15.8 and 18.3 us, of 9000 20.0 and 21.4.
-constexpr int kRegisterCols = 8 * 7 * 256;
+// compare and an add per key, for one key of four a compare and the scalar unit's count; a wave sum, one barrier) and ends as
+// soon as at most kLastKeys keys are left between the bounds (five to eight steps for column sums and neuron scores, 32 at
+// most), which one wave then finishes by itself with ballots.  No step depends on how the scores are spread over their bits: a
+// histogram of the leading digit sends most of a wave's atomics to a handful of bins.
+// What bounds it: with few rows a row's chain of loads and barriers, with many the vector units' issue slots (busy 94 to 100 %
+// of the time before), of which the halvings take under a third.  So the rest is kept short: a wave whose columns all exist
+// looks at none singly; smallest and largest key are two three-operand instructions per two keys; and where every column that
+// equals the threshold is taken (all but ties on it) a column's place comes from the lanes below in four ballots, once, before
+// the barrier, with no scan and no second count.  Us before and now: 14 448 x 4608 105.5, 79.0; 5194 x 10 853 (a quarter kept)
+// 114.9, 89.4; 14 289 x 2532 67.2, 54.8; 602 x 12 288 with previous scores 22.8, 19.6; 36 x 6138 9.7, 8.05; 27 x 1216 the same.
+// With half the keys counted by the scalar unit, or the last keys placed by ballots, that unit is the bound: 2 to 5 % slower.
+// 12 to 75 registers per lane and about 1 KB of LDS keep 24 to 32 waves on a CU.
+constexpr int kRegisterCols = 8 * 8 * 256, kRegisterColsOf16 = 16 * 6 * 256;   // of eight waves and of sixteen
 constexpr int kLastKeys = 256;
 
 // sum and maximum over the wave's lanes
@@ -325,15 +328,20 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
                max((uint32_t)__builtin_amdgcn_readlane((int)v, 47), (uint32_t)__builtin_amdgcn_readlane((int)v, 63)));
 }
 
+// base + how many of the lanes below this one are in `who`
+__device__ __forceinline__ uint32_t lanes_below(uint64_t who, uint32_t base) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, base));
+}
+
 template <bool HAS_PREV, int NT, int U>
-__global__ __launch_bounds__(NT, U >= 6 ? 6 : 8) void topk_register_rows_kernel(const float* __restrict__ cur,
+__global__ __launch_bounds__(NT, U >= 6 && NT < 1024 ? 6 : 8) void topk_register_rows_kernel(const float* __restrict__ cur,
                                                                             const float* __restrict__ prev, int C, int64_t ld,
                                                                             int k, int32_t* __restrict__ idx,
                                                                             int32_t* __restrict__ counts, int k_stride) {
     constexpr int NW = NT / 64;
     __shared__ __attribute__((aligned(16))) uint32_t s_set[2][2 * NW];   // per-wave totals, two sets used in turn
     __shared__ uint32_t s_last[kLastKeys];
-    __shared__ uint32_t s_found[3];                                      // threshold, how many equal to it; candidates
+    __shared__ uint32_t s_found[4];                                      // threshold, how many to take of those equal to it; candidates; equal
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t row = blockIdx.x;
@@ -348,7 +356,7 @@ __global__ __launch_bounds__(NT, U >= 6 ? 6 : 8) void topk_register_rows_kernel(
 
     // wave w holds the groups [w per_wave, (w + 1) per_wave) of 256 columns; a column that does not exist has key 0
     const int groups = (C + 255) >> 8, per_wave = (groups + NW - 1) / NW, last4 = ((C + 3) >> 2) - 1;
-    uint32_t key[U][4];
+    uint32_t key[U][4], top = 0, bottom = 0xffffffffu;   // largest and smallest key of an existing column
     {
         float4 cv[U], pv[U];
 #pragma unroll
@@ -360,26 +368,37 @@ __global__ __launch_bounds__(NT, U >= 6 ? 6 : 8) void topk_register_rows_kernel(
         }
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            const int exist = u < per_wave ? C - ((w * per_wave + u) * 256 + 4 * lane) : 0;
-            key[u][0] = exist > 0 ? score_key(cv[u].x, pv[u].x, HAS_PREV) : 0u;
-            key[u][1] = exist > 1 ? score_key(cv[u].y, pv[u].y, HAS_PREV) : 0u;
-            key[u][2] = exist > 2 ? score_key(cv[u].z, pv[u].z, HAS_PREV) : 0u;
-            key[u][3] = exist > 3 ? score_key(cv[u].w, pv[u].w, HAS_PREV) : 0u;
+            key[u][0] = score_key(cv[u].x, pv[u].x, HAS_PREV);
+            key[u][1] = score_key(cv[u].y, pv[u].y, HAS_PREV);
+            key[u][2] = score_key(cv[u].z, pv[u].z, HAS_PREV);
+            key[u][3] = score_key(cv[u].w, pv[u].w, HAS_PREV);
         }
     }
-    int flip = 0;   // a set is written again only behind the barrier in between, which no thread passes before it has read it
-    uint32_t lo, hi;
-    {
-        uint32_t top = 0, bottom = 0;   // largest key, largest complement of an existing key
+    if (__builtin_expect(per_wave == U && (w + 1) * U * 256 <= C, 1)) {   // all of the wave's columns exist, as in most waves of a long row
 #pragma unroll
         for (int u = 0; u < U; u++)
 #pragma unroll
             for (int e = 0; e < 4; e++) {
                 top = max(top, key[u][e]);
-                bottom = max(bottom, key[u][e] != 0 ? ~key[u][e] : 0u);
+                bottom = min(bottom, key[u][e]);
             }
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int exist = u < per_wave ? C - ((w * per_wave + u) * 256 + 4 * lane) : 0;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                bottom = min(bottom, exist > e ? key[u][e] : 0xffffffffu);
+                key[u][e] = exist > e ? key[u][e] : 0u;
+                top = max(top, key[u][e]);
+            }
+        }
+    }
+    int flip = 0;   // a set is written again only behind the barrier in between, which no thread passes before it has read it
+    uint32_t lo, hi;
+    {
         top = wave_max(top);
-        bottom = wave_max(bottom);
+        bottom = wave_max(~bottom);
         if (lane == 0) {
             s_set[0][w] = top;
             s_set[0][NW + w] = bottom;
@@ -399,12 +418,15 @@ __global__ __launch_bounds__(NT, U >= 6 ? 6 : 8) void topk_register_rows_kernel(
 #pragma unroll 1
     while (lo != hi && n_from - n_above > (uint32_t)kLastKeys) {
         const uint32_t pivot = hi - ((hi - lo) >> 1);   // lo < pivot <= hi
-        uint32_t n = 0;
+        // three keys of four counted by the vector unit (a comparison and an addition), one by a comparison and the scalar unit
+        uint32_t n = 0, n_scalar = 0;
 #pragma unroll
-        for (int u = 0; u < U; u++)
+        for (int u = 0; u < U; u++) {
 #pragma unroll
-            for (int e = 0; e < 4; e++) n += key[u][e] >= pivot;
-        n = wave_sum(n);
+            for (int e = 0; e < 3; e++) n += key[u][e] >= pivot;
+            n_scalar += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(key[u][3] >= pivot));
+        }
+        n = wave_sum(n) + n_scalar;
         if (lane == 0) s_set[flip][w] = n;
         __syncthreads();
         n = 0;
@@ -420,7 +442,7 @@ __global__ __launch_bounds__(NT, U >= 6 ? 6 : 8) void topk_register_rows_kernel(
             n_above = n;
         }
     }
-    uint32_t thr = lo, take_eq = (uint32_t)k - n_above;
+    uint32_t thr = lo, take_eq = (uint32_t)k - n_above, equal = n_from - n_above;   // of them
     if (lo != hi) {
         // the keys between the bounds, in any order
         const uint32_t span = hi - lo;
@@ -444,7 +466,7 @@ __global__ __launch_bounds__(NT, U >= 6 ? 6 : 8) void topk_register_rows_kernel(
             uint32_t last[kLastKeys / 64];
 #pragma unroll
             for (int i = 0; i < kLastKeys / 64; i++) last[i] = (uint32_t)(i * 64 + lane) < n_last ? s_last[i * 64 + lane] : 0u;
-            uint32_t above = 0;
+            uint32_t above = 0, from = n_last;
             while (lo != hi) {
                 const uint32_t pivot = hi - ((hi - lo) >> 1);
                 uint32_t n = 0;
@@ -452,6 +474,7 @@ __global__ __launch_bounds__(NT, U >= 6 ? 6 : 8) void topk_register_rows_kernel(
                 for (int i = 0; i < kLastKeys / 64; i++) n += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(last[i] >= pivot));
                 if (n >= want) {
                     lo = pivot;
+                    from = n;
                 } else {
                     hi = pivot - 1;
                     above = n;
@@ -460,11 +483,45 @@ __global__ __launch_bounds__(NT, U >= 6 ? 6 : 8) void topk_register_rows_kernel(
             if (lane == 0) {
                 s_found[0] = lo;
                 s_found[1] = want - above;
+                s_found[3] = from - above;
             }
         }
         __syncthreads();
         thr = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_found[0]);
         take_eq = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_found[1]);
+        equal = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_found[3]);
+    }
+    if (__builtin_expect(take_eq == equal, 1)) {   // every column from the threshold on, ascending
+        uint32_t rank[U], total = 0;   // of the lane's first column among the wave's taken ones
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            rank[u] = total;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const uint64_t who = __builtin_amdgcn_ballot_w64(key[u][e] >= thr);
+                rank[u] = lanes_below(who, rank[u]);
+                total += (uint32_t)__builtin_popcountll(who);
+            }
+        }
+        if (lane == 0) s_set[flip][w] = total;
+        __syncthreads();
+        uint32_t before = 0;
+#pragma unroll
+        for (int i = 0; i < NW; i++) before += i < w ? s_set[flip][i] : 0u;
+        before = (uint32_t)__builtin_amdgcn_readfirstlane((int)before);
+        int col = w * per_wave * 256 + 4 * lane;
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            uint32_t at = before + rank[u];
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const bool taken = key[u][e] >= thr;
+                if (taken) *reinterpret_cast<int32_t*>(reinterpret_cast<char*>(out) + 4u * at) = col + e;
+                at += taken;
+            }
+            col += 256;
+        }
+        return;
     }
     // every column above the threshold and the first take_eq columns that equal it, ascending
     uint32_t cnt[U], inc[U], total = 0;
@@ -983,12 +1040,12 @@ extern "C" int32_t chipmunk_topk_cols(const float* cur, const float* prev, int R
     hipStream_t s = (hipStream_t)stream;
     const dim3 grid((unsigned)R), block_long(kLongThreads);
     LongRowPlan plan;
-    // Rows that fit the registers of eight waves go there, except where the long rows' kernel is the faster one: single scores,
-    // more than 12 288 columns (seven units a wave, so fewer waves on a CU), a tenth of them kept at most.  Us in registers and
-    // there, column sums: 768 rows x 14 336, 3 % kept: 23.2, 19.1; 7 %: 24.7, 22.0; 12 %: 25.4, 23.7; 30 %: 27.3, 29.4; 14 448 x
-    // 13 000: 307, 277; 325, 293; 340, 332; 353, 421; 14 448 x 11 776: 272, 260; 287, 274; 293, 308; 308, 393; 14 448 x 10 240:
-    // 216, 250; 227, 273.  With previous scores 14 448 x 14 336, 7 %: 359, 460.
-    const bool in_registers = C <= kRegisterCols && (prev || C <= 12288 || (int64_t)k * 10 > C);
+    // Rows that fit the registers of eight waves go there.  Us in the long rows' kernel and in registers, column sums: 14 448 rows
+    // x 13 000, 3 % kept: 274, 222; 9 %: 308, 240; 14 448 x 16 320: 295, 251; 341, 271; 30 %: 459, 288; 300 x 16 320: 15.3, 14.3;
+    // 18.0, 15.2; 25.5, 17.6; with previous scores 1200 x 16 320, 3 %: 47.9, 36.6 (nearest: 20 x 14 400, 3 %: 10.4, 10.6).
+    // Sixteen waves take longer rows of which a third is kept, where the long rows' pass has that many candidates: 520 x 16 500,
+    // 50 %: 45.0, 30.0; 6000 x 24 576: 361, 235; 30 %: 520 x 20 600 33.6, 32.9; 1800 x 24 576 78.0, 78.3; 15 %: 26.0, 30.5; 63.6, 71.5.
+    const bool in_registers = C <= kRegisterCols || (C <= kRegisterColsOf16 && (int64_t)k * 3 >= C);
     if (in_registers) {
         // Waves per row: a step costs a wave its share of the counting and about 40 instructions of sums and exchange, so
         // few waves serve many short rows best, and eight a row whose keys would otherwise fill the registers of four.
@@ -996,7 +1053,7 @@ extern "C" int32_t chipmunk_topk_cols(const float* cur, const float* prev, int R
         // four and eight: 144, 210; 602 rows of 12 288 (with previous scores): 25.9 and 22.9.  Registers for four units of a wave
         // rather than five: 509 rows of 3392 (with previous scores) 9.9 -> 9.1, 769 of 8128 24.8 -> 21.9.
         const int groups = (C + 255) / 256;
-        const int waves = groups <= 4 ? 2 : groups <= 28 ? 4 : 8;
+        const int waves = groups <= 4 ? 2 : groups <= 28 ? 4 : groups <= 64 ? 8 : 16;
         const int per_wave = (groups + waves - 1) / waves;
         auto launch = [&](auto threads, auto u) {
             constexpr int NT = decltype(threads)::value, U = decltype(u)::value;
@@ -1008,6 +1065,7 @@ extern "C" int32_t chipmunk_topk_cols(const float* cur, const float* prev, int R
         std::integral_constant<int, 128> two;
         std::integral_constant<int, 256> four;
         std::integral_constant<int, 512> eight;
+        std::integral_constant<int, 1024> sixteen;
         if (waves == 2) {
             if (per_wave <= 1) launch(two, std::integral_constant<int, 1>{});
             else launch(two, std::integral_constant<int, 2>{});
@@ -1017,11 +1075,15 @@ extern "C" int32_t chipmunk_topk_cols(const float* cur, const float* prev, int R
             else if (per_wave <= 4) launch(four, std::integral_constant<int, 4>{});
             else if (per_wave <= 5) launch(four, std::integral_constant<int, 5>{});
             else launch(four, std::integral_constant<int, 7>{});
+        } else if (waves == 16) {
+            if (per_wave <= 5) launch(sixteen, std::integral_constant<int, 5>{});
+            else launch(sixteen, std::integral_constant<int, 6>{});
         } else {
             if (per_wave <= 4) launch(eight, std::integral_constant<int, 4>{});
             else if (per_wave <= 5) launch(eight, std::integral_constant<int, 5>{});
             else if (per_wave <= 6) launch(eight, std::integral_constant<int, 6>{});
-            else launch(eight, std::integral_constant<int, 7>{});
+            else if (per_wave <= 7) launch(eight, std::integral_constant<int, 7>{});
+            else launch(eight, std::integral_constant<int, 8>{});
         }
     } else if (plan_long_rows(C, k, &plan)) {
         auto kernel = plan.sample == 8192

@@ -194,6 +194,30 @@ def test_topk_of_rows_kept_in_registers(cm, oracle, C, kind):
             assert np.array_equal(counts.cpu().numpy(), ref_counts)
 
 
+@pytest.mark.parametrize("C", [14592, 14593, 16383, 16384, 16385, 20480, 20481, 24575, 24576, 24577])
+@pytest.mark.parametrize("kind", ["normal", "constant", "two_values", "few_ulps", "wide"])
+def test_topk_of_rows_kept_in_more_registers(cm, oracle, C, kind):
+    """Eight units of a wave, and sixteen waves, which take a row only where a third of it is kept."""
+    test_topk_of_rows_kept_in_registers(cm, oracle, C, kind)
+
+
+@pytest.mark.parametrize("C", [1024, 4000, 12288, 16384])
+@pytest.mark.parametrize("equal", [2, 300])
+def test_topk_of_ties_on_the_threshold(cm, oracle, C, equal):
+    """A few and many columns that equal the threshold, of which none but one, all but one and all are taken."""
+    rng = np.random.default_rng([27, C])
+    a = np.stack([rng.permutation(C) for _ in range(3)]).astype(np.float32)
+    above = C // 3                                          # columns above the shared score
+    a[(a >= C - above - equal) & (a < C - above)] = C - above - 1
+    cur = torch.from_numpy(a).to(DEV)
+    for k in (above, above + 1, above + equal - 1, above + equal, above + equal + 1):
+        idx = torch.full((3, k), -7, dtype=torch.int32, device=DEV)
+        counts = torch.full((3,), -7, dtype=torch.int32, device=DEV)
+        cm.topk_cols(cur, None, k, idx, counts)
+        ref_idx, _ = oracle.topk_cols(a, None, k, k_stride=k, idx_fill=-7)
+        assert np.array_equal(idx.cpu().numpy(), ref_idx), k
+
+
 @pytest.mark.parametrize("B,N,D,F,c,plan", [
     (1, 1, 128, 64, 128, (1, 2)),            # one token, one neuron tile half full, one piece, the high parts in two sums
     (1, 300, 512, 64, 128, (8, 2)),          # eight pieces of one step
