@@ -164,8 +164,7 @@ def test_dense_mlp_on_large_tiles(cm, oracle, B, N, D, F, c, act, bias, large):
 @pytest.mark.parametrize("C", [1, 3, 255, 257, 1024, 1025, 2049, 3073, 4096, 5121, 7168, 7169, 8192, 8193, 10241, 12288, 12289, 14336, 14337])
 @pytest.mark.parametrize("kind", ["normal", "constant", "two_values", "few_ulps", "spikes", "wide"])
 def test_topk_of_rows_kept_in_registers(cm, oracle, C, kind):
-    """Both sides of every limit between the instances (and of the long rows, which without previous scores and with few columns
-    kept begin at 12 289), on scores that halving the range of keys
+    """Both sides of every limit between the instances, on scores that halving the range of keys
     finds easy and on scores that it does not: one value, two, a range of a few ulps around a power of two, a few spikes
     over zeros of both signs, scores of both signs and all exponents with infinities.  Bit-exact, ties to the lower column."""
     rng = np.random.default_rng([25, C])
