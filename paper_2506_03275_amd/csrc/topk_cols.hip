@@ -409,8 +409,10 @@ __global__ __launch_bounds__(NT, U >= 6 && NT < 1024 ? 6 : 8) void topk_register
             top = max(top, s_set[0][i]);
             bottom = max(bottom, s_set[0][NW + i]);
         }
-        hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)top);
-        lo = ~(uint32_t)__builtin_amdgcn_readfirstlane((int)bottom);
+        // at least 1: an existing column whose bits are all ones, a NaN, may have the key of those that do not exist, which are
+        // never to be candidates (it is left out instead)
+        hi = max((uint32_t)__builtin_amdgcn_readfirstlane((int)top), 1u);
+        lo = max(~(uint32_t)__builtin_amdgcn_readfirstlane((int)bottom), 1u);
         flip = 1;
     }
     // invariant: at least k keys are >= lo (n_from of them), fewer than k are > hi (n_above of them)

@@ -1,0 +1,87 @@
+"""Where the top-k of rows kept in registers reads and writes, whatever bits the scores have: the kernel's own source run on the
+CPU (host_lanes.h), each access to the list of last keys checked, the rows of indices standing between guards.  A NaN is no
+score, so which columns such a row gives is open; that it stays inside its arrays is not."""
+import ctypes
+import os
+import re
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2506_03275_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def topk(tmp_path_factory):
+    out = tmp_path_factory.mktemp("lanes")
+    text = open(os.path.join(build.CSRC, "topk_cols.hip")).read()
+    text = text.replace('#include "common.h"', '#include "host_lanes.h"').replace("extern __shared__", "extern")
+    text, found = re.subn(r"__shared__ uint32_t s_last\[kLastKeys\];", "static lanes::Checked<uint32_t, kLastKeys> s_last;", text)
+    assert found == 1
+    (out / "topk.cpp").write_text(text)
+    subprocess.run([os.environ.get("HOSTCXX", "/opt/rocm/llvm/bin/clang++"), "-std=c++17", "-O1", "-w", "-shared", "-fPIC", "-I", HERE,
+                    "-I", os.path.join(HERE, "..", "include"), str(out / "topk.cpp"), "-o", str(out / "topk.so")], check=True)
+    lib = ctypes.CDLL(str(out / "topk.so"))
+    fn = lib.chipmunk_topk_cols
+    P, I, L = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64
+    fn.argtypes, fn.restype, fn.overruns = [P, P, I, I, L, I, P, P, I, P], ctypes.c_int32, lib.host_lanes_overruns
+    return fn
+
+
+def _aligned(shape):
+    raw = np.empty(int(np.prod(shape)) * 4 + 16, dtype=np.uint8)
+    at = -raw.ctypes.data % 16
+    return raw[at:at + int(np.prod(shape)) * 4].view(np.float32).reshape(shape)
+
+
+def _run(topk, bits, k):
+    R, C = bits.shape
+    ld = -(-C // 4) * 4
+    cur = _aligned((R, ld))
+    cur.view(np.uint32)[:, :C], cur.view(np.uint32)[:, C:] = bits, 0xffffffff
+    guard = 40960
+    idx, counts = np.full(guard + R * k + guard, -7, dtype=np.int32), np.full(R, -7, dtype=np.int32)
+    assert topk(cur.ctypes.data, None, R, C, ld, k, idx.ctypes.data + 4 * guard, counts.ctypes.data, k, None) == 0
+    assert topk.overruns() == 0
+    assert (idx[:guard] == -7).all() and (idx[guard + R * k:] == -7).all()
+    assert (counts == k).all()
+    return idx[guard:guard + R * k].reshape(R, k)
+
+
+def _scores(kind, C, rng):
+    """bits of two rows"""
+    any_bits = rng.integers(0, 2 ** 32, size=(2, C), dtype=np.uint32)
+    if kind == "any":
+        return any_bits
+    bits = rng.standard_normal((2, C)).astype(np.float32).view(np.uint32)
+    if kind == "one":
+        bits[:, C // 2] = 0xffffffff
+    elif kind == "most":
+        bits[:, C // 8:] = 0xffffffff
+    elif kind == "all":
+        bits[:] = 0xffffffff
+    return bits
+
+
+@pytest.mark.parametrize("C", [1, 5, 200, 257, 700, 1030, 5000, 16380])
+@pytest.mark.parametrize("kind", ["one", "most", "all", "any"])
+def test_rows_of_any_bits_stay_in_their_arrays(topk, C, kind):
+    bits = _scores(kind, C, np.random.default_rng([41, C]))
+    for k in sorted({1, -(-C // 3), max(C - 1, 1), C}):
+        idx = _run(topk, bits, k)
+        assert ((idx == -7) | ((idx >= 0) & (idx < C))).all()
+        for row in idx:                                      # what is written is ascending, without a gap in front
+            n = int((row != -7).sum())
+            assert (row[:n] != -7).all() and (np.diff(row[:n]) > 0).all()
+
+
+@pytest.mark.parametrize("C", [5, 200, 1030, 5000])
+def test_the_run_on_the_cpu_is_the_selection(topk, oracle, C):
+    bits = _scores("normal", C, np.random.default_rng([42, C]))
+    bits[1] = np.random.default_rng(43).choice(np.array([1., 2., -np.inf, 0.], dtype=np.float32), size=C).view(np.uint32)
+    for k in (1, C // 3 + 1, C):
+        ref, _ = oracle.topk_cols(bits.view(np.float32), None, k, k_stride=k, idx_fill=-7)
+        assert np.array_equal(_run(topk, bits, k), ref)
