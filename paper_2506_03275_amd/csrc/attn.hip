@@ -205,7 +205,7 @@ __device__ __forceinline__ void row16_sums_to_lds(float (&x)[8], float* part, in
         "v_add_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
         "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
         "v_add_f32_dpp %1, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa"
-        : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3])
+        : "+&v"(x[0]), "+&v"(x[1]), "+&v"(x[2]), "+&v"(x[3])   // written before the others are read
         : "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]));
     const bool b1 = l16 & 2;
     float z = (b1 ? x[1] : x[0]) + dpp_f32<0x1b>(b1 ? x[0] : x[1]);   // quad_perm 3,2,1,0

@@ -1,6 +1,7 @@
 """The dense GEMM kernels issue their products as inline assembly, so the compiler does not know how long a result takes: if
 it copied or spilled an accumulator inside the loop, it would read the register before the product has landed.  This compiles
-the kernels as the library is built and checks in their assembly that it does not, and what they keep in scratch memory."""
+the kernels as the library is built and checks in their assembly that it does not, and what they keep in scratch memory.  The
+exchange of the column sums is inline assembly as well: its operands are checked the same way."""
 import os
 import re
 import subprocess
@@ -98,3 +99,25 @@ def test_the_check_sees_what_it_is_for(assembly):
 def test_registers_in_scratch_memory(assembly):
     spills = re.findall(r"\.name:\s+_ZN\w*mlp_dense_gemm_kernelILi(\d+)ELi(\d+)E.*?\.vgpr_spill_count:\s*(\d+)", assembly, re.S)
     assert {(int(form), int(rows)): int(n) for form, rows, n in spills} == SPILLS
+
+
+def test_the_column_sums_exchange_keeps_its_inputs_apart(tmp_path):
+    """The exchange writes its first four values before it has read the other four.  Called with the second four equal to the
+    first, which the compiler sees, no input may share a register with what is written before it is read."""
+    text = open(os.path.join(build.CSRC, "attn.hip")).read()
+    start, end = text.index("template <int CTRL>\n"), text.index("// COLSUM (Alg. 4): also the tile's column sums")
+    (tmp_path / "exchange.hip").write_text('#include "%s"\nnamespace chipmunk {\n%s\n}\nusing namespace chipmunk;\n'
+        '__global__ void equal_halves(const float* in, float* out) {\n'
+        '    __shared__ float part[32];\n    float x[8];\n'
+        '    for (int i = 0; i < 4; i++) x[i] = x[i + 4] = in[threadIdx.x * 4 + i];\n'
+        '    row16_sums_to_lds(x, part, threadIdx.x >> 4, threadIdx.x & 15);\n    __syncthreads();\n'
+        '    out[threadIdx.x] = part[threadIdx.x & 31];\n}\n' % (os.path.join(build.CSRC, "common.h"), text[start:end]))
+    flags = [f for f in build.HIPCC_FLAGS if f != "-shared"]
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *flags, "--offload-device-only", "-S",
+                    str(tmp_path / "exchange.hip"), "-o", str(tmp_path / "exchange.s")], check=True, capture_output=True)
+    adds = [[int(r) for r in re.findall(r"\bv(\d+)", line)] for line in (tmp_path / "exchange.s").read_text().split("\n")
+            if re.match(r"\s*v_add_f32_dpp v\d+, v(\d+), v\1 row_(half_)?mirror\b", line)]
+    assert len(adds) == 12
+    written = {a[0] for a in adds[:4]}
+    assert len(written) == 4 and all(a[0] == a[1] for a in adds[:4])
+    assert not written & {a[1] for a in adds[4:8]}
