@@ -937,7 +937,10 @@ static FirstForm first_form(bool sparse, int B, int N, int D, int F, int c, int 
         small = price(small_dense, small_tiles, 64, steps);
     }
     const bool large_fits = sparse || B <= 65535;   // the dense form takes the batch from the second grid dimension
-    const bool small_fits = (small_tiles <= 128 || steps <= 14) && (!sparse || k_stride <= F / 2);
+    // a launch has fewer than 2^32 threads: 256 for each of the tiles of 64 x 64, up to six of which stand for one of the chunk's
+    const int64_t small_rows = sparse ? chunks * parts : (int64_t)B * ((N + kSmallTile - 1) / kSmallTile);
+    const bool small_launches = per_xcd(small_rows * cols(kSmallTile)) * 8 * 256 < 1LL << 32;
+    const bool small_fits = small_launches && (small_tiles <= 128 || steps <= 14) && (!sparse || k_stride <= F / 2);
     if (small_fits && small < chunk && (!large_fits || small < large)) return kFirstSmall;
     return large_fits && large < chunk ? kFirstLarge : kFirstChunk;
 }

@@ -129,6 +129,15 @@ def test_bad_arguments_are_rejected_without_a_launch(lib):
     assert tm(a, a, a, 1, 1024, 256, 1024, 100, a, 1 << 30, None) == -4
 
 
+@pytest.mark.parametrize("B,c,form", [(65400, 128, 2), (65600, 128, 0), (70000, 128, 0), (70000, 192, 0)])
+def test_first_gemm_takes_no_more_workgroups_than_a_launch_has(lib, B, c, form):
+    """A launch has fewer than 2^32 threads.  B sequences of 64 tokens with 16 384 neurons are 256 B tiles of 64 x 64, of 256 threads
+    each, beyond that limit from 65 536 sequences on, but half as many of 128 neurons."""
+    out = (ctypes.c_int64 * 6)()
+    lib.chipmunk_internal_mlp_tiles(B, 64, 128, 16384, c, 64, out)
+    assert out[0] == form
+
+
 @pytest.mark.parametrize("has_names", [False, True])
 def test_package_needs_no_private_names_of_torch(has_names):
     """The current stream is looked up the short way where torch has the names for it; without them the package imports and
