@@ -921,25 +921,15 @@ static FirstForm first_form(bool sparse, int B, int N, int D, int F, int c, int 
     const int64_t chunks = (int64_t)B * ((N + c - 1) / c);
     const int width = sparse ? k_stride : F;
     auto cols = [&](int tile) { return (int64_t)((width + tile - 1) / tile); };
-    // Short contractions of fewer than eight chunks with 64 column tiles or more are counted as if every chunk had an XCD to
-    // itself, which keeps them on the large tiles, where tests reach these: 700 x 1536 x 8192 45 us instead of 26.
-    const bool by_chunk = chunks < 8 && steps <= 24 && cols(kBN) >= 64;
-    const double chunk = price((sparse ? chunk_delta : chunk_dense)[at], by_chunk ? cols(kBN) : per_xcd(chunks * cols(kBN)), 32, steps);
-    double large, small;
-    int64_t small_tiles;
-    if (sparse) {
-        large = price(large_delta[at], by_chunk ? cols(kDenseTile) : per_xcd(chunks * cols(kDenseTile)), 32, steps);
-        small_tiles = per_xcd(chunks * parts * cols(kSmallTile));
-        small = price(small_delta, small_tiles, 64, steps);
-    } else {
-        large = price(large_dense, B * per_xcd((int64_t)((N + kDenseTile - 1) / kDenseTile) * cols(kDenseTile)), 32, steps);
-        small_tiles = by_chunk ? parts * cols(kSmallTile) : per_xcd((int64_t)B * ((N + kSmallTile - 1) / kSmallTile) * cols(kSmallTile));
-        small = price(small_dense, small_tiles, 64, steps);
-    }
+    const int64_t small_tiles = per_xcd((sparse ? chunks * parts : (int64_t)B * ((N + kSmallTile - 1) / kSmallTile)) * cols(kSmallTile));
+    const int64_t large_tiles = sparse ? per_xcd(chunks * cols(kDenseTile))
+                                       : B * per_xcd((int64_t)((N + kDenseTile - 1) / kDenseTile) * cols(kDenseTile));
+    const double chunk = price((sparse ? chunk_delta : chunk_dense)[at], per_xcd(chunks * cols(kBN)), 32, steps);
+    const double large = price(sparse ? large_delta[at] : large_dense, large_tiles, 32, steps);
+    const double small = price(sparse ? small_delta : small_dense, small_tiles, 64, steps);
     const bool large_fits = sparse || B <= 65535;   // the dense form takes the batch from the second grid dimension
     // a launch has fewer than 2^32 threads: 256 for each of the tiles of 64 x 64, up to six of which stand for one of the chunk's
-    const int64_t small_rows = sparse ? chunks * parts : (int64_t)B * ((N + kSmallTile - 1) / kSmallTile);
-    const bool small_launches = per_xcd(small_rows * cols(kSmallTile)) * 8 * 256 < 1LL << 32;
+    const bool small_launches = small_tiles * 8 * 256 < 1LL << 32;
     const bool small_fits = small_launches && (small_tiles <= 128 || steps <= 14) && (!sparse || k_stride <= F / 2);
     if (small_fits && small < chunk && (!large_fits || small < large)) return kFirstSmall;
     return large_fits && large < chunk ? kFirstLarge : kFirstChunk;

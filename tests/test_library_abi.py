@@ -138,6 +138,16 @@ def test_first_gemm_takes_no_more_workgroups_than_a_launch_has(lib, B, c, form):
     assert out[0] == form
 
 
+@pytest.mark.parametrize("N,D,F,c,form", [(700, 1536, 8192, 192, 0), (600, 1536, 8192, 192, 0), (506, 1152, 8512, 192, 0),
+                                          (525, 768, 8512, 128, 2), (922, 896, 8320, 192, 2)])
+def test_first_gemm_of_few_chunks_and_many_neurons(lib, N, D, F, c, form):
+    """Fewer than eight chunks are priced by the tiles that an XCD gets, like any other number: not 256 x 256 tiles here, which
+    take 8 to 31 per cent longer."""
+    out = (ctypes.c_int64 * 6)()
+    lib.chipmunk_internal_mlp_tiles(1, N, D, F, c, 1, out)
+    assert out[0] == form
+
+
 @pytest.mark.parametrize("has_names", [False, True])
 def test_package_needs_no_private_names_of_torch(has_names):
     """The current stream is looked up the short way where torch has the names for it; without them the package imports and
