@@ -389,23 +389,33 @@ struct Gemm2Params {
 
 // The deferred write-back of chunk u's new activations, by a workgroup of 256 threads.  These workgroups have the highest ids,
 // so they start when the tile workgroups' last round leaves compute units free, and their memory traffic runs beside that
-// round's products.
+// round's products.  Bound: the round trips of a thread, beyond the XCD's L2 where another XCD ran the chunk's first GEMM, so a
+// thread requests four cells before it stores the first.  Whole calls in us, one cell at a time and four: 16 chunks of 128 x 2000
+// of 4096 x 1024 93.1, 58.5 (72.6 while a chunk stayed on its XCD); 24 of 192 x 1229 of 12 288 x 3072 123.5, 97.2; 94 x 967 of
+// 13 824 x 5120 494, 470.
 __device__ __forceinline__ void write_back_activations(const Gemm2Params& p, int u, int c) {
+    constexpr int AHEAD = 4;
     const int ub = u / p.NB, urow0 = (u % p.NB) * c;
-    const int ucount = max(min(p.counts[u], p.k_stride), 0);
-    const int cells = c / 8;
-    for (int item = threadIdx.x; item < ucount * cells; item += 256) {
-        const int s = item / cells, ch = item - s * cells;
-        const int tok0 = urow0 + ch * 8;
-        const int nvalid = min(8, p.N - tok0);
-        if (nvalid <= 0) continue;
-        const int f = min(max(p.idx[(int64_t)u * p.k_stride + s], 0), p.F - 1);
-        const u32x4 a8 = *reinterpret_cast<const u32x4*>(p.act_t + ((int64_t)u * p.k_pad + s) * c + ch * 8);
-        uint16_t* arow = p.a_cache + ((int64_t)ub * p.F + f) * p.a_ld + tok0;
-        if (nvalid == 8) {
-            *reinterpret_cast<u32x4*>(arow) = a8;
-        } else {  // the cells past N in the last chunk stay as they are
-            for (int e = 0; e < nvalid; e++) arow[e] = (uint16_t)(a8[e >> 1] >> (16 * (e & 1)));
+    const int cells = c / 8, n = max(min(p.counts[u], p.k_stride), 0) * cells;
+    for (int first = threadIdx.x; first < n; first += 256 * AHEAD) {
+        int f[AHEAD];
+        u32x4 a8[AHEAD];
+#pragma unroll
+        for (int i = 0; i < AHEAD; i++) {
+            const int item = min(first + i * 256, n - 1), s = item / cells, ch = item - s * cells;
+            f[i] = p.idx[(int64_t)u * p.k_stride + s];
+            a8[i] = *reinterpret_cast<const u32x4*>(p.act_t + ((int64_t)u * p.k_pad + s) * c + ch * 8);
+        }
+#pragma unroll
+        for (int i = 0; i < AHEAD; i++) {
+            const int item = first + i * 256, tok0 = urow0 + item % cells * 8;
+            const int nvalid = item < n ? min(8, p.N - tok0) : 0;
+            uint16_t* arow = p.a_cache + ((int64_t)ub * p.F + min(max(f[i], 0), p.F - 1)) * p.a_ld + tok0;
+            if (nvalid == 8) {
+                *reinterpret_cast<u32x4*>(arow) = a8[i];
+            } else {  // the cells past N in the last chunk stay as they are
+                for (int e = 0; e < nvalid; e++) arow[e] = (uint16_t)(a8[i][e >> 1] >> (16 * (e & 1)));
+            }
         }
     }
 }

@@ -224,7 +224,9 @@ __global__ __launch_bounds__(256, 2) void mlp_small_gemm2_kernel(Gemm2Params p) 
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wt = w >> 1, wc = w & 1, g = lane >> 4, l16 = lane & 15;
     if (SPARSE && p.act_t && (int)blockIdx.x >= p.tile_blocks) {
-        write_back_activations(p, (int)blockIdx.x - p.tile_blocks, p.parts * kSmallTile);
+        // (the chunk's size a constant in each call: the loop divides by it)
+        if (p.parts == 3) write_back_activations(p, (int)blockIdx.x - p.tile_blocks, 192);
+        else write_back_activations(p, (int)blockIdx.x - p.tile_blocks, 128);
         return;
     }
     int unit, part, col_tile;
