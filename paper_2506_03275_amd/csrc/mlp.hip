@@ -913,6 +913,8 @@ static double price(const Price& p, int64_t tiles_per_xcd, int slots, int steps)
     return p.call + (p.step * steps + p.end) * ((double)(tiles_per_xcd / slots) + share);
 }
 static int64_t per_xcd(int64_t tiles) { return (tiles + 7) / 8; }
+// A launch has fewer than 2^32 threads: 256 for each of the tiles of 64 x 64, up to six of which stand for one of the chunk's.
+static bool small_launches(int64_t tiles_per_xcd) { return tiles_per_xcd * 8 * 256 < 1LL << 32; }
 
 enum FirstForm { kFirstChunk = 0, kFirstLarge = 1, kFirstSmall = 2 };   // 128 neurons of a chunk; 256 (dense: and 256 tokens); 64 x 64
 // Kernel times (chunk, large, small), us: delta, c = 192, 9 chunks x 395 of 7488 x 4864: 44, 83, 19; 47 x 1229 of 12 288 x 3072: 96, 82,
@@ -938,9 +940,7 @@ static FirstForm first_form(bool sparse, int B, int N, int D, int F, int c, int 
     const double large = price(sparse ? large_delta[at] : large_dense, large_tiles, 32, steps);
     const double small = price(sparse ? small_delta : small_dense, small_tiles, 64, steps);
     const bool large_fits = sparse || B <= 65535;   // the dense form takes the batch from the second grid dimension
-    // a launch has fewer than 2^32 threads: 256 for each of the tiles of 64 x 64, up to six of which stand for one of the chunk's
-    const bool small_launches = small_tiles * 8 * 256 < 1LL << 32;
-    const bool small_fits = small_launches && (small_tiles <= 128 || steps <= 14) && (!sparse || k_stride <= F / 2);
+    const bool small_fits = small_launches(small_tiles) && (small_tiles <= 128 || steps <= 14) && (!sparse || k_stride <= F / 2);
     if (small_fits && small < chunk && (!large_fits || small < large)) return kFirstSmall;
     return large_fits && large < chunk ? kFirstLarge : kFirstChunk;
 }
@@ -983,10 +983,12 @@ static SecondPlan second_plan(bool sparse, int B, int N, int D, int F, int c, in
     };
     consider({kSecondChunk, 0}, price(part, tiles * parts, 64, steps));
     if (sparse) {
-        if ((k_stride + kBN - 1) / kBN * kBN <= kSmallList)
-            consider({kSecondSmall, 0}, price(small_delta, per_xcd(chunks * parts * (D / kSmallTile)), 64, steps));
+        const int64_t small_tiles = per_xcd(chunks * parts * (D / kSmallTile));
+        if (small_launches(small_tiles) && (k_stride + kBN - 1) / kBN * kBN <= kSmallList)
+            consider({kSecondSmall, 0}, price(small_delta, small_tiles, 64, steps));
     } else {
-        consider({kSecondSmall, 0}, price(small_dense, per_xcd((int64_t)B * ((N + kSmallTile - 1) / kSmallTile) * (D / kSmallTile)), 64, steps));
+        const int64_t small_tiles = per_xcd((int64_t)B * ((N + kSmallTile - 1) / kSmallTile) * (D / kSmallTile));
+        if (small_launches(small_tiles)) consider({kSecondSmall, 0}, price(small_dense, small_tiles, 64, steps));
         if (B <= 65535)
             consider({kSecondLarge, 0}, price(large_dense, B * per_xcd((int64_t)((N + kDenseTile - 1) / kDenseTile) * ((D + kDenseTile - 1) / kDenseTile)), 32, steps));
     }

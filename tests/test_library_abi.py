@@ -138,6 +138,16 @@ def test_first_gemm_takes_no_more_workgroups_than_a_launch_has(lib, B, c, form):
     assert out[0] == form
 
 
+@pytest.mark.parametrize("B,N,D,F,c,form", [(1 << 19, 1, 1024, 64, 192, 2), (1 << 20, 1, 1024, 64, 192, 0), (1 << 18, 60, 4096, 128, 192, 0),
+                                            (1 << 18, 64, 4096, 8192, 128, 0), (1 << 20, 1, 1024, 4096, 128, 0)])
+def test_second_gemm_takes_no_more_workgroups_than_a_launch_has(lib, B, N, D, F, c, form):
+    """The same for the dense MLP's second GEMM: B sequences of up to 64 tokens are B D / 64 tiles of 64 x 64, half as many of 128
+    columns."""
+    out = (ctypes.c_int64 * 6)()
+    lib.chipmunk_internal_mlp_tiles(B, N, D, F, c, 64, out)
+    assert out[1] == form
+
+
 @pytest.mark.parametrize("N,D,F,c,form", [(700, 1536, 8192, 192, 0), (600, 1536, 8192, 192, 0), (506, 1152, 8512, 192, 0),
                                           (525, 768, 8512, 128, 2), (922, 896, 8320, 192, 2)])
 def test_first_gemm_of_few_chunks_and_many_neurons(lib, N, D, F, c, form):
