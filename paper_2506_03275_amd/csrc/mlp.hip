@@ -436,6 +436,14 @@ __device__ __forceinline__ void load_buffer_to_lds_4B(i32x4 buffer, uint32_t byt
                  : "memory");
 }
 
+// the same buffer `bytes` further on
+__device__ __forceinline__ i32x4 buffer_moved_on(i32x4 buffer, uint32_t bytes) {
+    const uint64_t base = ((uint64_t)(uint32_t)buffer[1] << 32 | (uint32_t)buffer[0]) + bytes;
+    buffer[0] = (int)(uint32_t)base;
+    buffer[1] = (int)(uint32_t)(base >> 32);
+    return buffer;
+}
+
 constexpr int kGemm2K = 32;   // contraction tile of the second GEMM
 template <int ROWS>
 struct Gemm2Shape {           // of a workgroup that owns ROWS token rows
@@ -455,7 +463,8 @@ struct Gemm2Shape {           // of a workgroup that owns ROWS token rows
 // drained at the head of every step, a CU had 40 KB in flight on average and took 10 TB/s into LDS.  Whole deltas in us, two
 // buffers and this ring: 394 chunks x 968 of 13 824 x 5120 1860 -> 1785, 24 x 1229 of 12 288 x 3072 101 -> 96.5, c = 128: 1350 x
 // 442 of 6144 x 2944 1440 -> 1324; dense, 11 chunks of 128 x 2176 x 5760: 120 -> 104.
-template <int BM, int ROWS, bool DENSE, bool STREAM>
+// LONG: a chunk's rows of A^T may be more than 32 bits of bytes.
+template <int BM, int ROWS, bool DENSE, bool STREAM, bool LONG>
 __device__ __forceinline__ void gemm2_rows(const Gemm2Params& p, int unit, int part, int col_tile) {
     typedef Gemm2Shape<ROWS> Shape;
     constexpr int NS = Shape::kStages, SLOTS = Shape::kListSlots, STAGE = Shape::kStage;
@@ -482,10 +491,12 @@ __device__ __forceinline__ void gemm2_rows(const Gemm2Params& p, int unit, int p
 
     // A^T source: row (selected slot or neuron) -> tokens of this chunk
     const int64_t a_row = DENSE ? p.a_ld : BM;     // elements between consecutive contraction rows
-    const i32x4 abuf = DENSE ? raw_buffer_words(p.a_t + (int64_t)b * p.F * p.a_ld, (uint32_t)p.F * (uint32_t)p.a_ld * 2u)
-                             : raw_buffer_words(p.a_t + (int64_t)unit * p.k_pad * BM, (uint32_t)p.k_pad * BM * 2u);
+    i32x4 abuf = DENSE ? raw_buffer_words(p.a_t + (int64_t)b * p.F * p.a_ld, (uint32_t)p.F * (uint32_t)p.a_ld * 2u)
+                       : raw_buffer_words(p.a_t + (int64_t)unit * p.k_pad * BM, LONG ? 0xffffffffu : (uint32_t)p.k_pad * BM * 2u);
     const i32x4 wbuf = raw_buffer_words(p.w2, (uint32_t)p.F * p.D * 2u);
     const i32x4 ibuf = DENSE ? wbuf : raw_buffer_words(p.idx + (int64_t)unit * p.k_stride, (uint32_t)p.k_stride * 4u);
+    constexpr int kMove = 1 << 17;                 // LONG: the steps' offsets count from `moved`, which follows in steps this far apart
+    int moved = 0;
     const uint32_t astep = (uint32_t)(kGemm2K * a_row * 2), wstep = DENSE ? (uint32_t)(kGemm2K * p.D * 2) : 0u;
     uint32_t aoff[NIA], woff[NIW];
 #pragma unroll
@@ -521,7 +532,7 @@ __device__ __forceinline__ void gemm2_rows(const Gemm2Params& p, int unit, int p
     // one of the NIA + NIW transfers of step t into stage t % NS
     auto request_piece = [&](int t, uint32_t stage, int j) {
         if (j < NIA) {
-            load_buffer_to_lds_16B(abuf, aoff[j], (uint32_t)t * astep, stage + (uint32_t)((j * 4 + w) * 1024));
+            load_buffer_to_lds_16B(abuf, aoff[j], (uint32_t)(t - moved) * astep, stage + (uint32_t)((j * 4 + w) * 1024));
         } else {
             const int i = j - NIA;
             const uint32_t row = DENSE ? 0u : (uint32_t)min(max((int)row_at[i], 0), p.F - 1) * (uint32_t)(p.D * 2);
@@ -630,9 +641,15 @@ __device__ __forceinline__ void gemm2_rows(const Gemm2Params& p, int unit, int p
         here = there;
     };
     int t = 0;
-    for (; t + NS + 1 < steps; t += 2) {
-        step(std::false_type{}, t, even, odd);
-        step(std::false_type{}, t + 1, odd, even);
+    for (;;) {
+        const int end = LONG ? min(steps, moved + kMove + NS + 1) : steps;
+        for (; t + NS + 1 < end; t += 2) {
+            step(std::false_type{}, t, even, odd);
+            step(std::false_type{}, t + 1, odd, even);
+        }
+        if (!LONG || end == steps) break;          // (a move at every step: 75 600 x 5120 x 7 % 1740 -> 1752 us; like this 1735)
+        abuf = buffer_moved_on(abuf, kMove * astep);
+        moved = t;
     }
     if (t + NS < steps) {
         step(std::false_type{}, t, even, odd);
@@ -742,11 +759,11 @@ __global__ __launch_bounds__(256, 2) void mlp_gemm2_kernel(Gemm2Params p) {
         return;
     if constexpr (PARTS) {
         if (beyond >= 0) {
-            gemm2_rows<BM, 64, DENSE, STREAM>(p, unit, beyond % parts, col_tile);
+            gemm2_rows<BM, 64, DENSE, STREAM, false>(p, unit, beyond % parts, col_tile);
             return;
         }
     }
-    gemm2_rows<BM, BM, DENSE, STREAM>(p, unit, 0, col_tile);
+    gemm2_rows<BM, BM, DENSE, STREAM, !DENSE && !PARTS>(p, unit, 0, col_tile);
 }
 
 }  // namespace chipmunk
@@ -970,8 +987,9 @@ static SecondPlan second_plan(bool sparse, int B, int N, int D, int F, int c, in
     const Price& whole = (sparse ? whole_delta : whole_dense)[at];
     const Price& part = (sparse ? parts_delta : parts_dense)[at];
     SecondPlan plan = {kSecondChunk, tiles};
-    double best;
+    if (sparse && ((int64_t)k_stride + kBN - 1) / kBN * kBN * c * 2 >= 1LL << 32) return plan;   // whole chunks only: more bytes than the parts' offsets hold
     const int64_t last = tiles % 64;
+    double best;
     if (tiles > 64 && last > 0 && last * parts <= 32) {
         plan.whole = tiles - last;
         best = price(whole, tiles - last, 64, steps) + price(part, last * parts, 64, steps) - part.call;

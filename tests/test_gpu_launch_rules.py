@@ -516,3 +516,27 @@ def test_voxel_rows_and_permutation_in_one_launch(cm, oracle, geom, batch, words
     perm.fill_(-1)
     cm.voxel_reorder(dst, back, perm, None, npre, T, H, W, nsuf, vt, vh, vw, inverse=True)
     assert torch.equal(back.view(bits), src.view(bits)) and np.array_equal(perm.cpu().numpy(), perm_ref)
+
+
+def test_mlp_delta_of_more_neurons_than_32_bits_of_bytes(cm, oracle):
+    """A chunk's rows in the second GEMM take k c 2 bytes: here 32 768 more than 2^32.  Only the last 256 neurons reach the output."""
+    N, D, c, last = 8, 128, 192, 256
+    F = k = (2 ** 32 // (2 * c) // 128 + 1) * 128
+    assert k * c * 2 > 2 ** 32
+    g = si.generator(42, DEV)
+    w1, w2 = (torch.empty((F, D), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    for r in range(0, F, 1 << 21):
+        w1[r:r + (1 << 21)].copy_(si.randn_bf16((min(1 << 21, F - r), D), g, D ** -0.5))
+    w2.zero_()
+    w2[-last:] = si.randn_bf16((last, D), g, last ** -0.5)
+    x, o_cache = si.randn_bf16((1, N, D), g), si.randn_bf16((1, N, D), g)
+    a_cache = torch.zeros((1, F, 8), dtype=torch.bfloat16, device=DEV)
+    idx = torch.arange(F, dtype=torch.int32, device=DEV).view(1, 1, F)
+    counts = torch.full((1, 1), k, dtype=torch.int32, device=DEV)
+    o_ref, a_ref = si.np_f32(o_cache).astype(np.float64), np.zeros((1, last, 8))
+    o_before = o_ref.copy()
+    cm.mlp_sparse_delta(x, w1, None, w2, idx, counts, a_cache, o_cache, c, 1, _u8(cm.mlp_workspace_bytes(1, N, D, F, c, k)))
+    oracle.mlp_sparse_delta(si.np_f32(x), si.np_f32(w1[-last:]), np.zeros(last, dtype=np.float32), si.np_f32(w2[-last:]),
+                            np.arange(last, dtype=np.int32).reshape(1, 1, last), np.array([[last]], dtype=np.int32), a_ref, o_ref, c, 1)
+    assert rel_err(si.np_f32(a_cache[:, -last:].contiguous()), a_ref) <= REL_TOL
+    assert rel_err(si.np_f32(o_cache), o_ref, o_ref - o_before) <= REL_TOL
