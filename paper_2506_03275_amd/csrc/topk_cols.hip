@@ -339,6 +339,13 @@ __global__ __launch_bounds__(NT, U >= 6 && NT < 1024 ? 6 : 8) void topk_register
                                                                             int k, int32_t* __restrict__ idx,
                                                                             int32_t* __restrict__ counts, int k_stride) {
     constexpr int NW = NT / 64;
+    // Keys of both signs, or of many octaves, span almost all 32 bits, of which five or six steps find only the exponent of the
+    // threshold.  Halving between the scores finds it in one to three, unless the threshold is near zero in a wide range (most of
+    // the row kept); at most eight times, so that no row takes more than 40 steps.  Normal scores, a tenth kept, us in the long
+    // rows' kernel, by keys alone, like this: 768 x 14 400 24.2, 26.6, 22.3; 300 x 14 400 18.4, 19.1, 15.9; 14 448 x 16 384 346, 336,
+    // 269; column sums (five octaves) as before.  In the instances of shorter rows, where keys alone were never the slower,
+    // the second loop would cost column sums 2 to 5 %.
+    constexpr bool kByValue = !HAS_PREV && NT == 512 && U >= 7;
     __shared__ __attribute__((aligned(16))) uint32_t s_set[2][2 * NW];   // per-wave totals, two sets used in turn
     __shared__ uint32_t s_last[kLastKeys];
     __shared__ uint32_t s_found[4];                                      // threshold, how many to take of those equal to it; candidates; equal
@@ -417,9 +424,7 @@ __global__ __launch_bounds__(NT, U >= 6 && NT < 1024 ? 6 : 8) void topk_register
     }
     // invariant: at least k keys are >= lo (n_from of them), fewer than k are > hi (n_above of them)
     uint32_t n_from = (uint32_t)C, n_above = 0;
-#pragma unroll 1
-    while (lo != hi && n_from - n_above > (uint32_t)kLastKeys) {
-        const uint32_t pivot = hi - ((hi - lo) >> 1);   // lo < pivot <= hi
+    auto keys_from = [&](uint32_t pivot) -> uint32_t {
         // three keys of four counted by the vector unit (a comparison and an addition), one by a comparison and the scalar unit
         uint32_t n = 0, n_scalar = 0;
 #pragma unroll
@@ -436,6 +441,27 @@ __global__ __launch_bounds__(NT, U >= 6 && NT < 1024 ? 6 : 8) void topk_register
         for (int i = 0; i < NW; i++) n += s_set[flip][i];
         n = (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
         flip ^= 1;
+        return n;
+    };
+    if (kByValue && (int64_t)k * 5 <= (int64_t)C * 2) {
+#pragma unroll 1
+        for (int i = 0; i < 8 && hi - lo > 1u << 26 && n_from - n_above > (uint32_t)kLastKeys; i++) {
+            const uint32_t middle = key_of_score(0.5f * score_of_key(lo) + 0.5f * score_of_key(hi));
+            const uint32_t pivot = min(max((uint32_t)__builtin_amdgcn_readfirstlane((int)middle), lo + 1u), hi);
+            const uint32_t n = keys_from(pivot);
+            if (n >= (uint32_t)k) {
+                lo = pivot;
+                n_from = n;
+            } else {
+                hi = pivot - 1;
+                n_above = n;
+            }
+        }
+    }
+#pragma unroll 1
+    while (lo != hi && n_from - n_above > (uint32_t)kLastKeys) {
+        const uint32_t pivot = hi - ((hi - lo) >> 1);   // lo < pivot <= hi
+        const uint32_t n = keys_from(pivot);
         if (n >= (uint32_t)k) {
             lo = pivot;
             n_from = n;

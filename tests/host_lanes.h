@@ -168,3 +168,4 @@ extern "C" int host_lanes_overruns() {   // since the last call of it
     lanes::overruns = 0;
     return n;
 }
+extern "C" int host_lanes_barriers() { return (int)lanes::barrier.round; }   // that the last workgroup passed

@@ -28,6 +28,7 @@ def topk(tmp_path_factory):
     fn = lib.chipmunk_topk_cols
     P, I, L = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64
     fn.argtypes, fn.restype, fn.overruns = [P, P, I, I, L, I, P, P, I, P], ctypes.c_int32, lib.host_lanes_overruns
+    fn.barriers = lib.host_lanes_barriers
     return fn
 
 
@@ -85,3 +86,25 @@ def test_the_run_on_the_cpu_is_the_selection(topk, oracle, C):
     for k in (1, C // 3 + 1, C):
         ref, _ = oracle.topk_cols(bits.view(np.float32), None, k, k_stride=k, idx_fill=-7)
         assert np.array_equal(_run(topk, bits, k), ref)
+
+
+@pytest.mark.parametrize("C", [12300, 14400, 16384])
+@pytest.mark.parametrize("kind", ["normal", "cauchy", "octaves", "infinite", "few"])
+def test_wide_ranges_are_halved_between_the_scores_first(topk, oracle, C, kind):
+    """Rows of seven and eight units a wave with 40 per cent kept and fewer, and one more: scores of both signs and of many octaves."""
+    rng = np.random.default_rng([44, C])
+    scores = rng.standard_normal((2, C))
+    if kind == "cauchy":
+        scores /= rng.standard_normal((2, C))
+    elif kind == "octaves":
+        scores = np.exp(20 * scores)
+    elif kind == "infinite":
+        scores[:, ::7], scores[1, 1::9], scores[0, 5] = -np.inf, np.inf, 3e38
+    elif kind == "few":
+        scores = rng.choice(np.array([-3e38, -1.5, -0.0, 0.0, 1e-40, 2.0, 3e38]), size=(2, C))
+    scores = scores.astype(np.float32)
+    for k in (1, C // 10, C * 2 // 5, C * 2 // 5 + 1):
+        ref, _ = oracle.topk_cols(scores, None, k, k_stride=k, idx_fill=-7)
+        assert np.array_equal(_run(topk, scores.view(np.uint32), k), ref)
+        if kind == "normal" and k == C // 10:   # a barrier a step: fifteen and more by halving the keys alone
+            assert topk.barriers() <= 12
