@@ -1121,6 +1121,9 @@ extern "C" int32_t chipmunk_attn_dense_colsum_stale(const uint16_t* q, const uin
     return launch_attn_fused(p, E, units, (hipStream_t)stream);
 }
 
+// Whether a refresh takes two launches; for the tests, like the next.
+extern "C" int32_t chipmunk_internal_attn_refresh_apart(int B, int H, int N, int c) { return refresh_apart((int64_t)B * H * ((N + c - 1) / c), N); }
+
 // What the rules above choose for these sizes: the rows of a workgroup that takes a whole chunk, the chunks that have one, the
 // chunks walked by a workgroup per 64 rows, and the pieces of the column-sum pass.  Not part of the library's interface:
 // for the tests, which have to reach each form and otherwise would not see that a rule has moved.

@@ -41,6 +41,14 @@ def _mlp_form(cm, B, N, D, F, c, k=1):
     return [bool(v) for v in out[:3]], tuple(out[3:])
 
 
+def _mlp_tiles(cm, B, N, D, F, c, k):
+    """dense: form of the first GEMM (0 a chunk's tiles, 1 large, 2 of 64 x 64), of the second (the same) and tiles per XCD taken
+    whole; then the delta's"""
+    out = (ctypes.c_int64 * 6)()
+    cm.load().chipmunk_internal_mlp_tiles(B, N, D, F, c, k, out)
+    return list(out)
+
+
 def _u8(nbytes):
     return torch.empty(max(int(nbytes), 16), dtype=torch.uint8, device=DEV)
 
@@ -51,7 +59,8 @@ def _u8(nbytes):
                                            (1, 15, 1535, 192, False), (1, 11, 2101, 192, False)])
 def test_refresh_in_one_kernel_and_apart(cm, oracle, B, H, N, E, c, apart):
     """Both sides of the rule, statistics updated in place.  Apart, the sums and the output are those of the two entry points
-    that make them alone, bit by bit; the one kernel's are rounded differently, which also shows which was taken."""
+    that make them alone, bit by bit; the one kernel's are rounded differently."""
+    assert bool(cm.load().chipmunk_internal_attn_refresh_apart(B, H, N, c)) == apart
     (q1, k1, _), (q2, k2, v), _ = si.attn_steps(B, H, N, E, 38, DEV)
     scale, NB, ld = 1 / math.sqrt(E), -(-N // c), -(-N // 4) * 4 + 4
     m_ref, l_ref = oracle.attn_row_stats(si.np_f32(q1), si.np_f32(k1), scale)
@@ -322,11 +331,18 @@ def test_unchanged_input_leaves_the_caches_alone(cm, B, N, D, F, c, k, large, wi
     assert torch.equal(a_cache, a_before) and torch.equal(out, o_before)
 
 
-@pytest.mark.parametrize("B,N,D,F,c,k", [(1, 100, 384, 320, 128, 200), (1, 7 * 128 - 5, 256, 512, 128, 140), (1, 9 * 192, 128, 640, 192, 300),
-                                         (3, 5 * 128 - 60, 640, 256, 128, 256), (1, 17 * 192 - 1, 256, 448, 192, 65)])
-def test_mlp_of_any_number_of_chunks(cm, oracle, B, N, D, F, c, k):
-    """1, 7, 9, 15 and 17 chunks: the tiles of the chunks beyond a multiple of eight are dealt out over the XCDs one by one, in the
+@pytest.mark.parametrize("B,N,D,F,c,k,tiles", [
+    (1, 100, 384, 320, 128, 200, [2, 2, 0, 0, 2, 0]), (1, 7 * 128 - 5, 256, 512, 128, 140, [2, 2, 0, 2, 2, 0]),
+    (1, 9 * 192, 128, 640, 192, 300, [2, 2, 0, 2, 2, 0]), (3, 5 * 128 - 60, 640, 256, 128, 256, [2, 2, 0, 0, 2, 0]),
+    (1, 17 * 192 - 1, 256, 448, 192, 65, [2, 2, 0, 2, 2, 0]),
+    # and on the chunk's tiles in all four GEMMs
+    (1, 7 * 192 - 5, 3328, 2560, 192, 1372, [0, 0, 23, 0, 0, 23]), (1, 14 * 128 - 5, 2432, 1344, 128, 785, [0, 0, 34, 0, 0, 34]),
+    (1, 15 * 192 - 5, 1664, 1152, 192, 642, [0, 0, 25, 0, 0, 25]), (1, 55 * 192 - 5, 512, 512, 192, 348, [0, 0, 28, 0, 0, 28]),
+    (3, 53 * 128 - 5, 384, 128, 128, 89, [0, 0, 60, 0, 0, 60])])
+def test_mlp_of_any_number_of_chunks(cm, oracle, B, N, D, F, c, k, tiles):
+    """1 to 159 chunks, none a multiple of eight: the tiles of the chunks beyond one are dealt out over the XCDs one by one, in the
     sparse and in the dense form, each exactly once."""
+    assert _mlp_tiles(cm, B, N, D, F, c, k) == tiles
     x1, x2, w1, b1, w2, b2 = recipes.mlp_inputs(B, N, D, F, 31, DEV)
     NB, a_ld = -(-N // c), -(-N // 8) * 8
     out = torch.empty_like(x1)
@@ -346,12 +362,14 @@ def test_mlp_of_any_number_of_chunks(cm, oracle, B, N, D, F, c, k):
     assert rel_err(si.np_f32(out), o_ref, o_ref - o_before) <= REL_TOL
 
 
-@pytest.mark.parametrize("c", [128, 192])
-def test_mlp_second_gemm_at_the_ends_of_its_ring(cm, oracle, c):
-    """Lists of 0 to 13 steps of 32 neurons, on both sides of a step's edge, and dense contractions of 2 to 10 steps: fewer steps
-    than the ring has stages, as many, more, odd and even."""
-    counts_of = [0, 1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 224, 257, 288, 320, 400]
-    B, N, D, F, k = 1, len(counts_of) * c - 37, 256, 448, 400
+@pytest.mark.parametrize("c,chunks,tiles", [(128, 22, [2, 0]), (192, 22, [2, 0]),      # of 64 x 64
+                                            (128, 132, [0, 33]), (192, 90, [0, 23])])   # whole chunks: four stages, three
+def test_mlp_second_gemm_at_the_ends_of_its_ring(cm, oracle, c, chunks, tiles):
+    """Lists of 0 to 14 steps of 32 neurons, on both sides of a step's edge: fewer steps than the ring has stages, as many, more, odd
+    and even."""
+    counts_of = [0, 1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 224, 257, 288, 320, 400, 417, 448]
+    B, N, D, F, k = 1, chunks * c - 37, 256, 512, 448
+    assert _mlp_tiles(cm, B, N, D, F, c, k)[4:] == tiles
     _, x2, w1, b1, w2, _ = recipes.mlp_inputs(B, N, D, F, 32, DEV)
     NB, a_ld = -(-N // c), -(-N // 8) * 8
     g = si.generator(32, DEV)
@@ -359,7 +377,7 @@ def test_mlp_second_gemm_at_the_ends_of_its_ring(cm, oracle, c):
     o_ref, a_ref = (si.np_f32(t).astype(np.float64) for t in (o_cache, a_cache))
     o_before = o_ref.copy()
     idx, _ = recipes.mlp_indices(NB, F, k, 32, DEV)
-    counts = torch.tensor(counts_of, dtype=torch.int32, device=DEV)
+    counts = torch.tensor([counts_of[i % len(counts_of)] for i in range(NB)], dtype=torch.int32, device=DEV)
     idx, counts = idx.view(B, NB, k), counts.view(B, NB)
     ws = torch.full((cm.mlp_workspace_bytes(B, N, D, F, c, k),), 255, dtype=torch.uint8, device=DEV)   # NaN wherever nothing is written
     cm.mlp_sparse_delta(x2, w1, b1, w2, idx, counts, a_cache, o_cache, c, 1, ws)
@@ -367,20 +385,22 @@ def test_mlp_second_gemm_at_the_ends_of_its_ring(cm, oracle, c):
                             a_ref, o_ref, c, 1)
     assert rel_err(si.np_f32(a_cache)[..., :N], a_ref[..., :N]) <= REL_TOL
     assert rel_err(si.np_f32(o_cache), o_ref, o_ref - o_before) <= REL_TOL
-    for F in (64, 128, 192, 320):
-        x, _, w1, b1, w2, b2 = recipes.mlp_inputs(1, 333, 128, F, 33, DEV)
-        out, a = torch.empty_like(x), torch.zeros((1, F, 336), dtype=torch.bfloat16, device=DEV)
-        cm.mlp_dense(x, w1, b1, w2, b2, out, a, c, 1)
-        ref, _, _ = oracle.mlp_dense(si.np_f32(x), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2), si.np_f32(b2), c, 1, a_ld=336)
-        assert rel_err(si.np_f32(out), ref) <= REL_TOL
 
 
-def _mlp_tiles(cm, B, N, D, F, c, k):
-    """dense: form of the first GEMM (0 a chunk's tiles, 1 large, 2 of 64 x 64), of the second (the same) and tiles per XCD taken
-    whole; then the delta's"""
-    out = (ctypes.c_int64 * 6)()
-    cm.load().chipmunk_internal_mlp_tiles(B, N, D, F, c, k, out)
-    return list(out)
+@pytest.mark.parametrize("F", [64, 128, 192, 320])
+@pytest.mark.parametrize("c,N,tiles", [(128, 333, [2, 0]), (192, 333, [2, 0]),                       # of 64 x 64
+                                       (128, 386 * 128 - 37, [0, 49]), (192, 337 * 192 - 37, [0, 43])])   # whole chunks
+def test_mlp_dense_second_gemm_at_the_ends_of_its_ring(cm, oracle, c, N, tiles, F):
+    """Dense contractions of 2, 4, 6 and 10 steps of 32; the first and the last rows against the oracle."""
+    assert _mlp_tiles(cm, 1, N, 128, F, c, 1)[1:3] == tiles
+    x, _, w1, b1, w2, b2 = recipes.mlp_inputs(1, N, 128, F, 33, DEV)
+    a_ld = -(-N // 8) * 8
+    out, a = torch.empty_like(x), torch.zeros((1, F, a_ld), dtype=torch.bfloat16, device=DEV)
+    cm.mlp_dense(x, w1, b1, w2, b2, out, a, c, 1)
+    for rows in (slice(0, min(N, 300)), slice(max(N - 700, 0), N)):
+        ref, _, _ = oracle.mlp_dense(si.np_f32(x[:, rows].contiguous()), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2), si.np_f32(b2), c, 1,
+                                     a_ld=-(-x[:, rows].shape[1] // 8) * 8)
+        assert rel_err(si.np_f32(out[:, rows].contiguous()), ref) <= REL_TOL
 
 
 @pytest.mark.parametrize("B,N,D,F,c,k,act,bias,tiles", [

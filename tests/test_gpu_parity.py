@@ -466,11 +466,13 @@ def test_attn_colsum_with_stale_normalisers_parity(cm, oracle, B, H, N, E, c):
     assert overlap >= 0.9      # the approximation App. B.2 relies on: stale normalisers barely move the top-k set
 
 
-@pytest.mark.parametrize("B,H,N,E,c", [(1, 2, 1024, 64, 128), (2, 2, 700, 128, 192), (1, 1, 100, 128, 128),
-                                       (1, 2, 333, 64, 192), (1, 1, 1, 128, 192)])
-def test_attn_dense_fused_with_stale_column_sums_parity(cm, oracle, B, H, N, E, c):
-    """Alg. 4 in one kernel: dense output, column sums against the previous step's normalisers, and this step's
+@pytest.mark.parametrize("B,H,N,E,c,apart", [(1, 2, 1024, 64, 128, True), (2, 2, 700, 128, 192, True), (1, 1, 100, 128, 128, False),
+                                             (1, 2, 333, 64, 192, False), (1, 1, 1, 128, 192, False),
+                                             (1, 11, 1024, 64, 128, False), (2, 11, 700, 128, 192, False)])
+def test_attn_dense_fused_with_stale_column_sums_parity(cm, oracle, B, H, N, E, c, apart):
+    """Alg. 4 in one kernel, or apart: dense output, column sums against the previous step's normalisers, and this step's
     normalisers for the next one."""
+    assert bool(cm.load().chipmunk_internal_attn_refresh_apart(B, H, N, c)) == apart
     (q1, k1, v1), (q2, k2, v2), _ = si.attn_steps(B, H, N, E, 11, DEV)
     scale = 1.0 / math.sqrt(E)
     NB = -(-N // c)
@@ -505,11 +507,13 @@ def test_attn_dense_fused_with_stale_column_sums_parity(cm, oracle, B, H, N, E, 
     assert torch.equal(out3, out2) and torch.equal(D3[..., :N], D2[..., :N])
 
 
-@pytest.mark.parametrize("B,H,N,E,c", [(1, 2, 700, 128, 192), (1, 1, 300, 64, 128)])
-def test_attn_column_sums_with_far_stale_normalisers(cm, oracle, B, H, N, E, c):
+@pytest.mark.parametrize("B,H,N,E,c,apart", [(1, 2, 700, 128, 192, True), (1, 1, 300, 64, 128, False), (2, 11, 700, 128, 192, False),
+                                             (1, 11, 1000, 128, 128, False), (1, 20, 900, 64, 192, False)])
+def test_attn_column_sums_with_far_stale_normalisers(cm, oracle, B, H, N, E, c, apart):
     """Normalisers far below the current scores.  60 below: every weight is near e^60, inside fp32, and both
     entry points still evaluate Alg. 4's expression.  200 below: every weight is beyond fp32; the separate pass
     overflows to +inf like the expression, the fused kernel saturates to a large number or +inf, neither to NaN."""
+    assert bool(cm.load().chipmunk_internal_attn_refresh_apart(B, H, N, c)) == apart
     (q1, k1, v1), (q2, k2, v2), _ = si.attn_steps(B, H, N, E, 13, DEV)
     scale = 1.0 / math.sqrt(E)
     NB = -(-N // c)
