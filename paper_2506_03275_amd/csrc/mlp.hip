@@ -30,7 +30,7 @@
 
 namespace chipmunk {
 
-constexpr int64_t kLastLevelCache = 256 << 20;   // bytes
+constexpr int64_t kAllL2 = 32 << 20, kLastLevelCache = 256 << 20;   // bytes
 constexpr int kBN = 128;  // neurons (GEMM1) or output columns (GEMM2) per workgroup
 constexpr int kBK = 64;   // contraction tile
 
@@ -741,8 +741,9 @@ __device__ __forceinline__ void gemm2_rows(const Gemm2Params& p, int unit, int p
 
 // PARTS: the tiles of an XCD beyond `whole` are taken 64 rows at a time.  (An instance of its own: with the second body in the
 // same kernel launches that never reach it were 0.5 to 1 % slower.)
-// STREAM: the cached output is read and written past the caches' usual order of replacement, which leaves them to the weights
-// but the output's next reader without it.
+// STREAM: the cached output is read and written past the caches' usual order of replacement, which leaves them to the weights:
+// where it is over twice the XCDs' L2s.  Whole deltas in us without and with: 75 600 x 5120 (774 MB) 1777, 1728; 28 438 x 4096
+// (233 MB) 216, 196; 19 327 x 2304 (89 MB) 92.6, 85.3; 2 x 7394 x 1792 (53 MB) 41.7, 42.9; 7669 x 1536 (24 MB) 37.6, 39.0.
 template <int BM, bool DENSE, bool PARTS, bool STREAM>
 __global__ __launch_bounds__(256, 2) void mlp_gemm2_kernel(Gemm2Params p) {
     if (!DENSE && p.act_t && (int)blockIdx.x >= p.tile_blocks) {
@@ -866,13 +867,6 @@ static int32_t launch_gemm1(Gemm1Params p, int col_tiles, int units, hipStream_t
     return launch_status();
 }
 
-// Whether the delta's cached output passes the caches by (STREAM): where it is so large that the next kernel would find little of
-// it there.  Delta and the addition that reads its output, four blocks in turn, us without and with: 71 MB 216.2, 217.8; 83 MB 260.2,
-// 263.0 and 254.5, 257.3; 111 MB 343.8, 345.6; 131 MB 448.4, 444.8; 154 MB 418.2, 418.2; 184 MB 554.9, 543.2; 246 MB 686.6, 675.7; 774 MB
-// 2112, 2051.  (With the result also written over: 71 MB 232.7, 238.2; 111 MB 378.4, 381.9; 131 MB 490.4, 488.7; 184 MB 615.8, 603.0.  The
-// delta alone is 1 to 1.5 % faster with it from 69 to 131 MB, 2 to 3 % from 184.)
-static bool stream_output(int64_t units, int c, int D) { return units * c * D * 2 > (int64_t)120 << 20; }
-
 // whole: tiles per XCD that a workgroup takes whole
 template <int BM, bool DENSE>
 static int32_t launch_gemm2(Gemm2Params p, int col_tiles, int units, int64_t whole, hipStream_t s) {
@@ -889,7 +883,7 @@ static int32_t launch_gemm2(Gemm2Params p, int col_tiles, int units, int64_t who
     };
     constexpr int lds = Gemm2Shape<BM>::kLds, lds64 = Gemm2Shape<64>::kLds;
     constexpr int lds_parts = lds > lds64 ? lds : lds64;
-    if (!DENSE && stream_output(units, BM, p.D))
+    if (!DENSE && (int64_t)units * BM * p.D * 2 > 2 * kAllL2)
         return p.whole == slots ? launch(mlp_gemm2_kernel<BM, DENSE, false, !DENSE>, lds)
                                 : launch(mlp_gemm2_kernel<BM, DENSE, true, !DENSE>, lds_parts);
     return p.whole == slots ? launch(mlp_gemm2_kernel<BM, DENSE, false, false>, lds)
@@ -1377,6 +1371,3 @@ extern "C" void chipmunk_internal_mlp_tiles(int B, int N, int D, int F, int c, i
         out[3 * sparse + 2] = plan.whole;
     }
 }
-
-// whether the delta's cached output passes the caches by
-extern "C" int32_t chipmunk_internal_mlp_streams(int B, int N, int D, int c) { return stream_output((int64_t)B * ((N + c - 1) / c), c, D); }
