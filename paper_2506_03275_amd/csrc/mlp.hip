@@ -743,7 +743,10 @@ __device__ __forceinline__ void gemm2_rows(const Gemm2Params& p, int unit, int p
 // same kernel launches that never reach it were 0.5 to 1 % slower.)
 // STREAM: the cached output is read and written past the caches' usual order of replacement, which leaves them to the weights:
 // where it is over twice the XCDs' L2s.  Whole deltas in us without and with: 75 600 x 5120 (774 MB) 1777, 1728; 28 438 x 4096
-// (233 MB) 216, 196; 19 327 x 2304 (89 MB) 92.6, 85.3; 2 x 7394 x 1792 (53 MB) 41.7, 42.9; 7669 x 1536 (24 MB) 37.6, 39.0.
+// (233 MB) 216, 196; 19 327 x 2304 (89 MB) 92.6, 85.3; 2 x 7394 x 1792 (53 MB) 41.7, 42.9; 7669 x 1536 (24 MB) 37.6, 39.0.  An
+// output of up to half the last-level cache could be read from there by the next kernel: delta and the addition that reads it, four
+// blocks in turn, 42 sizes of 65 to 126 MB: 0.977 to 1.013 of the time without, 0.995 in the mean (the delta alone 0.996 to 1.135,
+// 1.029); 18 of 126 to 250 MB: 0.998 to 1.029.
 template <int BM, bool DENSE, bool PARTS, bool STREAM>
 __global__ __launch_bounds__(256, 2) void mlp_gemm2_kernel(Gemm2Params p) {
     if (!DENSE && p.act_t && (int)blockIdx.x >= p.tile_blocks) {
@@ -867,6 +870,9 @@ static int32_t launch_gemm1(Gemm1Params p, int col_tiles, int units, hipStream_t
     return launch_status();
 }
 
+// whether the delta's cached output passes the caches by (STREAM)
+static bool stream_output(int64_t units, int c, int D) { return units * c * D * 2 > 2 * kAllL2; }
+
 // whole: tiles per XCD that a workgroup takes whole
 template <int BM, bool DENSE>
 static int32_t launch_gemm2(Gemm2Params p, int col_tiles, int units, int64_t whole, hipStream_t s) {
@@ -883,7 +889,7 @@ static int32_t launch_gemm2(Gemm2Params p, int col_tiles, int units, int64_t who
     };
     constexpr int lds = Gemm2Shape<BM>::kLds, lds64 = Gemm2Shape<64>::kLds;
     constexpr int lds_parts = lds > lds64 ? lds : lds64;
-    if (!DENSE && (int64_t)units * BM * p.D * 2 > 2 * kAllL2)
+    if (!DENSE && stream_output(units, BM, p.D))
         return p.whole == slots ? launch(mlp_gemm2_kernel<BM, DENSE, false, !DENSE>, lds)
                                 : launch(mlp_gemm2_kernel<BM, DENSE, true, !DENSE>, lds_parts);
     return p.whole == slots ? launch(mlp_gemm2_kernel<BM, DENSE, false, false>, lds)
@@ -1371,3 +1377,6 @@ extern "C" void chipmunk_internal_mlp_tiles(int B, int N, int D, int F, int c, i
         out[3 * sparse + 2] = plan.whole;
     }
 }
+
+// whether a delta with these sizes has its cached output pass the caches by
+extern "C" int32_t chipmunk_internal_mlp_streams(int B, int N, int D, int c) { return stream_output((int64_t)B * ((N + c - 1) / c), c, D); }

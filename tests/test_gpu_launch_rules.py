@@ -469,19 +469,25 @@ def test_unchanged_input_on_small_tiles(cm, B, N, D, F, c, k, first_dense, first
     assert torch.equal(a_cache, a_before) and torch.equal(out, o_before)
 
 
-@pytest.mark.parametrize("B,N,D,c,whole", [(1, 88 * 192 - 37, 2048, 192, 176), (2, 33 * 192 - 5, 3072, 192, 192),
-                                           (1, 70 * 128 - 100, 4096, 128, 280), (2, 44 * 128 - 1, 3072, 128, 256)])
-def test_mlp_delta_of_an_output_past_the_caches(cm, oracle, B, N, D, c, whole):
-    """Outputs of over 64 MB, with and without a last round in parts of 64 rows; the first two and the last two chunks of each
-    batch against the oracle."""
-    F, k = 256, 70
-    assert B * N * D * 2 > 64 << 20 and _mlp_tiles(cm, B, N, D, F, c, k)[5] == whole
+@pytest.mark.parametrize("B,N,D,c,F,k,whole,streams", [
+    (1, 88 * 192 - 37, 2048, 192, 256, 70, 176, True), (2, 33 * 192 - 5, 3072, 192, 256, 70, 192, True),
+    (1, 70 * 128 - 100, 4096, 128, 256, 70, 280, True), (2, 44 * 128 - 1, 3072, 128, 256, 70, 256, True),
+    (1, 88 * 192 - 37, 2048, 192, 512, 448, 176, True), (1, 65 * 192 - 5, 3072, 192, 512, 448, 192, True),
+    (1, 70 * 128 - 100, 4096, 128, 512, 448, 280, True), (2, 44 * 128 - 1, 3072, 128, 512, 448, 256, True),
+    (1, 63 * 128 - 5, 4096, 128, 512, 448, 252, False), (1, 42 * 192 - 1, 4096, 192, 512, 448, 168, False)])
+def test_mlp_delta_of_an_output_past_the_caches(cm, oracle, B, N, D, c, F, k, whole, streams):
+    """Outputs of over 67 MB, which pass the caches by, and just below, with and without a last round in parts of 64 rows; the first
+    two and the last two chunks of each batch against the oracle, the longer lists with 14, 5, 6 and 9 steps."""
+    assert _mlp_tiles(cm, B, N, D, F, c, k)[4:] == [0, whole]
+    assert bool(cm.load().chipmunk_internal_mlp_streams(B, N, D, c)) == streams
     g = si.generator(35, DEV)
     x, w1, w2 = si.randn_bf16((B, N, D), g), si.randn_bf16((F, D), g, D ** -0.5), si.randn_bf16((F, D), g, F ** -0.5)
     b1, NB, a_ld = si.randn_bf16((F,), g), -(-N // c), -(-N // 8) * 8
     a_cache, o_cache = si.randn_bf16((B, F, a_ld), g, 0.5), si.randn_bf16((B, N, D), g)
     idx, counts = recipes.mlp_indices(B * NB, F, k, 35, DEV, ragged=True)
     idx, counts = idx.view(B, NB, k), counts.view(B, NB)
+    if k == 448:
+        counts[:, [0, 1, -2, -1]] = torch.tensor([448, 129, 161, 288], dtype=torch.int32, device=DEV)
     a_new, o_new = a_cache.clone(), o_cache.clone()
     cm.mlp_sparse_delta(x, w1, b1, w2, idx, counts, a_new, o_new, c, 1, _u8(cm.mlp_workspace_bytes(B, N, D, F, c, k)))
     for first in (0, NB - 2):
