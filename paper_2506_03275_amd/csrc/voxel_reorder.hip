@@ -6,6 +6,8 @@
 // byte once on the way in and once on the way out: it is bound by HBM.
 #include "common.h"
 
+#include <algorithm>
+
 namespace chipmunk {
 
 // n / d for 0 <= n < 2^31 as (mulhi(n, m) + n) >> s with s = ceil(log2 d), m = floor(2^32 (2^s - d) / d) + 1 (Granlund and
@@ -82,11 +84,10 @@ __global__ __launch_bounds__(256) void voxel_perm_kernel(VoxelGeom g, int32_t* p
 }
 
 // One wave per row; the waves of the first batch also write the permutation, which would be a launch of its own.  VEC is
-// u32x4 (16-byte words) or uint32_t.  STREAM: loads and stores past the caches' usual order of replacement, for a source and a
-// destination that do not fit the last-level cache (256 MB) together.  us before (one word per lane at a time, the permutation
-// by a kernel of its own, plain divisions), now, and with the other choice of STREAM: 7 MB 9.8, 7.4, 7.4; 25 MB 12.1, 9.6, 10.8; 69
-// MB 30.3, 27.7, 24.9; 290 MB 108, 94.6, 109; 774 MB 293, 259.5 (6.0 TB/s), 285.  From the writer of the source to a reader of the
-// destination: 25 MB 36.3, 33.3, 35.4; 184 MB 179, 155, 174; 774 MB 721, 655, 722.
+// u32x4 (16-byte words) or uint32_t.  STREAM: loads and stores past the caches' usual order of replacement (the rules are at the
+// launch).  us before (one word per lane at a time, the permutation by a kernel of its own, plain divisions) and now: 7 MB 9.8, 7.4;
+// 25 MB 12.1, 9.6; 69 MB 30.3, 27.7; 290 MB 108, 94.6; 774 MB 293, 259.5 (6.0 TB/s).  U: rows of 10 240 bytes, 812 MB, with 3, 4, 5, 6
+// and 8 words of a lane in flight 285, 282, 274, 272, 269; of 6144 bytes 270, 270, 264, 262, 261; small copies alike.
 template <typename VEC, bool STREAM>
 __global__ __launch_bounds__(256) void voxel_copy_kernel(VoxelGeom g, const VEC* __restrict__ src, VEC* __restrict__ dst, int64_t total_rows,
                                                          int words_per_row, int inverse, int32_t* __restrict__ perm,
@@ -158,18 +159,24 @@ extern "C" int32_t chipmunk_voxel_reorder(const void* src, void* dst, int32_t* p
         return launch_status();
     }
     const int64_t total_rows = (int64_t)batch * g.N;
-    int64_t blocks = (total_rows + 3) / 4;
-    if (blocks > 1 << 22) blocks = 1 << 22;   // a launch has fewer than 2^32 threads; rows beyond are strided over the waves
-    const bool stream_through = total_rows * row_bytes > (int64_t)128 << 20;
-    auto launch = [&](auto kernel, auto from, auto to, int word) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, g, from, to, total_rows, row_bytes / word, inverse, perm, inv_perm);
+    const bool wide = row_bytes % 16 == 0 && aligned16(src) && aligned16(dst);
+    const int words = row_bytes / (wide ? 16 : 4);
+    // A launch has fewer than 2^32 threads; rows beyond are strided over the waves.  Of rows that are less than one word per lane a
+    // wave takes several: its start costs more than such a row.  us with a wave per row and like this: 24 heads x 128 columns of 16
+    // bits 12 MiB 15.3, 15.4, 40 MiB 38.8, 30.7, 150 MiB 161, 120, 600 MiB 644, 453; 64 columns 100 MiB 200, 137; 384 columns 600 MiB 254,
+    // 240; 448 columns 600 MiB 229, 236.
+    const int64_t blocks = std::min<int64_t>((total_rows + 3) / 4, words < 64 ? 1 << 14 : 1 << 22);
+    // Past the caches: a source and a destination that do not fit the last-level cache (256 MB) together.  Call alone, with a
+    // reader of the destination, and from the writer of the source to that reader, us without and with: 100 MiB 31.9, 35.5; 65.3,
+    // 69.2; 106.5, 101.2; 128 MiB 40.5, 44.5; 83.7, 87.9; 142, 132; 140 MiB 47.3, 48.9; 101, 94.9; 153, 144; 180 MiB 70.1, 61.7; 133, 121;
+    // 194, 190; 600 MiB 221, 192; 422, 399; 625, 592.  Not shorter rows and not words of 4 bytes, whose stores leave in pieces: 600 MiB of
+    // 256 columns 368, 395; 564, 601; 769, 784; of 2510 columns (4-byte words) 250, 261; 451, 471; 653, 662.
+    const bool stream_through = wide && words >= 64 && total_rows * row_bytes > (int64_t)128 << 20;
+    auto launch = [&](auto kernel, auto from, auto to) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, g, from, to, total_rows, words, inverse, perm, inv_perm);
     };
-    if (row_bytes % 16 == 0 && aligned16(src) && aligned16(dst)) {
-        if (stream_through) launch(voxel_copy_kernel<u32x4, true>, (const u32x4*)src, (u32x4*)dst, 16);
-        else launch(voxel_copy_kernel<u32x4, false>, (const u32x4*)src, (u32x4*)dst, 16);
-    } else {
-        if (stream_through) launch(voxel_copy_kernel<uint32_t, true>, (const uint32_t*)src, (uint32_t*)dst, 4);
-        else launch(voxel_copy_kernel<uint32_t, false>, (const uint32_t*)src, (uint32_t*)dst, 4);
-    }
+    if (stream_through) launch(voxel_copy_kernel<u32x4, true>, (const u32x4*)src, (u32x4*)dst);
+    else if (wide) launch(voxel_copy_kernel<u32x4, false>, (const u32x4*)src, (u32x4*)dst);
+    else launch(voxel_copy_kernel<uint32_t, false>, (const uint32_t*)src, (uint32_t*)dst);
     return launch_status();
 }

@@ -524,9 +524,13 @@ def test_neuron_scores_of_an_input_past_the_caches(cm, oracle, B, N, D, c):
     ((7, 1, 1, 1, 0, 3, 3, 3), 4, 1, torch.int32),              # no full voxel at all
     ((0, 7, 64, 67, 1, 4, 6, 8), 1, 2304, torch.bfloat16),      # 138 MB: streamed
     ((2, 7, 64, 67, 0, 2, 5, 8), 1, 1201, torch.int32),         # 144 MB in 4-byte words
+    ((3, 5, 50, 61, 2, 2, 4, 3), 5, 64, torch.bfloat16),        # 76 275 short rows, several a wave
+    ((1, 5, 50, 61, 0, 2, 4, 8), 9, 63, torch.int32),           # 137 259 in 4-byte words
+    ((0, 9, 50, 61, 3, 4, 6, 8), 20, 504, torch.bfloat16),      # 554 MB of them, just short
 ])
 def test_voxel_rows_and_permutation_in_one_launch(cm, oracle, geom, batch, words, dtype):
-    """The copy's launch also writes the permutation and its inverse; rows of one and more sweeps, small and streamed copies."""
+    """The copy's launch also writes the permutation and its inverse; rows of one and more sweeps, several rows a wave, small and
+    streamed copies."""
     npre, T, H, W, nsuf, vt, vh, vw = geom
     N = npre + T * H * W + nsuf
     perm_ref, inv_ref = oracle.voxel_perm(*geom)
