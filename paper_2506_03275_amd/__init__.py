@@ -231,7 +231,7 @@ def attn_colsum_stale(q, k, prev_m, prev_l, colsum, c, softmax_scale):
 
 
 def attn_dense_colsum_stale(q, k, v, out, prev_m, prev_l, colsum, c, softmax_scale, new_m=None, new_l=None):
-    """Alg. 4 in one kernel.  q,k,v,out: bf16 [B,H,N,E]; prev_m, prev_l, new_m, new_l: fp32 [B,H,N]; colsum: fp32
+    """Alg. 4 in one call.  q,k,v,out: bf16 [B,H,N,E]; prev_m, prev_l, new_m, new_l: fp32 [B,H,N]; colsum: fp32
     [B,H,NB,ld] (written)."""
     B, H, N, E = q.shape
     bf, f32 = torch.bfloat16, torch.float32

@@ -55,8 +55,8 @@ __device__ __forceinline__ void load_global_to_lds_16B(const void* base, uint32_
 }
 
 // Raw buffer resource (no stride, no swizzle) over `bytes` bytes at `base`, both wave-uniform.  Loads through it
-// are range-checked by the hardware on (per-lane offset + immediate offset): an access that starts at or beyond
-// `bytes` returns zero instead of touching memory.
+// are range-checked by the hardware on the offset (per-lane, immediate and wave-uniform part): an access that starts
+// at or beyond `bytes` returns zero instead of touching memory.
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 __device__ __forceinline__ i32x4 raw_buffer_words(const void* base, uint32_t bytes) {
     const uint64_t b = reinterpret_cast<uint64_t>(base);

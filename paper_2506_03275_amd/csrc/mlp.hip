@@ -13,7 +13,7 @@
 //        (chunk, neuron) cell has one writer: no atomics.
 // GEMM2  o_cache[tok, :] += sum_s delta[tok, s] * w2[idx[s], :]: one workgroup
 //        owns (token chunk, 128 output columns) and walks the selected rows in
-//        tiles of 64.  Both operands are stored with the contraction index as
+//        steps of 32.  Both operands are stored with the contraction index as
 //        the slow axis (delta^T rows, w2 rows), so both come out of LDS through
 //        the transposing 64-bit read.  Epilogue: fp32 tile through LDS, add to
 //        the cached output in fp32, round once, store in 256-byte runs.

@@ -58,7 +58,7 @@ class Block:
         """Alg. 2 + Alg. 5 on the inputs of `step`; colsum [B,H,NB,ld] fp32 and ws_attn are shared scratch."""
         i = self.inputs
         q, k, v, x = i["q"][step], i["k"][step], i["v"][step], i["x"][step]
-        if self.has_stats:   # Alg. 4: one kernel; the normalisers are replaced row by row by the workgroup that read them
+        if self.has_stats:   # Alg. 4: one call; the normalisers are replaced in place, after they have been read
             attn_dense_colsum_stale(q, k, v, self.attn_out, self.row_m, self.row_l, colsum, self.c, self.scale,
                                     self.row_m, self.row_l)
         else:
