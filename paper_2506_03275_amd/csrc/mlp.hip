@@ -968,9 +968,13 @@ static FirstForm first_form(bool sparse, int B, int N, int D, int F, int c, int 
     return large_fits && large < chunk ? kFirstLarge : kFirstChunk;
 }
 
-// Second GEMM.  kSecondChunk: a workgroup per chunk and 128 columns; those of the last round beyond `whole` tiles per XCD take 64
-// rows each where every such part has a CU to itself (24 chunks x 1229 of 12 288 x 3072, 72 tiles per XCD: 54.6 -> 47.2 us; 80 to 97 per cent
-// of the time over 23 sizes with one to three whole rounds), or all of them where that fills the chip better.
+// Second GEMM.  kSecondChunk: a workgroup per chunk and 128 columns; those beyond `whole` tiles per XCD take 64 rows each where they
+// fill that XCD's 32 CUs at most once: of the last round of two per CU (24 chunks x 1229 of 12 288 x 3072, 72 tiles per XCD: 54.6 ->
+// 47.2 us; 80 to 97 per cent of the time over 23 sizes with one to three whole rounds), of the only round those beyond one per CU, or all
+// of them where that fills the chip better.  In an only round the CUs with two whole tiles are the last to end, more so since the
+// ring leaves little idle beside a single one: dense, c = 128, 33 tiles, 2449 x 1664 x 10 304 with two buffers a workgroup 127.6 us, with
+// the ring 139.6.  Whole calls, 33 to 48 tiles (c = 192: 42), all whole and like this: 0.85 to 1.01 over 1133 sizes, 0.93 in the mean (one at
+// 1.08); 49 to 63 tiles, if they were taken so, 1.06 to 1.25.
 enum SecondForm { kSecondChunk = 0, kSecondLarge = 1, kSecondSmall = 2 };
 struct SecondPlan {
     SecondForm form;
@@ -994,11 +998,12 @@ static SecondPlan second_plan(bool sparse, int B, int N, int D, int F, int c, in
     const Price& part = (sparse ? parts_delta : parts_dense)[at];
     SecondPlan plan = {kSecondChunk, tiles};
     if (sparse && ((int64_t)k_stride + kBN - 1) / kBN * kBN * c * 2 >= 1LL << 32) return plan;   // whole chunks only: more bytes than the parts' offsets hold
-    const int64_t last = tiles % 64;
+    const int64_t beyond = tiles > 64 ? tiles % 64 : tiles - 32;
     double best;
-    if (tiles > 64 && last > 0 && last * parts <= 32) {
-        plan.whole = tiles - last;
-        best = price(whole, tiles - last, 64, steps) + price(part, last * parts, 64, steps) - part.call;
+    if (beyond > 0 && beyond * parts <= 32) {
+        plan.whole = tiles - beyond;
+        // (a part beside a whole tile costs about a third of what it takes alone)
+        best = price(whole, plan.whole, 64, steps) + (tiles > 64 ? 1. : 0.35) * (price(part, beyond * parts, 64, steps) - part.call);
     } else {
         best = price(whole, tiles, 64, steps);
     }
