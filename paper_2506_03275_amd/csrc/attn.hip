@@ -297,10 +297,15 @@ enum AttnMode { kColumnList = 0, kFusedDense = 1, kBlockList = 2, kEveryColumn =
 
 // The work of one workgroup: NWAVES waves, each owning NQB blocks of 16 queries; 16 * NQB * NWAVES rows, chunk `unit` or part
 // `part` of it.
-template <int E, int NQB, int NWAVES, int MODE>
+// KEYS = 2: the workgroup has half as many rows, and two waves share them: one takes the first tile of every step, the other
+// the second, each with a reference, denominator and accumulator of its own, and the two meet through LDS at the end.  What
+// bounds a workgroup of 64 rows is its chain of tiles and the LDS reads of its waves, each of which reads all of K and V: with 64
+// rows shared by pairs the waves read half as much, with 32 the chain is half as long (times at attn_part_form).
+template <int E, int NQB, int NWAVES, int MODE, int KEYS = 1>
 __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int part) {
     constexpr bool FUSED = MODE == kFusedDense;
     constexpr bool BLOCKS = MODE == kBlockList;
+    static_assert(KEYS == 1 || (KEYS == kTilesPerStep && !FUSED && !BLOCKS), "a wave takes all tiles of a step or one");
     // Every column in order: the columns are the list positions.  A mode of its own and not a null list inside
     // kColumnList: there the branch on the pointer put a wait for all memory behind each step's tile requests (the
     // compiler guards the registers that the other branch loads the column numbers into).
@@ -324,7 +329,8 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
     const int g = lane >> 4;
     const int l16 = lane & 15;
 
-    constexpr int ROWS = 16 * NQB * NWAVES;   // query rows of a workgroup
+    constexpr int ROWS = 16 * NQB * NWAVES / KEYS;   // query rows of a workgroup
+    const int wr = w / KEYS, kg = KEYS == 1 ? 0 : wu % KEYS;   // the wave's rows, and its tile of a step
     const int64_t bh = unit / p.NB;
     const int chunk = (int)(unit % p.NB);
     const int row0 = chunk * p.c + part * ROWS;
@@ -363,7 +369,7 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
         st.L[qb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int eb = 0; eb < E / 16; eb++) st.O[eb][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        int qrow = (w * NQB + qb) * 16 + l16;
+        int qrow = (wr * NQB + qb) * 16 + l16;
 #pragma unroll
         for (int es = 0; es < E / 32; es++) {
             u32x4 val = u32x4{0, 0, 0, 0};
@@ -372,7 +378,7 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
             st.Q[es][qb] = __builtin_bit_cast(bf16x8, val);
         }
     }
-    const bool wave_active = wu * NQB * 16 < rows_valid;   // wave-uniform, and known to be
+    const bool wave_active = wu / KEYS * NQB * 16 < rows_valid;   // wave-uniform, and known to be
     const float slack = kRescaleSlack / p.sl2;
     // FUSED: -prev_m (log2 units) - log2(prev_l) of the lane's queries; -inf drops a query row that does not exist
     float off[NQB];
@@ -409,9 +415,9 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
     const uint32_t smem_at = (uint32_t)(uintptr_t)CHIPMUNK_LDS_PTR(smem);
     uint32_t kaddr[E / 32], vaddr[E / 16];
 #pragma unroll
-    for (int es = 0; es < E / 32; es++) kaddr[es] = smem_at + (uint32_t)(koff ^ (64 * es));
+    for (int es = 0; es < E / 32; es++) kaddr[es] = smem_at + (uint32_t)((koff ^ (64 * es)) + kg * STAGE);
 #pragma unroll
-    for (int eb = 0; eb < E / 16; eb++) vaddr[eb] = smem_at + (uint32_t)(voff ^ (32 * eb));
+    for (int eb = 0; eb < E / 16; eb++) vaddr[eb] = smem_at + (uint32_t)((voff ^ (32 * eb)) + kg * STAGE);
     // The LDS base is a link-time constant; left visible, the compiler would keep the offsets without it and add
     // it again at every read.  Behind this barrier each address is just a register.
 #pragma unroll
@@ -518,6 +524,20 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
     };
     static_assert(kTilesPerStep * NI * 2 == E / 16, "one transfer per group of score products");
 
+    // KEYS = 2: a wave merges and stores half the columns of its rows.  The base rows' part of those waits in registers, as it is
+    // stored: the lane's eight columns of two blocks (requested here or in the last step: the same time).
+    u32x4 half_base[KEYS == 1 ? 1 : NQB][KEYS == 1 ? 1 : E / 64];
+    if constexpr (KEYS == 2) {
+#pragma unroll
+        for (int qb = 0; qb < NQB; qb++)
+#pragma unroll
+            for (int pair = 0; pair < E / 64; pair++) {
+                const int qrow = min((wr * NQB + qb) * 16 + l16, rows_valid - 1);
+                half_base[qb][pair] = baseh ? *reinterpret_cast<const u32x4*>(baseh + (int64_t)(row0 + qrow) * E + (kg * (E / 32) + 2 * pair + (g & 1)) * 16 + (g >> 1) * 8)
+                                            : u32x4{0, 0, 0, 0};
+            }
+    }
+
     // The query loads must not be left pending into the loop: a wait for them inside
     // the loop would also wait for every tile transfer in flight.  The columns of the
     // first step are requested beside them: one round trip for both.
@@ -561,6 +581,34 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
         if constexpr (!LAST) gather_offsets(t + 2 * kTilesPerStep >= ntiles);
         if constexpr (LAST && BLOCKS) block_now = block_next;
         if (FUSED && t > 0) flush_column_sums(t - kTilesPerStep);
+        if constexpr (KEYS == 2) {
+            f32x4 S[2][NQB];
+            // Both waves take their first reference from the unit's first tile, which the second one multiplies for that alone: as
+            // long as nothing raises it, a weight's rounding to bf16 is the same whichever wave forms it and however the rows
+            // are walked.
+            if (half == 0 && t == 0 && kg == 1) {
+                uint32_t first_tile[E / 32];
+#pragma unroll
+                for (int es = 0; es < E / 32; es++) first_tile[es] = kaddr[es] - STAGE;
+                attn_scores<E, NQB, 1>(S, st, first_tile, 0, [](int) {});
+                if constexpr (LAST) attn_mask_tail<E, NQB, true>(S, 0, 0, count, g);
+                else if (NOLIST && kTilesPerStep >= ntiles) attn_mask_tail<E, NQB>(S, 0, 0, count, g);
+                attn_update_max<E, NQB>(st, S, true, p.sl2, slack);
+            }
+            if constexpr (LAST) {
+                if ((t + kg) * kTileRows >= count) return;
+                attn_scores<E, NQB, 1>(S, st, kaddr, half * kTilesPerStep * STAGE, [](int) {});
+                attn_mask_tail<E, NQB, true>(S, t * kTileRows, kg, count, g);
+            } else {
+                attn_scores<E, NQB, 1>(S, st, kaddr, half * kTilesPerStep * STAGE,
+                                       [&](int j) { gather_piece(std::integral_constant<int, half ^ 1>{}, j); });
+                load_cols();
+                if (NOLIST && t + kTilesPerStep >= ntiles) attn_mask_tail<E, NQB>(S, t * kTileRows, kg, count, g);
+            }
+            attn_update_max<E, NQB>(st, S, t == 0 && kg == 0, p.sl2, slack);
+            attn_weights_and_pv<E, NQB, false, kVPrefetch>(st, S, vaddr, half * kTilesPerStep * STAGE + TILE, p.sl2, ones);
+            return;
+        }
 #pragma unroll
         for (int s = 0; s < kTilesPerStep; s++) {
             const int tile_off = (half * kTilesPerStep + s) * STAGE;   // a constant once the loop over s is unrolled
@@ -621,6 +669,63 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
         flush_column_sums(last_tile);
     }
 
+    if constexpr (KEYS == 2) {
+        // Each wave hands the half of its columns that the other one stores, and its reference and denominator, over in LDS.
+        constexpr int HALF = E / 32;          // blocks of 16 columns
+        constexpr int AREA = NQB * HALF * 1024, STATS = NWAVES * AREA;
+        static_assert(STATS + NWAVES * NQB * 512 <= kStages * STAGE, "the halves fit the tile buffers");
+        lds_accesses_then_barrier();          // every wave is done with the tiles
+#pragma unroll
+        for (int qb = 0; qb < NQB; qb++) {
+#pragma unroll
+            for (int i = 0; i < HALF; i++)
+                *reinterpret_cast<f32x4*>(smem + w * AREA + (qb * HALF + i) * 1024 + lane * 16) = kg ? st.O[i][qb] : st.O[HALF + i][qb];
+            *reinterpret_cast<f32x2*>(smem + STATS + (w * NQB + qb) * 512 + lane * 8) = f32x2{st.negm[qb][0], st.L[qb][0]};
+        }
+        lds_accesses_then_barrier();
+        if (!wave_active) return;
+#pragma unroll
+        for (int qb = 0; qb < NQB; qb++) {
+            const f32x2 theirs = *reinterpret_cast<const f32x2*>(smem + STATS + ((w ^ 1) * NQB + qb) * 512 + lane * 8);
+            const float m = fmaxf(-st.negm[qb][0], -theirs[0]);
+            const float mine = __builtin_amdgcn_exp2f((-st.negm[qb][0] - m) * p.sl2), their = __builtin_amdgcn_exp2f((-theirs[0] - m) * p.sl2);
+            const float ltot = st.L[qb][0] * mine + theirs[1] * their;
+            const float f = p.o_scale / ltot, f_mine = f * mine, f_their = f * their;
+            const int qrow = (wr * NQB + qb) * 16 + l16;
+            u32x4 r[HALF / 2];
+#pragma unroll
+            for (int pair = 0; pair < HALF / 2; pair++) {
+                // lanes 16 apart hold each other's halves of two blocks, which the swap brings to the accumulators' places
+                const u32x4 base = half_base[qb][pair];
+                const auto b02 = __builtin_amdgcn_permlane16_swap(base[0], base[2], false, false);
+                const auto b13 = __builtin_amdgcn_permlane16_swap(base[1], base[3], false, false);
+                u32x2 sum[2];
+#pragma unroll
+                for (int i = 0; i < 2; i++) {
+                    const int eb = 2 * pair + i;
+                    const f32x4 o = *reinterpret_cast<const f32x4*>(smem + (w ^ 1) * AREA + (qb * HALF + eb) * 1024 + lane * 16);
+                    const f32x4 own = kg ? st.O[HALF + eb][qb] : st.O[eb][qb];
+                    const u32x2 b = {b02[i], b13[i]};
+                    sum[i] = u32x2{pack_bf16x2(bf16_bits_to_float(b[0] & 0xffffu) + (f_mine * own[0] + f_their * o[0]),
+                                               bf16_bits_to_float(b[0] >> 16) + (f_mine * own[1] + f_their * o[1])),
+                                   pack_bf16x2(bf16_bits_to_float(b[1] & 0xffffu) + (f_mine * own[2] + f_their * o[2]),
+                                               bf16_bits_to_float(b[1] >> 16) + (f_mine * own[3] + f_their * o[3]))};
+                }
+                const auto lo = __builtin_amdgcn_permlane16_swap(sum[0][0], sum[1][0], false, false);
+                const auto hi = __builtin_amdgcn_permlane16_swap(sum[0][1], sum[1][1], false, false);
+                r[pair] = u32x4{lo[0], hi[0], lo[1], hi[1]};
+            }
+            if (qrow >= rows_valid) continue;
+            if (p.row_m && g == 0 && kg == 0) {
+                p.row_m[bh * p.N + row0 + qrow] = m * (p.sl2 * 0.6931471805599453f);
+                p.row_l[bh * p.N + row0 + qrow] = ltot;
+            }
+#pragma unroll
+            for (int pair = 0; pair < HALF / 2; pair++)
+                *reinterpret_cast<u32x4*>(outh + (int64_t)(row0 + qrow) * E + (kg * HALF + 2 * pair + (g & 1)) * 16 + (g >> 1) * 8) = r[pair];
+        }
+        return;
+    }
     if (!wave_active) return;
 #pragma unroll
     for (int qb = 0; qb < NQB; qb++) {
@@ -666,9 +771,12 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
     }
 }
 
+// How the chunks that have no workgroup of their own are walked (attn_part_form).
+enum AttnPart { kRows64 = 0, kRows64Shared = 1, kRows32Shared = 2 };
+
 // A workgroup per chunk, or, with a column list or every column, for the first p.whole chunks only: each of the others is
-// walked by a workgroup per 64 rows.  Those are the launch's last, partly filled round, or all of a small launch.
-template <int E, int NQB, int NWAVES, int MODE = kColumnList>
+// walked by a workgroup per 64 or 32 rows.  Those are the launch's last, partly filled round, or all of a small launch.
+template <int E, int NQB, int NWAVES, int MODE = kColumnList, int PART = kRows64>
 __global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_delta_kernel(AttnParams p) {
     uint32_t id = blockIdx.x, all = gridDim.x;
     if constexpr (MODE == kColumnList || MODE == kEveryColumn) {
@@ -677,7 +785,8 @@ __global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_
             id -= whole;
             all -= whole;
             if (p.by_xcd) id = attn_run_of_xcd(id, all);
-            attn_rows<E, 1, NWAVES, MODE>(p, whole + id / NQB, (int)(id % NQB));
+            constexpr int PARTS = PART == kRows32Shared ? 2 * NQB : NQB;   // per chunk
+            attn_rows<E, PART == kRows64Shared ? 2 : 1, NWAVES, MODE, PART == kRows64 ? 1 : 2>(p, whole + id / PARTS, (int)(id % PARTS));
             return;
         }
         all = whole;
@@ -853,16 +962,16 @@ __global__ __launch_bounds__(256, 4) void attn_colsum_kernel(ColsumParams p) {
     flush(ntiles - 1);
 }
 
-template <int E, int NQB, int NWAVES, int MODE = kColumnList>
+template <int E, int NQB, int NWAVES, int MODE = kColumnList, int PART = kRows64>
 static int32_t launch_attn_variant(const AttnParams& p, int64_t units, hipStream_t s) {
     // the tile buffers, and behind them, where there is a list, each wave's third block of base rows
     constexpr int lds = kStages * 2 * kTileRows * E * 2 + ((MODE == kColumnList || MODE == kBlockList) && NQB > 2 ? NWAVES * (NQB - 2) * 16 * E * 2 : 0);
     // set at every launch: the attribute is kept per device, and a flag remembered here would be neither
     // per device nor safe between host threads
-    if (hipFuncSetAttribute((const void*)attn_sparse_delta_kernel<E, NQB, NWAVES, MODE>,
+    if (hipFuncSetAttribute((const void*)attn_sparse_delta_kernel<E, NQB, NWAVES, MODE, PART>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
         return CHIPMUNK_ERR_LAUNCH;
-    hipLaunchKernelGGL((attn_sparse_delta_kernel<E, NQB, NWAVES, MODE>), dim3((unsigned)units), dim3(64 * NWAVES), lds, s, p);
+    hipLaunchKernelGGL((attn_sparse_delta_kernel<E, NQB, NWAVES, MODE, PART>), dim3((unsigned)units), dim3(64 * NWAVES), lds, s, p);
     return launch_status();
 }
 
@@ -901,17 +1010,46 @@ static int64_t attn_whole_chunks(int E, int blocks, int64_t units, double* cost)
     return in_parts ? rounds : units;
 }
 
+// How `parts` parts of 64 rows are walked, by the keys each has to walk.  kRows32Shared halves the chain of tiles and has twice
+// the workgroups: as long as those find an empty CU (E = 64: two to a CU cost each little).  kRows64Shared takes three quarters of the
+// time per step, and a merge of more rows: where the workgroups of 32 rows would meet on the CUs, and for long walks.
+// Launches in us of 64 rows, 64 shared and 32 shared, column lists, E = 128:
+//     parts  72: 128 keys 5.5, 6.7, 5.1   256 7.0, 8.0, 6.1   512 9.8, 10.1, 8.0    1024 15.7, 14.7, 11.7   2048 27.3, 23.8, 19.2
+//           180: 256 7.2, 8.0, 8.1   512 9.9, 10.3, 10.9   768 12.7, 12.4, 13.1   1024 15.7, 14.9, 15.9   2048 27.5, 23.9, 25.2
+//           360: 512 13.5, 15.4, 17.5   1024 21.6, 22.5, 27.4   2048 37.2, 35.8, 45.7
+// E = 64: 108: 128 keys 4.5, 5.0, 4.2   512 7.2, 7.3, 6.0; 180: 384 6.5, 6.8, 6.8   768 9.2, 9.1, 9.0   2048 18.7, 17.0, 16.4; 360: 1024 13.9,
+// 14.8, 16.4   2048 23.9, 23.8, 27.1.  Every column: E = 128, 192 parts, 512 keys 9.7, 9.3, 9.5; E = 64: 256 5.3, 5.4, 5.0.
+// Behind 512 whole chunks, E = 128: 120 parts, 256 keys 29.6, 30.0, 29.3   2048 110.8, 107.2, 104.6; 192: 512 39.8, 40.8, 42.3   1024 61.1, 60.2,
+// 65.5; E = 64: 192: 1024 40.9, 41.3, 44.7   2048 67.9, 66.7, 73.4; every column, E = 64: 189, 960 keys 37.6, 36.0, 39.5.
+static AttnPart attn_part_form(int E, int64_t whole, int64_t parts, int keys, bool list) {
+    if (parts <= 128) return keys > 3 * kTileRows ? kRows32Shared : kRows64;
+    if (whole > 0) return keys >= (!list ? 768 : E == 128 ? 1024 : 2048) ? kRows64Shared : kRows64;
+    if (parts <= 256) {
+        if (E == 64) return keys >= (list ? 768 : 256) ? kRows32Shared : kRows64;
+        return keys >= (list ? 768 : 512) ? kRows64Shared : kRows64;
+    }
+    return keys >= 2048 && (!list || E == 128) ? kRows64Shared : kRows64;
+}
+
+template <int MODE, int PART>
+static int32_t launch_attn_parts_as(const AttnParams& p, int E, int64_t units, hipStream_t s) {
+    const int blocks = p.c / 64;
+    const int64_t groups = p.whole + (units - p.whole) * blocks * (PART == kRows32Shared ? 2 : 1);
+    if (E == 128 && blocks == 3) return launch_attn_variant<128, 3, 4, MODE, PART>(p, groups, s);
+    if (E == 128) return launch_attn_variant<128, 2, 4, MODE, PART>(p, groups, s);
+    if (blocks == 3) return launch_attn_variant<64, 3, 4, MODE, PART>(p, groups, s);
+    return launch_attn_variant<64, 2, 4, MODE, PART>(p, groups, s);
+}
+
 template <int MODE>
 static int32_t launch_attn_parts(AttnParams p, int E, int64_t units, hipStream_t s) {
     const int blocks = p.c / 64;
     double cost;
-    const int64_t whole = attn_whole_chunks(E, blocks, units, &cost);
-    p.whole = (int)whole;
-    const int64_t groups = whole + (units - whole) * blocks;
-    if (E == 128 && blocks == 3) return launch_attn_variant<128, 3, 4, MODE>(p, groups, s);
-    if (E == 128) return launch_attn_variant<128, 2, 4, MODE>(p, groups, s);
-    if (blocks == 3) return launch_attn_variant<64, 3, 4, MODE>(p, groups, s);
-    return launch_attn_variant<64, 2, 4, MODE>(p, groups, s);
+    p.whole = (int)attn_whole_chunks(E, blocks, units, &cost);
+    const AttnPart form = attn_part_form(E, p.whole, (units - p.whole) * blocks, MODE == kColumnList ? p.k_stride : p.N, MODE == kColumnList);
+    if (form == kRows32Shared) return launch_attn_parts_as<MODE, kRows32Shared>(p, E, units, s);
+    if (form == kRows64Shared) return launch_attn_parts_as<MODE, kRows64Shared>(p, E, units, s);
+    return launch_attn_parts_as<MODE, kRows64>(p, E, units, s);
 }
 
 // Without a list the rows need not follow the chunks: 128 or 192 at a time, whichever is cheaper.
@@ -1123,6 +1261,16 @@ extern "C" int32_t chipmunk_attn_dense_colsum_stale(const uint16_t* q, const uin
 
 // Whether a refresh takes two launches; for the tests, like the next.
 extern "C" int32_t chipmunk_internal_attn_refresh_apart(int B, int H, int N, int c) { return refresh_apart((int64_t)B * H * ((N + c - 1) / c), N); }
+
+// How the chunks that have no workgroup of their own are walked (AttnPart); -1: there are none.
+extern "C" int32_t chipmunk_internal_attn_part_form(int B, int H, int N, int E, int c, int k_stride, int list) {
+    const int64_t bh = (int64_t)B * H;
+    const int rows = list ? c : attn_dense_rows(bh, N, E);
+    const int64_t units = bh * ((N + rows - 1) / rows);
+    double cost;
+    const int64_t whole = attn_whole_chunks(E, rows / 64, units, &cost);
+    return whole == units ? -1 : attn_part_form(E, whole, (units - whole) * (rows / 64), list ? k_stride : N, list);
+}
 
 // What the rules above choose for these sizes: the rows of a workgroup that takes a whole chunk, the chunks that have one, the
 // chunks walked by a workgroup per 64 rows, and the pieces of the column-sum pass.  Not part of the library's interface:

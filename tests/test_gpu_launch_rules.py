@@ -571,3 +571,69 @@ def test_mlp_delta_of_more_neurons_than_32_bits_of_bytes(cm, oracle):
                             np.arange(last, dtype=np.int32).reshape(1, 1, last), np.array([[last]], dtype=np.int32), a_ref, o_ref, c, 1)
     assert rel_err(si.np_f32(a_cache[:, -last:].contiguous()), a_ref) <= REL_TOL
     assert rel_err(si.np_f32(o_cache), o_ref, o_ref - o_before) <= REL_TOL
+
+
+def _attn_part_form(cm, H, N, E, c, k):
+    """how the chunks in parts are walked: 0 a workgroup per 64 rows, 1 the same with two waves to a row, 2 those per 32 rows"""
+    return cm.load().chipmunk_internal_attn_part_form(1, H, N, E, c, k, int(k > 0))
+
+
+@pytest.mark.parametrize("H,N,E,c,k,form", [
+    (1, 193, 128, 192, 96, 0), (1, 193, 128, 192, 97, 2), (2, 650, 64, 192, 300, 2),            # up to 128 parts
+    (11, 1000, 128, 192, 768, 1), (10, 1250, 128, 128, 800, 1), (11, 1000, 64, 192, 767, 0), (11, 1000, 64, 192, 768, 2),
+    (10, 2100, 128, 192, 2048, 1), (260, 300, 128, 192, 150, 2), (260, 300, 64, 192, 150, 2)])   # over 256 parts; behind whole chunks
+@pytest.mark.parametrize("masked", [False, True])
+def test_column_lists_walked_by_pairs_of_waves(cm, oracle, H, N, E, c, k, form, masked):
+    """Two waves share their rows and take every second tile: lists of one tile (the second wave has none), of an odd and an even
+    number, ending inside one.  masked: the first step's second tile holds columns whose scores are -inf (products beyond the largest
+    32-bit number): nothing of what the second wave multiplies there counts.  Judged chunk by chunk, each on the scale
+    of its own update: a weight is rounded to bf16 (2^-9 of it), and beside lists of hundreds of columns, whose updates are small,
+    one of 33 is off by more than 2 % of the whole tensor's RMS (0.023 at 768 columns)."""
+    assert _attn_part_form(cm, H, N, E, c, k) == form
+    q, kk, v = recipes.attn_inputs(1, H, N, E, 41, DEV)
+    scale, NB = 1 / math.sqrt(E), -(-N // c)
+    idx, _ = recipes.attn_indices(H * NB, N, k, 41, DEV)
+    edges = torch.tensor([n for n in (k, 0, 1, 32, 33, 63, 64, 65, 95, 97, 128, 129) if n <= k], dtype=torch.int32)
+    counts = edges[torch.arange(H * NB) % len(edges)].to(DEV)
+    if masked:   # column 0 in those places (only one list has them all), every query's first column large
+        q[..., 0], kk[..., 0, :], kk[..., 0, 0] = 2.0 ** 100, 0.0, -(2.0 ** 100)
+        kk[..., 1:, 0] = 0.0
+        place = torch.arange(64, device=DEV)
+        second = place // (E // 64) % 2 == 1
+        idx = torch.where(idx == 0, 1, idx)
+        idx[:, :64][:, second[:min(64, k)]] = 0
+        counts = torch.where(counts < 65, torch.where(counts == 0, 0, k), counts).to(torch.int32)   # no list may be masked whole
+    idx, counts = idx.view(1, H, NB, k).contiguous(), counts.view(1, H, NB)
+    base = recipes.attn_base(tuple(q.shape), k, "delta", 41, DEV)
+    out = torch.full_like(q, 7.0)
+    cm.attn_sparse_delta(q, kk, v, idx, counts, base, out, c, scale, 1.0)
+    basen = si.np_f32(base).astype(np.float64)
+    ref = oracle.attn_sparse_delta(si.np_f32(q), si.np_f32(kk), si.np_f32(v), idx.cpu().numpy(), counts.cpu().numpy(),
+                                   basen, c, scale, 1.0)
+    got = si.np_f32(out)
+    for rows in (slice(i * c, min(N, (i + 1) * c)) for i in range(NB)):
+        for h in range(H):
+            assert rel_err(got[0, h, rows], ref[0, h, rows], ref[0, h, rows] - basen[0, h, rows]) <= REL_TOL
+    cm.attn_sparse_delta(q, kk, v, idx, counts, base, base, c, scale, 1.0)      # in place
+    assert torch.equal(base, out)
+
+
+@pytest.mark.parametrize("H,N,E,form", [(2, 2, 128, 0), (3, 96, 128, 0), (3, 97, 64, 2), (20, 384, 128, 2), (20, 700, 128, 1),
+                                        (22, 400, 64, 2), (10, 2050, 64, 1)])
+def test_dense_attention_walked_by_pairs_of_waves(cm, oracle, H, N, E, form):
+    """The same without a list, and the statistics that the column sums are made with: a reference within 2^8 of the row's maximum
+    and the sum against it."""
+    c, scale = 192, 1 / math.sqrt(E)
+    assert _attn_part_form(cm, H, N, E, c, 0) == form
+    q, k, v = recipes.attn_inputs(1, H, N, E, 42, DEV)
+    out, NB, ld = torch.full_like(q, 7.0), -(-N // c), -(-N // 4) * 4
+    D = torch.zeros((1, H, NB, ld), dtype=torch.float32, device=DEV)
+    ws = _u8(cm.attn_dense_workspace_bytes(1, H, N))
+    cm.attn_dense(q, k, v, out, D, c, scale, ws)
+    ref, D_ref = oracle.attn_dense(si.np_f32(q), si.np_f32(k), si.np_f32(v), c, scale, want_colsum=True)
+    assert rel_err(si.np_f32(out), ref) <= REL_TOL
+    assert rel_err(D.cpu().numpy()[..., :N].astype(np.float64), D_ref) <= REL_TOL
+    m, l = (t.cpu().numpy().astype(np.float64) for t in cm.attn_dense_row_stats(ws, 1, H, N))
+    m_ref, l_ref = oracle.attn_row_stats(si.np_f32(q), si.np_f32(k), scale)
+    assert np.abs(m + np.log(l) - (m_ref + np.log(l_ref))).max() <= 2e-3
+    assert (m <= m_ref + 1e-3).all() and (m >= m_ref - 8 * math.log(2.0) - 1e-3).all()
