@@ -782,31 +782,34 @@ namespace chipmunk {
 // 8 of 128 x 256 7.2 -> 4.4 us, 602 of 192 x 3072 139 -> 127 us (5.6 TB/s).
 // STREAM: loads past the caches' usual order of replacement, for an x that does not fit the last-level cache.  Means and scores
 // together, us without and with: 709 MB 220.6, 201.6; 414 MB 127, 109; 298 MB 108, 99; 162 MB (just read) 43.8, 47.3.
+// LANES: lanes per row, 64 or, where a workgroup per 512 columns leaves the chip idle, 16 (128 columns, four rows a load: a chunk
+// of 192 is requested at once).
 constexpr int kMeanWaves = 8, kMeanAhead = 6;
-template <bool STREAM>
+template <bool STREAM, int LANES>
 __global__ __launch_bounds__(64 * kMeanWaves) void chunk_mean_kernel(const uint16_t* __restrict__ x, uint16_t* __restrict__ xm,
                                                                      int N, int NB, int D, int c) {
-    __shared__ float s_part[kMeanWaves - 1][8][64];
-    const int col_blocks = (D / 8 + 63) / 64;        // grid.x = units * col_blocks
+    constexpr int ROWS = 64 / LANES;                 // rows per load
+    __shared__ float s_part[kMeanWaves - 1][8][LANES];
+    const int col_blocks = (D / 8 + LANES - 1) / LANES;   // grid.x = units * col_blocks
     const int unit = blockIdx.x / col_blocks;
     const int b = unit / NB, chunk = unit % NB;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int col8 = (blockIdx.x % col_blocks) * 64 + lane;
+    const int col8 = (blockIdx.x % col_blocks) * LANES + lane % LANES;
     const bool live = col8 * 8 < D;
     const int r0 = chunk * c, r1 = min(N, r0 + c);
     float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (live) {
         const uint16_t* xc = x + (int64_t)b * N * D + col8 * 8;
-        for (int r = r0 + w; r < r1; r += kMeanWaves * kMeanAhead) {
+        for (int r = r0 + w * ROWS + lane / LANES; r < r1; r += kMeanWaves * ROWS * kMeanAhead) {
             u32x4 v[kMeanAhead];
 #pragma unroll
             for (int i = 0; i < kMeanAhead; i++) {
-                const u32x4* at = reinterpret_cast<const u32x4*>(xc + (int64_t)min(r + i * kMeanWaves, r1 - 1) * D);
+                const u32x4* at = reinterpret_cast<const u32x4*>(xc + (int64_t)min(r + i * kMeanWaves * ROWS, r1 - 1) * D);
                 v[i] = STREAM ? __builtin_nontemporal_load(at) : *at;
             }
 #pragma unroll
             for (int i = 0; i < kMeanAhead; i++) {
-                const bool exists = r + i * kMeanWaves < r1;
+                const bool exists = r + i * kMeanWaves * ROWS < r1;
 #pragma unroll
                 for (int e = 0; e < 4; e++) {
                     const uint32_t pair = exists ? v[i][e] : 0u;
@@ -816,12 +819,16 @@ __global__ __launch_bounds__(64 * kMeanWaves) void chunk_mean_kernel(const uint1
             }
         }
     }
-    if (w > 0) {
+    if (ROWS == 4) {
+#pragma unroll
+        for (int e = 0; e < 8; e++) s[e] = rows4_sum(s[e]);
+    }
+    if (w > 0 && lane < LANES) {
 #pragma unroll
         for (int e = 0; e < 8; e++) s_part[w - 1][e][lane] = s[e];
     }
     __syncthreads();
-    if (w > 0 || !live) return;
+    if (w > 0 || lane >= LANES || !live) return;
 #pragma unroll
     for (int i = 0; i < kMeanWaves - 1; i++)
 #pragma unroll
@@ -838,6 +845,77 @@ __global__ __launch_bounds__(64 * kMeanWaves) void chunk_mean_kernel(const uint1
     uint16_t* orow = xm + (int64_t)unit * 2 * D;
     *reinterpret_cast<u32x4*>(orow + col8 * 8) = hi4;
     *reinterpret_cast<u32x4*>(orow + D + col8 * 8) = lo4;
+}
+
+// Scores of few chunks: T[n][f] = <hi[n] + lo[n], w1[f]> for up to 16 UB chunks and 16 NBK neurons per workgroup.
+// Bound: w1 from memory, read once, as long as the means, which every workgroup reads whole from L2, are few (few_scores).  The
+// eight waves of a workgroup cut the contraction among them, 64 entries (a cache line of a row) at a time in turn, and load both
+// operands from memory in the products' own layout; the partial sums meet in LDS in a fixed order, so no partial result goes
+// through memory and nothing is left for another launch.
+constexpr int kFewWaves = 8;
+template <int UB, int NBK>
+__global__ __launch_bounds__(64 * kFewWaves) void mlp_few_scores_kernel(const uint16_t* __restrict__ xm, const uint16_t* __restrict__ w1,
+                                                                       float* __restrict__ T, int units, int D, int F) {
+    constexpr int AHEAD = UB * NBK <= 2 && NBK == 1 ? 2 : 1;   // more was not faster: the waves cover each other
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    f32x4 (*s_part)[NBK * UB][64] = reinterpret_cast<f32x4 (*)[NBK * UB][64]>(smem);
+    const int lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int f0 = (int)blockIdx.x * 16 * NBK;
+    const __amdgpu_buffer_rsrc_t wbuf = raw_buffer(w1, (uint32_t)F * D * 2u), mbuf = raw_buffer(xm, (uint32_t)units * D * 4u);
+    uint32_t wat[NBK], mat[UB];   // byte offsets of the lane's rows; chunks beyond the last repeat it and are not stored
+#pragma unroll
+    for (int nb = 0; nb < NBK; nb++) wat[nb] = (uint32_t)(f0 + nb * 16 + l16) * (uint32_t)(D * 2) + g * 16;
+#pragma unroll
+    for (int ub = 0; ub < UB; ub++) mat[ub] = (uint32_t)min(ub * 16 + l16, units - 1) * (uint32_t)(D * 4) + g * 16;
+    struct Entries { bf16x8 w[NBK][2], m[UB][2][2]; };   // [slice of 32]; means: [high, low][slice]
+    auto load = [&](Entries& e, int at) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++) {
+            const int from = at * 128 + ks * 64;
+#pragma unroll
+            for (int nb = 0; nb < NBK; nb++) e.w[nb][ks] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wbuf, wat[nb], from, 0));
+#pragma unroll
+            for (int ub = 0; ub < UB; ub++)
+#pragma unroll
+                for (int hl = 0; hl < 2; hl++)
+                    e.m[ub][hl][ks] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(mbuf, mat[ub], from + hl * D * 2, 0));
+        }
+    };
+    f32x4 acc[NBK][UB][2] = {};   // high and low parts apart: added to the high parts' sum, every low product costs it a rounding
+    const int all = D / 64;
+    Entries ring[AHEAD];
+#pragma unroll
+    for (int i = 0; i < AHEAD; i++) load(ring[i], min(w + i * kFewWaves, all - 1));
+    for (int at = w; at < all; at += AHEAD * kFewWaves) {
+#pragma unroll
+        for (int i = 0; i < AHEAD; i++) {
+            if (at + i * kFewWaves < all) {
+#pragma unroll
+                for (int ks = 0; ks < 2; ks++)
+#pragma unroll
+                    for (int nb = 0; nb < NBK; nb++)
+#pragma unroll
+                        for (int ub = 0; ub < UB; ub++)
+#pragma unroll
+                            for (int hl = 0; hl < 2; hl++)
+                                acc[nb][ub][hl] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ring[i].w[nb][ks], ring[i].m[ub][hl][ks], acc[nb][ub][hl], 0, 0, 0);
+            }
+            if (at + (i + AHEAD) * kFewWaves < all) load(ring[i], at + (i + AHEAD) * kFewWaves);
+        }
+    }
+#pragma unroll
+    for (int nb = 0; nb < NBK; nb++)
+#pragma unroll
+        for (int ub = 0; ub < UB; ub++) s_part[w][nb * UB + ub][lane] = acc[nb][ub][0] + acc[nb][ub][1];
+    __syncthreads();
+    for (int i = threadIdx.x; i < NBK * UB * 64; i += 64 * kFewWaves) {
+        const int block = i >> 6, l = i & 63, n = block % UB * 16 + (l & 15);
+        f32x4 sum = s_part[0][block][l];
+#pragma unroll
+        for (int ww = 1; ww < kFewWaves; ww++) sum += s_part[ww][block][l];
+        if (n < units) *reinterpret_cast<f32x4*>(T + (int64_t)n * F + f0 + block / UB * 16 + (l >> 4) * 4) = sum;
+    }
 }
 
 // out[i] = sum over the pieces of a split contraction, in piece order (deterministic)
@@ -1119,6 +1197,23 @@ static ScoresPlan scores_plan(int units, int D, int F) {
     return {two_is_exact ? two : std::max(1, chains / 2), true};
 }
 
+// Chunk means by workgroups of 128 columns where those of 512 leave most of the CUs without one.  Whole calls in us, 512 and
+// 128 columns: 8 chunks of 192 x 3072 (F = 4096) 13.3, 12.0; 24 x 1024 (12 288) 14.3, 13.1; 40 x 1408 (4096) 14.9, 14.4; 60 x 2048
+// (4096) 25.9, 26.2; 108 x 512 (3136) 17.4, 18.3.
+static bool narrow_means(int units, int D) { return (D + 511) / 512 * units <= 96; }
+
+// Few chunks: a workgroup per 16, 32 or 64 neurons, the fewest that give every CU at most one, with all chunks.  Every workgroup reads
+// all means (4 D bytes a chunk), which is what sets the limits; just above 8192 neurons the workgroups are fewest and read most.
+// Whole calls in us, with the tiles of mlp_dense.h (and the sum of their pieces) and with these: 3 chunks x 512 x 2048 neurons 12.0, 8.8;
+// 8 x 1024 x 4096 13.3, 8.7; 8 x 3072 x 12 288 28.0, 20.8; 16 x 3072 x 8192 24.2, 18.3; 24 x 1024 x 12 288 19.8, 13.1; 24 x 3072 x 12 288 32.3,
+// 28.8; 40 x 1408 x 4096 16.0, 14.4; beyond the limits 20 x 2816 x 9408 23.1, 24.5; 24 x 3072 x 4096 1.02 to 1.16 of the time; 48 x 2048 x 6144
+// 1.08 to 1.2.
+static int few_neuron_blocks(int F) { return F <= 16 * 256 ? 1 : F <= 32 * 256 ? 2 : 4; }
+static bool few_scores(int units, int D, int F) {
+    const int64_t limit = F <= 32 * 256 ? 57344 : F <= 44 * 256 ? 40960 : 73728;
+    return units <= 48 && (int64_t)units * D <= limit;
+}
+
 // Workspace of the token-merged pre-activation with the contraction cut in `pieces`: the chunk means in split
 // precision [units, 2 D] bf16 (rounded up to 256 bytes), then, with more than one piece, the pieces' partial
 // results [pieces, units, F] fp32.  0 when the shapes are out of range.
@@ -1274,10 +1369,23 @@ static int32_t run_tile_mean(const uint16_t* x, const uint16_t* w1, float* T, in
                              void* ws, int pieces, hipStream_t s) {
     const int NB = (N + c - 1) / c, units = B * NB;
     const bool stream_x = (int64_t)B * N * D * 2 > kLastLevelCache;
-    hipLaunchKernelGGL(stream_x ? chunk_mean_kernel<true> : chunk_mean_kernel<false>, dim3((unsigned)(((D / 8 + 63) / 64) * units)),
-                       dim3(64 * kMeanWaves), 0, s, x, (uint16_t*)ws, N, NB, D, c);
+    const bool narrow = !stream_x && narrow_means(units, D);
+    hipLaunchKernelGGL((stream_x ? chunk_mean_kernel<true, 64> : narrow ? chunk_mean_kernel<false, 16> : chunk_mean_kernel<false, 64>),
+                       dim3((unsigned)((narrow ? D / 128 : (D / 8 + 63) / 64) * units)), dim3(64 * kMeanWaves), 0, s, x, (uint16_t*)ws, N, NB, D, c);
     if (launch_status() != CHIPMUNK_OK) return CHIPMUNK_ERR_LAUNCH;
     // scores[unit, f] = <hi(unit) + lo(unit), w1_f>
+    if (few_scores(units, D, F)) {
+        const int blocks = few_neuron_blocks(F);
+        auto launch = [&](auto kernel) {
+            const int lds = kFewWaves * blocks * ((units + 15) / 16) * 1024;
+            if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return (int32_t)CHIPMUNK_ERR_LAUNCH;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(F / (16 * blocks))), dim3(64 * kFewWaves), lds, s, (const uint16_t*)ws, w1, T, units, D, F);
+            return launch_status();
+        };
+        if (units <= 16) return launch(blocks == 1 ? mlp_few_scores_kernel<1, 1> : blocks == 2 ? mlp_few_scores_kernel<1, 2> : mlp_few_scores_kernel<1, 4>);
+        if (units <= 32) return launch(blocks == 1 ? mlp_few_scores_kernel<2, 1> : blocks == 2 ? mlp_few_scores_kernel<2, 2> : mlp_few_scores_kernel<2, 4>);
+        return launch(blocks == 1 ? mlp_few_scores_kernel<3, 1> : blocks == 2 ? mlp_few_scores_kernel<3, 2> : mlp_few_scores_kernel<3, 4>);
+    }
     const ScoresPlan plan = scores_plan(units, D, F);
     pieces = std::min(pieces, plan.pieces);
     size_t means = ((size_t)units * 2 * D * 2 + 255) / 256 * 256;
@@ -1385,3 +1493,11 @@ extern "C" void chipmunk_internal_mlp_tiles(int B, int N, int D, int F, int c, i
 
 // whether a delta with these sizes has its cached output pass the caches by
 extern "C" int32_t chipmunk_internal_mlp_streams(int B, int N, int D, int c) { return stream_output((int64_t)B * ((N + c - 1) / c), c, D); }
+
+// how the scores of these sizes are made: 16-neuron blocks of a workgroup where the chunks are few, else 0; whether the means come in
+// workgroups of 128 columns
+extern "C" void chipmunk_internal_scores_form(int B, int N, int D, int F, int c, int32_t* out) {
+    const int units = B * ((N + c - 1) / c);
+    out[0] = few_scores(units, D, F) ? few_neuron_blocks(F) : 0;
+    out[1] = (int64_t)B * N * D * 2 <= kLastLevelCache && narrow_means(units, D);
+}

@@ -637,3 +637,28 @@ def test_dense_attention_walked_by_pairs_of_waves(cm, oracle, H, N, E, form):
     m_ref, l_ref = oracle.attn_row_stats(si.np_f32(q), si.np_f32(k), scale)
     assert np.abs(m + np.log(l) - (m_ref + np.log(l_ref))).max() <= 2e-3
     assert (m <= m_ref + 1e-3).all() and (m >= m_ref - 8 * math.log(2.0) - 1e-3).all()
+
+
+@pytest.mark.parametrize("B,N,D,F,c,form", [
+    (1, 1, 128, 64, 192, (1, 1)), (1, 15 * 128 + 7, 128, 4096, 128, (1, 1)), (2, 8 * 192, 1152, 4160, 192, (2, 1)),
+    (1, 16 * 128 + 1, 640, 8192, 128, (2, 1)), (2, 15 * 128 + 1, 1408, 320, 128, (1, 1)), (1, 32 * 128 - 1, 384, 8256, 128, (4, 1)),
+    (1, 32 * 128 + 1, 256, 576, 128, (1, 1)), (3, 16 * 192, 1152, 4224, 192, (2, 0)), (1, 47 * 128 + 3, 512, 11328, 128, (4, 1)),
+    (1, 48 * 128 + 1, 512, 64, 128, (0, 1)), (1, 128 * 128, 640, 64, 128, (0, 0)), (2, 50 * 128 - 3, 640, 2048, 128, (0, 0)),
+    (1, 64 * 128, 1024, 5120, 128, (0, 0))])
+def test_neuron_scores_of_few_chunks(cm, oracle, B, N, D, F, c, form):
+    """Up to 48 chunks: one to three blocks of 16 of them, the last ragged; workgroups of 16, 32 and 64 neurons; contractions of fewer
+    lines than a workgroup has waves, and of a number that its waves do not divide; both sides of the limit, beyond which the
+    contraction is cut into pieces or not.  Means in workgroups of 128 and of 512 columns.  Tolerance as for the pieces."""
+    out = (ctypes.c_int32 * 2)()
+    cm.load().chipmunk_internal_scores_form(B, N, D, F, c, out)
+    assert tuple(out) == form
+    g = si.generator(43, DEV)
+    x, w1 = si.randn_bf16((B, N, D), g), si.randn_bf16((F, D), g, 1 / math.sqrt(D))
+    NB = -(-N // c)
+    T = torch.full((B * NB + 1, F), float("nan"), dtype=torch.float32, device=DEV)
+    cm.mlp_tile_mean_preact(x, w1, T[:-1].view(B, NB, F), c, _u8(cm.mlp_tile_mean_workspace_bytes(B, N, D, F, c)))
+    assert rel_err(T[:-1].view(B, NB, F).cpu().numpy(), oracle.mlp_tile_scores(si.np_f32(x), si.np_f32(w1), c)) <= SUM_TOL
+    assert bool(T[-1].isnan().all())
+    again = torch.empty((B, NB, F), dtype=torch.float32, device=DEV)
+    cm.mlp_tile_mean_preact_static(x, w1, again, c)
+    assert torch.equal(again.view(-1, F), T[:-1])
