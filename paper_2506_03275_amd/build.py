@@ -1,15 +1,19 @@
 """Builds the HIP kernels and the C-ABI library (libchipmunk_hip.so) for gfx950, in-tree, and beside it the
-device-ceiling probes that bench.py --ceilings times (libchipmunk_ceilings.so)."""
+device-ceiling probes that bench.py --ceilings times (libchipmunk_ceilings.so) and the compiled part of the
+Python binding (_native.so)."""
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libchipmunk_hip.so")
 PROBE_SRC = os.path.join(HERE, "probe", "ceilings.hip")
 PROBE_LIB = os.path.join(HERE, "libchipmunk_ceilings.so")
+NATIVE_SRC = os.path.join(HERE, "binding", "native.cpp")
+NATIVE = os.path.join(HERE, "_native.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fno-honor-nans",
@@ -26,14 +30,27 @@ def sources():
 def is_stale():
     if not os.path.exists(LIB):
         return True
+    if not os.path.exists(NATIVE) or os.path.getmtime(NATIVE_SRC) > os.path.getmtime(NATIVE):
+        return True
     deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + [os.path.join(HERE, "..", "include", "chipmunk.h")]
     return any(os.path.getmtime(d) > os.path.getmtime(LIB) for d in deps)
+
+
+def _native_command():
+    """The compiled binding is host code against the headers of the torch that imports it."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
+            "-I" + sysconfig.get_paths()["include"], NATIVE_SRC, "-o", NATIVE,
+            "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
 
 
 def build(verbose=False):
     """Compile every .hip source into one shared library.  Always recompiles."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objs = []
+    native = subprocess.Popen(_native_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     procs = []
     for src in sources():
         obj = src[:-4] + ".o"
@@ -51,8 +68,12 @@ def build(verbose=False):
             sys.stderr.write(f"hipcc failed on {src}:\n{out}\n")
         elif verbose and out.strip():
             print(out)
+    out, _ = native.communicate()
+    if native.returncode != 0:
+        failed = True
+        sys.stderr.write(f"{native.args[0]} failed on {NATIVE_SRC}:\n{out}\n")
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("the compiler failed")
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.run(cmd, check=True)
     for o in objs:

@@ -108,7 +108,6 @@ def sparse_step(blocks, step, side_stream=None, after_block=None):
     """Runs one column-sparse step of every block.  With side_stream, block b+1's MLP indices are computed on it
     while block b runs on the current stream.  after_block(b, blk), if given, is called after block b's calls were
     enqueued (tests use it to copy results out)."""
-    main = torch.cuda.current_stream()
     if side_stream is None:
         for b, blk in enumerate(blocks):
             blk.attn_delta(step)
@@ -117,6 +116,7 @@ def sparse_step(blocks, step, side_stream=None, after_block=None):
             if after_block:
                 after_block(b, blk)
         return
+    main = torch.cuda.current_stream()
     ready = [torch.cuda.Event() for _ in blocks]
     side_stream.wait_stream(main)        # everything enqueued so far (previous step's caches) is visible to the side stream
     with torch.cuda.stream(side_stream):

@@ -1,0 +1,107 @@
+"""The compiled binding (binding/native.cpp) against the Python functions that it stands in front of: the same results for what it
+answers, and everything else left to them, so that the same calls raise the same errors."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as si
+
+
+@pytest.fixture(scope="module")
+def cm():
+    import paper_2506_03275_amd as cm
+    cm.load()
+    return cm
+
+
+def _calls(dev):
+    """Arguments of every function that the binding has, small and valid."""
+    B, H, N, E, c, D, F, k = 1, 2, 200, 64, 128, 128, 64, 33
+    g = si.generator(51, dev)
+    r = lambda *shape: si.randn_bf16(shape, g)   # noqa: E731
+    q, kk, v, x, w1, w2 = r(B, H, N, E), r(B, H, N, E), r(B, H, N, E), r(B, N, D), r(F, D), r(F, D)
+    f32 = lambda *shape: torch.zeros(shape, dtype=torch.float32, device=dev)   # noqa: E731
+    i32 = lambda *shape: torch.zeros(shape, dtype=torch.int32, device=dev)     # noqa: E731
+    u8 = lambda n: torch.zeros(n, dtype=torch.uint8, device=dev)               # noqa: E731
+    idx = torch.arange(k, dtype=torch.int32, device=dev).expand(B, H, 2, k).contiguous()
+    counts = torch.full((B, H, 2), k, dtype=torch.int32, device=dev)
+    midx, mcounts = idx[:, 0].contiguous(), counts[:, 0].contiguous()
+    scale = 1 / math.sqrt(E)
+    scores = torch.arange(5 * 104, dtype=torch.float32, device=dev).view(5, 104).sin()
+    ones = f32(B, H, N) + 1
+    return dict(
+        voxel_reorder=[x, torch.empty_like(x), i32(N), None, 4, 2, 7, 14, 0, 2, 4, 4, False],
+        topk_cols=[scores[:, :101], scores.flip(0)[:, :101], 7, i32(5, 8), i32(5)],
+        attn_sparse_delta=[q, kk, v, idx, counts, r(B, H, N, E), torch.empty_like(q), c, scale, -1.0],
+        attn_dense=[q, kk, v, torch.empty_like(q), f32(B, H, 2, N), c, scale, u8(B * H * N * 8)],
+        attn_dense_colsum_stale=[q, kk, v, torch.empty_like(q), ones, ones * 50, f32(B, H, 2, N), c, scale, f32(B, H, N), f32(B, H, N)],
+        mlp_tile_mean_preact=[x, w1, f32(B, 2, F), c, u8(1 << 20)],
+        mlp_sparse_delta=[x, w1, r(F), w2, midx, mcounts, r(B, F, N), r(B, N, D), c, 1, u8(1 << 20)],
+        mlp_dense=[x, w1, r(F), w2, r(D), r(B, N, D), r(B, F, N), c, 0])
+
+
+NAMES = list(_calls("cpu"))
+
+
+def _outcome(cm, fast, name, args):
+    """What a call raises, or the tensors that it was given, as they are behind it."""
+    args = [a.clone(memory_format=torch.preserve_format) if type(a) is torch.Tensor and a._base is None else a for a in args]
+    before, cm._fast = cm._fast, fast
+    try:
+        getattr(cm, name)(*args)
+    except Exception as e:   # noqa: BLE001
+        return type(e).__name__, str(e)
+    finally:
+        cm._fast = before
+    return [a for a in args if isinstance(a, torch.Tensor)]
+
+
+def _wrong(args):
+    """The same arguments with one of them spoiled, each in the ways that a caller may get it wrong."""
+    for i, a in enumerate(args):
+        if isinstance(a, torch.Tensor):
+            spoiled = [a.double(), a[..., :0], a[0], np.zeros(3), 3, None, a.float() if a.dtype != torch.float32 else a.to(torch.bfloat16)]
+            spoiled += [torch.cat([a, a], -1)[..., ::2], a.cpu()] if a.dim() and a.shape[-1] > 1 else []
+        elif a is None:
+            spoiled = ["x"]
+        else:
+            spoiled = [str(a), 2 ** 40 if isinstance(a, int) else math.nan, None, -1, 0.5]
+        for s in spoiled:
+            yield i, args[:i] + [s] + args[i + 1:]
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_what_is_wrong_raises_what_it_raised(cm, name):
+    """On the CPU every call is refused; which error it is must not hang on the binding, whose answer is always None."""
+    native = cm._fast
+    assert native.__name__.endswith("_native")
+    args = _calls("cpu")[name]
+    assert getattr(native, name)(*args) is None and getattr(native, name)(*args[:-1]) is None and getattr(native, name)() is None
+    for i, bad in _wrong(args):
+        assert getattr(native, name)(*bad) is None, i
+        got = _outcome(cm, native, name, bad)
+        assert isinstance(got, tuple) and got == _outcome(cm, cm._Python(), name, bad), i
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", NAMES)
+def test_the_binding_does_what_the_python_functions_do(cm, name):
+    native = cm._fast
+    args = _calls("cuda")[name]
+    assert getattr(native, name)(*[a.clone(memory_format=torch.preserve_format) if type(a) is torch.Tensor and a._base is None else a for a in args]) == 0
+    got, want = _outcome(cm, native, name, args), _outcome(cm, cm._Python(), name, args)
+    assert isinstance(got, list) and all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) if a.is_contiguous() else torch.equal(a, b)
+                                         for a, b in zip(got, want))
+    optional = {"voxel_reorder": (2,), "topk_cols": (1,), "attn_dense": (4,), "mlp_sparse_delta": (2,), "mlp_dense": (2, 4)}
+    for i in optional.get(name, ()):
+        less = args[:i] + [None] + args[i + 1:]
+        got, want = _outcome(cm, native, name, less), _outcome(cm, cm._Python(), name, less)
+        assert isinstance(got, list) and all(torch.equal(a, b) for a, b in zip(got, want))
+    side = torch.cuda.Stream()   # on the caller's stream, whichever it is
+    with torch.cuda.stream(side):
+        assert cm._raw_stream(torch.cuda.current_device()) == side.cuda_stream
+        again = _outcome(cm, native, name, args)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(again, _outcome(cm, cm._Python(), name, args)))
