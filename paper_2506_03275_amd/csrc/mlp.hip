@@ -1023,7 +1023,8 @@ enum FirstForm { kFirstChunk = 0, kFirstLarge = 1, kFirstSmall = 2 };   // 128 n
 // 1664 x 1024 17, 41, 7; 4608 x 3072 x 12 288: 352, 274, -.
 // Tiles of 64 x 64 are left out where they take more than two rounds, but for contractions of at most 14 steps (of 100 calls two fewer
 // are 4 per cent slower than with the best tiles), and for lists of more than half the neurons, which were not measured.
-static FirstForm first_form(bool sparse, int B, int N, int D, int F, int c, int k_stride) {
+// *us: the price of the form that is taken.
+static FirstForm first_form(bool sparse, int B, int N, int D, int F, int c, int k_stride, double* us = nullptr) {
     static const Price chunk_delta[2] = {{0.74, 10.87, 6, 0.52, 0.19, 0.71, 0.19}, {0.648, 5, 6, 0.46, 0.2, 0.66, 0.2}};   // c = 192, 128
     static const Price large_delta[2] = {{1.222, 21.22, 6, 0.67, 0.17, 0.84, 0.17}, {1.015, 9.69, 5.7, 0.55, 0.17, 0.72, 0.17}};
     static const Price small_delta = {0.411, 2.64, 4.53, 0.35, 0.12, 0.77, 0.17};
@@ -1042,8 +1043,11 @@ static FirstForm first_form(bool sparse, int B, int N, int D, int F, int c, int 
     const double small = price(sparse ? small_delta : small_dense, small_tiles, 64, steps);
     const bool large_fits = sparse || B <= 65535;   // the dense form takes the batch from the second grid dimension
     const bool small_fits = small_launches(small_tiles) && (small_tiles <= 128 || steps <= 14) && (!sparse || k_stride <= F / 2);
-    if (small_fits && small < chunk && (!large_fits || small < large)) return kFirstSmall;
-    return large_fits && large < chunk ? kFirstLarge : kFirstChunk;
+    const FirstForm form = small_fits && small < chunk && (!large_fits || small < large) ? kFirstSmall
+                           : large_fits && large < chunk                               ? kFirstLarge
+                                                                                       : kFirstChunk;
+    if (us) *us = form == kFirstSmall ? small : form == kFirstLarge ? large : chunk;
+    return form;
 }
 
 // Second GEMM.  kSecondChunk: a workgroup per chunk and 128 columns; those beyond `whole` tiles per XCD take 64 rows each where they
@@ -1057,6 +1061,7 @@ enum SecondForm { kSecondChunk = 0, kSecondLarge = 1, kSecondSmall = 2 };
 struct SecondPlan {
     SecondForm form;
     int64_t whole;   // tiles per XCD
+    double us;       // its price
 };
 constexpr int kSmallList = 4096;   // entries of a list that fit LDS beside the ring of tiles of 64 x 64, two workgroups per CU
 // Kernel times (whole, parts, small, large), us: delta, c = 192, 4 chunks x 249 of 5248 x 1408: 9.3, 5.6, 5.0, -; 9 x 395 of 7488 x 4864: 18,
@@ -1074,7 +1079,7 @@ static SecondPlan second_plan(bool sparse, int B, int N, int D, int F, int c, in
     const int64_t chunks = (int64_t)B * ((N + c - 1) / c), tiles = per_xcd(chunks * (D / kBN));
     const Price& whole = (sparse ? whole_delta : whole_dense)[at];
     const Price& part = (sparse ? parts_delta : parts_dense)[at];
-    SecondPlan plan = {kSecondChunk, tiles};
+    SecondPlan plan = {kSecondChunk, tiles, 0.};
     if (sparse && ((int64_t)k_stride + kBN - 1) / kBN * kBN * c * 2 >= 1LL << 32) return plan;   // whole chunks only: more bytes than the parts' offsets hold
     const int64_t beyond = tiles > 64 ? tiles % 64 : tiles - 32;
     double best;
@@ -1088,18 +1093,40 @@ static SecondPlan second_plan(bool sparse, int B, int N, int D, int F, int c, in
     auto consider = [&](SecondPlan other, double us) {
         if (us < best) best = us, plan = other;
     };
-    consider({kSecondChunk, 0}, price(part, tiles * parts, 64, steps));
+    consider({kSecondChunk, 0, 0.}, price(part, tiles * parts, 64, steps));
     if (sparse) {
         const int64_t small_tiles = per_xcd(chunks * parts * (D / kSmallTile));
         if (small_launches(small_tiles) && (k_stride + kBN - 1) / kBN * kBN <= kSmallList)
-            consider({kSecondSmall, 0}, price(small_delta, small_tiles, 64, steps));
+            consider({kSecondSmall, 0, 0.}, price(small_delta, small_tiles, 64, steps));
     } else {
         const int64_t small_tiles = per_xcd((int64_t)B * ((N + kSmallTile - 1) / kSmallTile) * (D / kSmallTile));
-        if (small_launches(small_tiles)) consider({kSecondSmall, 0}, price(small_dense, small_tiles, 64, steps));
+        if (small_launches(small_tiles)) consider({kSecondSmall, 0, 0.}, price(small_dense, small_tiles, 64, steps));
         if (B <= 65535)
-            consider({kSecondLarge, 0}, price(large_dense, B * per_xcd((int64_t)((N + kDenseTile - 1) / kDenseTile) * ((D + kDenseTile - 1) / kDenseTile)), 32, steps));
+            consider({kSecondLarge, 0, 0.}, price(large_dense, B * per_xcd((int64_t)((N + kDenseTile - 1) / kDenseTile) * ((D + kDenseTile - 1) / kDenseTile)), 32, steps));
     }
+    plan.us = best;
     return plan;
+}
+
+// The rows of a chunk's tile in the two GEMMs of a dense MLP, whose tiles need not follow the chunks: those of the other chunk size
+// where the prices above say 6 % less, for the widths that models have (hidden wider than the model's).  In the second GEMM up to
+// 4.5e10 products: beyond, the prices of its tiles of 192 and 128 rows are not that exact (1.01 of the time over 59 sizes).  Whole
+// calls, of the time on the chunk's rows, 380 sizes of 3e9 to 4.5e10 products: 0.91 in the mean, both GEMMs on 128 rows instead of 192
+// 0.84 (93), the first 0.90 (93), the second 0.93 (245); on 192 instead of 128 0.90 to 0.95.
+constexpr double kOtherRows = 0.94;
+struct DenseRows { int first, second; };
+static DenseRows dense_rows(int B, int N, int D, int F, int c) {
+    const int other = 192 + 128 - c;
+    DenseRows rows = {c, c};
+    if (F <= D || D < 512) return rows;
+    double us, other_us;
+    first_form(false, B, N, D, F, c, 0, &us);
+    if (first_form(false, B, N, D, F, other, 0, &other_us) == kFirstChunk && other_us < kOtherRows * us) rows.first = other;
+    if ((double)B * N * D * F < 4.5e10) {
+        const SecondPlan plan = second_plan(false, B, N, D, F, c, 0), other_plan = second_plan(false, B, N, D, F, other, 0);
+        if (other_plan.form == kSecondChunk && other_plan.us < kOtherRows * plan.us) rows.second = other;
+    }
+    return rows;
 }
 
 template <int MODE, int BM = kDenseTile>
@@ -1322,14 +1349,14 @@ extern "C" int32_t chipmunk_mlp_dense(const uint16_t* x, const uint16_t* w1, con
     if (!aligned16(x) || !aligned16(w1) || !aligned16(w2) || !aligned16(a_cache) || !aligned16(out) ||
         (reinterpret_cast<uintptr_t>(b1) & 1u) || (reinterpret_cast<uintptr_t>(b2) & 7u) || (a_ld % 8) != 0)
         return CHIPMUNK_ERR_ALIGN;
-    const int NB = (N + c - 1) / c, units = B * NB;
     hipStream_t s = (hipStream_t)stream;
     DenseGemmParams g;
     g.x = x; g.w1 = w1; g.w2 = w2; g.a_cache = a_cache; g.out = out; g.a_ld = a_ld;
     g.scores = nullptr; g.N = N; g.D = D; g.F = F; g.act = act; g.pieces = 1;
 
-    const FirstForm first = first_form(false, B, N, D, F, c, 0);
-    const SecondPlan second = second_plan(false, B, N, D, F, c, 0);
+    const DenseRows rows = dense_rows(B, N, D, F, c);
+    const FirstForm first = first_form(false, B, N, D, F, rows.first, 0);
+    const SecondPlan second = second_plan(false, B, N, D, F, rows.second, 0);
     const int row_tiles = (N + kSmallTile - 1) / kSmallTile;   // of 64 x 64
     if (first == kFirstLarge) {
         g.bias = b1;
@@ -1338,14 +1365,14 @@ extern "C" int32_t chipmunk_mlp_dense(const uint16_t* x, const uint16_t* w1, con
         Gemm1Params g1;
         g1.x = x; g1.w1 = w1; g1.b1 = b1; g1.idx = nullptr; g1.counts = nullptr; g1.a_cache = a_cache;
         g1.delta_t = nullptr; g1.act_t = nullptr; g1.a_ld = a_ld;
-        g1.N = N; g1.NB = NB; g1.D = D; g1.F = F;
+        g1.N = N; g1.NB = (N + rows.first - 1) / rows.first; g1.D = D; g1.F = F;
         g1.k_stride = F; g1.k_pad = F; g1.act = act; g1.parts = 1;
         if (first == kFirstSmall) {
             g1.NB = row_tiles;
             st = launch_small_gemm1<kDenseAct>(g1, B * row_tiles, s);
         } else {
-            st = c == 192 ? launch_gemm1<192, kDenseAct>(g1, (F + kBN - 1) / kBN, units, s)
-                          : launch_gemm1<128, kDenseAct>(g1, (F + kBN - 1) / kBN, units, s);
+            st = rows.first == 192 ? launch_gemm1<192, kDenseAct>(g1, (F + kBN - 1) / kBN, B * g1.NB, s)
+                                   : launch_gemm1<128, kDenseAct>(g1, (F + kBN - 1) / kBN, B * g1.NB, s);
         }
     }
     if (st != CHIPMUNK_OK) return st;
@@ -1355,13 +1382,14 @@ extern "C" int32_t chipmunk_mlp_dense(const uint16_t* x, const uint16_t* w1, con
     }
     Gemm2Params g2;
     g2.a_t = a_cache; g2.w2 = w2; g2.bias = b2; g2.idx = nullptr; g2.counts = nullptr; g2.o = out;
-    g2.a_ld = a_ld; g2.N = N; g2.NB = NB; g2.D = D; g2.F = F; g2.k_stride = F; g2.k_pad = F;
+    g2.a_ld = a_ld; g2.N = N; g2.NB = (N + rows.second - 1) / rows.second; g2.D = D; g2.F = F; g2.k_stride = F; g2.k_pad = F;
     g2.act_t = nullptr; g2.a_cache = nullptr; g2.parts = 1;
     if (second.form == kSecondSmall) {
         g2.NB = row_tiles;
         return launch_small_gemm2<false>(g2, B * row_tiles, s);
     }
-    return c == 192 ? launch_gemm2<192, true>(g2, D / kBN, units, second.whole, s) : launch_gemm2<128, true>(g2, D / kBN, units, second.whole, s);
+    return rows.second == 192 ? launch_gemm2<192, true>(g2, D / kBN, B * g2.NB, second.whole, s)
+                              : launch_gemm2<128, true>(g2, D / kBN, B * g2.NB, second.whole, s);
 }
 
 // chunk means -> scores GEMM (-> sum of the pieces); ws holds tile_mean_bytes(..., pieces) bytes
@@ -1484,11 +1512,19 @@ extern "C" void chipmunk_internal_mlp_form(int B, int N, int D, int F, int c, in
 // whole), then the delta's.
 extern "C" void chipmunk_internal_mlp_tiles(int B, int N, int D, int F, int c, int k_stride, int64_t* out) {
     for (int sparse = 0; sparse < 2; sparse++) {
-        const SecondPlan plan = second_plan(sparse, B, N, D, F, c, k_stride);
-        out[3 * sparse] = first_form(sparse, B, N, D, F, c, k_stride);
+        const DenseRows rows = sparse ? DenseRows{c, c} : dense_rows(B, N, D, F, c);
+        const SecondPlan plan = second_plan(sparse, B, N, D, F, rows.second, k_stride);
+        out[3 * sparse] = first_form(sparse, B, N, D, F, rows.first, k_stride);
         out[3 * sparse + 1] = plan.form;
         out[3 * sparse + 2] = plan.whole;
     }
+}
+
+// the rows of a chunk's tile in the dense MLP's GEMMs
+extern "C" void chipmunk_internal_mlp_dense_rows(int B, int N, int D, int F, int c, int32_t* out) {
+    const DenseRows rows = dense_rows(B, N, D, F, c);
+    out[0] = rows.first;
+    out[1] = rows.second;
 }
 
 // whether a delta with these sizes has its cached output pass the caches by

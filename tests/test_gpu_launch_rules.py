@@ -662,3 +662,36 @@ def test_neuron_scores_of_few_chunks(cm, oracle, B, N, D, F, c, form):
     again = torch.empty((B, NB, F), dtype=torch.float32, device=DEV)
     cm.mlp_tile_mean_preact_static(x, w1, again, c)
     assert torch.equal(again.view(-1, F), T[:-1])
+
+
+@pytest.mark.parametrize("B,N,D,F,c,act,bias,rows", [
+    (1, 2376, 512, 896, 192, 1, True, (128, 128)), (2, 1347, 640, 768, 192, 0, False, (128, 128)), (1, 584, 512, 3392, 192, 1, True, (128, 192)),
+    (2, 465, 512, 2176, 192, 0, True, (128, 192)), (1, 2116, 512, 576, 192, 1, False, (192, 128)), (2, 1036, 512, 576, 192, 1, True, (192, 128)),
+    (2, 834, 640, 2944, 128, 1, True, (192, 128)), (2, 534, 1664, 1728, 128, 0, True, (128, 192)),
+    (1, 2376, 896, 512, 192, 1, True, (192, 192))])
+def test_dense_mlp_on_the_other_chunk_sizes_rows(cm, oracle, B, N, D, F, c, act, bias, rows):
+    """The tiles of a dense MLP need not follow the chunks: both GEMMs, the first, the second on 128 rows for chunks of 192 and the other
+    way round, the last tile ragged; the cells past N stay as they are, and the delta of the same input, on the chunk's own rows, is
+    nothing, bit for bit."""
+    out = (ctypes.c_int32 * 2)()
+    cm.load().chipmunk_internal_mlp_dense_rows(B, N, D, F, c, out)
+    assert tuple(out) == rows
+    tiles = _mlp_tiles(cm, B, N, D, F, c, 1)
+    assert (rows[0] == c or tiles[0] == 0) and (rows[1] == c or tiles[1] == 0)
+    x, _, w1, b1, w2, b2 = recipes.mlp_inputs(B, N, D, F, 44, DEV)
+    if not bias:
+        b1, b2 = torch.zeros_like(b1), torch.zeros_like(b2)
+    NB, a_ld = -(-N // c), -(-N // 8) * 8 + 8
+    o = torch.full_like(x, 7.0)
+    a_cache = torch.full((B, F, a_ld), 3.0, dtype=torch.bfloat16, device=DEV)
+    cm.mlp_dense(x, w1, b1 if bias else None, w2, b2 if bias else None, o, a_cache, c, act)
+    ref, a_ref, _ = oracle.mlp_dense(si.np_f32(x), si.np_f32(w1), si.np_f32(b1), si.np_f32(w2), si.np_f32(b2), c, act, a_ld=a_ld)
+    assert rel_err(si.np_f32(a_cache)[..., :N], a_ref[..., :N]) <= REL_TOL
+    assert torch.all(a_cache[..., N:] == 3.0)
+    assert rel_err(si.np_f32(o), ref) <= REL_TOL
+    o_before, a_before, k = o.clone(), a_cache.clone(), 200
+    idx, _ = recipes.mlp_indices(B * NB, F, k, 44, DEV)
+    counts = torch.full((B, NB), k, dtype=torch.int32, device=DEV)
+    cm.mlp_sparse_delta(x, w1, b1 if bias else None, w2, idx.view(B, NB, k), counts, a_cache, o, c, act,
+                        _u8(cm.mlp_workspace_bytes(B, N, D, F, c, k)))
+    assert torch.equal(a_cache, a_before) and torch.equal(o, o_before)
