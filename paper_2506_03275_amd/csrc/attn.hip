@@ -45,6 +45,7 @@ struct AttnParams {
     const float* prev_l;   // [B,H,N]
     float* colsum;         // [B,H,NB,ld_colsum]
     int64_t ld_colsum;
+    int first = 0;         // every column: the launch's first chunk
 };
 
 constexpr int kTileRows = 32;         // key rows per LDS tile = one step of the online softmax
@@ -781,17 +782,19 @@ __global__ __launch_bounds__(64 * NWAVES, NWAVES == 4 ? 2 : 1) void attn_sparse_
     uint32_t id = blockIdx.x, all = gridDim.x;
     if constexpr (MODE == kColumnList || MODE == kEveryColumn) {
         const uint32_t whole = (uint32_t)p.whole;   // a multiple of eight, or all of them
+        const uint32_t first = MODE == kEveryColumn ? (uint32_t)p.first : 0;   // a refresh's last round
         if (id >= whole) {
             id -= whole;
             all -= whole;
             if (p.by_xcd) id = attn_run_of_xcd(id, all);
             constexpr int PARTS = PART == kRows32Shared ? 2 * NQB : NQB;   // per chunk
-            attn_rows<E, PART == kRows64Shared ? 2 : 1, NWAVES, MODE, PART == kRows64 ? 1 : 2>(p, whole + id / PARTS, (int)(id % PARTS));
+            attn_rows<E, PART == kRows64Shared ? 2 : 1, NWAVES, MODE, PART == kRows64 ? 1 : 2>(p, first + whole + id / PARTS, (int)(id % PARTS));
             return;
         }
         all = whole;
     }
     if (p.by_xcd) id = attn_run_of_xcd(id, all);
+    if constexpr (MODE == kEveryColumn) id += (uint32_t)p.first;
     attn_rows<E, NQB, NWAVES, MODE>(p, id, 0);
 }
 
@@ -812,6 +815,7 @@ struct ColsumParams {
     int N, NB, c;
     float sl2;
     int pieces;   // a chunk's keys are cut into so many runs of whole tiles, one workgroup each
+    int first = 0;   // the launch's first chunk
 };
 
 // What bounds it: the vector instructions of the scores.  A score costs an FMA, an exponential (two issue slots) and an
@@ -836,7 +840,7 @@ __global__ __launch_bounds__(256, 4) void attn_colsum_kernel(ColsumParams p) {
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int g = lane >> 4, l16 = lane & 15;
-    const int64_t unit = blockIdx.x / p.pieces;
+    const int64_t unit = p.first + blockIdx.x / p.pieces;
     const int piece = (int)(blockIdx.x % p.pieces);
     const int64_t bh = unit / p.NB;
     const int chunk = (int)(unit % p.NB);
@@ -1229,6 +1233,26 @@ extern "C" int32_t chipmunk_attn_colsum_stale(const uint16_t* q, const uint16_t*
 // The sums' error against 64 bits, one kernel and apart: 2e-7 to 4e-7, 5e-8 to 7e-8 (RMS).
 static bool refresh_apart(int64_t units, int N) { return (units <= 80 && N >= 640) || (units <= 120 && N >= 1536); }
 
+
+// How many of a refresh's chunks the one kernel takes, the first ones; the sums and the attention of the others are made apart.
+// More than 120 chunks: apart while the attention's workgroups of 64 rows all have a slot, which long keys make worth the
+// second reading; a workgroup of the one kernel is quick with 128 rows at E = 128, so there only while each has a CU.  One kernel and apart,
+// E = 64: 128 chunks of 192 rows, 5000 to 6500 keys 0.74 of the time, 160, 2300 to 3000 0.89, 170 0.96, 180 1.21; 200 of 128 rows 0.98, 4500 and more
+// 0.84; E = 128: 125 of 128 rows 0.79, 135 1.09; 150 of 192 rows, 2300 to 3000 keys 1.01, from 4500 0.96, from 6500 0.91; 175 1.2.
+// Beyond a round of all slots (three workgroups to a CU at E = 64 with 128 rows, else two): a last round of few chunks takes the one kernel more than half
+// as long as a full one.  Apart, last rounds of up to 50, to 75 and to 100 chunks, behind one round, E = 128, 192 rows: 2300 to
+// 3500 keys 0.91, 0.92, 0.99 of the time, from 6000 0.86, 0.88, 0.94 (594 chunks of 22 heads x 5184: 427 and 378 us), up to 1536 keys 0.96, -, 1.07; 128 rows: 1536 to 2300 keys 0.95, 0.97, 1.01, from 6000
+// 0.88, 0.91, 0.91; behind two rounds 0.94, 0.95, 0.99 and (128 rows) 0.96, 0.97, 0.99; behind four and more the workgroups no longer end together: 0.98
+// to 1.04.  E = 64, 128 rows behind 768: 2300 to 3500 keys 0.98, 1.00, 1.02, from 3500 0.95, 0.97, 0.99.  Last rounds that begin at half of the slots: 0.95 to 1.3.
+static int64_t refresh_fused_chunks(int64_t units, int N, int E, int c) {
+    if (refresh_apart(units, N)) return 0;
+    const int64_t parts = units * (c / 64);
+    if (E == 64 ? parts <= 512 && N >= 2300 : c == 192 ? parts <= 512 && N >= 5000 : parts <= 256 && N >= 2300) return 0;
+    const bool three = E == 64 && c == 128;
+    const int64_t slots = three ? 768 : 512, last = units % slots;
+    return units > slots && units < 2048 && last <= 80 && N >= (three ? 3500 : 2300) ? units - last : units;
+}
+
 extern "C" int32_t chipmunk_attn_dense_colsum_stale(const uint16_t* q, const uint16_t* k, const uint16_t* v,
                                                     uint16_t* out, const float* prev_m, const float* prev_l,
                                                     float* colsum, int64_t ld_colsum, float* new_m, float* new_l,
@@ -1251,16 +1275,29 @@ extern "C" int32_t chipmunk_attn_dense_colsum_stale(const uint16_t* q, const uin
     p.N = N; p.NB = NB; p.c = c; p.whole = 0; p.by_xcd = attn_by_xcd(N, E); p.k_stride = 0;
     p.sl2 = softmax_scale * 1.4426950408889634f;
     p.o_scale = 1.f;
-    if (refresh_apart(units, N)) {
-        // the sums first: the attention may write its statistics over the ones that the sums take
-        const int32_t st = chipmunk_attn_colsum_stale(q, k, prev_m, prev_l, colsum, ld_colsum, B, H, N, E, c, softmax_scale, stream);
-        return st != CHIPMUNK_OK ? st : launch_attn(p, E, units, (hipStream_t)stream);
+    const hipStream_t s = (hipStream_t)stream;
+    const int64_t fused = refresh_fused_chunks(units, N, E, c);
+    if (fused > 0) {
+        const int32_t st = launch_attn_fused(p, E, fused, s);
+        if (st != CHIPMUNK_OK || fused == units) return st;
     }
-    return launch_attn_fused(p, E, units, (hipStream_t)stream);
+    // apart, the sums first: the attention may write its statistics over the ones that the sums take
+    ColsumParams cp;
+    cp.q = q; cp.k = k; cp.row_m = prev_m; cp.row_l = prev_l; cp.colsum = colsum; cp.ld = ld_colsum;
+    cp.N = N; cp.NB = NB; cp.c = c; cp.sl2 = p.sl2;
+    cp.first = p.first = (int)fused;
+    const int32_t st = launch_colsum(cp, E, units - fused, s);
+    if (st != CHIPMUNK_OK) return st;
+    return fused == 0 ? launch_attn(p, E, units, s) : launch_attn_parts<kEveryColumn>(p, E, units - fused, s);
 }
 
-// Whether a refresh takes two launches; for the tests, like the next.
+// Whether a refresh is made apart by the number and length of its chunks alone; how many chunks the one kernel takes, by all
+// rules.  For the tests, like the next.
 extern "C" int32_t chipmunk_internal_attn_refresh_apart(int B, int H, int N, int c) { return refresh_apart((int64_t)B * H * ((N + c - 1) / c), N); }
+
+extern "C" int32_t chipmunk_internal_attn_refresh_fused(int B, int H, int N, int E, int c) {
+    return (int32_t)refresh_fused_chunks((int64_t)B * H * ((N + c - 1) / c), N, E, c);
+}
 
 // How the chunks that have no workgroup of their own are walked (AttnPart); -1: there are none.
 extern "C" int32_t chipmunk_internal_attn_part_form(int B, int H, int N, int E, int c, int k_stride, int list) {

@@ -695,3 +695,37 @@ def test_dense_mlp_on_the_other_chunk_sizes_rows(cm, oracle, B, N, D, F, c, act,
     cm.mlp_sparse_delta(x, w1, b1 if bias else None, w2, idx.view(B, NB, k), counts, a_cache, o, c, act,
                         _u8(cm.mlp_workspace_bytes(B, N, D, F, c, k)))
     assert torch.equal(a_cache, a_before) and torch.equal(o, o_before)
+
+
+@pytest.mark.parametrize("H,N,E,c,fused", [(43, 2304, 128, 192, 512), (43, 2304, 64, 192, 512), (43, 2303, 128, 192, 512),
+                                           (31, 2305, 128, 128, 512), (28, 3501, 64, 128, 768), (37, 3000, 64, 192, 512),
+                                           (28, 3499, 64, 128, 784), (10, 3072, 64, 192, 0), (10, 3072, 128, 192, 160),
+                                           (12, 2500, 64, 192, 0), (6, 5376, 128, 192, 0), (7, 2304, 128, 128, 0),
+                                           (43, 2299, 64, 192, 516), (43, 2700, 64, 192, 645)])
+def test_refresh_with_its_last_chunks_apart(cm, oracle, H, N, E, c, fused):
+    """The first chunks in the one kernel, those of a short last round apart, statistics updated in place: the heads at both
+    ends and the one in which the launches meet against the oracle; the sums made apart are those of the entry point that makes
+    them alone, bit by bit, and the one kernel's are not."""
+    assert cm.load().chipmunk_internal_attn_refresh_fused(1, H, N, E, c) == fused
+    (q1, k1, _), (q2, k2, v), _ = si.attn_steps(1, H, N, E, 41, DEV)
+    scale, NB, ld = 1 / math.sqrt(E), -(-N // c), -(-N // 4) * 4 + 4
+    s1 = torch.matmul(q1.float(), k1.float().transpose(-1, -2).contiguous()) * scale
+    m = s1.amax(-1)
+    l = torch.exp(s1 - m[..., None]).sum(-1)
+    del s1
+    m0, l0 = m.clone(), l.clone()
+    out, D = torch.full_like(q2, float("nan")), torch.full((1, H, NB, ld), -1.0, dtype=torch.float32, device=DEV)
+    cm.attn_dense_colsum_stale(q2, k2, v, out, m, l, D, c, scale, m, l)
+    D_alone = torch.full_like(D, -1.0)
+    cm.attn_colsum_stale(q2, k2, m0, l0, D_alone, c, scale)
+    assert torch.equal(D.view(-1, ld)[fused:], D_alone.view(-1, ld)[fused:])
+    assert fused == 0 or not torch.equal(D.view(-1, ld)[:fused], D_alone.view(-1, ld)[:fused])
+    assert bool((D[..., N:] == -1.0).all())
+    heads = sorted({0, min(fused // NB, H - 1), H - 1})
+    qn, kn, vn = (si.np_f32(t[:, heads]) for t in (q2, k2, v))
+    f64 = lambda t: t[:, heads].cpu().numpy().astype(np.float64)
+    assert rel_err(f64(D[..., :N]), oracle.attn_colsum_stale(qn, kn, f64(m0), f64(l0), c, scale)) <= SUM_TOL
+    assert rel_err(si.np_f32(out[:, heads]), oracle.attn_dense(qn, kn, vn, c, scale)) <= REL_TOL
+    m_ref, l_ref = oracle.attn_row_stats(qn, kn, scale)
+    assert np.abs(f64(m) + np.log(f64(l)) - (m_ref + np.log(l_ref))).max() <= 2e-3
+    assert bool(torch.isfinite(out).all()) and bool(torch.isfinite(m).all()) and bool((l > 0).all())
