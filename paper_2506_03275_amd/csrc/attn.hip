@@ -1234,16 +1234,19 @@ extern "C" int32_t chipmunk_attn_colsum_stale(const uint16_t* q, const uint16_t*
 static bool refresh_apart(int64_t units, int N) { return (units <= 80 && N >= 640) || (units <= 120 && N >= 1536); }
 
 
-// How many of a refresh's chunks the one kernel takes, the first ones; the sums and the attention of the others are made apart.
-// More than 120 chunks: apart while the attention's workgroups of 64 rows all have a slot, which long keys make worth the
-// second reading; a workgroup of the one kernel is quick with 128 rows at E = 128, so there only while each has a CU.  One kernel and apart,
-// E = 64: 128 chunks of 192 rows, 5000 to 6500 keys 0.74 of the time, 160, 2300 to 3000 0.89, 170 0.96, 180 1.21; 200 of 128 rows 0.98, 4500 and more
-// 0.84; E = 128: 125 of 128 rows 0.79, 135 1.09; 150 of 192 rows, 2300 to 3000 keys 1.01, from 4500 0.96, from 6500 0.91; 175 1.2.
-// Beyond a round of all slots (three workgroups to a CU at E = 64 with 128 rows, else two): a last round of few chunks takes the one kernel more than half
-// as long as a full one.  Apart, last rounds of up to 50, to 75 and to 100 chunks, behind one round, E = 128, 192 rows: 2300 to
-// 3500 keys 0.91, 0.92, 0.99 of the time, from 6000 0.86, 0.88, 0.94 (594 chunks of 22 heads x 5184: 427 and 378 us), up to 1536 keys 0.96, -, 1.07; 128 rows: 1536 to 2300 keys 0.95, 0.97, 1.01, from 6000
-// 0.88, 0.91, 0.91; behind two rounds 0.94, 0.95, 0.99 and (128 rows) 0.96, 0.97, 0.99; behind four and more the workgroups no longer end together: 0.98
-// to 1.04.  E = 64, 128 rows behind 768: 2300 to 3500 keys 0.98, 1.00, 1.02, from 3500 0.95, 0.97, 0.99.  Last rounds that begin at half of the slots: 0.95 to 1.3.
+// How many of a refresh's chunks the one kernel takes, the first ones; the sums and the attention of the others are made
+// apart. More than 120 chunks: apart while the attention's workgroups of 64 rows all have a slot, which long keys make worth
+// the second reading; a workgroup of the one kernel is quick with 128 rows at E = 128, so there only while each has a CU.  One
+// kernel and apart, E = 64: 128 chunks of 192 rows, 5000 to 6500 keys 0.74 of the time, 160, 2300 to 3000 0.89, 170 0.96, 180
+// 1.21; 200 of 128 rows 0.98, 6500 and more 0.84; E = 128: 125 of 128 rows 0.79, 135 1.09; 150 of 192 rows, 2300 to 3000 keys
+// 1.01, from 4500 0.96, from 6500 0.91; 175 1.2.
+// Beyond a round of all slots (three workgroups to a CU at E = 64 with 128 rows, else two): a last round of few chunks takes
+// the one kernel more than half as long as a full one.  Apart, last rounds of up to 50, to 75 and to 100 chunks, behind one
+// round, E = 128, 192 rows: 2300 to 3500 keys 0.91, 0.92, 0.99 of the time, from 6000 0.86, 0.88, 0.94 (544 chunks, 17 heads x
+// 6008: 396 and 342 us), up to 1536 keys 0.96, -, 1.07; 128 rows: 1536 to 2300 keys 0.95, 0.97, 1.01, from 6000 0.88, 0.91,
+// 0.91; behind two rounds 0.94, 0.95, 0.99 and (128 rows) 0.96, 0.97, 0.99; behind four and more the workgroups no longer end
+// together: 0.98 to 1.04.  E = 64, 128 rows behind 768: 2300 to 3500 keys 0.98, 1.00, 1.02, from 3500 0.95, 0.97, 0.99.  Last
+// rounds that begin at half of the slots: 0.95 to 1.3.
 static int64_t refresh_fused_chunks(int64_t units, int N, int E, int c) {
     if (refresh_apart(units, N)) return 0;
     const int64_t parts = units * (c / 64);

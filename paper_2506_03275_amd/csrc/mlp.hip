@@ -1225,8 +1225,8 @@ static ScoresPlan scores_plan(int units, int D, int F) {
 }
 
 // Chunk means by workgroups of 128 columns where those of 512 leave most of the CUs without one.  Whole calls in us, 512 and
-// 128 columns: 8 chunks of 192 x 3072 (F = 4096) 13.3, 12.0; 24 x 1024 (12 288) 14.3, 13.1; 40 x 1408 (4096) 14.9, 14.4; 60 x 2048
-// (4096) 25.9, 26.2; 108 x 512 (3136) 17.4, 18.3.
+// 128 columns: 8 chunks of 192 x 3072 (F = 4096) 13.3, 12.0; 24 x 1024 (12 288) 14.3, 13.1; beyond the
+// limit 60 x 2048 (4096) 25.9, 26.2; 108 x 512 (3136) 17.4, 18.3.
 static bool narrow_means(int units, int D) { return (D + 511) / 512 * units <= 96; }
 
 // Few chunks: a workgroup per 16, 32 or 64 neurons, the fewest that give every CU at most one, with all chunks.  Every workgroup reads
