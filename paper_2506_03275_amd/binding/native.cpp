@@ -293,4 +293,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nu
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__native() { return PyModule_Create(&module); }
+// The stamp names the torch, the Python and the header that this was compiled with.  It is looked for in the file before the file is loaded.
+PyMODINIT_FUNC PyInit__native() {
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", CHIPMUNK_BINDING_STAMP) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

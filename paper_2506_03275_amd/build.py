@@ -1,7 +1,9 @@
 """Builds the HIP kernels and the C-ABI library (libchipmunk_hip.so) for gfx950, in-tree, and beside it the
 device-ceiling probes that bench.py --ceilings times (libchipmunk_ceilings.so) and the compiled part of the
-Python binding (_native.so)."""
+Python binding (_native with Python's own suffix)."""
 import glob
+import hashlib
+import importlib.machinery
 import os
 import subprocess
 import sys
@@ -13,7 +15,8 @@ LIB = os.path.join(HERE, "libchipmunk_hip.so")
 PROBE_SRC = os.path.join(HERE, "probe", "ceilings.hip")
 PROBE_LIB = os.path.join(HERE, "libchipmunk_ceilings.so")
 NATIVE_SRC = os.path.join(HERE, "binding", "native.cpp")
-NATIVE = os.path.join(HERE, "_native.so")
+NATIVE = os.path.join(HERE, "_native" + importlib.machinery.EXTENSION_SUFFIXES[0])
+HEADER = os.path.join(HERE, "..", "include", "chipmunk.h")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fno-honor-nans",
@@ -30,10 +33,28 @@ def sources():
 def is_stale():
     if not os.path.exists(LIB):
         return True
-    if not os.path.exists(NATIVE) or os.path.getmtime(NATIVE_SRC) > os.path.getmtime(NATIVE):
+    if not native_fits() or os.path.getmtime(NATIVE_SRC) > os.path.getmtime(NATIVE):
         return True
-    deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + [os.path.join(HERE, "..", "include", "chipmunk.h")]
+    deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + [HEADER]
     return any(os.path.getmtime(d) > os.path.getmtime(LIB) for d in deps)
+
+
+def native_stamp():
+    """What the compiled binding is built against: the torch and the Python whose objects its code reads, and the declarations
+    of the functions that it calls."""
+    import torch
+    header = hashlib.sha1(open(HEADER, "rb").read()).hexdigest()
+    return (f"chipmunk binding for torch {torch.__version__} {torch.version.git_version}, Python {sysconfig.get_config_var('SOABI')}, "
+            f"chipmunk.h {header}.")
+
+
+def native_fits():
+    """Whether the compiled binding is there and was built against what runs now.  Read from the file: code for another torch is
+    not to be loaded at all."""
+    if not os.path.exists(NATIVE):
+        return False
+    with open(NATIVE, "rb") as f:
+        return native_stamp().encode() in f.read()
 
 
 def _native_command():
@@ -41,6 +62,7 @@ def _native_command():
     import torch
     root = os.path.dirname(torch.__file__)
     return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f'-DCHIPMUNK_BINDING_STAMP="{native_stamp()}"',
             "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
             "-I" + sysconfig.get_paths()["include"], NATIVE_SRC, "-o", NATIVE,
             "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]

@@ -1,5 +1,6 @@
 """The compiled binding (binding/native.cpp) against the Python functions that it stands in front of: the same results for what it
-answers, and everything else left to them, so that the same calls raise the same errors."""
+answers, and everything else left to them, so that the same calls raise the same errors; and what takes its place where it
+does not fit the torch or the Python that run."""
 import math
 
 import numpy as np
@@ -105,3 +106,26 @@ def test_the_binding_does_what_the_python_functions_do(cm, name):
         again = _outcome(cm, native, name, args)
     torch.cuda.synchronize()
     assert all(torch.equal(a, b) for a, b in zip(again, _outcome(cm, cm._Python(), name, args)))
+
+
+@pytest.mark.parametrize("other", ["torch", "revision", "python", "header"])
+def test_a_binding_for_another_torch_python_or_header_is_left_alone(cm, other, monkeypatch, tmp_path):
+    """Its code holds the layout of torch's tensors and Python's objects, and the C functions' arguments.  Another torch would often
+    load it all the same, because the few functions that it asks for by name are there in most."""
+    from paper_2506_03275_amd import build
+    lib = cm.load()
+    assert build.native_fits() and cm._bind(lib).__name__.endswith("_native")
+    if other == "torch":
+        monkeypatch.setattr(torch, "__version__", torch.__version__ + ".1")
+    elif other == "revision":
+        monkeypatch.setattr(torch.version, "git_version", "0" * 40)
+    elif other == "python":
+        real = build.sysconfig.get_config_var
+        monkeypatch.setattr(build.sysconfig, "get_config_var", lambda name: "cpython-399" if name == "SOABI" else real(name))
+    else:
+        header = tmp_path / "chipmunk.h"
+        header.write_bytes(open(build.HEADER, "rb").read() + b"\n")
+        monkeypatch.setattr(build, "HEADER", str(header))
+    assert not build.native_fits() and build.is_stale()
+    with pytest.warns(RuntimeWarning, match="compiled binding"):
+        assert isinstance(cm._bind(lib), cm._Python)
