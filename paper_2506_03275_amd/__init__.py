@@ -92,7 +92,7 @@ def load():
     """Load libchipmunk_hip.so (building it first only when it does not exist)."""
     global _lib, _fast
     if _lib is None:
-        if not os.path.exists(_build.LIB) or not os.path.exists(_build.NATIVE):
+        if not os.path.exists(_build.LIB):
             _build.build()
         lib = ctypes.CDLL(_build.LIB)
         for name, (argtypes, restype) in _SIGNATURES.items():

@@ -1,6 +1,7 @@
 """The compiled binding (binding/native.cpp) against the Python functions that it stands in front of: the same results for what it
 answers, and everything else left to them, so that the same calls raise the same errors; and what takes its place where it
 does not fit the torch or the Python that run."""
+import ctypes
 import math
 
 import numpy as np
@@ -129,3 +130,33 @@ def test_a_binding_for_another_torch_python_or_header_is_left_alone(cm, other, m
     assert not build.native_fits() and build.is_stale()
     with pytest.warns(RuntimeWarning, match="compiled binding"):
         assert isinstance(cm._bind(lib), cm._Python)
+
+
+def test_the_library_does_not_need_the_compiled_binding(cm, monkeypatch, tmp_path):
+    """The Python functions do every call: a box with the library and no host compiler loads it as it is."""
+    from paper_2506_03275_amd import build
+    monkeypatch.setattr(build, "NATIVE", str(tmp_path / "none.so"))
+    monkeypatch.setattr(build, "build", lambda verbose=False: pytest.fail("built anew"))
+    monkeypatch.setattr(cm, "_lib", None)
+    monkeypatch.setattr(cm, "_fast", cm._fast)
+    with pytest.warns(RuntimeWarning, match="compiled binding"):
+        assert cm.load().chipmunk_status_string(0) == b"ok"
+    assert isinstance(cm._fast, cm._Python)
+    args = _calls("cpu")["mlp_dense"]
+    with pytest.raises(ValueError, match="must live on the GPU"):
+        cm.mlp_dense(*args)
+
+
+@pytest.mark.parametrize("compiler", ["/nonexistent/c++", "false"])
+def test_a_build_without_a_host_compiler_gives_the_library(monkeypatch, tmp_path, capfd, compiler):
+    """And takes away the binding of an earlier build, whose functions need not be the library's any more."""
+    from paper_2506_03275_amd import build
+    (tmp_path / "one.hip").write_text('extern "C" int one() { return 1; }\n')
+    for name, value in (("CSRC", str(tmp_path)), ("LIB", str(tmp_path / "lib.so")), ("NATIVE", str(tmp_path / "native.so")),
+                        ("PROBE_SRC", str(tmp_path / "one.hip")), ("PROBE_LIB", str(tmp_path / "probe.so"))):
+        monkeypatch.setattr(build, name, value)
+    (tmp_path / "native.so").write_text("of an earlier build")
+    monkeypatch.setenv("CXX", compiler)
+    assert build.build() == str(tmp_path / "lib.so")
+    assert ctypes.CDLL(str(tmp_path / "lib.so")).one() == 1
+    assert not (tmp_path / "native.so").exists() and "binding" in capfd.readouterr().err
