@@ -1024,9 +1024,15 @@ static int64_t attn_whole_chunks(int E, int blocks, int64_t units, double* cost)
 // E = 64: 108: 128 keys 4.5, 5.0, 4.2   512 7.2, 7.3, 6.0; 180: 384 6.5, 6.8, 6.8   768 9.2, 9.1, 9.0   2048 18.7, 17.0, 16.4; 360: 1024 13.9,
 // 14.8, 16.4   2048 23.9, 23.8, 27.1.  Every column: E = 128, 192 parts, 512 keys 9.7, 9.3, 9.5; E = 64: 256 5.3, 5.4, 5.0.
 // Behind 512 whole chunks, E = 128: 120 parts, 256 keys 29.6, 30.0, 29.3   2048 110.8, 107.2, 104.6; 192: 512 39.8, 40.8, 42.3   1024 61.1, 60.2,
-// 65.5; E = 64: 192: 1024 40.9, 41.3, 44.7   2048 67.9, 66.7, 73.4; every column, E = 64: 189, 960 keys 37.6, 36.0, 39.5.
-static AttnPart attn_part_form(int E, int64_t whole, int64_t parts, int keys, bool list) {
+// 65.5; E = 64 (192 rows): 192: 1024 40.9, 41.3, 44.7   2048 67.9, 66.7, 73.4; every column, E = 64: 189, 960 keys 37.6, 36.0, 39.5.
+// Whole chunks of 128 rows at E = 64 have four workgroups to a CU, which the shared walk's registers in the same kernel make
+// three (133 and 138 instead of 128 and 122).  That costs a list's whole rounds more than it saves behind them: 512 chunks
+// and 272 to 400 parts of 2048 to 6000 keys 1.04 to 1.10 of the time, 176 to 248 parts 0.98 to 1.01, behind 1024 0.99 to
+// 1.02.  (Held to 128 registers, 6 of them in scratch memory: 0.99 to 1.03.)  Every column comes to 128 rows only behind 1024
+// chunks: 768 to 1700 keys 0.97 to 1.02, from 2304 0.98 to 0.99.
+static AttnPart attn_part_form(int E, int rows, int64_t whole, int64_t parts, int keys, bool list) {
     if (parts <= 128) return keys > 3 * kTileRows ? kRows32Shared : kRows64;
+    if (whole > 0 && list && E == 64 && rows == 128) return kRows64;
     if (whole > 0) return keys >= (!list ? 768 : E == 128 ? 1024 : 2048) ? kRows64Shared : kRows64;
     if (parts <= 256) {
         if (E == 64) return keys >= (list ? 768 : 256) ? kRows32Shared : kRows64;
@@ -1042,7 +1048,8 @@ static int32_t launch_attn_parts_as(const AttnParams& p, int E, int64_t units, h
     if (E == 128 && blocks == 3) return launch_attn_variant<128, 3, 4, MODE, PART>(p, groups, s);
     if (E == 128) return launch_attn_variant<128, 2, 4, MODE, PART>(p, groups, s);
     if (blocks == 3) return launch_attn_variant<64, 3, 4, MODE, PART>(p, groups, s);
-    return launch_attn_variant<64, 2, 4, MODE, PART>(p, groups, s);
+    constexpr int part = MODE == kColumnList && PART == kRows64Shared ? kRows64 : PART;   // (never asked for: see attn_part_form)
+    return launch_attn_variant<64, 2, 4, MODE, part>(p, groups, s);
 }
 
 template <int MODE>
@@ -1050,7 +1057,7 @@ static int32_t launch_attn_parts(AttnParams p, int E, int64_t units, hipStream_t
     const int blocks = p.c / 64;
     double cost;
     p.whole = (int)attn_whole_chunks(E, blocks, units, &cost);
-    const AttnPart form = attn_part_form(E, p.whole, (units - p.whole) * blocks, MODE == kColumnList ? p.k_stride : p.N, MODE == kColumnList);
+    const AttnPart form = attn_part_form(E, p.c, p.whole, (units - p.whole) * blocks, MODE == kColumnList ? p.k_stride : p.N, MODE == kColumnList);
     if (form == kRows32Shared) return launch_attn_parts_as<MODE, kRows32Shared>(p, E, units, s);
     if (form == kRows64Shared) return launch_attn_parts_as<MODE, kRows64Shared>(p, E, units, s);
     return launch_attn_parts_as<MODE, kRows64>(p, E, units, s);
@@ -1309,7 +1316,7 @@ extern "C" int32_t chipmunk_internal_attn_part_form(int B, int H, int N, int E, 
     const int64_t units = bh * ((N + rows - 1) / rows);
     double cost;
     const int64_t whole = attn_whole_chunks(E, rows / 64, units, &cost);
-    return whole == units ? -1 : attn_part_form(E, whole, (units - whole) * (rows / 64), list ? k_stride : N, list);
+    return whole == units ? -1 : attn_part_form(E, rows, whole, (units - whole) * (rows / 64), list ? k_stride : N, list);
 }
 
 // What the rules above choose for these sizes: the rows of a workgroup that takes a whole chunk, the chunks that have one, the

@@ -2,6 +2,7 @@
 it copied or spilled an accumulator inside the loop, it would read the register before the product has landed.  This compiles
 the kernels as the library is built and checks in their assembly that it does not, and what they keep in scratch memory.  The
 exchange of the column sums is inline assembly as well: its operands are checked the same way."""
+import ctypes
 import os
 import re
 import subprocess
@@ -121,3 +122,18 @@ def test_the_column_sums_exchange_keeps_its_inputs_apart(tmp_path):
     written = {a[0] for a in adds[:4]}
     assert len(written) == 4 and all(a[0] == a[1] for a in adds[:4])
     assert not written & {a[1] for a in adds[4:8]}
+
+
+def test_whole_rounds_of_narrow_heads_keep_their_workgroups(tmp_path):
+    """The attention kernel holds the walk of whole chunks and that of the parts behind them.  For chunks of 128 rows at E = 64 the
+    first fits 128 registers, four workgroups to a CU; no column list may be walked by an instance whose other walk takes
+    more."""
+    flags = [f for f in build.HIPCC_FLAGS if f != "-shared"]
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *flags, "--offload-device-only", "-S",
+                    os.path.join(build.CSRC, "attn.hip"), "-o", str(tmp_path / "attn.s")], check=True, capture_output=True)
+    metadata = re.findall(r"\.name:\s+_ZN\w*attn_sparse_delta_kernelILi64ELi2ELi4ELi0ELi(\d)E.*?\.vgpr_count:\s*(\d+).*?"
+                          r"\.vgpr_spill_count:\s*(\d+)", (tmp_path / "attn.s").read_text(), re.S)
+    assert {int(part) for part, _, _ in metadata} == {0, 2}   # a workgroup per 64 rows, and per 32
+    assert all(int(registers) <= 128 and spilled == "0" for _, registers, spilled in metadata), metadata
+    form = ctypes.CDLL(build.LIB).chipmunk_internal_attn_part_form   # B, H, N, E, c, keys of a list (0: every column), list
+    assert form(1, 11, 7500, 64, 128, 2500, 1) == 0 and form(1, 16, 7500, 64, 192, 2500, 1) == 1
