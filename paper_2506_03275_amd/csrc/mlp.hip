@@ -1229,16 +1229,23 @@ static ScoresPlan scores_plan(int units, int D, int F) {
 // limit 60 x 2048 (4096) 25.9, 26.2; 108 x 512 (3136) 17.4, 18.3.
 static bool narrow_means(int units, int D) { return (D + 511) / 512 * units <= 96; }
 
-// Few chunks: a workgroup per 16, 32 or 64 neurons, the fewest that give every CU at most one, with all chunks.  Every workgroup reads
-// all means (4 D bytes a chunk), which is what sets the limits; just above 8192 neurons the workgroups are fewest and read most.
-// Whole calls in us, with the tiles of mlp_dense.h (and the sum of their pieces) and with these: 3 chunks x 512 x 2048 neurons 12.0, 8.8;
-// 8 x 1024 x 4096 13.3, 8.7; 8 x 3072 x 12 288 28.0, 20.8; 16 x 3072 x 8192 24.2, 18.3; 24 x 1024 x 12 288 19.8, 13.1; 24 x 3072 x 12 288 32.3,
-// 28.8; 40 x 1408 x 4096 16.0, 14.4; beyond the limits 20 x 2816 x 9408 23.1, 24.5; 24 x 3072 x 4096 1.02 to 1.16 of the time; 48 x 2048 x 6144
-// 1.08 to 1.2.
+// Few chunks: a workgroup per 16, 32 or 64 neurons, up to 16 384 neurons the fewest that give every CU at most one, with all
+// chunks.  Every workgroup reads all means (4 D bytes a chunk), which is what sets the limits of units * D; just above 8192 neurons
+// the workgroups are fewest and read most.  Whole calls in us, with the tiles of mlp_dense.h (and the sum of their pieces) and with
+// these: 3 chunks x 512 x 2048 neurons 12.0, 8.8; 8 x 1024 x 4096 13.3, 8.7; 8 x 3072 x 12 288 28.0, 20.8; 16 x 3072 x 8192 24.2, 18.3;
+// 24 x 1024 x 12 288 19.8, 13.1; 24 x 3072 x 12 288 32.3, 28.8; 40 x 1408 x 4096 16.0, 14.4.
+// The limits by 1863 sizes, W1 not in the caches, of the time with the tiles (few chunks to many):
+//     F = 64: 24 000 0.81 to 1.01, 30 000 up to 1.03 (D = 3712); 512: 41 000 0.84 to 0.99, 46 000 up to 1.02; 1536: 41 000 0.81 to 0.96;
+//     below 2048 neurons with D above 4608 1.0 to 1.4 (a long contraction in a few workgroups);
+//     4160: 57 000 0.94 to 1.00, 66 000 1.01 to 1.14; 8256: 41 000 0.76 to 0.98, 50 000 up to 1.05; 11 328 to 16 384: 74 000 0.75 to 0.97,
+//     90 000 up to 1.02.
+// Beyond 16 384 neurons some CUs have more than one workgroup, each with all means: up to 16 chunks 0.71 to 0.97, 24 up to
+// 1.15, 48 up to 1.47 (131 072 neurons).
 static int few_neuron_blocks(int F) { return F <= 16 * 256 ? 1 : F <= 32 * 256 ? 2 : 4; }
 static bool few_scores(int units, int D, int F) {
-    const int64_t limit = F <= 32 * 256 ? 57344 : F <= 44 * 256 ? 40960 : 73728;
-    return units <= 48 && (int64_t)units * D <= limit;
+    if (units > (F <= 64 * 256 ? 48 : 16) || (F < 2048 && D > 4608)) return false;
+    const int64_t limit = F < 256 ? 24576 : F < 2048 ? 40960 : F <= 32 * 256 ? 57344 : F <= 44 * 256 ? 40960 : 73728;
+    return (int64_t)units * D <= limit;
 }
 
 // Workspace of the token-merged pre-activation with the contraction cut in `pieces`: the chunk means in split

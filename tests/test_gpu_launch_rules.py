@@ -641,14 +641,16 @@ def test_dense_attention_walked_by_pairs_of_waves(cm, oracle, H, N, E, form):
 
 @pytest.mark.parametrize("B,N,D,F,c,form", [
     (1, 1, 128, 64, 192, (1, 1)), (1, 15 * 128 + 7, 128, 4096, 128, (1, 1)), (2, 8 * 192, 1152, 4160, 192, (2, 1)),
-    (1, 16 * 128 + 1, 640, 8192, 128, (2, 1)), (2, 15 * 128 + 1, 1408, 320, 128, (1, 1)), (1, 32 * 128 - 1, 384, 8256, 128, (4, 1)),
+    (1, 16 * 128 + 1, 640, 8192, 128, (2, 1)), (2, 15 * 128 + 1, 1280, 320, 128, (1, 1)), (1, 32 * 128 - 1, 384, 8256, 128, (4, 1)),
     (1, 32 * 128 + 1, 256, 576, 128, (1, 1)), (3, 16 * 192, 1152, 4224, 192, (2, 0)), (1, 47 * 128 + 3, 512, 11328, 128, (4, 1)),
     (1, 48 * 128 + 1, 512, 64, 128, (0, 1)), (1, 128 * 128, 640, 64, 128, (0, 0)), (2, 50 * 128 - 3, 640, 2048, 128, (0, 0)),
-    (1, 64 * 128, 1024, 5120, 128, (0, 0))])
+    (1, 64 * 128, 1024, 5120, 128, (0, 0)), (2, 15 * 128 + 1, 1408, 320, 128, (0, 1)), (1, 6 * 192, 4736, 1984, 192, (0, 1)),
+    (1, 8 * 128, 3200, 192, 128, (0, 1)), (1, 16 * 192, 256, 16448, 192, (4, 1)), (1, 16 * 192 + 1, 256, 16448, 192, (0, 1)),
+    (1, 17 * 128, 256, 16384, 128, (4, 1))])
 def test_neuron_scores_of_few_chunks(cm, oracle, B, N, D, F, c, form):
     """Up to 48 chunks: one to three blocks of 16 of them, the last ragged; workgroups of 16, 32 and 64 neurons; contractions of fewer
-    lines than a workgroup has waves, and of a number that its waves do not divide; both sides of the limit, beyond which the
-    contraction is cut into pieces or not.  Means in workgroups of 128 and of 512 columns.  Tolerance as for the pieces."""
+    lines than a workgroup has waves, and of a number that its waves do not divide; both sides of the limits (of chunks
+    by entries, of entries with few neurons, of chunks with many), beyond which the contraction is cut into pieces or not.  Means in workgroups of 128 and of 512 columns.  Tolerance as for the pieces."""
     out = (ctypes.c_int32 * 2)()
     cm.load().chipmunk_internal_scores_form(B, N, D, F, c, out)
     assert tuple(out) == form
