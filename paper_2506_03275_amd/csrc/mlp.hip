@@ -1110,18 +1110,21 @@ static SecondPlan second_plan(bool sparse, int B, int N, int D, int F, int c, in
 
 // The rows of a chunk's tile in the two GEMMs of a dense MLP, whose tiles need not follow the chunks: those of the other chunk size
 // where the prices above say 6 % less, for the widths that models have (hidden wider than the model's).  In the second GEMM up to
-// 4.5e10 products: beyond, the prices of its tiles of 192 and 128 rows are not that exact (1.01 of the time over 59 sizes).  Whole
-// calls, of the time on the chunk's rows, 380 sizes of 3e9 to 4.5e10 products: 0.91 in the mean, both GEMMs on 128 rows instead of 192
-// 0.84 (93), the first 0.90 (93), the second 0.93 (245); on 192 instead of 128 0.90 to 0.95.
-constexpr double kOtherRows = 0.94;
+// 4.5e10 products: beyond, the prices of its tiles of 192 and 128 rows are not that exact (1.01 of the time over 59 sizes).  In the
+// first without a limit: 4.5e10 to 1.6e11 products 0.94 (1759 sizes, one lost more than 1 %).  Against the first GEMM's tiles of 64 x 64 13 % less:
+// their price errs by more (7 to 13 % less by price: 0.98 of the time, of 825 sizes 221 lost more than 1 %, up to 16).
+// Whole calls, of the time on the chunk's rows, 11 500 sizes of 5e8 to 3e11 products: 0.91 in the mean, both GEMMs on 128 rows
+// instead of 192 0.84, the first 0.91, the second 0.94; on 192 instead of 128 the first 0.92, the second 0.94, both 0.84.  One in 75
+// loses more than 2 %, 9 % at most: second GEMMs that go from parts of 64 rows to whole tiles of 128, with four to nine chunks.
+constexpr double kOtherRows = 0.94, kOtherRowsThanSmall = 0.87;
 struct DenseRows { int first, second; };
 static DenseRows dense_rows(int B, int N, int D, int F, int c) {
     const int other = 192 + 128 - c;
     DenseRows rows = {c, c};
     if (F <= D || D < 512) return rows;
     double us, other_us;
-    first_form(false, B, N, D, F, c, 0, &us);
-    if (first_form(false, B, N, D, F, other, 0, &other_us) == kFirstChunk && other_us < kOtherRows * us) rows.first = other;
+    const double less = first_form(false, B, N, D, F, c, 0, &us) == kFirstSmall ? kOtherRowsThanSmall : kOtherRows;
+    if (first_form(false, B, N, D, F, other, 0, &other_us) == kFirstChunk && other_us < less * us) rows.first = other;
     if ((double)B * N * D * F < 4.5e10) {
         const SecondPlan plan = second_plan(false, B, N, D, F, c, 0), other_plan = second_plan(false, B, N, D, F, other, 0);
         if (other_plan.form == kSecondChunk && other_plan.us < kOtherRows * plan.us) rows.second = other;
