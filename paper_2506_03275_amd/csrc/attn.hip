@@ -1251,16 +1251,18 @@ static bool refresh_apart(int64_t units, int N) { return (units <= 80 && N >= 64
 // the one kernel more than half as long as a full one.  Apart, last rounds of up to 50, to 75 and to 100 chunks, behind one
 // round, E = 128, 192 rows: 2300 to 3500 keys 0.91, 0.92, 0.99 of the time, from 6000 0.86, 0.88, 0.94 (544 chunks, 17 heads x
 // 6008: 396 and 342 us), up to 1536 keys 0.96, -, 1.07; 128 rows: 1536 to 2300 keys 0.95, 0.97, 1.01, from 6000 0.88, 0.91,
-// 0.91; behind two rounds 0.94, 0.95, 0.99 and (128 rows) 0.96, 0.97, 0.99; behind four and more the workgroups no longer end
-// together: 0.98 to 1.04.  E = 64, 128 rows behind 768: 2300 to 3500 keys 0.98, 1.00, 1.02, from 3500 0.95, 0.97, 0.99.  Last
-// rounds that begin at half of the slots: 0.95 to 1.3.
+// 0.91; behind two rounds 0.94, 0.95, 0.99 and (128 rows) 0.96, 0.97, 0.99; behind three (up to 60 chunks) 0.96 to 0.98 and
+// (128 rows) 0.98 to 1.01 below 4000 keys, 0.975 to 0.99 from there; behind four and more the workgroups no longer end together:
+// 0.98 to 1.04.  E = 64, 128 rows behind 768: 2300 to 3500 keys 0.98, 1.00, 1.02, from 3500 0.95, 0.97, 0.99; behind 1536 0.99 to
+// 1.02.  Last rounds that begin at half of the slots: 0.95 to 1.3.
 static int64_t refresh_fused_chunks(int64_t units, int N, int E, int c) {
     if (refresh_apart(units, N)) return 0;
     const int64_t parts = units * (c / 64);
     if (E == 64 ? parts <= 512 && N >= 2300 : c == 192 ? parts <= 512 && N >= 5000 : parts <= 256 && N >= 2300) return 0;
     const bool three = E == 64 && c == 128;
-    const int64_t slots = three ? 768 : 512, last = units % slots;
-    return units > slots && units < 2048 && last <= 80 && N >= (three ? 3500 : 2300) ? units - last : units;
+    const int64_t slots = three ? 768 : 512, last = units % slots, rounds = units / slots;
+    const int keys = three ? 3500 : c == 128 && rounds == 3 ? 4000 : 2300;
+    return rounds >= 1 && rounds <= (three ? 1 : 3) && last <= 80 && N >= keys ? units - last : units;
 }
 
 extern "C" int32_t chipmunk_attn_dense_colsum_stale(const uint16_t* q, const uint16_t* k, const uint16_t* v,

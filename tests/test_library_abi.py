@@ -210,3 +210,15 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode != 0
     assert "one GPU" in (r.stdout + r.stderr)
+
+
+def test_where_a_refreshs_last_chunks_are_apart(lib):
+    """Behind the rounds where that was measured to be faster, from the lengths where it was.  No launch."""
+    def one_kernel(H, N, E, c):
+        return lib.chipmunk_internal_attn_refresh_fused(1, H, N, E, c)
+    assert one_kernel(43, 2304, 128, 192) == 512 and one_kernel(103, 2875, 128, 192) == 1536        # 516 and 1545 chunks of 192
+    assert one_kernel(31, 2305, 128, 128) == 512 and one_kernel(43, 3067, 128, 128) == 1024         # of 128, behind one round, two
+    assert one_kernel(55, 3579, 128, 128) == 1540 and one_kernel(43, 4603, 128, 128) == 1536        # and three
+    assert one_kernel(28, 3501, 64, 128) == 768 and one_kernel(55, 3579, 64, 128) == 1540           # three workgroups to a CU
+    assert one_kernel(128, 3071, 128, 192) == 2048 and one_kernel(52, 7680, 128, 192) == 2080       # four rounds
+    assert one_kernel(32, 3072, 128, 192) == 512 and one_kernel(32, 3071, 128, 192) == 512          # whole rounds, or one alone
