@@ -36,7 +36,7 @@ struct AttnParams {
                     // scaled scores (natural logarithm); within 2^8 of the row maximum, not necessarily equal to it
     float* row_l;   // optional [B,H,N]: sum_j exp(score_j - row_m)
     int N, NB, c, k_stride;
-    int whole;      // the first so many chunks have a workgroup each, the others one per 64 rows (see attn_sparse_delta_kernel)
+    int whole;      // the first so many chunks have a workgroup each, the others are walked in parts (attn_part_form)
     int by_xcd;     // see attn_run_of_xcd
     float sl2;      // softmax_scale * log2(e)
     float o_scale;
@@ -1322,7 +1322,7 @@ extern "C" int32_t chipmunk_internal_attn_part_form(int B, int H, int N, int E, 
 }
 
 // What the rules above choose for these sizes: the rows of a workgroup that takes a whole chunk, the chunks that have one, the
-// chunks walked by a workgroup per 64 rows, and the pieces of the column-sum pass.  Not part of the library's interface:
+// chunks walked in parts (attn_part_form), and the pieces of the column-sum pass.  Not part of the library's interface:
 // for the tests, which have to reach each form and otherwise would not see that a rule has moved.
 extern "C" void chipmunk_internal_attn_form(int B, int H, int N, int E, int c, int list, int32_t* out) {
     const int64_t bh = (int64_t)B * H;

@@ -1506,16 +1506,17 @@ extern "C" int32_t chipmunk_mlp_tile_mean_preact_static(const uint16_t* x, const
 }
 
 // What the rules above choose for these sizes: whether the two dense GEMMs take the tiles of 256 x 256, whether the delta
-// takes 256 neurons per workgroup, and the scores GEMM's pieces and sums.  Not part of the library's interface: for the
+// takes 256 neurons per workgroup, and the scores GEMM's pieces and sums (0 and 0: the kernel for few chunks).  Not part of the library's interface: for the
 // tests, which have to reach each form and otherwise would not see that a rule has moved.
 extern "C" void chipmunk_internal_mlp_form(int B, int N, int D, int F, int c, int k_stride, int32_t* out) {
     const int units = B * ((N + c - 1) / c);
-    const ScoresPlan plan = scores_plan(units, D, F);
-    out[0] = first_form(false, B, N, D, F, c, 0) == kFirstLarge;
-    out[1] = second_plan(false, B, N, D, F, c, 0).form == kSecondLarge;
+    const ScoresPlan plan = few_scores(units, D, F) ? ScoresPlan{0, false} : scores_plan(units, D, F);
+    const DenseRows rows = dense_rows(B, N, D, F, c);
+    out[0] = first_form(false, B, N, D, F, rows.first, 0) == kFirstLarge;
+    out[1] = second_plan(false, B, N, D, F, rows.second, 0).form == kSecondLarge;
     out[2] = first_form(true, B, N, D, F, c, k_stride) == kFirstLarge;
     out[3] = plan.pieces;
-    out[4] = plan.two_sums ? 2 : 1;
+    out[4] = plan.pieces == 0 ? 0 : plan.two_sums ? 2 : 1;
 }
 
 // The same for every form of the GEMMs: the dense MLP's first (FirstForm) and second (SecondForm, and the tiles per XCD taken

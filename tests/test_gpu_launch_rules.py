@@ -28,14 +28,21 @@ def cm():
 
 
 def _attn_form(cm, H, N, E, c, with_list):
-    """(rows of a whole chunk's workgroup, chunks taken whole, chunks in parts of 64 rows), pieces of the column-sum pass"""
+    """(rows of a whole chunk's workgroup, chunks taken whole, chunks in parts), pieces of the column-sum pass"""
     out = (ctypes.c_int32 * 4)()
     cm.load().chipmunk_internal_attn_form(1, H, N, E, c, int(with_list), out)
     return tuple(out[:3]), out[3]
 
 
+def _attn_part_form(cm, H, N, E, c, k):
+    """how the chunks in parts are walked: 0 a workgroup per 64 rows, 1 the same with two waves to a row, 2 those per 32 rows, -1 there are
+    none; k: a list's columns, 0 without one"""
+    return cm.load().chipmunk_internal_attn_part_form(1, H, N, E, c, k, int(k > 0))
+
+
 def _mlp_form(cm, B, N, D, F, c, k=1):
-    """first and second dense GEMM on 256 x 256 tiles, delta with 256 neurons per workgroup; scores: pieces, sums"""
+    """first and second dense GEMM on 256 x 256 tiles, delta with 256 neurons per workgroup; scores: pieces, sums, or (0, 0):
+    the kernel for few chunks"""
     out = (ctypes.c_int32 * 5)()
     cm.load().chipmunk_internal_mlp_form(B, N, D, F, c, k, out)
     return [bool(v) for v in out[:3]], tuple(out[3:])
@@ -104,16 +111,17 @@ def test_column_sums_in_pieces_of_the_keys(cm, oracle, N, E, c, pieces):
 
 
 @pytest.mark.parametrize("E", [64, 128])
-@pytest.mark.parametrize("H,N,form", [
-    (2, 1, (192, 0, 2)), (3, 130, (192, 0, 3)),                                      # all in parts of 64 rows
-    (200, 256, (128, 400, 0)), (400, 65, (128, 400, 0)), (400, 192, (192, 400, 0)),  # all whole
-    (520, 190, (192, 512, 8)), (530, 129, (192, 512, 18)),                           # the last round in parts
-    (200, 190, None)])                                                               # another form for each E
-def test_dense_attention_in_workgroups_of_64_128_and_192_rows(cm, oracle, E, H, N, form):
+@pytest.mark.parametrize("H,N,form,part", [
+    (2, 1, (192, 0, 2), 0), (50, 130, (192, 0, 50), 0), (3, 130, (192, 0, 3), 2),    # all in parts of 64 rows, or of 32
+    (200, 256, (128, 400, 0), -1), (400, 65, (128, 400, 0), -1), (400, 192, (192, 400, 0), -1),   # all whole
+    (520, 190, (192, 512, 8), 2), (530, 129, (192, 512, 18), 2), (560, 190, (192, 512, 48), 0),   # the last round in parts
+    (200, 190, None, -1)])                                                           # another form for each E
+def test_dense_attention_in_workgroups_of_64_128_and_192_rows(cm, oracle, E, H, N, form, part):
     """Without a list a workgroup takes one, two or three blocks of 64 rows, by the number of workgroups, those of the last
-    round one where that is cheaper; c is 128 here and 192 there, which no longer decides it.  The ends of the sequence
+    round one (or two waves half of one each) where that is cheaper; c is 128 here and 192 there, which no longer decides it.  The ends of the sequence
     leave waves and whole blocks without rows."""
     assert _attn_form(cm, H, N, E, 128 if N % 2 else 192, False)[0] == (form or {64: (128, 400, 0), 128: (192, 200, 0)}[E])
+    assert _attn_part_form(cm, H, N, E, 128 if N % 2 else 192, 0) == part
     q, k, v = recipes.attn_inputs(1, H, N, E, 22, DEV)
     scale = 1 / math.sqrt(E)
     c = 128 if N % 2 else 192
@@ -124,14 +132,15 @@ def test_dense_attention_in_workgroups_of_64_128_and_192_rows(cm, oracle, E, H, 
     assert rel_err(si.np_f32(out), basen - dense, dense) <= REL_TOL
 
 
-@pytest.mark.parametrize("H,N,E,c,k,form", [
-    (1, 193, 128, 192, 70, (0, 2)), (2, 650, 64, 192, 33, (0, 8)), (2, 300, 128, 128, 129, (0, 6)),   # all in parts
-    (110, 320, 64, 128, 20, (330, 0)), (200, 384, 128, 192, 9, (400, 0)),                             # all whole
-    (200, 500, 128, 192, 70, (512, 88)), (260, 300, 128, 192, 40, (512, 8)), (520, 129, 64, 128, 65, (1024, 16))])
-def test_column_lists_walked_by_parts_of_a_chunk(cm, oracle, H, N, E, c, k, form):
-    """Few chunks: a workgroup per 64 rows, all of a chunk walking its one list; the last chunk ends before its last
+@pytest.mark.parametrize("H,N,E,c,k,form,part", [
+    (1, 193, 128, 192, 70, (0, 2), 0), (2, 650, 64, 192, 33, (0, 8), 0), (2, 300, 128, 128, 129, (0, 6), 2),   # all in parts
+    (22, 300, 128, 128, 129, (0, 66), 0),
+    (110, 320, 64, 128, 20, (330, 0), -1), (200, 384, 128, 192, 9, (400, 0), -1),                              # all whole
+    (200, 500, 128, 192, 70, (512, 88), 0), (260, 300, 128, 192, 40, (512, 8), 0), (520, 129, 64, 128, 65, (1024, 16), 0)])
+def test_column_lists_walked_by_parts_of_a_chunk(cm, oracle, H, N, E, c, k, form, part):
+    """Few chunks: a workgroup per 64 rows or per 32, all of a chunk walking its one list; the last chunk ends before its last
     part.  Then cases with enough chunks to be walked whole, and cases whose last round alone is in parts."""
-    assert _attn_form(cm, H, N, E, c, True)[0] == (c, *form)
+    assert _attn_form(cm, H, N, E, c, True)[0] == (c, *form) and _attn_part_form(cm, H, N, E, c, k) == part
     q, kk, v = recipes.attn_inputs(1, H, N, E, 23, DEV)
     scale, NB = 1 / math.sqrt(E), -(-N // c)
     base = recipes.attn_base(tuple(q.shape), k, "delta", 23, DEV)
@@ -227,15 +236,16 @@ def test_topk_of_ties_on_the_threshold(cm, oracle, C, equal):
 
 
 @pytest.mark.parametrize("B,N,D,F,c,plan", [
-    (1, 1, 128, 64, 128, (1, 2)),            # one token, one neuron tile half full, one piece, the high parts in two sums
-    (1, 300, 512, 64, 128, (8, 2)),          # eight pieces of one step
-    (1, 384, 640, 7680, 192, (4, 2)),        # two chunks; ten steps in four pieces
-    (1, 4500, 640, 12288, 192, (5, 1)),      # ten steps in five pieces, one sum each
+    (1, 1, 4864, 64, 128, (16, 2)),          # one token, one neuron tile half full, 76 steps in sixteen pieces
+    (1, 49 * 128 - 60, 512, 64, 128, (8, 2)),   # eight pieces of one step
+    (1, 9500, 640, 7680, 192, (4, 2)),       # ten steps in four pieces
+    (1, 9500, 640, 12224, 192, (5, 1)),      # in five, one sum each, the last of 256 neurons' tiles three quarters full
+    (1, 129 * 128 - 1, 512, 8576, 128, (3, 1)),   # 129 chunks, eight steps in three pieces, one sum each, the last tile half full
     (1, 127 * 128, 128, 320, 128, (1, 2)),   # 127, 128 and 129 chunks: both sides of a tile
     (2, 64 * 192, 256, 576, 192, (1, 2)),
     (1, 128 * 128 + 5, 384, 64, 128, (1, 2)),
     (1, 128 * 128 + 5, 512, 16960, 128, (1, 2)),   # eight steps, one piece in two sums, many neuron tiles
-    (2, 700, 3968, 10304, 192, (4, 2)),      # 62 steps in four pieces, two sums each, the last neuron tile half full
+    (2, 1400, 3968, 10304, 192, (4, 2)),     # 62 steps in four pieces, two sums each, the last neuron tile half full
 ])
 def test_neuron_scores_in_pieces_of_the_contraction(cm, oracle, B, N, D, F, c, plan):
     """Chunk means of full, ragged and one-row chunks, and the scores GEMM's pieces and sums.  Tolerance: the mean enters as two
@@ -253,14 +263,14 @@ def test_neuron_scores_in_pieces_of_the_contraction(cm, oracle, B, N, D, F, c, p
 
 
 @pytest.mark.parametrize("E", [64, 128])
-@pytest.mark.parametrize("H,N,c,form", [(2, 900, 192, (0, 10)), (2, 600, 128, (0, 10)), (100, 700, 192, (400, 0)),
-                                        (80, 600, 128, (400, 0))])
-def test_last_step_of_column_lists(cm, oracle, E, H, N, c, form):
+@pytest.mark.parametrize("H,N,c,form,part", [(2, 900, 192, (0, 10), 2), (2, 600, 128, (0, 10), 2), (9, 900, 192, (0, 45), 0),
+                                             (14, 600, 128, (0, 70), 0), (100, 700, 192, (400, 0), -1), (80, 600, 128, (400, 0), -1)])
+def test_last_step_of_column_lists(cm, oracle, E, H, N, c, form, part):
     """Lists that end at, before and behind the edges of tiles (32 columns) and steps (64), one step to three, in either half
     of the buffers: the last step leaves out an empty second tile and brings the base rows (ragged last chunk: some do
-    not exist).  Chunks in parts of 64 rows, and chunks walked whole: two or three blocks of rows per wave."""
-    assert _attn_form(cm, H, N, E, c, True)[0] == (c, *form)
+    not exist).  Chunks in parts of 32 rows and of 64, and chunks walked whole: two or three blocks of rows per wave."""
     NB, k = -(-N // c), 193
+    assert _attn_form(cm, H, N, E, c, True)[0] == (c, *form) and _attn_part_form(cm, H, N, E, c, k) == part
     q, kk, v = recipes.attn_inputs(1, H, N, E, 27, DEV)
     base = recipes.attn_base(tuple(q.shape), 64, "delta", 27, DEV)
     idx, counts = recipes.attn_indices(H * NB, N, k, 27, DEV)
@@ -571,11 +581,6 @@ def test_mlp_delta_of_more_neurons_than_32_bits_of_bytes(cm, oracle):
                             np.arange(last, dtype=np.int32).reshape(1, 1, last), np.array([[last]], dtype=np.int32), a_ref, o_ref, c, 1)
     assert rel_err(si.np_f32(a_cache[:, -last:].contiguous()), a_ref) <= REL_TOL
     assert rel_err(si.np_f32(o_cache), o_ref, o_ref - o_before) <= REL_TOL
-
-
-def _attn_part_form(cm, H, N, E, c, k):
-    """how the chunks in parts are walked: 0 a workgroup per 64 rows, 1 the same with two waves to a row, 2 those per 32 rows"""
-    return cm.load().chipmunk_internal_attn_part_form(1, H, N, E, c, k, int(k > 0))
 
 
 @pytest.mark.parametrize("H,N,E,c,k,form", [

@@ -1,5 +1,6 @@
 """The errors of the 32-bit sums: not only that they stay below a tolerance of the whole path, but that they are as small as
 the arithmetic allows."""
+import ctypes
 import math
 
 import pytest
@@ -46,20 +47,25 @@ def test_column_sums_of_given_normalisers(cm, N, E, c):
     assert _rms_err(D[0, :, :, :N], ref) <= 1.2e-7
 
 
-@pytest.mark.parametrize("chunks,D,F", [
-    (1, 128, 64), (8, 256, 1024), (300, 384, 2048),          # one piece, two sums
-    (8, 1792, 1024), (14, 2048, 8704), (24, 3072, 10240),    # 16 and 3 pieces, two sums each
-    (24, 3072, 12288),                                       # five pieces, one sum each
-    (40, 4096, 10240),                                       # four pieces, two sums each: fewer would be too long
-    (258, 1024, 6912), (129, 1024, 16640),                   # two pieces and one, two sums each
-    (602, 1024, 12288),                                      # one piece, one sum
+@pytest.mark.parametrize("chunks,D,F,plan", [
+    (1, 128, 64, (0, 0)), (8, 256, 1024, (0, 0)), (8, 1792, 1024, (0, 0)),         # the kernel for few chunks
+    (14, 2048, 8704, (0, 0)), (24, 3072, 12288, (0, 0)),
+    (300, 384, 2048, (1, 2)),                                 # one piece, two sums
+    (1, 4864, 64, (16, 2)), (60, 4096, 1088, (16, 2)), (24, 3072, 10240, (3, 2)),   # 16 and 3 pieces, two sums each
+    (48, 5120, 12224, (5, 1)), (129, 512, 8576, (3, 1)),      # five pieces and three, one sum each
+    (40, 4096, 10240, (4, 2)),                                # four pieces, two sums each: fewer would be too long
+    (258, 1024, 6912, (2, 2)), (129, 1024, 16640, (1, 2)),    # two pieces and one, two sums each
+    (602, 1024, 12288, (1, 1)),                               # one piece, one sum
 ])
-def test_neuron_scores_add_no_longer_sums_than_the_workspace_has_pieces_for(cm, chunks, D, F):
+def test_neuron_scores_add_no_longer_sums_than_the_workspace_has_pieces_for(cm, chunks, D, F, plan):
     """Chunk means that two bf16 numbers hold exactly, so that what is left is the error of the GEMM's 32-bit sums.  One rounding
     of the result is 2^-23 * sqrt(0.52 / 12) in the mean square (0.52: of the squared mantissas).  Eight products are added
     with one rounding, so D / 8 additions in h chains of the high parts leave D / 16 / h of its variance; merging h chains of
     high and as many of low parts leaves 1.5 h.  h is half of the pieces that the workspace is sized for."""
     c = 128
+    form = (ctypes.c_int32 * 5)()
+    cm.load().chipmunk_internal_mlp_form(1, chunks * c, D, F, c, 1, form)
+    assert tuple(form[3:]) == plan
     g = si.generator(32, DEV)
     pair = (1 + torch.randint(0, 128, (2, chunks, D), generator=g, device=DEV) / 128)
     pair = pair * (1 - 2 * torch.randint(0, 2, (chunks, D), generator=g, device=DEV))
