@@ -77,11 +77,13 @@ def _bind(lib):
     """The compiled binding over the entry points of `lib`."""
     if _current_device is None or _raw_stream is None:
         return _Python()
-    if not _build.native_fits():   # missing, or its code reads another torch's tensors: the Python functions do the same calls
-        warnings.warn("the compiled binding is not there or was built against another torch or Python: calls take some 2 us longer "
-                      "(build() makes it anew)", RuntimeWarning)
+    try:   # missing, or its code reads another torch's tensors: the Python functions do the same calls
+        if not _build.native_fits():
+            raise ImportError("not there, or built against another torch or Python")
+        from . import _native
+    except ImportError as e:
+        warnings.warn(f"the compiled binding is not used ({e}): calls take some 2 us longer (build() makes it anew)", RuntimeWarning)
         return _Python()
-    from . import _native
     names = ("voxel_reorder", "topk_cols", "attn_sparse_delta", "attn_dense", "attn_dense_colsum_stale", "mlp_tile_mean_preact",
              "mlp_sparse_delta", "mlp_dense")
     _native.bind({"chipmunk_" + n: ctypes.cast(getattr(lib, "chipmunk_" + n), _c_ptr).value for n in names}, _current_device, _raw_stream)

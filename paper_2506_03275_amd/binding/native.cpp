@@ -104,7 +104,8 @@ struct Args {
     }
 };
 
-// call(a): the library's status, the GIL released around the library itself by `run`
+// call(a): the library's status, the GIL released around the library itself by `run`, whose first argument only names the
+// function's type (a reference to the function itself would need the library at link time)
 template <typename Call>
 PyObject* answer(int entry, PyObject* const* args, Py_ssize_t n, Py_ssize_t want, Call&& call) {
     if (!entries[entry].at || n != want) Py_RETURN_NONE;
@@ -145,7 +146,7 @@ PyObject* voxel_reorder(PyObject*, PyObject* const* args, Py_ssize_t n) {
         int g[8];
         for (int i = 0; i < 8; i++) g[i] = a.integer(4 + i);
         void* s = a.stream();
-        run(&chipmunk_voxel_reorder, from, to, perm, inv, (int)src->size(0), g[0], g[1], g[2], g[3], g[4], g[5], g[6], g[7], (int)row,
+        run(decltype(&chipmunk_voxel_reorder){}, from, to, perm, inv, (int)src->size(0), g[0], g[1], g[2], g[3], g[4], g[5], g[6], g[7], (int)row,
             (int)(a.v[12] == Py_True), s);
     });
 }
@@ -168,7 +169,7 @@ PyObject* topk_cols(PyObject*, PyObject* const* args, Py_ssize_t n) {
         int32_t *idx = a.i32(3), *counts = a.i32(4);
         const int k_stride = a.size(3, -1, 0);
         void* s = a.stream();
-        run(&chipmunk_topk_cols, (const float*)cur->data_ptr(), prev ? (const float*)prev->data_ptr() : nullptr, (int)cur->size(0), (int)cur->size(1),
+        run(decltype(&chipmunk_topk_cols){}, (const float*)cur->data_ptr(), prev ? (const float*)prev->data_ptr() : nullptr, (int)cur->size(0), (int)cur->size(1),
             (int64_t)cur->stride(0), k, idx, counts, k_stride, s);
     });
 }
@@ -185,7 +186,7 @@ PyObject* attn_sparse_delta(PyObject*, PyObject* const* args, Py_ssize_t n) {
         const int c = a.integer(7);
         const float scale = a.real(8), o_scale = a.real(9);
         void* s = a.stream();
-        run(&chipmunk_attn_sparse_delta, q, k, v, idx, counts, base, out, B, H, N, E, c, k_stride, scale, o_scale, s);
+        run(decltype(&chipmunk_attn_sparse_delta){}, q, k, v, idx, counts, base, out, B, H, N, E, c, k_stride, scale, o_scale, s);
     });
 }
 
@@ -202,7 +203,7 @@ PyObject* attn_dense(PyObject*, PyObject* const* args, Py_ssize_t n) {
         void* ws = a.data(7, at::kByte);
         const size_t bytes = a.elements(7);
         void* s = a.stream();
-        run(&chipmunk_attn_dense, q, k, v, out, colsum, ld, B, H, N, E, c, scale, ws, bytes, s);
+        run(decltype(&chipmunk_attn_dense){}, q, k, v, out, colsum, ld, B, H, N, E, c, scale, ws, bytes, s);
     });
 }
 
@@ -219,7 +220,7 @@ PyObject* attn_dense_colsum_stale(PyObject*, PyObject* const* args, Py_ssize_t n
         const float scale = a.real(8);
         float *new_m = a.f32(9), *new_l = a.f32(10);
         void* s = a.stream();
-        run(&chipmunk_attn_dense_colsum_stale, q, k, v, out, prev_m, prev_l, colsum, ld, new_m, new_l, B, H, N, E, c, scale, s);
+        run(decltype(&chipmunk_attn_dense_colsum_stale){}, q, k, v, out, prev_m, prev_l, colsum, ld, new_m, new_l, B, H, N, E, c, scale, s);
     });
 }
 
@@ -233,7 +234,7 @@ PyObject* mlp_tile_mean_preact(PyObject*, PyObject* const* args, Py_ssize_t n) {
         void* ws = a.data(4, at::kByte);
         const size_t bytes = a.elements(4);
         void* s = a.stream();
-        run(&chipmunk_mlp_tile_mean_preact, x, w1, T, B, N, D, F, c, ws, bytes, s);
+        run(decltype(&chipmunk_mlp_tile_mean_preact){}, x, w1, T, B, N, D, F, c, ws, bytes, s);
     });
 }
 
@@ -250,7 +251,7 @@ PyObject* mlp_sparse_delta(PyObject*, PyObject* const* args, Py_ssize_t n) {
         void* ws = a.data(10, at::kByte);
         const size_t bytes = a.elements(10);
         void* s = a.stream();
-        run(&chipmunk_mlp_sparse_delta, x, w1, b1, w2, idx, counts, a_cache, a_ld, o_cache, B, N, D, F, c, k_stride, act, ws, bytes, s);
+        run(decltype(&chipmunk_mlp_sparse_delta){}, x, w1, b1, w2, idx, counts, a_cache, a_ld, o_cache, B, N, D, F, c, k_stride, act, ws, bytes, s);
     });
 }
 
@@ -263,7 +264,7 @@ PyObject* mlp_dense(PyObject*, PyObject* const* args, Py_ssize_t n) {
         const int64_t a_ld = a.size(6, -1, 0);
         const int c = a.integer(7), act = a.integer(8);
         void* s = a.stream();
-        run(&chipmunk_mlp_dense, x, w1, b1, w2, b2, out, a_cache, a_ld, B, N, D, F, c, act, s);
+        run(decltype(&chipmunk_mlp_dense){}, x, w1, b1, w2, b2, out, a_cache, a_ld, B, N, D, F, c, act, s);
     });
 }
 
