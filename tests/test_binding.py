@@ -2,7 +2,11 @@
 answers, and everything else left to them, so that the same calls raise the same errors; and what takes its place where it
 does not fit the torch or the Python that run."""
 import ctypes
+import importlib.util
 import math
+import os
+import subprocess
+import types
 
 import numpy as np
 import pytest
@@ -65,18 +69,80 @@ def _wrong(args):
     for i, a in enumerate(args):
         if isinstance(a, torch.Tensor):
             spoiled = [a.double(), a[..., :0], a[0], np.zeros(3), 3, None, a.float() if a.dtype != torch.float32 else a.to(torch.bfloat16)]
-            spoiled += [torch.cat([a, a], -1)[..., ::2], a.cpu()] if a.dim() and a.shape[-1] > 1 else []
+            spoiled += [torch.cat([a, a], -1)[..., ::2], torch.cat([a, a]), torch.cat([a, a])[::2], a.unsqueeze(0), a.unsqueeze(-1), a.transpose(0, -1)]
+            spoiled += [torch.cat([a, a], -1)[..., :a.shape[-1]], a.to("meta"), torch.nn.Parameter(a, requires_grad=False)]
         elif a is None:
-            spoiled = ["x"]
+            spoiled = ["x", 0]
         else:
-            spoiled = [str(a), 2 ** 40 if isinstance(a, int) else math.nan, None, -1, 0.5]
+            spoiled = [str(a), 2 ** 40 if isinstance(a, int) else math.nan, 2 ** 64 + 7, None, -1, 0.5, True, torch.tensor(1)]
         for s in spoiled:
             yield i, args[:i] + [s] + args[i + 1:]
 
 
+@pytest.fixture(scope="module")
+def on_the_cpu(cm, tmp_path_factory):
+    """Both sides with their one question for the GPU turned into one for the CPU, over functions that write down what they are
+    given: what a call does, as ('called', arguments), or ('raised', type, text), or None for one that the binding leaves."""
+    from paper_2506_03275_amd import build
+    at = tmp_path_factory.mktemp("binding")
+    text = open(build.NATIVE_SRC).read()
+    assert text.count("is_cuda()") == 2
+    (at / "native.cpp").write_text(text.replace("is_cuda()", "is_cpu()").replace('"../../include/chipmunk.h"', f'"{os.path.abspath(build.HEADER)}"'))
+    swap = {"-O2": "-O0", build.NATIVE_SRC: str(at / "native.cpp"), build.NATIVE: str(at / "native.so")}
+    subprocess.run([swap.get(word, word) for word in build._native_command()], check=True, capture_output=True)
+    spec = importlib.util.spec_from_file_location("on_the_cpu._native", str(at / "native.so"))
+    native = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(native)
+    python = types.ModuleType("paper_2506_03275_amd")
+    python.__package__, python.__path__, python.__file__ = cm.__package__, cm.__path__, cm.__file__
+    text = open(cm.__file__).read()
+    assert text.count(".is_cuda") == 3
+    exec(compile(text.replace(".is_cuda", ".is_cpu"), "on_the_cpu", "exec"), python.__dict__)
+    seen, functions = [], {}
+
+    def recorder(symbol):
+        argtypes, restype = cm._SIGNATURES[symbol]
+        return ctypes.CFUNCTYPE(restype, *argtypes)(lambda *args: seen.append([str(a) for a in args]) or 0)   # (a NaN is a NaN)
+    for name in NAMES:
+        functions["chipmunk_" + name] = recorder("chipmunk_" + name)
+    native.bind({n: ctypes.cast(f, ctypes.c_void_p).value for n, f in functions.items()}, lambda: 3, lambda device: 70 + device)
+    python._lib = types.SimpleNamespace(**functions)
+    python._current_device, python._raw_stream = lambda: 3, lambda device: 70 + device
+
+    def outcome(side, name, args):
+        seen.clear()
+        try:
+            answer = getattr(native if side == "native" else python, name)(*args)
+        except Exception as e:   # noqa: BLE001
+            assert not seen
+            return "raised", type(e).__name__, str(e)
+        assert len(seen) == (0 if side == "native" and answer is None else 1)
+        return ("called", seen[0]) if seen else None
+    return outcome
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_the_binding_calls_what_the_python_functions_call(on_the_cpu, name):
+    """What the binding answers it hands to the library as the Python function does, argument for argument; so whatever that one
+    refuses, or takes another way, the binding has left alone."""
+    args = _calls("cpu")[name]
+    optional = {"voxel_reorder": (2, 3), "topk_cols": (1,), "attn_sparse_delta": (4, 5), "attn_dense": (4, 7), "mlp_sparse_delta": (2, 10),
+                "attn_dense_colsum_stale": (9, 10), "mlp_tile_mean_preact": (4,), "mlp_dense": (2, 4)}
+    for plain in [args] + [args[:i] + [None] + args[i + 1:] for i in optional[name]]:
+        called = on_the_cpu("native", name, plain)
+        assert called and called[0] == "called" and called == on_the_cpu("python", name, plain)
+        assert called[1][-1] == "73"   # the current device's stream
+        refused = 0
+        for i, bad in _wrong(plain):
+            answer, expected = on_the_cpu("native", name, bad), on_the_cpu("python", name, bad)
+            assert answer is None or answer == expected, (i, bad[i])
+            refused += expected[0] == "raised"
+        assert refused >= 4 * len(args)
+
+
 @pytest.mark.parametrize("name", NAMES)
 def test_what_is_wrong_raises_what_it_raised(cm, name):
-    """On the CPU every call is refused; which error it is must not hang on the binding, whose answer is always None."""
+    """As built, on the CPU, every call is refused; which error it is must not hang on the binding, whose answer is always None."""
     native = cm._fast
     assert native.__name__.endswith("_native")
     args = _calls("cpu")[name]
