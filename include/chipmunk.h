@@ -173,7 +173,8 @@ int32_t chipmunk_attn_colsum_stale(const uint16_t* q, const uint16_t* k, const f
  *                     exp(softmax_scale * <q[n],k[j]> - prev_m[n]) / prev_l[n]
  * from the same score tiles (no second pass over q k^T and no workspace); with
  * few chunks of many keys, which one pass would leave most of the chip idle
- * for, by chipmunk_attn_colsum_stale's pass and then the attention's.
+ * for, by chipmunk_attn_colsum_stale's pass and then the attention's; so too
+ * the last chunks of a call that would be a short last round of that one pass.
  * new_m, new_l: [B,H,N] fp32 or both NULL; they receive this step's statistics
  * in the form chipmunk_attn_dense leaves them, for the next step's prev_m,
  * prev_l.  new_m == prev_m and new_l == prev_l (update in place) is allowed:
@@ -187,7 +188,9 @@ int32_t chipmunk_attn_colsum_stale(const uint16_t* q, const uint16_t* k, const f
  * that (normalisers more than about 80 below a row's current maximum) the
  * row's contributions are scaled down together: a column's sum is then a large
  * finite number or +inf, never NaN, and the two entry points may order such
- * columns differently. */
+ * columns differently.  Where a call's chunks are divided between the two ways
+ * the sums of some chunks are capped like this and those of the others are +inf
+ * like chipmunk_attn_colsum_stale's; a chunk's columns are all made one way. */
 int32_t chipmunk_attn_dense_colsum_stale(const uint16_t* q, const uint16_t* k, const uint16_t* v,
                                          uint16_t* out, const float* prev_m, const float* prev_l,
                                          float* colsum, int64_t ld_colsum, float* new_m, float* new_l,

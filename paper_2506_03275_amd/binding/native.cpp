@@ -1,9 +1,10 @@
-// The hot entry points of the Python binding without Python in between: a small call took 2.5 us of attribute look-ups on its
-// tensors before it reached the library, of the 6 that it took in all, and the smallest kernels take 4.
+// The hot entry points of the Python binding without Python in between: a small call took 2.5 us of attribute look-ups on
+// its tensors before it reached the library, of the 6 that it took in all, and the smallest kernels take 4.
 //
-// Each function here takes exactly what the Python function of its name takes, by position.  It answers only the plain case (exact
-// torch tensors of the right type and layout, ints and floats) with the library's status; for everything else, also for whatever
-// is wrong, it returns None, and the Python function does the whole call itself, with its own checks and messages.
+// Each function here takes exactly what the Python function of its name takes, by position.  It answers only the plain
+// case (exact torch tensors of the right type and layout, ints and floats) with the library's status; for everything
+// else, also for whatever is wrong, it returns None, and the Python function does the whole call itself, with its own
+// checks and messages.
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <climits>
@@ -128,7 +129,8 @@ PyObject* answer(int entry, PyObject* const* args, Py_ssize_t n, Py_ssize_t want
     return PyLong_FromLong(status);
 }
 
-// Arguments are read into variables, in order, before the call: a call's own arguments have no order, and `ok` must be known.
+// Arguments are read into variables, in order, before the call: a call's own arguments have no order, and `ok` must be
+// known.
 
 // src, dst, perm, inv_perm, n_prefix, T, H, W, n_suffix, vt, vh, vw, inverse
 PyObject* voxel_reorder(PyObject*, PyObject* const* args, Py_ssize_t n) {
@@ -294,7 +296,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nu
 
 }  // namespace
 
-// The stamp names the torch, the Python and the header that this was compiled with.  It is looked for in the file before the file is loaded.
+// The stamp names the torch, the Python and the header that this was compiled with.  It is looked for in the file before
+// the file is loaded.
 PyMODINIT_FUNC PyInit__native() {
     PyObject* m = PyModule_Create(&module);
     if (m && PyModule_AddStringConstant(m, "built_for", CHIPMUNK_BINDING_STAMP) < 0) {

@@ -296,12 +296,13 @@ static int attn_by_xcd(int N, int E) { return (int64_t)N * E <= (1 << 22); }
 // positions are the blocks' columns in order, so the rows of a step are one contiguous run of K and V.
 enum AttnMode { kColumnList = 0, kFusedDense = 1, kBlockList = 2, kEveryColumn = 3 };
 
-// The work of one workgroup: NWAVES waves, each owning NQB blocks of 16 queries; 16 * NQB * NWAVES rows, chunk `unit` or part
-// `part` of it.
-// KEYS = 2: the workgroup has half as many rows, and two waves share them: one takes the first tile of every step, the other
-// the second, each with a reference, denominator and accumulator of its own, and the two meet through LDS at the end.  What
-// bounds a workgroup of 64 rows is its chain of tiles and the LDS reads of its waves, each of which reads all of K and V: with 64
-// rows shared by pairs the waves read half as much, with 32 the chain is half as long (times at attn_part_form).
+// The work of one workgroup: NWAVES waves, each owning NQB blocks of 16 queries; 16 * NQB * NWAVES rows, chunk `unit` or
+// part `part` of it.
+// KEYS = 2: the workgroup has half as many rows, and two waves share them: one takes the first tile of every step, the
+// other the second, each with a reference, denominator and accumulator of its own, and the two meet through LDS at the
+// end.  What bounds a workgroup of 64 rows is its chain of tiles and the LDS reads of its waves, each of which reads all
+// of K and V: with 64 rows shared by pairs the waves read half as much, with 32 the chain is half as long (times at
+// attn_part_form).
 template <int E, int NQB, int NWAVES, int MODE, int KEYS = 1>
 __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int part) {
     constexpr bool FUSED = MODE == kFusedDense;
@@ -525,8 +526,8 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
     };
     static_assert(kTilesPerStep * NI * 2 == E / 16, "one transfer per group of score products");
 
-    // KEYS = 2: a wave merges and stores half the columns of its rows.  The base rows' part of those waits in registers, as it is
-    // stored: the lane's eight columns of two blocks (requested here or in the last step: the same time).
+    // KEYS = 2: a wave merges and stores half the columns of its rows.  The base rows' part of those waits in registers,
+    // as it is stored: the lane's eight columns of two blocks (requested here or in the last step: the same time).
     u32x4 half_base[KEYS == 1 ? 1 : NQB][KEYS == 1 ? 1 : E / 64];
     if constexpr (KEYS == 2) {
 #pragma unroll
@@ -584,9 +585,9 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
         if (FUSED && t > 0) flush_column_sums(t - kTilesPerStep);
         if constexpr (KEYS == 2) {
             f32x4 S[2][NQB];
-            // Both waves take their first reference from the unit's first tile, which the second one multiplies for that alone: as
-            // long as nothing raises it, a weight's rounding to bf16 is the same whichever wave forms it and however the rows
-            // are walked.
+            // Both waves take their first reference from the unit's first tile, which the second one multiplies for that
+            // alone: as long as nothing raises it, a weight's rounding to bf16 is the same whichever wave forms it and
+            // however the rows are walked.
             if (half == 0 && t == 0 && kg == 1) {
                 uint32_t first_tile[E / 32];
 #pragma unroll
@@ -671,7 +672,8 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
     }
 
     if constexpr (KEYS == 2) {
-        // Each wave hands the half of its columns that the other one stores, and its reference and denominator, over in LDS.
+        // Each wave hands the half of its columns that the other one stores, and its reference and denominator, over in
+        // LDS.
         constexpr int HALF = E / 32;          // blocks of 16 columns
         constexpr int AREA = NQB * HALF * 1024, STATS = NWAVES * AREA;
         static_assert(STATS + NWAVES * NQB * 512 <= kStages * STAGE, "the halves fit the tile buffers");
@@ -696,7 +698,8 @@ __device__ __forceinline__ void attn_rows(const AttnParams& p, int64_t unit, int
             u32x4 r[HALF / 2];
 #pragma unroll
             for (int pair = 0; pair < HALF / 2; pair++) {
-                // lanes 16 apart hold each other's halves of two blocks, which the swap brings to the accumulators' places
+                // lanes 16 apart hold each other's halves of two blocks, which the swap brings to the accumulators'
+                // places
                 const u32x4 base = half_base[qb][pair];
                 const auto b02 = __builtin_amdgcn_permlane16_swap(base[0], base[2], false, false);
                 const auto b13 = __builtin_amdgcn_permlane16_swap(base[1], base[3], false, false);
@@ -1004,7 +1007,8 @@ static double attn_rounds_cost(int E, int blocks, int64_t workgroups) {
 // the launch then takes.  Parts have to come out 4 % cheaper: they read their list and its K and V rows two or three times,
 // which the prices of tiles leave out (column lists, parts / whole priced and measured: 8 heads x 57 180, 3 %: 0.99, 1.07;
 // 3 x 82 722, 18 %, ragged: 0.98, 1.08; 31 x 14 649, 36 %: 0.99, 1.02; in 220 sizes those priced below 0.96 lost by 2 % at
-// most).
+// most).  Parts are priced as a workgroup per 64 rows; those that pairs of waves walk take 0.7 to 0.97 of that
+// (attn_part_form), which only leaves some launches near the line whole.
 static int64_t attn_whole_chunks(int E, int blocks, int64_t units, double* cost) {
     const int64_t last = units % 512, rounds = units - last;
     const double whole = attn_rounds_cost(E, blocks, units);
@@ -1014,22 +1018,27 @@ static int64_t attn_whole_chunks(int E, int blocks, int64_t units, double* cost)
     return in_parts ? rounds : units;
 }
 
-// How `parts` parts of 64 rows are walked, by the keys each has to walk.  kRows32Shared halves the chain of tiles and has twice
-// the workgroups: as long as those find an empty CU (E = 64: two to a CU cost each little).  kRows64Shared takes three quarters of the
-// time per step, and a merge of more rows: where the workgroups of 32 rows would meet on the CUs, and for long walks.
-// Launches in us of 64 rows, 64 shared and 32 shared, column lists, E = 128:
-//     parts  72: 128 keys 5.5, 6.7, 5.1   256 7.0, 8.0, 6.1   512 9.8, 10.1, 8.0    1024 15.7, 14.7, 11.7   2048 27.3, 23.8, 19.2
-//           180: 256 7.2, 8.0, 8.1   512 9.9, 10.3, 10.9   768 12.7, 12.4, 13.1   1024 15.7, 14.9, 15.9   2048 27.5, 23.9, 25.2
+// How `parts` parts of 64 rows are walked, by the keys each has to walk.  kRows32Shared halves the chain of tiles and has
+// twice the workgroups: as long as those find an empty CU (E = 64: two to a CU cost each little).  kRows64Shared takes
+// three quarters of the time per step, and a merge of more rows: where the workgroups of 32 rows would meet on the CUs,
+// and for long walks. Launches in us of 64 rows, 64 shared and 32 shared, column lists, E = 128:
+//     parts  72: 128 keys 5.5, 6.7, 5.1   256 7.0, 8.0, 6.1   512 9.8, 10.1, 8.0   1024 15.7, 14.7, 11.7
+//                2048 27.3, 23.8, 19.2
+//           180: 256 7.2, 8.0, 8.1   512 9.9, 10.3, 10.9   768 12.7, 12.4, 13.1   1024 15.7, 14.9, 15.9
+//                2048 27.5, 23.9, 25.2
 //           360: 512 13.5, 15.4, 17.5   1024 21.6, 22.5, 27.4   2048 37.2, 35.8, 45.7
-// E = 64: 108: 128 keys 4.5, 5.0, 4.2   512 7.2, 7.3, 6.0; 180: 384 6.5, 6.8, 6.8   768 9.2, 9.1, 9.0   2048 18.7, 17.0, 16.4; 360: 1024 13.9,
-// 14.8, 16.4   2048 23.9, 23.8, 27.1.  Every column: E = 128, 192 parts, 512 keys 9.7, 9.3, 9.5; E = 64: 256 5.3, 5.4, 5.0.
-// Behind 512 whole chunks, E = 128: 120 parts, 256 keys 29.6, 30.0, 29.3   2048 110.8, 107.2, 104.6; 192: 512 39.8, 40.8, 42.3   1024 61.1, 60.2,
-// 65.5; E = 64 (192 rows): 192: 1024 40.9, 41.3, 44.7   2048 67.9, 66.7, 73.4; every column, E = 64: 189, 960 keys 37.6, 36.0, 39.5.
-// Whole chunks of 128 rows at E = 64 have four workgroups to a CU, which the shared walk's registers in the same kernel make
-// three (133 and 138 instead of 128 and 122).  That costs a list's whole rounds more than it saves behind them: 512 chunks
-// and 272 to 400 parts of 2048 to 6000 keys 1.04 to 1.10 of the time, 176 to 248 parts 0.98 to 1.01, behind 1024 0.99 to
-// 1.02.  (Held to 128 registers, 6 of them in scratch memory: 0.99 to 1.03.)  Every column comes to 128 rows only behind 1024
-// chunks: 768 to 1700 keys 0.97 to 1.02, from 2304 0.98 to 0.99.
+// E = 64:   108: 128 keys 4.5, 5.0, 4.2   512 7.2, 7.3, 6.0
+//           180: 384 6.5, 6.8, 6.8   768 9.2, 9.1, 9.0   2048 18.7, 17.0, 16.4
+//           360: 1024 13.9, 14.8, 16.4   2048 23.9, 23.8, 27.1
+// Every column: E = 128, 192 parts, 512 keys 9.7, 9.3, 9.5; E = 64: 256 5.3, 5.4, 5.0.
+// Behind 512 whole chunks, E = 128: 120 parts, 256 keys 29.6, 30.0, 29.3   2048 110.8, 107.2, 104.6
+//           192: 512 39.8, 40.8, 42.3   1024 61.1, 60.2, 65.5; E = 64 (192 rows): 192: 1024 40.9, 41.3, 44.7
+//                2048 67.9, 66.7, 73.4; every column, E = 64: 189, 960 keys 37.6, 36.0, 39.5.
+// Whole chunks of 128 rows at E = 64 have four workgroups to a CU, which the shared walk's registers in the same kernel
+// make three (133 and 138 instead of 128 and 122).  That costs a list's whole rounds more than it saves behind them: 512
+// chunks and 272 to 400 parts of 2048 to 6000 keys 1.04 to 1.10 of the time, 176 to 248 parts 0.98 to 1.01, behind 1024
+// 0.99 to 1.02.  (Held to 128 registers, 6 of them in scratch memory: 0.99 to 1.03.)  Every column comes to 128 rows only
+// behind 1024 chunks: 768 to 1700 keys 0.97 to 1.02, from 2304 0.98 to 0.99.
 static AttnPart attn_part_form(int E, int rows, int64_t whole, int64_t parts, int keys, bool list) {
     if (parts <= 128) return keys > 3 * kTileRows ? kRows32Shared : kRows64;
     if (whole > 0 && list && E == 64 && rows == 128) return kRows64;
@@ -1240,21 +1249,20 @@ extern "C" int32_t chipmunk_attn_colsum_stale(const uint16_t* q, const uint16_t*
 // The sums' error against 64 bits, one kernel and apart: 2e-7 to 4e-7, 5e-8 to 7e-8 (RMS).
 static bool refresh_apart(int64_t units, int N) { return (units <= 80 && N >= 640) || (units <= 120 && N >= 1536); }
 
-
 // How many of a refresh's chunks the one kernel takes, the first ones; the sums and the attention of the others are made
-// apart. More than 120 chunks: apart while the attention's workgroups of 64 rows all have a slot, which long keys make worth
-// the second reading; a workgroup of the one kernel is quick with 128 rows at E = 128, so there only while each has a CU.  One
-// kernel and apart, E = 64: 128 chunks of 192 rows, 5000 to 6500 keys 0.74 of the time, 160, 2300 to 3000 0.89, 170 0.96, 180
-// 1.21; 200 of 128 rows 0.98, 6500 and more 0.84; E = 128: 125 of 128 rows 0.79, 135 1.09; 150 of 192 rows, 2300 to 3000 keys
-// 1.01, from 4500 0.96, from 6500 0.91; 175 1.2.
-// Beyond a round of all slots (three workgroups to a CU at E = 64 with 128 rows, else two): a last round of few chunks takes
-// the one kernel more than half as long as a full one.  Apart, last rounds of up to 50, to 75 and to 100 chunks, behind one
-// round, E = 128, 192 rows: 2300 to 3500 keys 0.91, 0.92, 0.99 of the time, from 6000 0.86, 0.88, 0.94 (544 chunks, 17 heads x
-// 6008: 396 and 342 us), up to 1536 keys 0.96, -, 1.07; 128 rows: 1536 to 2300 keys 0.95, 0.97, 1.01, from 6000 0.88, 0.91,
-// 0.91; behind two rounds 0.94, 0.95, 0.99 and (128 rows) 0.96, 0.97, 0.99; behind three (up to 60 chunks) 0.96 to 0.98 and
-// (128 rows) 0.98 to 1.01 below 4000 keys, 0.975 to 0.99 from there; behind four and more the workgroups no longer end together:
-// 0.98 to 1.04.  E = 64, 128 rows behind 768: 2300 to 3500 keys 0.98, 1.00, 1.02, from 3500 0.95, 0.97, 0.99; behind 1536 0.99 to
-// 1.02.  Last rounds that begin at half of the slots: 0.95 to 1.3.
+// apart. More than 120 chunks: apart while the attention's workgroups of 64 rows all have a slot, which long keys make
+// worth the second reading; a workgroup of the one kernel is quick with 128 rows at E = 128, so there only while each has
+// a CU.  One kernel and apart, E = 64: 128 chunks of 192 rows, 5000 to 6500 keys 0.74 of the time, 160, 2300 to 3000
+// 0.89, 170 0.96, 180 1.21; 200 of 128 rows 0.98, 6500 and more 0.84; E = 128: 125 of 128 rows 0.79, 135 1.09; 150 of 192
+// rows, 2300 to 3000 keys 1.01, from 4500 0.96, from 6500 0.91; 175 1.2.
+// Beyond a round of all slots (three workgroups to a CU at E = 64 with 128 rows, else two): a last round of few chunks
+// takes the one kernel more than half as long as a full one.  Apart, last rounds of up to 50, to 75 and to 100 chunks,
+// behind one round, E = 128, 192 rows: 2300 to 3500 keys 0.91, 0.92, 0.99 of the time, from 6000 0.86, 0.88, 0.94 (544
+// chunks, 17 heads x 6008: 396 and 342 us), up to 1536 keys 0.96, -, 1.07; 128 rows: 1536 to 2300 keys 0.95, 0.97, 1.01,
+// from 6000 0.88, 0.91, 0.91; behind two rounds 0.94, 0.95, 0.99 and (128 rows) 0.96, 0.97, 0.99; behind three (up to 60
+// chunks) 0.96 to 0.98 and (128 rows) 0.98 to 1.01 below 4000 keys, 0.975 to 0.99 from there; behind four and more the
+// workgroups no longer end together: 0.98 to 1.04.  E = 64, 128 rows behind 768: 2300 to 3500 keys 0.98, 1.00, 1.02, from
+// 3500 0.95, 0.97, 0.99; behind 1536 0.99 to 1.02.  Last rounds that begin at half of the slots: 0.95 to 1.3.
 static int64_t refresh_fused_chunks(int64_t units, int N, int E, int c) {
     if (refresh_apart(units, N)) return 0;
     const int64_t parts = units * (c / 64);
@@ -1303,8 +1311,8 @@ extern "C" int32_t chipmunk_attn_dense_colsum_stale(const uint16_t* q, const uin
     return fused == 0 ? launch_attn(p, E, units, s) : launch_attn_parts<kEveryColumn>(p, E, units - fused, s);
 }
 
-// Whether a refresh is made apart by the number and length of its chunks alone; how many chunks the one kernel takes, by all
-// rules.  For the tests, like the next.
+// Whether a refresh is made apart by the number and length of its chunks alone; how many chunks the one kernel takes, by
+// all rules.  For the tests, like the next.
 extern "C" int32_t chipmunk_internal_attn_refresh_apart(int B, int H, int N, int c) { return refresh_apart((int64_t)B * H * ((N + c - 1) / c), N); }
 
 extern "C" int32_t chipmunk_internal_attn_refresh_fused(int B, int H, int N, int E, int c) {

@@ -773,17 +773,17 @@ __global__ __launch_bounds__(256, 2) void mlp_gemm2_kernel(Gemm2Params p) {
 #include "mlp_small.h"
 namespace chipmunk {
 
-// Chunk means of x in split precision: mean = hi + lo with hi = bf16(mean),
-// lo = bf16(mean - hi); out row = [hi(0..D-1) | lo(0..D-1)].  A workgroup owns
-// (chunk, 512 columns): each of its eight waves sums an eighth of the chunk's rows
-// for 64 groups of 8 columns, the partial sums meet in LDS.
-// Bound: HBM (x read once).  A wave requests six rows (16 bytes per lane each) before it adds the first: with one row at a
-// time and four waves a small problem took as many round trips as a wave had rows: 24 chunks of 192 x 3072 15.5 -> 6.9 us,
-// 8 of 128 x 256 7.2 -> 4.4 us, 602 of 192 x 3072 139 -> 127 us (5.6 TB/s).
-// STREAM: loads past the caches' usual order of replacement, for an x that does not fit the last-level cache.  Means and scores
-// together, us without and with: 709 MB 220.6, 201.6; 414 MB 127, 109; 298 MB 108, 99; 162 MB (just read) 43.8, 47.3.
-// LANES: lanes per row, 64 or, where a workgroup per 512 columns leaves the chip idle, 16 (128 columns, four rows a load: a chunk
-// of 192 is requested at once).
+// Chunk means of x in split precision: mean = hi + lo with hi = bf16(mean), lo = bf16(mean - hi); out row = [hi(0..D-1) |
+// lo(0..D-1)].  A workgroup owns (chunk, 512 columns): each of its eight waves sums an eighth of the chunk's rows for 64
+// groups of 8 columns, the partial sums meet in LDS.
+// Bound: HBM (x read once).  A wave requests six rows (16 bytes per lane each) before it adds the first: with one row at
+// a time and four waves a small problem took as many round trips as a wave had rows: 24 chunks of 192 x 3072 15.5 -> 6.9
+// us, 8 of 128 x 256 7.2 -> 4.4 us, 602 of 192 x 3072 139 -> 127 us (5.6 TB/s).
+// STREAM: loads past the caches' usual order of replacement, for an x that does not fit the last-level cache.  Means and
+// scores together, us without and with: 709 MB 220.6, 201.6; 414 MB 127, 109; 298 MB 108, 99; 162 MB (just read) 43.8,
+// 47.3.
+// LANES: lanes per row, 64 or, where a workgroup per 512 columns leaves the chip idle, 16 (128 columns, four rows a load:
+// a chunk of 192 is requested at once).
 constexpr int kMeanWaves = 8, kMeanAhead = 6;
 template <bool STREAM, int LANES>
 __global__ __launch_bounds__(64 * kMeanWaves) void chunk_mean_kernel(const uint16_t* __restrict__ x, uint16_t* __restrict__ xm,
@@ -848,10 +848,10 @@ __global__ __launch_bounds__(64 * kMeanWaves) void chunk_mean_kernel(const uint1
 }
 
 // Scores of few chunks: T[n][f] = <hi[n] + lo[n], w1[f]> for up to 16 UB chunks and 16 NBK neurons per workgroup.
-// Bound: w1 from memory, read once, as long as the means, which every workgroup reads whole from L2, are few (few_scores).  The
-// eight waves of a workgroup cut the contraction among them, 64 entries (a cache line of a row) at a time in turn, and load both
-// operands from memory in the products' own layout; the partial sums meet in LDS in a fixed order, so no partial result goes
-// through memory and nothing is left for another launch.
+// Bound: w1 from memory, read once, as long as the means, which every workgroup reads whole from L2, are few
+// (few_scores).  The eight waves of a workgroup cut the contraction among them, 64 entries (a cache line of a row) at a
+// time in turn, and load both operands from memory in the products' own layout; the partial sums meet in LDS in a fixed
+// order, so no partial result goes through memory and nothing is left for another launch.
 constexpr int kFewWaves = 8;
 template <int UB, int NBK>
 __global__ __launch_bounds__(64 * kFewWaves) void mlp_few_scores_kernel(const uint16_t* __restrict__ xm, const uint16_t* __restrict__ w1,
@@ -1108,14 +1108,15 @@ static SecondPlan second_plan(bool sparse, int B, int N, int D, int F, int c, in
     return plan;
 }
 
-// The rows of a chunk's tile in the two GEMMs of a dense MLP, whose tiles need not follow the chunks: those of the other chunk size
-// where the prices above say 6 % less, for the widths that models have (hidden wider than the model's).  In the second GEMM up to
-// 4.5e10 products: beyond, the prices of its tiles of 192 and 128 rows are not that exact (1.01 of the time over 59 sizes).  In the
-// first without a limit: 4.5e10 to 1.6e11 products 0.94 (1759 sizes, one lost more than 1 %).  Against the first GEMM's tiles of 64 x 64 13 % less:
-// their price errs by more (7 to 13 % less by price: 0.98 of the time, of 825 sizes 221 lost more than 1 %, up to 16).
-// Whole calls, of the time on the chunk's rows, 11 500 sizes of 5e8 to 3e11 products: 0.91 in the mean, both GEMMs on 128 rows
-// instead of 192 0.84, the first 0.91, the second 0.94; on 192 instead of 128 the first 0.92, the second 0.94, both 0.84.  One in 75
-// loses more than 2 %, 9 % at most: second GEMMs that go from parts of 64 rows to whole tiles of 128, with four to nine chunks.
+// The rows of a chunk's tile in the two GEMMs of a dense MLP, whose tiles need not follow the chunks: those of the other
+// chunk size where the prices above say 6 % less, for the widths that models have (hidden wider than the model's).  In
+// the second GEMM up to 4.5e10 products: beyond, the prices of its tiles of 192 and 128 rows are not that exact (1.01 of
+// the time over 59 sizes).  In the first without a limit: 4.5e10 to 1.6e11 products 0.94 (1759 sizes, one lost more than
+// 1 %).  Against the first GEMM's tiles of 64 x 64 13 % less: their price errs by more (7 to 13 % less by price: 0.98 of
+// the time, of 825 sizes 221 lost more than 1 %, up to 16). Whole calls, of the time on the chunk's rows, 11 500 sizes of
+// 5e8 to 3e11 products: 0.91 in the mean, both GEMMs on 128 rows instead of 192 0.84, the first 0.91, the second 0.94; on
+// 192 instead of 128 the first 0.92, the second 0.94, both 0.84.  One in 75 loses more than 2 %, 9 % at most: second
+// GEMMs that go from parts of 64 rows to whole tiles of 128, with four to nine chunks.
 constexpr double kOtherRows = 0.94, kOtherRowsThanSmall = 0.87;
 struct DenseRows { int first, second; };
 static DenseRows dense_rows(int B, int N, int D, int F, int c) {
@@ -1227,23 +1228,25 @@ static ScoresPlan scores_plan(int units, int D, int F) {
     return {two_is_exact ? two : std::max(1, chains / 2), true};
 }
 
-// Chunk means by workgroups of 128 columns where those of 512 leave most of the CUs without one.  Whole calls in us, 512 and
-// 128 columns: 8 chunks of 192 x 3072 (F = 4096) 13.3, 12.0; 24 x 1024 (12 288) 14.3, 13.1; beyond the
-// limit 60 x 2048 (4096) 25.9, 26.2; 108 x 512 (3136) 17.4, 18.3.
+// Chunk means by workgroups of 128 columns where those of 512 leave most of the CUs without one.  Whole calls in us, 512
+// and 128 columns: 8 chunks of 192 x 3072 (F = 4096) 13.3, 12.0; 24 x 1024 (12 288) 14.3, 13.1; beyond the limit 60 x
+// 2048 (4096) 25.9, 26.2; 108 x 512 (3136) 17.4, 18.3.
 static bool narrow_means(int units, int D) { return (D + 511) / 512 * units <= 96; }
 
-// Few chunks: a workgroup per 16, 32 or 64 neurons, up to 16 384 neurons the fewest that give every CU at most one, with all
-// chunks.  Every workgroup reads all means (4 D bytes a chunk), which is what sets the limits of units * D; just above 8192 neurons
-// the workgroups are fewest and read most.  Whole calls in us, with the tiles of mlp_dense.h (and the sum of their pieces) and with
-// these: 3 chunks x 512 x 2048 neurons 12.0, 8.8; 8 x 1024 x 4096 13.3, 8.7; 8 x 3072 x 12 288 28.0, 20.8; 16 x 3072 x 8192 24.2, 18.3;
-// 24 x 1024 x 12 288 19.8, 13.1; 24 x 3072 x 12 288 32.3, 28.8; 40 x 1408 x 4096 16.0, 14.4.
+// Few chunks: a workgroup per 16, 32 or 64 neurons, up to 16 384 neurons the fewest that give every CU at most one, with
+// all chunks.  Every workgroup reads all means (4 D bytes a chunk), which is what sets the limits of units * D; just
+// above 8192 neurons the workgroups are fewest and read most.  Whole calls in us, with the tiles of mlp_dense.h (and the
+// sum of their pieces) and with these: 3 chunks x 512 x 2048 neurons 12.0, 8.8; 8 x 1024 x 4096 13.3, 8.7; 8 x 3072 x
+// 12 288 28.0, 20.8; 16 x 3072 x 8192 24.2, 18.3; 24 x 1024 x 12 288 19.8, 13.1; 24 x 3072 x 12 288 32.3, 28.8; 40 x 1408
+// x 4096 16.0, 14.4.
 // The limits by 1863 sizes, W1 not in the caches, of the time with the tiles (few chunks to many):
-//     F = 64: 24 000 0.81 to 1.01, 30 000 up to 1.03 (D = 3712); 512: 41 000 0.84 to 0.99, 46 000 up to 1.02; 1536: 41 000 0.81 to 0.96;
-//     below 2048 neurons with D above 4608 1.0 to 1.4 (a long contraction in a few workgroups);
-//     4160: 57 000 0.94 to 1.00, 66 000 1.01 to 1.14; 8256: 41 000 0.76 to 0.98, 50 000 up to 1.05; 11 328 to 16 384: 74 000 0.75 to 0.97,
-//     90 000 up to 1.02.
-// Beyond 16 384 neurons some CUs have more than one workgroup, each with all means: up to 16 chunks 0.71 to 0.97, 24 up to
-// 1.15, 48 up to 1.47 (131 072 neurons).
+//     F = 64: 24 000 0.81 to 1.01, 30 000 up to 1.03 (D = 3712);   512: 41 000 0.84 to 0.99, 46 000 up to 1.02;
+//     1536: 41 000 0.81 to 0.96; below 2048 neurons with D above 4608 1.0 to 1.4 (a long contraction in a few
+//     workgroups);
+//     4160: 57 000 0.94 to 1.00 (D above F up to 1.03), 66 000 1.01 to 1.14;   8256: 41 000 0.76 to 0.98, 50 000 up to 1.05;
+//     11 328 to 16 384: 74 000 0.75 to 0.97, 90 000 up to 1.02.
+// Beyond 16 384 neurons some CUs have more than one workgroup, each with all means: up to 16 chunks 0.71 to 0.97, 24 up
+// to 1.15, 48 up to 1.47 (131 072 neurons).
 static int few_neuron_blocks(int F) { return F <= 16 * 256 ? 1 : F <= 32 * 256 ? 2 : 4; }
 static bool few_scores(int units, int D, int F) {
     if (units > (F <= 64 * 256 ? 48 : 16) || (F < 2048 && D > 4608)) return false;
@@ -1506,8 +1509,9 @@ extern "C" int32_t chipmunk_mlp_tile_mean_preact_static(const uint16_t* x, const
 }
 
 // What the rules above choose for these sizes: whether the two dense GEMMs take the tiles of 256 x 256, whether the delta
-// takes 256 neurons per workgroup, and the scores GEMM's pieces and sums (0 and 0: the kernel for few chunks).  Not part of the library's interface: for the
-// tests, which have to reach each form and otherwise would not see that a rule has moved.
+// takes 256 neurons per workgroup, and the scores GEMM's pieces and sums (0 and 0: the kernel for few chunks).  Not part
+// of the library's interface: for the tests, which have to reach each form and otherwise would not see that a rule has
+// moved.
 extern "C" void chipmunk_internal_mlp_form(int B, int N, int D, int F, int c, int k_stride, int32_t* out) {
     const int units = B * ((N + c - 1) / c);
     const ScoresPlan plan = few_scores(units, D, F) ? ScoresPlan{0, false} : scores_plan(units, D, F);
@@ -1541,8 +1545,8 @@ extern "C" void chipmunk_internal_mlp_dense_rows(int B, int N, int D, int F, int
 // whether a delta with these sizes has its cached output pass the caches by
 extern "C" int32_t chipmunk_internal_mlp_streams(int B, int N, int D, int c) { return stream_output((int64_t)B * ((N + c - 1) / c), c, D); }
 
-// how the scores of these sizes are made: 16-neuron blocks of a workgroup where the chunks are few, else 0; whether the means come in
-// workgroups of 128 columns
+// how the scores of these sizes are made: 16-neuron blocks of a workgroup where the chunks are few, else 0; whether the
+// means come in workgroups of 128 columns
 extern "C" void chipmunk_internal_scores_form(int B, int N, int D, int F, int c, int32_t* out) {
     const int units = B * ((N + c - 1) / c);
     out[0] = few_scores(units, D, F) ? few_neuron_blocks(F) : 0;

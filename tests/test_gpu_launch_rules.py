@@ -35,8 +35,8 @@ def _attn_form(cm, H, N, E, c, with_list):
 
 
 def _attn_part_form(cm, H, N, E, c, k):
-    """how the chunks in parts are walked: 0 a workgroup per 64 rows, 1 the same with two waves to a row, 2 those per 32 rows, -1 there are
-    none; k: a list's columns, 0 without one"""
+    """how the chunks in parts are walked: 0 a workgroup per 64 rows, 1 the same with two waves to a row, 2 those per 32 rows,
+    -1 there are none; k: a list's columns, 0 without one"""
     return cm.load().chipmunk_internal_attn_part_form(1, H, N, E, c, k, int(k > 0))
 
 
@@ -118,8 +118,8 @@ def test_column_sums_in_pieces_of_the_keys(cm, oracle, N, E, c, pieces):
     (200, 190, None, -1)])                                                           # another form for each E
 def test_dense_attention_in_workgroups_of_64_128_and_192_rows(cm, oracle, E, H, N, form, part):
     """Without a list a workgroup takes one, two or three blocks of 64 rows, by the number of workgroups, those of the last
-    round one (or two waves half of one each) where that is cheaper; c is 128 here and 192 there, which no longer decides it.  The ends of the sequence
-    leave waves and whole blocks without rows."""
+    round one (or two waves half of one each) where that is cheaper; c is 128 here and 192 there, which no longer decides
+    it.  The ends of the sequence leave waves and whole blocks without rows."""
     assert _attn_form(cm, H, N, E, 128 if N % 2 else 192, False)[0] == (form or {64: (128, 400, 0), 128: (192, 200, 0)}[E])
     assert _attn_part_form(cm, H, N, E, 128 if N % 2 else 192, 0) == part
     q, k, v = recipes.attn_inputs(1, H, N, E, 22, DEV)
@@ -655,7 +655,8 @@ def test_dense_attention_walked_by_pairs_of_waves(cm, oracle, H, N, E, form):
 def test_neuron_scores_of_few_chunks(cm, oracle, B, N, D, F, c, form):
     """Up to 48 chunks: one to three blocks of 16 of them, the last ragged; workgroups of 16, 32 and 64 neurons; contractions of fewer
     lines than a workgroup has waves, and of a number that its waves do not divide; both sides of the limits (of chunks
-    by entries, of entries with few neurons, of chunks with many), beyond which the contraction is cut into pieces or not.  Means in workgroups of 128 and of 512 columns.  Tolerance as for the pieces."""
+    by entries, of entries with few neurons, of chunks with many), beyond which the contraction is cut into pieces or not.
+    Means in workgroups of 128 and of 512 columns.  Tolerance as for the pieces."""
     out = (ctypes.c_int32 * 2)()
     cm.load().chipmunk_internal_scores_form(B, N, D, F, c, out)
     assert tuple(out) == form
