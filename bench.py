@@ -50,11 +50,11 @@ CALIBRATION_COPY_BYTES = 256 << 20
 # attention kernel's sources are the ones the counters were taken on (ATTN_SOURCES_MEASURED is the
 # digest attn_sources_digest() gave then); after any change to them `traffic` is null until the
 # counters are taken again.
-ATTN_SOURCES_MEASURED = "c2d4eb91189b8c69"
+ATTN_SOURCES_MEASURED = "ca42258d34d895a3"
 MEASURED_ATTN_TRAFFIC_BYTES = {   # read factor * FETCH_SIZE KiB + write factor * WRITE_SIZE KiB (mean of the last four launches of the counter runs)
-    "flux": 2.0 * 46262 * 1024 + 1.0 * 27648 * 1024,
-    "hunyuan": 2.0 * 12470988 * 1024 + 1.0 * 692740 * 1024,
-    "wan": 2.0 * 9391427 * 1024 + 1.0 * 756005 * 1024,
+    "flux": 2.0 * 46260 * 1024 + 1.0 * 27648 * 1024,
+    "hunyuan": 2.0 * 12560410 * 1024 + 1.0 * 692739 * 1024,
+    "wan": 2.0 * 9383112 * 1024 + 1.0 * 756007 * 1024,
 }
 
 
