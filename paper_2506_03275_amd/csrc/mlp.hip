@@ -1113,13 +1113,18 @@ static SecondPlan second_plan(bool sparse, int B, int N, int D, int F, int c, in
 // the second GEMM up to 4.5e10 products: beyond, the prices of its tiles of 192 and 128 rows are not that exact (1.01 of
 // the time over 59 sizes).  In the first without a limit: 4.5e10 to 1.6e11 products 0.94 (1759 sizes, one lost more than
 // 1 %).  Against the first GEMM's tiles of 64 x 64 13 % less: their price errs by more (7 to 13 % less by price: 0.98 of
-// the time, of 825 sizes 221 lost more than 1 %, up to 16). Whole calls, of the time on the chunk's rows, 11 500 sizes of
-// 5e8 to 3e11 products: 0.91 in the mean, both GEMMs on 128 rows instead of 192 0.84, the first 0.91, the second 0.94; on
-// 192 instead of 128 the first 0.92, the second 0.94, both 0.84.  One in 75 loses more than 2 %, 9 % at most: second
-// GEMMs that go from parts of 64 rows to whole tiles of 128, with four to nine chunks.
+// the time, of 825 sizes 221 lost more than 1 %, up to 16).
+// Parts of 64 tokens whose rows in the cache are whole lines (a_ld a multiple of 64: 128 bytes) keep their rows: the price is that
+// of rows that meet two lines, and they are up to a fifth quicker (830 tokens x 2688 x 5440, a_ld 832, second GEMM 45.1 us in
+// parts, 52.3 on whole tiles of 128, priced 55.8 and 52.3; the change gave 0.97 of the time over 497 sizes, 119 of which lost
+// more than 1 %, up to 9).
+// Whole calls, of the time on the chunk's rows, 11 000 sizes of 5e8 to 3e11 products: 0.91 in the mean, both GEMMs on 128 rows
+// instead of 192 0.84, the first 0.91, the second 0.93; on 192 instead of 128 the first 0.92, the second 0.94, both 0.84.
+// One in 150 loses more than 2 %, 8 % at most: second GEMMs that go from parts of 64 rows to whole tiles of 128, with four to
+// nine chunks whose last one has few rows.
 constexpr double kOtherRows = 0.94, kOtherRowsThanSmall = 0.87;
 struct DenseRows { int first, second; };
-static DenseRows dense_rows(int B, int N, int D, int F, int c) {
+static DenseRows dense_rows(int B, int N, int D, int F, int c, int64_t a_ld) {
     const int other = 192 + 128 - c;
     DenseRows rows = {c, c};
     if (F <= D || D < 512) return rows;
@@ -1128,7 +1133,8 @@ static DenseRows dense_rows(int B, int N, int D, int F, int c) {
     if (first_form(false, B, N, D, F, other, 0, &other_us) == kFirstChunk && other_us < less * us) rows.first = other;
     if ((double)B * N * D * F < 4.5e10) {
         const SecondPlan plan = second_plan(false, B, N, D, F, c, 0), other_plan = second_plan(false, B, N, D, F, other, 0);
-        if (other_plan.form == kSecondChunk && other_plan.us < kOtherRows * plan.us) rows.second = other;
+        const bool parts_of_lines = plan.form == kSecondChunk && plan.whole == 0 && a_ld % 64 == 0;
+        if (!parts_of_lines && other_plan.form == kSecondChunk && other_plan.us < kOtherRows * plan.us) rows.second = other;
     }
     return rows;
 }
@@ -1367,7 +1373,7 @@ extern "C" int32_t chipmunk_mlp_dense(const uint16_t* x, const uint16_t* w1, con
     g.x = x; g.w1 = w1; g.w2 = w2; g.a_cache = a_cache; g.out = out; g.a_ld = a_ld;
     g.scores = nullptr; g.N = N; g.D = D; g.F = F; g.act = act; g.pieces = 1;
 
-    const DenseRows rows = dense_rows(B, N, D, F, c);
+    const DenseRows rows = dense_rows(B, N, D, F, c, a_ld);
     const FirstForm first = first_form(false, B, N, D, F, rows.first, 0);
     const SecondPlan second = second_plan(false, B, N, D, F, rows.second, 0);
     const int row_tiles = (N + kSmallTile - 1) / kSmallTile;   // of 64 x 64
@@ -1512,10 +1518,10 @@ extern "C" int32_t chipmunk_mlp_tile_mean_preact_static(const uint16_t* x, const
 // takes 256 neurons per workgroup, and the scores GEMM's pieces and sums (0 and 0: the kernel for few chunks).  Not part
 // of the library's interface: for the tests, which have to reach each form and otherwise would not see that a rule has
 // moved.
-extern "C" void chipmunk_internal_mlp_form(int B, int N, int D, int F, int c, int k_stride, int32_t* out) {
+extern "C" void chipmunk_internal_mlp_form(int B, int N, int D, int F, int c, int k_stride, int a_ld, int32_t* out) {
     const int units = B * ((N + c - 1) / c);
     const ScoresPlan plan = few_scores(units, D, F) ? ScoresPlan{0, false} : scores_plan(units, D, F);
-    const DenseRows rows = dense_rows(B, N, D, F, c);
+    const DenseRows rows = dense_rows(B, N, D, F, c, a_ld);
     out[0] = first_form(false, B, N, D, F, rows.first, 0) == kFirstLarge;
     out[1] = second_plan(false, B, N, D, F, rows.second, 0).form == kSecondLarge;
     out[2] = first_form(true, B, N, D, F, c, k_stride) == kFirstLarge;
@@ -1525,9 +1531,9 @@ extern "C" void chipmunk_internal_mlp_form(int B, int N, int D, int F, int c, in
 
 // The same for every form of the GEMMs: the dense MLP's first (FirstForm) and second (SecondForm, and the tiles per XCD taken
 // whole), then the delta's.
-extern "C" void chipmunk_internal_mlp_tiles(int B, int N, int D, int F, int c, int k_stride, int64_t* out) {
+extern "C" void chipmunk_internal_mlp_tiles(int B, int N, int D, int F, int c, int k_stride, int a_ld, int64_t* out) {
     for (int sparse = 0; sparse < 2; sparse++) {
-        const DenseRows rows = sparse ? DenseRows{c, c} : dense_rows(B, N, D, F, c);
+        const DenseRows rows = sparse ? DenseRows{c, c} : dense_rows(B, N, D, F, c, a_ld);
         const SecondPlan plan = second_plan(sparse, B, N, D, F, rows.second, k_stride);
         out[3 * sparse] = first_form(sparse, B, N, D, F, rows.first, k_stride);
         out[3 * sparse + 1] = plan.form;
@@ -1536,8 +1542,8 @@ extern "C" void chipmunk_internal_mlp_tiles(int B, int N, int D, int F, int c, i
 }
 
 // the rows of a chunk's tile in the dense MLP's GEMMs
-extern "C" void chipmunk_internal_mlp_dense_rows(int B, int N, int D, int F, int c, int32_t* out) {
-    const DenseRows rows = dense_rows(B, N, D, F, c);
+extern "C" void chipmunk_internal_mlp_dense_rows(int B, int N, int D, int F, int c, int a_ld, int32_t* out) {
+    const DenseRows rows = dense_rows(B, N, D, F, c, a_ld);
     out[0] = rows.first;
     out[1] = rows.second;
 }

@@ -40,19 +40,19 @@ def _attn_part_form(cm, H, N, E, c, k):
     return cm.load().chipmunk_internal_attn_part_form(1, H, N, E, c, k, int(k > 0))
 
 
-def _mlp_form(cm, B, N, D, F, c, k=1):
+def _mlp_form(cm, B, N, D, F, c, k=1, a_ld=None):
     """first and second dense GEMM on 256 x 256 tiles, delta with 256 neurons per workgroup; scores: pieces, sums, or (0, 0):
     the kernel for few chunks"""
     out = (ctypes.c_int32 * 5)()
-    cm.load().chipmunk_internal_mlp_form(B, N, D, F, c, k, out)
+    cm.load().chipmunk_internal_mlp_form(B, N, D, F, c, k, a_ld or -(-N // 8) * 8, out)
     return [bool(v) for v in out[:3]], tuple(out[3:])
 
 
-def _mlp_tiles(cm, B, N, D, F, c, k):
+def _mlp_tiles(cm, B, N, D, F, c, k, a_ld=None):
     """dense: form of the first GEMM (0 a chunk's tiles, 1 large, 2 of 64 x 64), of the second (the same) and tiles per XCD taken
     whole; then the delta's"""
     out = (ctypes.c_int64 * 6)()
-    cm.load().chipmunk_internal_mlp_tiles(B, N, D, F, c, k, out)
+    cm.load().chipmunk_internal_mlp_tiles(B, N, D, F, c, k, a_ld or -(-N // 8) * 8, out)
     return list(out)
 
 
@@ -165,7 +165,7 @@ def test_column_lists_walked_by_parts_of_a_chunk(cm, oracle, H, N, E, c, k, form
 ])
 def test_dense_mlp_on_large_tiles(cm, oracle, B, N, D, F, c, act, bias, large):
     """The dense GEMMs whose problem is large enough for 256 x 256 tiles; the cache cells past N stay as they are."""
-    assert tuple(_mlp_form(cm, B, N, D, F, c)[0][:2]) == large
+    assert tuple(_mlp_form(cm, B, N, D, F, c, a_ld=-(-N // 8) * 8 + 8)[0][:2]) == large
     x, _, w1, b1, w2, b2 = recipes.mlp_inputs(B, N, D, F, 24, DEV)
     if not bias:
         b1, b2 = torch.zeros_like(b1), torch.zeros_like(b2)
@@ -429,7 +429,7 @@ def test_mlp_on_small_tiles(cm, oracle, B, N, D, F, c, k, act, bias, tiles):
     """Few tiles: 64 x 64 in both GEMMs, chunks in parts of 64 rows, the last round in parts.  Lists that end at and beside the
     edges of tiles and steps, an empty one; the workspace holds NaN wherever nothing is written; both forms of the cache
     write-back alike; the cells past N stay as they are."""
-    assert _mlp_tiles(cm, B, N, D, F, c, k) == tiles
+    assert _mlp_tiles(cm, B, N, D, F, c, k, -(-N // 8) * 8 + 8) == tiles
     x1, x2, w1, b1, w2, b2 = recipes.mlp_inputs(B, N, D, F, 34, DEV)
     if not bias:
         b1, b2 = torch.zeros_like(b1), torch.zeros_like(b2)
@@ -682,9 +682,9 @@ def test_dense_mlp_on_the_other_chunk_sizes_rows(cm, oracle, B, N, D, F, c, act,
     way round, the last tile ragged; the cells past N stay as they are, and the delta of the same input, on the chunk's own rows, is
     nothing, bit for bit."""
     out = (ctypes.c_int32 * 2)()
-    cm.load().chipmunk_internal_mlp_dense_rows(B, N, D, F, c, out)
+    cm.load().chipmunk_internal_mlp_dense_rows(B, N, D, F, c, -(-N // 8) * 8 + 8, out)
     assert tuple(out) == rows
-    tiles = _mlp_tiles(cm, B, N, D, F, c, 1)
+    tiles = _mlp_tiles(cm, B, N, D, F, c, 1, -(-N // 8) * 8 + 8)
     assert (rows[0] == c or tiles[0] == 0) and (rows[1] == c or tiles[1] == 0)
     x, _, w1, b1, w2, b2 = recipes.mlp_inputs(B, N, D, F, 44, DEV)
     if not bias:

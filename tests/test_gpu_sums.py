@@ -64,7 +64,7 @@ def test_neuron_scores_add_no_longer_sums_than_the_workspace_has_pieces_for(cm, 
     high and as many of low parts leaves 1.5 h.  h is half of the pieces that the workspace is sized for."""
     c = 128
     form = (ctypes.c_int32 * 5)()
-    cm.load().chipmunk_internal_mlp_form(1, chunks * c, D, F, c, 1, form)
+    cm.load().chipmunk_internal_mlp_form(1, chunks * c, D, F, c, 1, chunks * c, form)
     assert tuple(form[3:]) == plan
     g = si.generator(32, DEV)
     pair = (1 + torch.randint(0, 128, (2, chunks, D), generator=g, device=DEV) / 128)

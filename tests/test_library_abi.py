@@ -134,7 +134,7 @@ def test_first_gemm_takes_no_more_workgroups_than_a_launch_has(lib, B, c, form):
     """A launch has fewer than 2^32 threads.  B sequences of 64 tokens with 16 384 neurons are 256 B tiles of 64 x 64, of 256 threads
     each, beyond that limit from 65 536 sequences on, but half as many of 128 neurons."""
     out = (ctypes.c_int64 * 6)()
-    lib.chipmunk_internal_mlp_tiles(B, 64, 128, 16384, c, 64, out)
+    lib.chipmunk_internal_mlp_tiles(B, 64, 128, 16384, c, 64, 64, out)
     assert out[0] == form
 
 
@@ -144,7 +144,7 @@ def test_second_gemm_takes_no_more_workgroups_than_a_launch_has(lib, B, N, D, F,
     """The same for the dense MLP's second GEMM: B sequences of up to 64 tokens are B D / 64 tiles of 64 x 64, half as many of 128
     columns."""
     out = (ctypes.c_int64 * 6)()
-    lib.chipmunk_internal_mlp_tiles(B, N, D, F, c, 64, out)
+    lib.chipmunk_internal_mlp_tiles(B, N, D, F, c, 64, -(-N // 8) * 8, out)
     assert out[1] == form
 
 
@@ -154,8 +154,17 @@ def test_first_gemm_of_few_chunks_and_many_neurons(lib, N, D, F, c, form):
     """Fewer than eight chunks are priced by the tiles that an XCD gets, like any other number: not 256 x 256 tiles here, which
     take 8 to 31 per cent longer."""
     out = (ctypes.c_int64 * 6)()
-    lib.chipmunk_internal_mlp_tiles(1, N, D, F, c, 1, out)
+    lib.chipmunk_internal_mlp_tiles(1, N, D, F, c, 1, -(-N // 8) * 8, out)
     assert out[0] == form
+
+
+@pytest.mark.parametrize("N,D,F,a_ld,second", [(830, 2688, 5440, 832, 192), (830, 2688, 5440, 840, 128), (960, 3968, 10880, 960, 192),
+                                               (960, 3968, 10880, 968, 128), (1265, 2688, 9472, 1272, 128)])
+def test_parts_of_whole_lines_keep_their_rows(lib, N, D, F, a_ld, second):
+    """The dense MLP's second GEMM in parts of 64 tokens is quicker than its price where a cache row's 64 tokens are one line."""
+    out = (ctypes.c_int32 * 2)()
+    lib.chipmunk_internal_mlp_dense_rows(1, N, D, F, 192, a_ld, out)
+    assert out[1] == second
 
 
 @pytest.mark.parametrize("has_names", [False, True])
