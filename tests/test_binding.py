@@ -199,7 +199,7 @@ def test_a_binding_for_another_torch_python_or_header_is_left_alone(cm, other, m
 
 
 def test_the_library_does_not_need_the_compiled_binding(cm, monkeypatch, tmp_path):
-    """The Python functions do every call: a box with the library and no host compiler loads it as it is."""
+    """The Python functions do every call: a machine with the library and no host compiler loads it as it is."""
     from paper_2506_03275_amd import build
     monkeypatch.setattr(build, "NATIVE", str(tmp_path / "none.so"))
     monkeypatch.setattr(build, "build", lambda verbose=False: pytest.fail("built anew"))

@@ -737,3 +737,21 @@ def test_refresh_with_its_last_chunks_apart(cm, oracle, H, N, E, c, fused):
     m_ref, l_ref = oracle.attn_row_stats(qn, kn, scale)
     assert np.abs(f64(m) + np.log(f64(l)) - (m_ref + np.log(l_ref))).max() <= 2e-3
     assert bool(torch.isfinite(out).all()) and bool(torch.isfinite(m).all()) and bool((l > 0).all())
+
+
+def test_refresh_with_its_last_chunks_apart_and_far_normalisers(cm):
+    """Normalisers 60 below the current scores: every weight is inside 32 bits and the two ways agree.  200 below: the one kernel caps
+    its factors, the pass that makes the last chunks' sums overflows like the formula; neither gives a NaN."""
+    H, N, E, c, fused = 43, 2304, 128, 192, 512
+    assert cm.load().chipmunk_internal_attn_refresh_fused(1, H, N, E, c) == fused
+    q, k, v = recipes.attn_inputs(1, H, N, E, 45, DEV)
+    scale, NB = 1 / math.sqrt(E), -(-N // c)
+    out, D, alone = torch.empty_like(q), *(torch.empty((1, H, NB, N), dtype=torch.float32, device=DEV) for _ in range(2))
+    m, l = torch.full((1, H, N), -60.0, device=DEV), torch.full((1, H, N), float(N), device=DEV)
+    cm.attn_dense_colsum_stale(q, k, v, out, m, l, D, c, scale)
+    cm.attn_colsum_stale(q, k, m, l, alone, c, scale)
+    assert bool(torch.isfinite(D).all()) and float(((D - alone).abs() / alone).max()) <= 1e-3
+    cm.attn_dense_colsum_stale(q, k, v, out, m - 140, l, D, c, scale)
+    one, apart = D.view(-1, N)[:fused], D.view(-1, N)[fused:]
+    assert not bool(D.isnan().any()) and bool((one >= 2.0 ** 100).all()) and bool(torch.isinf(apart).all())
+    assert bool(torch.isfinite(out).all())
