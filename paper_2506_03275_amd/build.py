@@ -44,14 +44,14 @@ def native_stamp():
     of the functions that it calls."""
     import torch
     header = hashlib.sha1(open(HEADER, "rb").read()).hexdigest()
-    return (f"chipmunk binding for torch {torch.__version__} {torch.version.git_version}, Python {sysconfig.get_config_var('SOABI')}, "
+    return (f"chipmunk binding for torch {torch.__version__} {getattr(torch.version, 'git_version', None)}, Python {sysconfig.get_config_var('SOABI')}, "
             f"chipmunk.h {header}.")
 
 
 def native_fits():
     """Whether the compiled binding is there and was built against what runs now.  Read from the file: code for another torch is
     not to be loaded at all."""
-    if not os.path.exists(NATIVE):
+    if not os.path.exists(NATIVE) or not os.path.exists(HEADER):
         return False
     with open(NATIVE, "rb") as f:
         return native_stamp().encode() in f.read()

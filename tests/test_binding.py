@@ -175,7 +175,7 @@ def test_the_binding_does_what_the_python_functions_do(cm, name):
     assert all(torch.equal(a, b) for a, b in zip(again, _outcome(cm, cm._Python(), name, args)))
 
 
-@pytest.mark.parametrize("other", ["torch", "revision", "python", "header"])
+@pytest.mark.parametrize("other", ["torch", "revision", "python", "header", "no header"])
 def test_a_binding_for_another_torch_python_or_header_is_left_alone(cm, other, monkeypatch, tmp_path):
     """Its code holds the layout of torch's tensors and Python's objects, and the C functions' arguments.  Another torch would often
     load it all the same, because the few functions that it asks for by name are there in most."""
@@ -189,6 +189,8 @@ def test_a_binding_for_another_torch_python_or_header_is_left_alone(cm, other, m
     elif other == "python":
         real = build.sysconfig.get_config_var
         monkeypatch.setattr(build.sysconfig, "get_config_var", lambda name: "cpython-399" if name == "SOABI" else real(name))
+    elif other == "no header":   # the package alone, without the tree around it
+        monkeypatch.setattr(build, "HEADER", str(tmp_path / "none.h"))
     else:
         header = tmp_path / "chipmunk.h"
         header.write_bytes(open(build.HEADER, "rb").read() + b"\n")
